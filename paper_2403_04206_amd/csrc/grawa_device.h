@@ -151,8 +151,17 @@ template <> struct Grad<uint16_t> { // bfloat16 bit patterns
     }
 };
 
-// V gradient elements (V * sizeof(GT) = 4 or 8 bytes, naturally aligned) widened to float.
+// V gradient elements (naturally aligned) widened to float; `lane` takes a wave-uniform base and the
+// lane's byte offset.
 template <typename GT, int V, bool NT> struct GradVec;
+template <bool NT> struct GradVec<float, 2, NT> {
+    static __device__ __forceinline__ void lane(uint64_t base, unsigned off, float (&f)[2])
+    {
+        const v2f w = ld_lane<NT, v2f>(base, off);
+        f[0] = w.x;
+        f[1] = w.y;
+    }
+};
 template <bool NT> struct GradVec<float, 1, NT> {
     static __device__ __forceinline__ void load(const float *p, float (&f)[1]) { f[0] = NT ? __builtin_nontemporal_load(p) : *p; }
 };
@@ -169,6 +178,12 @@ template <bool NT> struct GradVec<float, 4, NT> {
     }
 };
 template <bool NT> struct GradVec<uint16_t, 2, NT> {
+    static __device__ __forceinline__ void lane(uint64_t base, unsigned off, float (&f)[2])
+    {
+        const uint32_t w = ld_lane<NT, uint32_t>(base, off);
+        f[0] = bf16_lo(w);
+        f[1] = bf16_hi(w);
+    }
     static __device__ __forceinline__ void load(const uint16_t *p, float (&f)[2])
     {
         const uint32_t *q = reinterpret_cast<const uint32_t *>(p);
