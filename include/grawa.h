@@ -280,7 +280,7 @@ grawa_status_t grawa_lsgd_update(grawa_plan_t *plan, float *x, int64_t ldx, cons
  * forbid allocation.  It needs no plan.  The workspace a plan would own (tile
  * map, cell map, per-tile partial sums, the K x L tables) lives in a fixed
  * 32 MiB array inside the library's device image, one copy per GPU, held until
- * the process ends; the maps are built by two small kernels from layer offsets
+ * the process ends; the maps are built by a small kernel from layer offsets
  * that are already in DEVICE memory.  The call enqueues kernels on `stream` and
  * nothing else (no hipMalloc / hipFree / memset / copy, no synchronisation), and
  * gives bit for bit what grawa_lgrawa_update gives for the same inputs.

@@ -4,6 +4,7 @@
 #include <cmath>
 #include <cstring>
 #include <new>
+#include <vector>
 
 #include "grawa_internal.h"
 
@@ -78,12 +79,15 @@ grawa_status_t run_update(grawa_plan *p, float *x, int64_t ldx, const void *g, i
 
     GRAWA_TRY_HIP(grawa_launch_sumsq(p, g, ldg, dt, s, prof ? ev[0] : nullptr, prof ? ev[1] : nullptr));
 
-    GRAWA_TRY_HIP(grawa_launch_finalize_layers(p, nullptr, per_layer ? weights_out : nullptr, s, 0, 0.0));
-    if (!per_layer) GRAWA_TRY_HIP(grawa_launch_finalize_model(p, mode, weights_out, s));
+    const bool from_tiles = per_layer && grawa_pull_from_tiles(p);
+    const int goal = per_layer ? GRAWA_GOAL_LAYER_WEIGHTS
+                               : (mode == GRAWA_NORM_LAYERSUM ? GRAWA_GOAL_MODEL_SUM : GRAWA_GOAL_MODEL_FLAT);
+    if (!from_tiles) GRAWA_TRY_HIP(grawa_launch_finalize_layers(p, goal, nullptr, weights_out, s));
 
-    GRAWA_TRY_HIP(grawa_launch_center_pull(p, x, ldx, per_layer ? p->d_beta_layer : p->d_beta_model,
+    GRAWA_TRY_HIP(grawa_launch_center_pull(p, x, ldx, from_tiles ? nullptr : per_layer ? p->d_beta_layer : p->d_beta_model,
                                            per_layer, lambda, g_sgd, ldg_sgd, dt, lr, fuse_sgd,
-                                           center_out, 0.f, 0, s, prof ? ev[2] : nullptr, prof ? ev[3] : nullptr));
+                                           center_out, 0.f, 0, weights_out, s, prof ? ev[2] : nullptr,
+                                           prof ? ev[3] : nullptr));
     if (prof) prof_commit(p, true);
     return GRAWA_OK;
 }
@@ -140,6 +144,8 @@ static grawa_status_t plan_create_impl(grawa_plan_t **out, int K, int64_t P, int
     const int64_t nrb = (int64_t)m.block_rtile0.size() - 1;
     const int64_t nc = (int64_t)m.cell_layer.size();
 
+    const std::vector<float> uniform((size_t)K, 1.f / (float)K);
+
     grawa_plan *p = new (std::nothrow) grawa_plan();
     if (!p) return GRAWA_ERR_WORKSPACE;
     std::memset(p, 0, sizeof(*p));
@@ -163,12 +169,13 @@ static grawa_status_t plan_create_impl(grawa_plan_t **out, int K, int64_t P, int
     const size_t b_brt0 = round256(sizeof(int32_t) * ((size_t)nrb + 1));
     const size_t b_part = round256(sizeof(double) * (size_t)K * (size_t)(nrt > nt ? nrt : nt));
     const size_t b_S = round256(sizeof(double) * (size_t)K * (size_t)L);
-    const size_t b_A = round256(sizeof(float) * (size_t)K * (size_t)L);
-    const size_t b_bl = b_A;
+    const size_t b_bl = round256(sizeof(float) * (size_t)K * (size_t)L);
     const size_t b_bm = round256(sizeof(float) * (size_t)K);
     const size_t b_mvg = b_S;
+    const size_t b_ckl = round256(sizeof(unsigned) * (size_t)K * (size_t)L);
     const size_t b_t = 256;
-    p->ws_bytes = b_off + b_cells + b_tiles + b_lt0 + b_rtiles + b_lt0 + b_brt0 + b_part + b_S + b_A + b_bl + b_bm + b_mvg + b_t;
+    const size_t b_zeroed = b_part + b_S + b_bl + b_bm + b_mvg + b_ckl + b_t;
+    p->ws_bytes = b_off + b_cells + b_tiles + b_lt0 + b_rtiles + b_lt0 + b_brt0 + b_bm + b_zeroed;
     if (hipMalloc(&p->ws, p->ws_bytes) != hipSuccess) {
         (void)hipGetLastError();
         delete p;
@@ -179,17 +186,20 @@ static grawa_status_t plan_create_impl(grawa_plan_t **out, int K, int64_t P, int
     p->d_cell_layer = reinterpret_cast<int32_t *>(w); w += b_cells;
     p->d_tiles = reinterpret_cast<GrawaTile *>(w); w += b_tiles;
     p->d_layer_tile0 = reinterpret_cast<int32_t *>(w); w += b_lt0;
+    p->d_layer_tile1 = p->d_layer_tile0 + 1;
     p->d_rtiles = reinterpret_cast<GrawaTile *>(w); w += b_rtiles;
     p->d_layer_rtile0 = reinterpret_cast<int32_t *>(w); w += b_lt0;
     p->d_block_rtile0 = reinterpret_cast<int32_t *>(w); w += b_brt0;
+    p->d_beta_uniform = reinterpret_cast<float *>(w); w += b_bm;
     p->d_partials = reinterpret_cast<double *>(w); w += b_part;
     p->d_S = reinterpret_cast<double *>(w); w += b_S;
-    p->d_A = reinterpret_cast<float *>(w); w += b_A;
     p->d_beta_layer = reinterpret_cast<float *>(w); w += b_bl;
     p->d_beta_model = reinterpret_cast<float *>(w); w += b_bm;
     p->d_mvg = reinterpret_cast<double *>(w); w += b_mvg;
+    p->d_cnt_kl = reinterpret_cast<unsigned *>(w); w += b_ckl;
     p->d_local_t = reinterpret_cast<int64_t *>(w);
     p->d_flags = reinterpret_cast<unsigned *>(w + 64);
+    p->d_cnt_all = reinterpret_cast<unsigned *>(w + 128);
 
     if (hipMemcpy(p->d_off, off, sizeof(int64_t) * ((size_t)L + 1), hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(p->d_cell_layer, m.cell_layer.data(), sizeof(int32_t) * (size_t)nc, hipMemcpyHostToDevice) != hipSuccess ||
@@ -198,7 +208,8 @@ static grawa_status_t plan_create_impl(grawa_plan_t **out, int K, int64_t P, int
         hipMemcpy(p->d_rtiles, m.rtiles.data(), sizeof(GrawaTile) * (size_t)nrt, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(p->d_layer_rtile0, m.layer_rtile0.data(), sizeof(int32_t) * ((size_t)L + 1), hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(p->d_block_rtile0, m.block_rtile0.data(), sizeof(int32_t) * ((size_t)nrb + 1), hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemset(p->d_partials, 0, b_part + b_S + b_A + b_bl + b_bm + b_mvg + b_t) != hipSuccess) {
+        hipMemcpy(p->d_beta_uniform, uniform.data(), sizeof(float) * (size_t)K, hipMemcpyHostToDevice) != hipSuccess ||
+        hipMemset(p->d_partials, 0, b_zeroed) != hipSuccess) {
         (void)hipFree(p->ws);
         delete p;
         return GRAWA_ERR_HIP;
@@ -240,7 +251,7 @@ grawa_status_t grawa_grad_norms(grawa_plan_t *p, const void *g, int64_t ldg, gra
     if (!guard.ok) return GRAWA_ERR_HIP;
     hipStream_t s = static_cast<hipStream_t>(stream);
     GRAWA_TRY_HIP(grawa_launch_sumsq(p, g, ldg, dt, s, nullptr, nullptr));
-    GRAWA_TRY_HIP(grawa_launch_finalize_layers(p, norms_out, nullptr, s, 0, 0.0));
+    GRAWA_TRY_HIP(grawa_launch_finalize_layers(p, GRAWA_GOAL_SCORES, norms_out, nullptr, s));
     return GRAWA_OK;
 }
 
@@ -291,7 +302,7 @@ grawa_status_t grawa_center_pull(grawa_plan_t *p, float *x, int64_t ldx, const f
     const bool prof = prof_active(p);
     hipEvent_t *ev = prof ? p->ev + 4 * (size_t)p->profile_n : nullptr;
     GRAWA_TRY_HIP(grawa_launch_center_pull(p, x, ldx, weights, per_layer ? 1 : 0, lambda, nullptr, 0, GRAWA_F32,
-                                           0.f, 0, center_out, 0.f, 0, s, prof ? ev[2] : nullptr,
+                                           0.f, 0, center_out, 0.f, 0, nullptr, s, prof ? ev[2] : nullptr,
                                            prof ? ev[3] : nullptr));
     if (prof) prof_commit(p, false);
     return GRAWA_OK;
@@ -306,7 +317,7 @@ grawa_status_t grawa_local_sgd(float *x, int64_t ldx, const void *g, int64_t ldg
     grawa_status_t st = check_grads(P, g, ldg, dt);
     if (st != GRAWA_OK) return st;
     if (!std::isfinite(lr)) return GRAWA_ERR_INVALID_ARG;
-    GRAWA_TRY_HIP(grawa_launch_row_step(x, ldx, g, ldg, dt, lr, nullptr, 0.f, K, P, nullptr, nullptr, 0, nullptr,
+    GRAWA_TRY_HIP(grawa_launch_row_step(x, ldx, g, ldg, dt, lr, nullptr, 0.f, K, P,
                                         static_cast<hipStream_t>(stream)));
     return GRAWA_OK;
 }
@@ -330,8 +341,7 @@ grawa_status_t grawa_local_nesterov(float *x, int64_t ldx, const void *g, int64_
 
 /* EASGD and LSGD share the pull kernel: only the weights (and the moving center) differ. */
 static grawa_status_t run_fixed_center(grawa_plan_t *p, float *x, int64_t ldx, const float *loss, float lambda,
-                                       float rho, int moving, float *center, float *weights_out, int *leader_out,
-                                       void *stream)
+                                       float rho, int moving, float *center, int *leader_out, void *stream)
 {
     grawa_status_t st;
     if ((st = check_params(p, x, ldx)) != GRAWA_OK) return st;
@@ -340,9 +350,9 @@ static grawa_status_t run_fixed_center(grawa_plan_t *p, float *x, int64_t ldx, c
     DeviceGuard guard(p->device);
     if (!guard.ok) return GRAWA_ERR_HIP;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    GRAWA_TRY_HIP(grawa_launch_center_weights(p, loss, weights_out, leader_out, s));
-    GRAWA_TRY_HIP(grawa_launch_center_pull(p, x, ldx, p->d_beta_model, 0, lambda, nullptr, 0, GRAWA_F32, 0.f, 0,
-                                           center, rho, moving, s, nullptr, nullptr));
+    if (loss) GRAWA_TRY_HIP(grawa_launch_leader_weights(p, loss, leader_out, s));
+    GRAWA_TRY_HIP(grawa_launch_center_pull(p, x, ldx, loss ? p->d_beta_model : p->d_beta_uniform, 0, lambda, nullptr, 0, GRAWA_F32, 0.f, 0,
+                                           center, rho, moving, nullptr, s, nullptr, nullptr));
     return GRAWA_OK;
 }
 
@@ -350,14 +360,14 @@ grawa_status_t grawa_easgd_update(grawa_plan_t *p, float *x, int64_t ldx, float 
                                   void *stream)
 {
     if (!center || !(rho >= 0.f && rho <= 1.f)) return GRAWA_ERR_INVALID_ARG;
-    return run_fixed_center(p, x, ldx, nullptr, lambda, rho, 1, center, nullptr, nullptr, stream);
+    return run_fixed_center(p, x, ldx, nullptr, lambda, rho, 1, center, nullptr, stream);
 }
 
 grawa_status_t grawa_lsgd_update(grawa_plan_t *p, float *x, int64_t ldx, const float *losses, float lambda,
                                  float *center_out, int *leader_out, void *stream)
 {
     if (!losses) return GRAWA_ERR_INVALID_ARG;
-    return run_fixed_center(p, x, ldx, losses, lambda, 0.f, 0, center_out, nullptr, leader_out, stream);
+    return run_fixed_center(p, x, ldx, losses, lambda, 0.f, 0, center_out, leader_out, stream);
 }
 
 grawa_status_t grawa_local_sgd_prox(float *x, int64_t ldx, const void *g, int64_t ldg, grawa_dtype_t dt, int K,
@@ -370,7 +380,7 @@ grawa_status_t grawa_local_sgd_prox(float *x, int64_t ldx, const void *g, int64_
     if (st != GRAWA_OK) return st;
     if (!std::isfinite(lr) || !std::isfinite(mu) || !std::isfinite(tau) || !(tau > 0.f) || mu < 0.f || mu > tau)
         return GRAWA_ERR_INVALID_ARG;
-    GRAWA_TRY_HIP(grawa_launch_row_step(x, ldx, g, ldg, dt, lr, center, mu / tau, K, P, nullptr, nullptr, 0, nullptr,
+    GRAWA_TRY_HIP(grawa_launch_row_step(x, ldx, g, ldg, dt, lr, center, mu / tau, K, P,
                                         static_cast<hipStream_t>(stream)));
     return GRAWA_OK;
 }
@@ -394,9 +404,7 @@ grawa_status_t grawa_local_step_scored(grawa_plan_t *p, float *x, int64_t ldx, c
     DeviceGuard guard(p->device);
     if (!guard.ok) return GRAWA_ERR_HIP;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    GRAWA_TRY_HIP(grawa_launch_row_step(x, ldx, g, ldg, dt, lr, center, w, p->K, p->P, p->d_rtiles,
-                                        p->d_block_rtile0, p->n_rtiles, p->d_partials, s));
-    GRAWA_TRY_HIP(grawa_launch_finalize_layers(p, nullptr, nullptr, s, 1, (double)gamma));
+    GRAWA_TRY_HIP(grawa_launch_row_step_scored(p, x, ldx, g, ldg, dt, lr, center, w, (double)gamma, s));
     p->local_t += 1;
     p->local_gamma = (double)gamma;
     return GRAWA_OK;
@@ -417,10 +425,9 @@ grawa_status_t local_update(grawa_plan_t *p, float *x, int64_t ldx, int per_laye
     const bool prof = prof_active(p);
     hipEvent_t *ev = prof ? p->ev + 4 * (size_t)p->profile_n : nullptr;
     GRAWA_TRY_HIP(grawa_launch_center_pull(p, x, ldx, per_layer ? p->d_beta_layer : p->d_beta_model, per_layer,
-                                           lambda, nullptr, 0, GRAWA_F32, 0.f, 0, center_out, 0.f, 0, s,
+                                           lambda, nullptr, 0, GRAWA_F32, 0.f, 0, center_out, 0.f, 0, nullptr, s,
                                            prof ? ev[2] : nullptr, prof ? ev[3] : nullptr));
     if (prof) prof_commit(p, false);
-    GRAWA_TRY_HIP(grawa_launch_zero_estimate(p, s));
     p->local_t = 0;
     return GRAWA_OK;
 }

@@ -44,13 +44,17 @@ __device__ __forceinline__ double wave_sum(double v)
 
 __device__ __forceinline__ double wave_min(double v)
 {
-    for (int m = 1; m < GRAWA_WAVE; m <<= 1) v = fmin(v, __shfl_xor(v, m, GRAWA_WAVE));
+    v = fmin(v, dpp_move_f64<0xB1>(v));
+    v = fmin(v, dpp_move_f64<0x4E>(v));
+    v = fmin(v, dpp_move_f64<0x141>(v));
+    v = fmin(v, dpp_move_f64<0x140>(v));
+    v = fmin(v, __shfl_xor(v, 16, GRAWA_WAVE));
+    v = fmin(v, __shfl_xor(v, 32, GRAWA_WAVE));
     return v;
 }
 
-// Sum over a 256-thread block through LDS; every thread gets the result.  `sm` holds one
-// double per wave.
-__device__ __forceinline__ double block_sum(double v, double *sm)
+// Sum over a block through LDS; every thread gets the result.  `sm` holds one double per wave.
+template <int BLOCK> __device__ __forceinline__ double block_sum(double v, double *sm)
 {
     v = wave_sum(v);
     const int w = threadIdx.x / GRAWA_WAVE;
@@ -58,7 +62,7 @@ __device__ __forceinline__ double block_sum(double v, double *sm)
     if ((threadIdx.x & (GRAWA_WAVE - 1)) == 0) sm[w] = v;
     __syncthreads();
     double t = 0.0;
-    for (int i = 0; i < GRAWA_BLOCK / GRAWA_WAVE; ++i) t += sm[i];
+    for (int i = 0; i < BLOCK / GRAWA_WAVE; ++i) t += sm[i];
     return t;
 }
 

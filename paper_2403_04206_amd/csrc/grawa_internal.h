@@ -27,6 +27,7 @@ struct grawa_plan {
     int64_t *d_off;         // [L+1] layer offsets
     GrawaTile *d_tiles;     // [n_tiles]
     int32_t *d_layer_tile0; // [L+1] first tile of every layer
+    int32_t *d_layer_tile1; // [L] one past the last tile of every layer (d_layer_tile0 + 1 in a plan)
     GrawaTile *d_rtiles;    // [n_rtiles] short tiles (1024 columns) of the scored local step
     int32_t *d_layer_rtile0; // [L+1]
     int32_t *d_block_rtile0; // [ceil(P/1024)+1] first short tile of every aligned block of 1024 columns
@@ -34,9 +35,11 @@ struct grawa_plan {
     int32_t *d_cell_layer;  // [n_cells] layer of a 256-column cell, or ~(first layer) if it holds a boundary
     double *d_partials;     // [K][n_tiles] per-tile sums of squares
     double *d_S;            // [K][L] squared Frobenius norms
-    float *d_A;             // [K][L] layer norms
     float *d_beta_layer;    // [K][L] per-layer weights
     float *d_beta_model;    // [K] model-level weights
+    float *d_beta_uniform;  // [K] 1/K each (EASGD), written once
+    unsigned *d_cnt_kl;     // [K][L] arrivals of the tiles of a (worker, layer); every counter is 0 between calls
+    unsigned *d_cnt_all;    // [1] arrivals of the layers
     double *d_mvg;          // [K][L] moving average of the layer norms (running estimate, Appendix G)
     int64_t *d_local_t;     // device: local steps since the last communication (what the kernels use)
     unsigned *d_flags;      // device: GRAWA_NONFINITE_* bits, sticky until read-and-cleared (may be null)
@@ -47,6 +50,13 @@ struct grawa_plan {
     int profile_n;
     hipEvent_t *ev;          // 4 per slot: norm begin/end, pull begin/end
     unsigned char *ev_norm;  // per slot: 1 if the call recorded norm-kernel events
+};
+
+enum { // what the layer scores are wanted for
+    GRAWA_GOAL_SCORES = 0,        // the layer norms only
+    GRAWA_GOAL_LAYER_WEIGHTS = 1, // weights per layer, eq. (7)
+    GRAWA_GOAL_MODEL_SUM = 2,     // weights per worker from the sum of its layer norms, eq. (3)-(4)
+    GRAWA_GOAL_MODEL_FLAT = 3     // weights per worker from the norm of its whole gradient, eq. (2), (4)
 };
 
 // Argument checks shared by the entry points (host only; nothing is launched on failure).
@@ -85,27 +95,30 @@ static inline grawa_status_t grawa_check_center(const float *c)
 // e0/e1: optional start/stop events of the launch itself (null when not profiling).
 hipError_t grawa_launch_sumsq(const grawa_plan *p, const void *g, int64_t ldg, grawa_dtype_t dt,
                               hipStream_t s, hipEvent_t e0, hipEvent_t e1);
-hipError_t grawa_launch_finalize_layers(const grawa_plan *p, float *norms_user, float *beta_user,
-                                        hipStream_t s, int update_estimate, double gamma);
+hipError_t grawa_launch_finalize_layers(const grawa_plan *p, int goal, float *norms_user, float *beta_user,
+                                        hipStream_t s);
+hipError_t grawa_launch_estimate(const grawa_plan *p, double gamma, hipStream_t s);
 hipError_t grawa_launch_local_weights(const grawa_plan *p, double gamma, int per_layer, float *beta_user,
                                       float *est_user, hipStream_t s);
 hipError_t grawa_launch_zero_estimate(const grawa_plan *p, hipStream_t s);
 hipError_t grawa_launch_clear_flags(const grawa_plan *p, hipStream_t s);
 hipError_t grawa_launch_row_step(float *x, int64_t ldx, const void *g, int64_t ldg, grawa_dtype_t dt, float lr,
-                                 const float *center, float w, int K, int64_t P, const GrawaTile *tiles,
-                                 const int32_t *block_tile0, int64_t n_tiles, double *partials, hipStream_t s);
-hipError_t grawa_launch_finalize_model(const grawa_plan *p, grawa_norm_mode_t mode, float *beta_user,
-                                       hipStream_t s);
+                                 const float *center, float w, int K, int64_t P, hipStream_t s);
+hipError_t grawa_launch_row_step_scored(const grawa_plan *p, float *x, int64_t ldx, const void *g, int64_t ldg,
+                                        grawa_dtype_t dt, float lr, const float *center, float w, double gamma,
+                                        hipStream_t s);
+// Whether the pull pass of a per-layer update takes its weights straight from the tile sums (grawa_pull.hip).
+bool grawa_pull_from_tiles(const grawa_plan *p);
+// per_layer: beta is [K][L], or null: straight from the tile sums, to weights_out as well if not null.
 hipError_t grawa_launch_center_pull(const grawa_plan *p, float *x, int64_t ldx, const float *beta,
                                     int per_layer, float lambda, const void *g_sgd,
                                     int64_t ldg_sgd, grawa_dtype_t dt, float lr, int fuse_sgd,
-                                    float *center_out, float rho, int moving, hipStream_t s, hipEvent_t e0,
-                                    hipEvent_t e1);
+                                    float *center_out, float rho, int moving, float *weights_out, hipStream_t s,
+                                    hipEvent_t e0, hipEvent_t e1);
 hipError_t grawa_launch_nesterov(float *x, int64_t ldx, const void *g, int64_t ldg, grawa_dtype_t dt,
                                  float *buf, int64_t ldb, int K, int64_t P, float lr, float momentum,
                                  float wd, hipStream_t s);
-hipError_t grawa_launch_center_weights(const grawa_plan *p, const float *loss, float *beta_user,
-                                       int *leader_out, hipStream_t s);
+hipError_t grawa_launch_leader_weights(const grawa_plan *p, const float *loss, int *leader_out, hipStream_t s);
 hipError_t grawa_launch_stream_copy(void *dst, const void *src, int64_t nbytes, hipStream_t s);
 
 #endif

@@ -7,7 +7,7 @@
 //   k_stream_copy  plain copy (measurement aid)
 // All are read-modify-write streams with no reuse: global loads and stores kept in flight, one
 // row (worker) per block, which is the access shape that streams fastest on this part.
-#include "grawa_device.h"
+#include "grawa_scores.h"
 
 // ---------------------------------------------------------------------------------
 // local step, row by row
@@ -16,10 +16,54 @@
 #define GRAWA_ROW_BLOCK 1024 // columns per block
 #define GRAWA_ROW_GROUP 4096 // column blocks of one row launched back to back (4 Mi columns)
 
+// Where the tile sums of a scored step go.
+struct RowScores {
+    const GrawaTile *tiles;      // 1024-column tiles, and the first one of every aligned block of 1024 columns
+    const int32_t *block_tile0;
+    const int32_t *layer_tile0;  // [L+1]
+    int L;
+    double *partials;            // [K][n_tiles]
+    int64_t n_tiles;
+    unsigned *cnt_kl;            // [K][L]
+    double *mvg;                 // [K][L]
+    double gamma;
+    int64_t *local_t;
+    unsigned *flags;
+};
+
+// Tile t of worker k is summed up (acc: one part per thread).  SCORE 1: the sum is left for k_estimate.
+// SCORE 2: the block that brings the last tile of (worker, layer) adds the layer's tiles and updates the estimate.
+template <int SCORE>
+__device__ __forceinline__ void row_tile_done(const RowScores &a, unsigned k, int t, double acc, double *sm,
+                                              unsigned *sh_last)
+{
+    double tot = block_sum<GRAWA_BLOCK>(acc, sm);
+    double *row = a.partials + (int64_t)k * a.n_tiles;
+    if constexpr (SCORE == 1) {
+        if (threadIdx.x == 0) row[t] = tot;
+        return;
+    }
+    const int l = a.tiles[t].layer;
+    const int first = a.layer_tile0[l], end = a.layer_tile0[l + 1];
+    const int64_t at = (int64_t)k * a.L + l;
+    if (end - first > 1) {
+        if (threadIdx.x == 0) hand_over(row + t, tot);
+        if (!last_to_arrive(a.cnt_kl + at, (unsigned)(end - first), sh_last)) return;
+        double s = 0.0;
+        for (int j = first + (int)threadIdx.x; j < end; j += GRAWA_BLOCK) s += take_over(row + j);
+        tot = block_sum<GRAWA_BLOCK>(s, sm);
+    }
+    if (threadIdx.x == 0) {
+        estimate_step(a.mvg + at, sqrt(tot), a.gamma, a.flags);
+        if (at == 0) *a.local_t += 1;
+    }
+}
+
 // One block = one aligned block of 1024 columns of one worker; V * U * 256 = 1024, a lane handles U
 // vectors of V adjacent columns.  All loads are issued at once, then
 //     x <- x - lr g ;   PROX: x <- x + w (c - x), c the stored center, w = mu/tau ;
-//     SCORE: partials[k][tile] = sum over the tile of g^2 in fp64, from the values in registers.
+//     SCORE: sum over each tile of g^2 in fp64, from the values in registers; 1: left in partials[k][tile] for
+//     k_estimate, 2: taken up to the running estimate inside this launch (see row_tile_done).
 // grid (group, K, n_groups): the column blocks are cut into groups of gridDim.x; blocks are started
 // with x fastest, so within a group the blocks of worker 0 come first, then worker 1, ..., and no
 // index arithmetic is needed to find a block's place.  Blocks that run together therefore stream one
@@ -32,18 +76,14 @@
 // block_tile0[m] .. block_tile0[m+1]-1 lie in aligned block m, each inside one layer).  Nearly
 // every block holds one tile; a block that contains layer boundaries reduces once per tile.
 // The last P % V columns of a row are handled element by element.
-template <typename GT, int V, int U, bool NT, bool PROX, bool SCORE>
+template <typename GT, int V, int U, bool NT, bool PROX, int SCORE>
 __global__ __launch_bounds__(GRAWA_CELL) void k_row_step(float *__restrict__ x, int64_t ldx,
                                                          const GT *__restrict__ g, int64_t ldg, float lr,
                                                          const float *__restrict__ center, float w, int64_t P,
-                                                         unsigned n_blocks,
-                                                         const GrawaTile *__restrict__ tiles,
-                                                         const int32_t *__restrict__ block_tile0, int64_t n_tiles,
-                                                         double *__restrict__ partials)
+                                                         unsigned n_blocks, const RowScores a)
 {
     static_assert(V * U * GRAWA_CELL == GRAWA_ROW_BLOCK, "one trip covers one aligned block of columns");
     typedef typename FloatVec<V>::T XV;
-    __shared__ double sm[GRAWA_BLOCK / GRAWA_WAVE];
     const unsigned k = blockIdx.y;
     const unsigned m = blockIdx.z * gridDim.x + blockIdx.x;
     if (m >= n_blocks) return; // the last group may be short (whole block leaves, before any barrier)
@@ -67,8 +107,8 @@ __global__ __launch_bounds__(GRAWA_CELL) void k_row_step(float *__restrict__ x, 
     }
     int r0 = 0, r1 = 1;
     if (SCORE) {
-        r0 = block_tile0[m];
-        r1 = block_tile0[m + 1];
+        r0 = a.block_tile0[m];
+        r1 = a.block_tile0[m + 1];
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -96,29 +136,29 @@ __global__ __launch_bounds__(GRAWA_CELL) void k_row_step(float *__restrict__ x, 
                 }
         }
     }
-    if (!SCORE) return;
-    double *out = partials + (int64_t)k * n_tiles;
-    if (r1 - r0 == 1) { // the usual case: the whole block lies in one tile
-        double acc = 0.0; // squares and sums in fp64: exact squares at any gradient magnitude
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int e = 0; e < V; ++e) acc = sq_add(gf[u][e], acc);
-        const double tot = block_sum(acc, sm);
-        if (threadIdx.x == 0) out[r0] = tot;
-    } else {
-        for (int t = r0; t < r1; ++t) {
-            const int64_t lo = tiles[t].start, hi = lo + tiles[t].len;
-            double acc = 0.0;
+    if constexpr (SCORE != 0) {
+        __shared__ double sm[GRAWA_BLOCK / GRAWA_WAVE];
+        __shared__ unsigned sh_last;
+        if (r1 - r0 == 1) { // the usual case: the whole block lies in one tile
+            double acc = 0.0; // squares and sums in fp64: exact squares at any gradient magnitude
 #pragma unroll
             for (int u = 0; u < U; ++u)
 #pragma unroll
-                for (int e = 0; e < V; ++e) {
-                    const int64_t c = c0 + (int64_t)u * (GRAWA_CELL * V) + e;
-                    acc = (c >= lo && c < hi) ? sq_add(gf[u][e], acc) : acc;
-                }
-            const double tot = block_sum(acc, sm);
-            if (threadIdx.x == 0) out[t] = tot;
+                for (int e = 0; e < V; ++e) acc = sq_add(gf[u][e], acc);
+            row_tile_done<SCORE>(a, k, r0, acc, sm, &sh_last);
+        } else {
+            for (int t = r0; t < r1; ++t) {
+                const int64_t lo = a.tiles[t].start, hi = lo + a.tiles[t].len;
+                double acc = 0.0;
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int e = 0; e < V; ++e) {
+                        const int64_t c = c0 + (int64_t)u * (GRAWA_CELL * V) + e;
+                        acc = (c >= lo && c < hi) ? sq_add(gf[u][e], acc) : acc;
+                    }
+                row_tile_done<SCORE>(a, k, t, acc, sm, &sh_last);
+            }
         }
     }
 }
@@ -217,18 +257,22 @@ __global__ __launch_bounds__(GRAWA_COPY_BLOCK) void k_stream_copy(v4u *__restric
 // launchers
 // ---------------------------------------------------------------------------------
 
-// center == nullptr: no proximity step.  partials == nullptr: no scores (tiles, block_tile0 and
-// n_tiles are then unused); otherwise they are the plan's 1024-column tile map, its index by
-// aligned block and its length.  Vector shapes: fp32 gradients V = 1, U = 4 for the plain step,
+// Up to here the scored step finishes the estimate in its own launch: the launch it saves is worth more than the
+// device-scope traffic of its blocks (us of a round of 4 scored steps and the communication, two launches a step /
+// one: 1056 blocks 67.8 / 59.1, 2112 65.2 / 57.9, 2344 64.9 / 67.6, 4224 66.4 / 78.9, 15 632 189 / 278).
+#define GRAWA_FUSE_MAX_ROW_BLOCKS 2200
+
+// center == nullptr: no proximity step.  p == nullptr: no scores; otherwise the plan's 1024-column tile map and
+// workspace take them.  Vector shapes: fp32 gradients V = 1, U = 4 for the plain step,
 // V = 4, U = 1 with the proximity step or the scores; bf16 V = 2, U = 2 for the plain step, else
 // V = 4, U = 1 (each the fastest measured for its case on arrays of random values; the spread
 // between shapes is 3-10 %).
-hipError_t grawa_launch_row_step(float *x, int64_t ldx, const void *g, int64_t ldg, grawa_dtype_t dt, float lr,
-                                 const float *center, float w, int K, int64_t P, const GrawaTile *tiles,
-                                 const int32_t *block_tile0, int64_t n_tiles, double *partials, hipStream_t s)
+static hipError_t launch_row_step(const grawa_plan *p, float *x, int64_t ldx, const void *g, int64_t ldg,
+                                  grawa_dtype_t dt, float lr, const float *center, float w, int K, int64_t P,
+                                  double gamma, hipStream_t s)
 {
     const int64_t nb = (P + GRAWA_ROW_BLOCK - 1) / GRAWA_ROW_BLOCK;
-    const bool prox = center != nullptr, score = partials != nullptr;
+    const bool prox = center != nullptr;
     // Nothing is shared between the rows without a center: one group, i.e. row after row (3 % faster).
     const int64_t group = (prox && nb > GRAWA_ROW_GROUP) ? GRAWA_ROW_GROUP : nb;
     const int64_t n_groups = (nb + group - 1) / group;
@@ -236,29 +280,56 @@ hipError_t grawa_launch_row_step(float *x, int64_t ldx, const void *g, int64_t l
     const dim3 grid((unsigned)group, (unsigned)K, (unsigned)n_groups), block(GRAWA_CELL);
     const bool nt = (int64_t)K * P * 4 > GRAWA_STREAMING_MIN_BYTES && rows_line_aligned(x, ldx, 4) &&
                     rows_line_aligned(g, ldg, dt == GRAWA_BF16 ? 2 : 4);
+    RowScores a = {};
+    int score = 0;
+    if (p) {
+        a = RowScores{p->d_rtiles, p->d_block_rtile0, p->d_layer_rtile0, p->L, p->d_partials, p->n_rtiles, p->d_cnt_kl,
+                      p->d_mvg, gamma, p->d_local_t, p->d_flags};
+        score = nb * K <= GRAWA_FUSE_MAX_ROW_BLOCKS ? 2 : 1;
+    }
 #define GRAWA_RS_GO(GT, V, U, NT, PROX, SCORE)                                                                   \
     k_row_step<GT, V, U, NT, PROX, SCORE><<<grid, block, 0, s>>>(x, ldx, (const GT *)g, ldg, lr, center, w, P, \
-                                                                 (unsigned)nb, tiles, block_tile0, n_tiles,    \
-                                                                 partials)
+                                                                 (unsigned)nb, a)
 #define GRAWA_RS_NT(GT, V, U, PROX, SCORE)              \
     do {                                                \
         if (nt) GRAWA_RS_GO(GT, V, U, true, PROX, SCORE); \
         else GRAWA_RS_GO(GT, V, U, false, PROX, SCORE);   \
     } while (0)
+#define GRAWA_RS_SCORE(GT, SCORE)                     \
+    do {                                              \
+        if (prox) GRAWA_RS_NT(GT, 4, 1, true, SCORE); \
+        else GRAWA_RS_NT(GT, 4, 1, false, SCORE);     \
+    } while (0)
     if (dt == GRAWA_BF16) {
-        if (prox && score) GRAWA_RS_NT(uint16_t, 4, 1, true, true);
-        else if (prox) GRAWA_RS_NT(uint16_t, 4, 1, true, false);
-        else if (score) GRAWA_RS_NT(uint16_t, 4, 1, false, true);
-        else GRAWA_RS_NT(uint16_t, 2, 2, false, false);
+        if (score == 2) GRAWA_RS_SCORE(uint16_t, 2);
+        else if (score == 1) GRAWA_RS_SCORE(uint16_t, 1);
+        else if (prox) GRAWA_RS_NT(uint16_t, 4, 1, true, 0);
+        else GRAWA_RS_NT(uint16_t, 2, 2, false, 0);
     } else {
-        if (prox && score) GRAWA_RS_NT(float, 4, 1, true, true);
-        else if (prox) GRAWA_RS_NT(float, 4, 1, true, false);
-        else if (score) GRAWA_RS_NT(float, 4, 1, false, true);
-        else GRAWA_RS_NT(float, 1, 4, false, false);
+        if (score == 2) GRAWA_RS_SCORE(float, 2);
+        else if (score == 1) GRAWA_RS_SCORE(float, 1);
+        else if (prox) GRAWA_RS_NT(float, 4, 1, true, 0);
+        else GRAWA_RS_NT(float, 1, 4, false, 0);
     }
+#undef GRAWA_RS_SCORE
 #undef GRAWA_RS_NT
 #undef GRAWA_RS_GO
-    return hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || score != 1) return e;
+    return grawa_launch_estimate(p, gamma, s);
+}
+
+hipError_t grawa_launch_row_step(float *x, int64_t ldx, const void *g, int64_t ldg, grawa_dtype_t dt, float lr,
+                                 const float *center, float w, int K, int64_t P, hipStream_t s)
+{
+    return launch_row_step(nullptr, x, ldx, g, ldg, dt, lr, center, w, K, P, 0.0, s);
+}
+
+hipError_t grawa_launch_row_step_scored(const grawa_plan *p, float *x, int64_t ldx, const void *g, int64_t ldg,
+                                        grawa_dtype_t dt, float lr, const float *center, float w, double gamma,
+                                        hipStream_t s)
+{
+    return launch_row_step(p, x, ldx, g, ldg, dt, lr, center, w, p->K, p->P, gamma, s);
 }
 
 hipError_t grawa_launch_nesterov(float *x, int64_t ldx, const void *g, int64_t ldg, grawa_dtype_t dt, float *buf,

@@ -1,16 +1,15 @@
 // Gradient norms and weights of the GRAWA update (gfx950, wave64).
 //
 //   k_sumsq            per (tile, worker) sum of squares of the gradient   [eq. (3), (5)]
-//   k_finalize_layers  per layer: tile partials -> ||G||_F^2, ||G||_F, per-layer weights
-//                      (optionally the running estimate of Appendix G)     [eq. (5)-(7)]
-//   k_finalize_model   per worker: model score, model-level weights        [eq. (2)-(4)]
+//   k_finalize_layers  tile sums -> ||G||_F, per-layer or model-level weights [eq. (2)-(7)]
+//   k_estimate         tile sums of a scored step -> running norm estimate [App. G]
 //   k_local_weights    weights from the running norm estimate              [App. G]
-//   k_center_weights   EASGD (uniform) and LSGD (leader) weights           [App. F]
+//   k_leader_weights   LSGD (leader) weights                               [App. F]
 //
 // The norm pass is a read-only stream: it runs fastest with several non-temporal loads per
 // lane in flight and a capped occupancy.  Squares and sums are fp64 throughout, added in a
 // fixed order (no atomics), so results are bit-reproducible.
-#include "grawa_device.h"
+#include "grawa_scores.h"
 
 // ---------------------------------------------------------------------------------
 // gradient norms: per-tile sums of squares
@@ -85,51 +84,16 @@ __global__ __launch_bounds__(GRAWA_BLOCK) __attribute__((amdgpu_waves_per_eu(1, 
     double lane = 0.0;
 #pragma unroll
     for (int u = 0; u < GRAWA_SUMSQ_U; ++u) lane += acc[u];
-    const double total = block_sum(lane, sm);
+    const double total = block_sum<GRAWA_BLOCK>(lane, sm);
     if (tid == 0) partials[(int64_t)k * n_tiles + blockIdx.x] = total;
 }
 
 // ---------------------------------------------------------------------------------
-// weights
+// scores and weights
 // ---------------------------------------------------------------------------------
 
 #define GRAWA_FIN_BLOCK 1024
 #define GRAWA_FIN_WAVES (GRAWA_FIN_BLOCK / GRAWA_WAVE)
-
-// Weights of one group of K scores held in LDS (sA[k], k < K): beta_k proportional to
-// 1/A_k, summing to one, evaluated as (A_min/A_k) / sum_j (A_min/A_j) so that nothing
-// overflows.  Scores of exactly zero share the weight equally and take all of it (the
-// limit A -> 0+).  Called by ONE full wave (all 64 lanes); lanes stride over the workers.
-// A score that is +inf or NaN sets `bit` in the plan's flag word (flags may be null).
-__device__ __forceinline__ void group_weights(const double *sA, int K, float *beta, int64_t stride,
-                                              float *beta_user, unsigned *flags, unsigned bit)
-{
-    const int lane = threadIdx.x & (GRAWA_WAVE - 1);
-    double mn = INFINITY, nz = 0.0, bad = 0.0;
-    for (int k = lane; k < K; k += GRAWA_WAVE) {
-        const double a = sA[k];
-        mn = fmin(mn, a);
-        nz += (a == 0.0) ? 1.0 : 0.0;
-        bad += isfinite(a) ? 0.0 : 1.0;
-    }
-    const double a_min = wave_min(mn);
-    const double n_zero = wave_sum(nz);
-    if (flags && wave_sum(bad) > 0.0 && lane == 0) atomicOr(flags, bit);
-    double z = 0.0;
-    if (n_zero == 0.0)
-        for (int k = lane; k < K; k += GRAWA_WAVE) z += a_min / sA[k];
-    const double zsum = wave_sum(z);
-    for (int k = lane; k < K; k += GRAWA_WAVE) {
-        const double a = sA[k];
-        double b;
-        if (n_zero > 0.0)
-            b = (a == 0.0) ? 1.0 / n_zero : 0.0;
-        else
-            b = (a_min / a) / zsum;
-        beta[(int64_t)k * stride] = (float)b;
-        if (beta_user) beta_user[(int64_t)k * stride] = (float)b;
-    }
-}
 
 // Sum of p[t0 + first], p[t0 + first + step], ... below t1 over the lanes of one wave, four
 // independent loads in flight per lane; every lane gets the total.
@@ -151,20 +115,21 @@ __device__ __forceinline__ double wave_strided_sum(const double *__restrict__ p,
 // grid L, block 1024 (16 waves).  Block l adds the tile partials of layer l for every worker
 // and turns the K layer norms into the K per-layer weights.  With K >= 16 every wave takes
 // workers w, w+16, ...; with fewer workers 16/K waves share one worker's tiles and their
-// results are added in wave order.  All sums are fp64 in a fixed order (no atomics).
+// results are added in wave order.  All sums are fp64 in a fixed order.
+// Model level (goal): the blocks hand their squared norms S[k][l] over, and the last one forms every worker's
+// score (the sum of its layer norms, or the norm of the flattened gradient) and the K weights; as a kernel of its
+// own that last step took 4.7 us and a launch.
 __global__ __launch_bounds__(GRAWA_FIN_BLOCK) void k_finalize_layers(
-    const double *__restrict__ partials, int64_t n_tiles, const int32_t *__restrict__ layer_tile0,
-    int K, int L, double *__restrict__ S, float *__restrict__ A, float *__restrict__ A_user,
-    float *__restrict__ beta, float *__restrict__ beta_user, double *__restrict__ mvg, double gamma,
-    int64_t *__restrict__ local_t, unsigned *__restrict__ flags)
+    const double *__restrict__ partials, int64_t n_tiles, const int32_t *__restrict__ tile_begin,
+    const int32_t *__restrict__ tile_end, int K, int L, int goal, double *__restrict__ S, float *__restrict__ A_user,
+    float *__restrict__ beta, float *__restrict__ beta_user, unsigned *__restrict__ cnt_all,
+    unsigned *__restrict__ flags)
 {
     __shared__ double sA[GRAWA_MAX_WORKERS];
     __shared__ double sw[GRAWA_FIN_WAVES];
+    __shared__ unsigned sh_last;
     const int l = blockIdx.x;
-    // One more local step has fed the running estimate (Appendix G: t <- t + 1).  The counter lives
-    // on the device so that a recorded and replayed call still counts.
-    if (mvg && l == 0 && threadIdx.x == 0) *local_t += 1;
-    const int t0 = layer_tile0[l], t1 = layer_tile0[l + 1];
+    const int t0 = tile_begin[l], t1 = tile_end[l];
     const int lane = threadIdx.x & (GRAWA_WAVE - 1);
     const int wave = threadIdx.x / GRAWA_WAVE;
     if (K >= GRAWA_FIN_WAVES) {
@@ -190,66 +155,125 @@ __global__ __launch_bounds__(GRAWA_FIN_BLOCK) void k_finalize_layers(
         __syncthreads();
     }
     // sA[k] holds the squared norm; publish it, replace it by the norm, then the weights
+    const bool model = goal >= GRAWA_GOAL_MODEL_SUM;
     for (int k = threadIdx.x; k < K; k += GRAWA_FIN_BLOCK) {
         const double s = sA[k];
         const double a = sqrt(s);
-        S[(int64_t)k * L + l] = s;
-        A[(int64_t)k * L + l] = (float)a;
+        if (model) hand_over(S + (int64_t)k * L + l, s);
         if (A_user) A_user[(int64_t)k * L + l] = (float)a;
+        if (goal != GRAWA_GOAL_LAYER_WEIGHTS && flags && !isfinite(a)) atomicOr(flags, GRAWA_NONFINITE_LAYER_SCORE);
         sA[k] = a;
-        // running estimate of Appendix G: g_mvg <- gamma g_mvg + (1 - gamma) g_cur
-        if (mvg) mvg[(int64_t)k * L + l] = gamma * mvg[(int64_t)k * L + l] + (1.0 - gamma) * a;
+    }
+    if (goal == GRAWA_GOAL_SCORES) return;
+    if (!model) {
+        __syncthreads();
+        if (wave == 0) group_weights(sA, K, beta + l, L, beta_user ? beta_user + l : nullptr, flags, GRAWA_NONFINITE_LAYER_SCORE);
+        return;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // every thread's hand-over is acknowledged
+    if (!last_to_arrive(cnt_all, (unsigned)L, &sh_last)) return;
+    for (int k = wave; k < K; k += GRAWA_FIN_WAVES) {
+        double *p = S + (int64_t)k * L;
+        double s = 0.0;
+        for (int j = lane; j < L; j += GRAWA_WAVE) {
+            const double v = take_over(p + j);
+            s += goal == GRAWA_GOAL_MODEL_SUM ? sqrt(v) : v;
+        }
+        s = wave_sum(s);
+        if (goal == GRAWA_GOAL_MODEL_FLAT) s = sqrt(s);
+        if (lane == 0) sA[k] = s;
     }
     __syncthreads();
-    if (wave == 0) group_weights(sA, K, beta + l, L, beta_user ? beta_user + l : nullptr, flags, GRAWA_NONFINITE_LAYER_SCORE);
+    if (wave == 0) group_weights(sA, K, beta, 1, beta_user, flags, GRAWA_NONFINITE_MODEL_SCORE);
+}
+
+// grid (L, min(K, GRAWA_EST_ROWS)), block 512: the tile sums of a scored local step -> running estimate of
+// Appendix G, g_mvg <- gamma g_mvg + (1 - gamma) g_cur, t <- t + 1.  Block (l, y) adds the tiles of layer l for
+// workers y, y + gridDim.y, ....  The tiles of this step are short: with one block per layer the 50 000 tiles
+// of the largest layer of the 350 M transformer for each of 8 workers took 72 us.
+// The counter lives on the device so that a recorded and replayed call still counts.
+#define GRAWA_EST_BLOCK 512
+#define GRAWA_EST_ROWS 64
+__global__ __launch_bounds__(GRAWA_EST_BLOCK) void k_estimate(const double *__restrict__ partials, int64_t n_tiles,
+                                                              const int32_t *__restrict__ layer_tile0, int K, int L,
+                                                              double *__restrict__ mvg, double gamma,
+                                                              int64_t *__restrict__ local_t,
+                                                              unsigned *__restrict__ flags)
+{
+    __shared__ double sm[GRAWA_EST_BLOCK / GRAWA_WAVE];
+    const int l = blockIdx.x;
+    const int t0 = layer_tile0[l], t1 = layer_tile0[l + 1];
+    for (int k = blockIdx.y; k < K; k += gridDim.y) {
+        const double *p = partials + (int64_t)k * n_tiles;
+        double s[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s[u] = 0.0;
+        int t = t0 + (int)threadIdx.x;
+        for (; t + 7 * GRAWA_EST_BLOCK < t1; t += 8 * GRAWA_EST_BLOCK)
+#pragma unroll
+            for (int u = 0; u < 8; ++u) s[u] += p[t + u * GRAWA_EST_BLOCK];
+        for (; t < t1; t += GRAWA_EST_BLOCK) s[0] += p[t];
+        const double tot = block_sum<GRAWA_EST_BLOCK>(((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7])), sm);
+        if (threadIdx.x == 0) estimate_step(mvg + (int64_t)k * L + l, sqrt(tot), gamma, flags);
+    }
+    if (l == 0 && blockIdx.y == 0 && threadIdx.x == 0) *local_t += 1;
 }
 
 // Weights from the running norm estimate g_est = gamma g_mvg / (1 - gamma^t) (Appendix G), t =
-// the device-side count of local steps since the last communication.  per_layer: grid L, block
-// l normalises column l over the workers (eq. (7)); otherwise grid 1: score of worker k is the
-// sum of its layer estimates (eq. (3) applied to the estimates), then eq. (4).  est_user (float
+// the device-side count of local steps since the last communication, and then g_mvg <- 0, t <- 0.
+// per_layer: grid L, block l normalises column l over the workers (eq. (7)); otherwise grid 1: score of worker k
+// is the sum of its layer estimates (eq. (3) applied to the estimates), then eq. (4).  est_user (float
 // [K][L], may be null) receives g_est.  With t = 0 (no step was counted) the estimates are taken
 // as zero, which the zero-norm rule turns into the plain average.
-__global__ __launch_bounds__(GRAWA_FIN_BLOCK) void k_local_weights(const double *__restrict__ mvg, double gamma,
-                                                                   const int64_t *__restrict__ local_t,
-                                                                   int K, int L, int per_layer,
-                                                                   float *__restrict__ beta,
-                                                                   float *__restrict__ beta_user,
-                                                                   float *__restrict__ est_user,
-                                                                   unsigned *__restrict__ flags)
+#define GRAWA_LW_BLOCK 256
+__global__ __launch_bounds__(GRAWA_LW_BLOCK) void k_local_weights(double *__restrict__ mvg, double gamma,
+                                                                  int64_t *__restrict__ local_t, int K, int L,
+                                                                  int per_layer, float *__restrict__ beta,
+                                                                  float *__restrict__ beta_user,
+                                                                  float *__restrict__ est_user,
+                                                                  unsigned *__restrict__ flags,
+                                                                  unsigned *__restrict__ cnt_all)
 {
     __shared__ double sA[GRAWA_MAX_WORKERS];
+    __shared__ unsigned sh_last;
     const int lane = threadIdx.x & (GRAWA_WAVE - 1);
     const int wave = threadIdx.x / GRAWA_WAVE;
     const int64_t t = *local_t;
     const double scale = t > 0 ? gamma / (1.0 - pow(gamma, (double)t)) : 0.0;
     if (per_layer) {
         const int l = blockIdx.x;
-        for (int k = threadIdx.x; k < K; k += GRAWA_FIN_BLOCK) {
-            const double e = scale * mvg[(int64_t)k * L + l];
+        for (int k = threadIdx.x; k < K; k += GRAWA_LW_BLOCK) {
+            const int64_t at = (int64_t)k * L + l;
+            const double e = scale * mvg[at];
             sA[k] = e;
-            if (est_user) est_user[(int64_t)k * L + l] = (float)e;
+            if (est_user) est_user[at] = (float)e;
+            mvg[at] = 0.0;
         }
         __syncthreads();
         if (wave == 0)
             group_weights(sA, K, beta + l, L, beta_user ? beta_user + l : nullptr, flags, GRAWA_NONFINITE_LAYER_SCORE);
+        // every block has read t (its value is in the weights above) before it counts itself in
+        if (last_to_arrive(cnt_all, (unsigned)L, &sh_last) && threadIdx.x == 0) *local_t = 0;
     } else {
-        for (int k = wave; k < K; k += GRAWA_FIN_WAVES) {
+        for (int k = wave; k < K; k += GRAWA_LW_BLOCK / GRAWA_WAVE) {
             double s = 0.0;
             for (int l = lane; l < L; l += GRAWA_WAVE) {
-                const double e = scale * mvg[(int64_t)k * L + l];
+                const int64_t at = (int64_t)k * L + l;
+                const double e = scale * mvg[at];
                 s += e;
-                if (est_user) est_user[(int64_t)k * L + l] = (float)e;
+                if (est_user) est_user[at] = (float)e;
+                mvg[at] = 0.0;
             }
             s = wave_sum(s);
             if (lane == 0) sA[k] = s;
         }
-        __syncthreads();
+        __syncthreads(); // also: every thread has read t
+        if (threadIdx.x == 0) *local_t = 0;
         if (wave == 0) group_weights(sA, K, beta, 1, beta_user, flags, GRAWA_NONFINITE_MODEL_SCORE);
     }
 }
 
-// g_mvg <- 0 and t <- 0 (after a communication, or an explicit reset).
+// g_mvg <- 0 and t <- 0 (an explicit reset).
 __global__ __launch_bounds__(GRAWA_BLOCK) void k_zero_estimate(double *__restrict__ p, int64_t n,
                                                                int64_t *__restrict__ local_t)
 {
@@ -258,58 +282,43 @@ __global__ __launch_bounds__(GRAWA_BLOCK) void k_zero_estimate(double *__restric
     if (i == 0) *local_t = 0;
 }
 
-// grid 1, block 1024.  Model-level score per worker from the [K][L] squared layer norms:
-// mode 0: sum of the layer norms; mode 1: norm of the flattened gradient.  Then the K weights.
-__global__ __launch_bounds__(GRAWA_FIN_BLOCK) void k_finalize_model(const double *__restrict__ S, int K,
-                                                                    int L, int mode,
-                                                                    float *__restrict__ beta,
-                                                                    float *__restrict__ beta_user,
-                                                                    unsigned *__restrict__ flags)
-{
-    __shared__ double sA[GRAWA_MAX_WORKERS];
-    const int lane = threadIdx.x & (GRAWA_WAVE - 1);
-    const int wave = threadIdx.x / GRAWA_WAVE;
-    for (int k = wave; k < K; k += GRAWA_FIN_WAVES) {
-        const double *p = S + (int64_t)k * L;
-        double s = 0.0;
-        if (mode == GRAWA_NORM_LAYERSUM)
-            for (int l = lane; l < L; l += GRAWA_WAVE) s += sqrt(p[l]);
-        else
-            for (int l = lane; l < L; l += GRAWA_WAVE) s += p[l];
-        s = wave_sum(s);
-        if (mode != GRAWA_NORM_LAYERSUM) s = sqrt(s);
-        if (lane == 0) sA[k] = s;
-    }
-    __syncthreads();
-    if (wave == 0) group_weights(sA, K, beta, 1, beta_user, flags, GRAWA_NONFINITE_MODEL_SCORE);
-}
-
 // flag word <- 0
 __global__ void k_clear_flags(unsigned *__restrict__ flags)
 {
     if (blockIdx.x == 0 && threadIdx.x == 0) *flags = 0u;
 }
 
-// Weights of the competing centers of Appendix F, written where the pull kernel reads its
-// model-level weights.  loss == nullptr: EASGD, every worker 1/K.  Otherwise LSGD: weight 1 for
-// the worker with the smallest loss (the first one on ties), 0 for the rest; its index goes to
-// leader_out when given.  One thread: K is at most 1024.
-__global__ void k_center_weights(const float *__restrict__ loss, int K, float *__restrict__ beta,
-                                 float *__restrict__ beta_user, int *__restrict__ leader_out)
+// Weights of the LSGD center (Appendix F), written where the pull kernel reads its model-level
+// weights: 1 for the worker with the smallest loss (the first one on ties), 0 for the rest; its index goes to
+// leader_out when given.  A NaN loss never leads, except that worker 0 leads when its own loss is NaN (the rule
+// of a scan that starts at worker 0 and moves on strictly smaller losses).  One wave: a lane scans the workers
+// lane, lane + 64, ..., then the lanes are combined (4.9 us with one thread for K = 4, dominated by its
+// chain of loads).
+__global__ __launch_bounds__(GRAWA_WAVE) void k_leader_weights(const float *__restrict__ loss, int K,
+                                                              float *__restrict__ beta, int *__restrict__ leader_out)
 {
-    if (blockIdx.x != 0 || threadIdx.x != 0) return;
-    int best = -1;
-    if (loss) {
-        best = 0;
-        for (int k = 1; k < K; ++k)
-            if (loss[k] < loss[best]) best = k;
-        if (leader_out) *leader_out = best;
+    const int lane = threadIdx.x;
+    int best = K;
+    float low = INFINITY;
+    for (int k = lane; k < K; k += GRAWA_WAVE) {
+        const float v = loss[k];
+        if (v < low || (v == low && best == K)) { // the second: a loss of +inf may still lead
+            low = v;
+            best = k;
+        }
     }
-    for (int k = 0; k < K; ++k) {
-        const float b = loss ? (k == best ? 1.f : 0.f) : 1.f / (float)K;
-        beta[k] = b;
-        if (beta_user) beta_user[k] = b;
+    for (int m = 1; m < GRAWA_WAVE; m <<= 1) {
+        const float v = __shfl_xor(low, m, GRAWA_WAVE);
+        const int k = __shfl_xor(best, m, GRAWA_WAVE);
+        if (k < K && (best == K || v < low || (v == low && k < best))) {
+            low = v;
+            best = k;
+        }
     }
+    const float first = loss[0];
+    if (best == K || !(first == first)) best = 0;
+    if (lane == 0 && leader_out) *leader_out = best;
+    for (int k = lane; k < K; k += GRAWA_WAVE) beta[k] = k == best ? 1.f : 0.f;
 }
 
 // ---------------------------------------------------------------------------------
@@ -331,24 +340,29 @@ hipError_t grawa_launch_sumsq(const grawa_plan *p, const void *g, int64_t ldg, g
     return hipGetLastError();
 }
 
-// update_estimate != 0: the partials come from the local step (short-tile map) and the running
-// norm estimate is updated with the new norms.
-hipError_t grawa_launch_finalize_layers(const grawa_plan *p, float *norms_user, float *beta_user,
-                                        hipStream_t s, int update_estimate, double gamma)
+hipError_t grawa_launch_finalize_layers(const grawa_plan *p, int goal, float *norms_user, float *beta_user,
+                                        hipStream_t s)
 {
     k_finalize_layers<<<dim3((unsigned)p->L), dim3(GRAWA_FIN_BLOCK), 0, s>>>(
-        p->d_partials, update_estimate ? p->n_rtiles : p->n_tiles,
-        update_estimate ? p->d_layer_rtile0 : p->d_layer_tile0, p->K, p->L, p->d_S, p->d_A, norms_user,
-        p->d_beta_layer, beta_user, update_estimate ? p->d_mvg : nullptr, gamma, p->d_local_t, p->d_flags);
+        p->d_partials, p->n_tiles, p->d_layer_tile0, p->d_layer_tile1, p->K, p->L, goal, p->d_S, norms_user,
+        goal == GRAWA_GOAL_LAYER_WEIGHTS ? p->d_beta_layer : p->d_beta_model, beta_user, p->d_cnt_all, p->d_flags);
+    return hipGetLastError();
+}
+
+hipError_t grawa_launch_estimate(const grawa_plan *p, double gamma, hipStream_t s)
+{
+    const unsigned rows = p->K < GRAWA_EST_ROWS ? (unsigned)p->K : (unsigned)GRAWA_EST_ROWS;
+    k_estimate<<<dim3((unsigned)p->L, rows), dim3(GRAWA_EST_BLOCK), 0, s>>>(
+        p->d_partials, p->n_rtiles, p->d_layer_rtile0, p->K, p->L, p->d_mvg, gamma, p->d_local_t, p->d_flags);
     return hipGetLastError();
 }
 
 hipError_t grawa_launch_local_weights(const grawa_plan *p, double gamma, int per_layer, float *beta_user,
                                       float *est_user, hipStream_t s)
 {
-    k_local_weights<<<dim3(per_layer ? (unsigned)p->L : 1u), dim3(GRAWA_FIN_BLOCK), 0, s>>>(
+    k_local_weights<<<dim3(per_layer ? (unsigned)p->L : 1u), dim3(GRAWA_LW_BLOCK), 0, s>>>(
         p->d_mvg, gamma, p->d_local_t, p->K, p->L, per_layer, per_layer ? p->d_beta_layer : p->d_beta_model,
-        beta_user, est_user, p->d_flags);
+        beta_user, est_user, p->d_flags, p->d_cnt_all);
     return hipGetLastError();
 }
 
@@ -360,23 +374,14 @@ hipError_t grawa_launch_zero_estimate(const grawa_plan *p, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t grawa_launch_finalize_model(const grawa_plan *p, grawa_norm_mode_t mode, float *beta_user,
-                                       hipStream_t s)
-{
-    k_finalize_model<<<dim3(1), dim3(GRAWA_FIN_BLOCK), 0, s>>>(p->d_S, p->K, p->L, (int)mode,
-                                                          p->d_beta_model, beta_user, p->d_flags);
-    return hipGetLastError();
-}
-
 hipError_t grawa_launch_clear_flags(const grawa_plan *p, hipStream_t s)
 {
     k_clear_flags<<<dim3(1), dim3(GRAWA_WAVE), 0, s>>>(p->d_flags);
     return hipGetLastError();
 }
 
-hipError_t grawa_launch_center_weights(const grawa_plan *p, const float *loss, float *beta_user, int *leader_out,
-                                       hipStream_t s)
+hipError_t grawa_launch_leader_weights(const grawa_plan *p, const float *loss, int *leader_out, hipStream_t s)
 {
-    k_center_weights<<<dim3(1), dim3(GRAWA_WAVE), 0, s>>>(loss, p->K, p->d_beta_model, beta_user, leader_out);
+    k_leader_weights<<<dim3(1), dim3(GRAWA_WAVE), 0, s>>>(loss, p->K, p->d_beta_model, leader_out);
     return hipGetLastError();
 }

@@ -7,7 +7,7 @@
 // 256-byte piece of every row (one 32-bit element per lane per row), blocks are small and many,
 // and accesses are non-temporal -- provided every row starts on a 128-byte boundary, so that no
 // cache line is written in two parts.  There is no dense contraction, hence no matrix-core code.
-#include "grawa_device.h"
+#include "grawa_scores.h"
 
 // ---------------------------------------------------------------------------------
 // center + pull (+ SGD on the way in)
@@ -19,6 +19,98 @@ __device__ __forceinline__ int layer_of(const int64_t *__restrict__ off, int lay
     while (layer + 1 < L && off[layer + 1] <= i) ++layer;
     return layer;
 }
+
+// Per-layer weights straight from the tile sums of the norm pass, computed by every block for the layers of its own
+// cell (TILES).  A small update is a chain of short launches, and this one drops a link: for 270 k parameters and
+// 4 workers the weights as a launch of their own took 4.0 us plus the boundary.  The loads of x are in flight
+// meanwhile.  K <= 64; every wave of the block takes one layer at a time; the layer's first cell writes weights_out.
+struct TileWeights {
+    const double *partials;
+    int64_t pitch;
+    const int32_t *tile_begin, *tile_end; // [L]
+    float *weights_out;                   // [K][L] or null
+    unsigned *flags;
+    int group;                            // lanes per worker: the largest power of two not above 64 / K
+};
+
+#define GRAWA_CELL_BETAS 2048  // weights of one cell kept in LDS
+#define GRAWA_CELL_LAYERS 64   // layers of one cell kept in LDS; beyond either, every lane works for itself
+struct CellWeights {
+    float beta[GRAWA_CELL_BETAS]; // [layer of the cell][K]
+    int start[GRAWA_CELL_LAYERS]; // first column of the layer, relative to the cell
+};
+
+// Fills `sh` for the cell at column cell0 whose first layer is l0; returns the number of layers, or 0 if they do not
+// fit.  Called by the whole block; ends with a barrier.
+__device__ __forceinline__ int cell_weights(const TileWeights &w, const int64_t *__restrict__ off, int L, int K,
+                                            int64_t P, int64_t cell0, int l0, bool boundary, int waves, CellWeights &sh)
+{
+    const int lane = threadIdx.x & (GRAWA_WAVE - 1);
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / GRAWA_WAVE));
+    int nl = 1;
+    if (boundary) {
+        const int64_t end = cell0 + GRAWA_CELL < P ? cell0 + GRAWA_CELL : P;
+        for (int l = l0 + 1;; l += GRAWA_WAVE) {
+            const unsigned long long in = __ballot(l + lane < L && off[l + lane] < end);
+            nl += __popcll(in);
+            if (in != ~0ull) break;
+        }
+    }
+    if (nl > GRAWA_CELL_LAYERS || nl * K > GRAWA_CELL_BETAS) return 0;
+    if (wave == 0 && lane < nl) sh.start[lane] = lane ? (int)(off[l0 + lane] - cell0) : 0;
+    for (int i = wave; i < nl; i += waves) {
+        const int l = l0 + i;
+        wave_layer_weights(w.partials, w.pitch, w.tile_begin[l], w.tile_end[l], K, w.group, sh.beta + i * K,
+                           off[l] >= cell0, w.weights_out ? w.weights_out + l : nullptr, L, w.flags);
+    }
+    __syncthreads();
+    return nl;
+}
+
+// Which of the nl layers of the cell column `col` (relative to the cell) lies in.
+__device__ __forceinline__ int cell_layer_of(const CellWeights &sh, int nl, int col)
+{
+    int i = 0;
+    for (int j = 1; j < nl; ++j) i += sh.start[j] <= col ? 1 : 0;
+    return i;
+}
+
+// One lane's own way to the weights of layer l (cells with more layers than the table above holds).
+struct LaneWeights {
+    const double *p;
+    int64_t pitch;
+    int t0, t1;
+    double a_min, n_zero, z;
+    __device__ __forceinline__ double score(int k) const
+    {
+        double s = 0.0;
+        for (int t = t0; t < t1; ++t) s += p[(int64_t)k * pitch + t];
+        return sqrt(s);
+    }
+    __device__ __forceinline__ LaneWeights(const TileWeights &w, int l, int K)
+        : p(w.partials), pitch(w.pitch), t0(w.tile_begin[l]), t1(w.tile_end[l]), a_min(INFINITY), n_zero(0.0), z(0.0)
+    {
+        for (int k = 0; k < K; ++k) {
+            const double a = score(k);
+            a_min = fmin(a_min, a);
+            n_zero += a == 0.0 ? 1.0 : 0.0;
+        }
+        if (n_zero == 0.0)
+            for (int k = 0; k < K; ++k) z += a_min / score(k);
+    }
+    __device__ __forceinline__ float beta(int k) const
+    {
+        const double a = score(k);
+        return (float)(n_zero > 0.0 ? (a == 0.0 ? 1.0 / n_zero : 0.0) : (a_min / a) / z);
+    }
+    __device__ __forceinline__ void publish(const TileWeights &w, int l, int K, int L) const
+    {
+        for (int k = 0; k < K; ++k) {
+            if (w.weights_out) w.weights_out[(int64_t)k * L + l] = beta(k);
+            if (w.flags && !isfinite(score(k))) atomicOr(w.flags, GRAWA_NONFINITE_LAYER_SCORE);
+        }
+    }
+};
 
 // Plain form, K <= 23 (16 without the SGD step excepted).  grid ceil(P/256), block 256: a lane owns one
 // column.  It loads x[k][i] for its K workers (all loads in flight together; with SGD also g[k][i] and
@@ -35,12 +127,12 @@ __device__ __forceinline__ int layer_of(const int64_t *__restrict__ off, int lay
 // WPE caps the waves per SIMD: the form is fastest with roughly 32-48 row loads in flight per
 // SIMD (K x WPE); more only queues requests to K far-apart rows and costs DRAM efficiency
 // (measured: K = 16 at 3 waves 6.1 TB/s, at 8 waves 5.7; K = 8 at 4 waves 6.5, at 8 waves 6.2).
-template <int K, bool SGD, typename GT, bool NT, int WPE>
+template <int K, bool SGD, typename GT, bool NT, int WPE, bool TILES>
 __global__ __launch_bounds__(GRAWA_CELL) __attribute__((amdgpu_waves_per_eu(1, WPE))) void k_center_pull(
     float *__restrict__ x, int64_t ldx, const GT *__restrict__ g, int64_t ldg, float lr,
     const float *__restrict__ beta, int64_t beta_stride, const int32_t *__restrict__ cell_layer,
     const int64_t *__restrict__ off, int L, int64_t P, float lambda,
-    float *__restrict__ center_out, float rho, int moving)
+    float *__restrict__ center_out, float rho, int moving, const TileWeights tw)
 {
     const int64_t cell0 = (int64_t)blockIdx.x * GRAWA_CELL; // wave-uniform
     const unsigned col = threadIdx.x;
@@ -66,7 +158,22 @@ __global__ __launch_bounds__(GRAWA_CELL) __attribute__((amdgpu_waves_per_eu(1, W
 
     const int info = cell_layer ? cell_layer[blockIdx.x] : 0;
     float c = 0.f;
-    if (info >= 0) { // one layer for the whole cell: weights through scalar loads
+    if constexpr (TILES) {
+        __shared__ CellWeights cw;
+        const int l0 = info >= 0 ? info : ~info;
+        const int nl = cell_weights(tw, off, L, K, P, cell0, l0, info < 0, GRAWA_CELL / GRAWA_WAVE, cw);
+        if (nl > 0) {
+            const float *b = cw.beta + (nl > 1 ? cell_layer_of(cw, nl, (int)col) * K : 0);
+#pragma unroll
+            for (int k = 0; k < K; ++k) c = fmaf(b[k], v[k], c);
+        } else if (ok) {
+            const int l = layer_of(off, l0, L, cell0 + col);
+            const LaneWeights lw(tw, l, K);
+#pragma unroll
+            for (int k = 0; k < K; ++k) c = fmaf(lw.beta(k), v[k], c);
+            if (off[l] == cell0 + col) lw.publish(tw, l, K, L);
+        }
+    } else if (info >= 0) { // one layer for the whole cell: weights through scalar loads
         const uint64_t bb = uniform_base(beta + info);
 #pragma unroll
         for (int k = 0; k < K; ++k) c = fmaf(ld_uniform_f32(bb, (int64_t)k * beta_stride), v[k], c);
@@ -270,16 +377,17 @@ constexpr int grawa_waves_for(int k, bool sgd)
 
 #define GRAWA_CP_ARGS                                                                                                 \
     const grawa_plan *p, float *x, int64_t ldx, const void *g, int64_t ldg, float lr, const float *beta, int per_layer, \
-        float lambda, float *center_out, float rho, int moving, hipStream_t s, hipEvent_t e0, hipEvent_t e1
-#define GRAWA_CP_PASS p, x, ldx, g, ldg, lr, beta, per_layer, lambda, center_out, rho, moving, s, e0, e1
+        float lambda, float *center_out, float rho, int moving, const TileWeights &tw, hipStream_t s, hipEvent_t e0,     \
+        hipEvent_t e1
+#define GRAWA_CP_PASS p, x, ldx, g, ldg, lr, beta, per_layer, lambda, center_out, rho, moving, tw, s, e0, e1
 #define GRAWA_CP_STRIDE per_layer ? (int64_t)p->L : (int64_t)1
 #define GRAWA_CP_CELLS per_layer ? (const int32_t *)p->d_cell_layer : (const int32_t *)nullptr
 
-template <int K, bool SGD, typename GT, bool NT> static void launch_plain(GRAWA_CP_ARGS)
+template <int K, bool SGD, typename GT, bool NT, bool TILES> static void launch_plain(GRAWA_CP_ARGS)
 {
-    hipExtLaunchKernelGGL((k_center_pull<K, SGD, GT, NT, grawa_waves_for(K, SGD)>), dim3((unsigned)p->n_cells),
+    hipExtLaunchKernelGGL((k_center_pull<K, SGD, GT, NT, grawa_waves_for(K, SGD), TILES>), dim3((unsigned)p->n_cells),
                           dim3(GRAWA_CELL), 0, s, e0, e1, 0, x, ldx, (const GT *)g, ldg, lr, beta, GRAWA_CP_STRIDE,
-                          GRAWA_CP_CELLS, (const int64_t *)p->d_off, p->L, p->P, lambda, center_out, rho, moving);
+                          GRAWA_CP_CELLS, (const int64_t *)p->d_off, p->L, p->P, lambda, center_out, rho, moving, tw);
 }
 
 template <int Q, bool REM, int S, int V, bool SGD, typename GT, bool NT> static void launch_split(GRAWA_CP_ARGS)
@@ -295,20 +403,19 @@ template <int Q, bool REM, int S, int V, bool SGD, typename GT, bool NT> static 
 template <bool SGD, typename GT, bool NT> static void dispatch_cp(GRAWA_CP_ARGS)
 {
 #define GRAWA_CP_PLAIN(N) \
-    case N: launch_plain<N, SGD, GT, NT>(GRAWA_CP_PASS); return;
-#define GRAWA_CP_SPLIT(N)                                                        \
-    case N:                                                                      \
+    case N: launch_plain<N, SGD, GT, NT, false>(GRAWA_CP_PASS); return;
+#define GRAWA_CP_SPLIT(N)                                                            \
+    case N:                                                                          \
         if (p->K % 8 == 0) launch_split<N, false, 8, 2, SGD, GT, NT>(GRAWA_CP_PASS); \
-        else launch_split<N, true, 8, 2, SGD, GT, NT>(GRAWA_CP_PASS);            \
+        else launch_split<N, true, 8, 2, SGD, GT, NT>(GRAWA_CP_PASS);                \
         return;
     switch (p->K) {
         GRAWA_CP_PLAIN(1) GRAWA_CP_PLAIN(2) GRAWA_CP_PLAIN(3) GRAWA_CP_PLAIN(4) GRAWA_CP_PLAIN(5) GRAWA_CP_PLAIN(6)
         GRAWA_CP_PLAIN(7) GRAWA_CP_PLAIN(8) GRAWA_CP_PLAIN(9) GRAWA_CP_PLAIN(10) GRAWA_CP_PLAIN(11) GRAWA_CP_PLAIN(12)
         GRAWA_CP_PLAIN(13) GRAWA_CP_PLAIN(14) GRAWA_CP_PLAIN(15) GRAWA_CP_PLAIN(17) GRAWA_CP_PLAIN(18)
-        GRAWA_CP_PLAIN(19) GRAWA_CP_PLAIN(20) GRAWA_CP_PLAIN(21) GRAWA_CP_PLAIN(22)
-        GRAWA_CP_PLAIN(23)
+        GRAWA_CP_PLAIN(19) GRAWA_CP_PLAIN(20) GRAWA_CP_PLAIN(21) GRAWA_CP_PLAIN(22) GRAWA_CP_PLAIN(23)
     case 16:
-        if constexpr (SGD) launch_plain<16, SGD, GT, NT>(GRAWA_CP_PASS);
+        if constexpr (SGD) launch_plain<16, SGD, GT, NT, false>(GRAWA_CP_PASS);
         else launch_split<4, false, 4, 1, SGD, GT, NT>(GRAWA_CP_PASS);
         return;
     }
@@ -322,24 +429,55 @@ template <bool SGD, typename GT, bool NT> static void dispatch_cp(GRAWA_CP_ARGS)
 #undef GRAWA_CP_SPLIT
 }
 
+// Weights straight from the tile sums: K <= 15 (grawa_pull_from_tiles), cached accesses.
+template <bool SGD, typename GT> static void dispatch_cp_tiles(GRAWA_CP_ARGS)
+{
+#define GRAWA_CP_TILES(N) \
+    case N: launch_plain<N, SGD, GT, false, true>(GRAWA_CP_PASS); return;
+    switch (p->K) {
+        GRAWA_CP_TILES(1) GRAWA_CP_TILES(2) GRAWA_CP_TILES(3) GRAWA_CP_TILES(4) GRAWA_CP_TILES(5) GRAWA_CP_TILES(6)
+        GRAWA_CP_TILES(7) GRAWA_CP_TILES(8) GRAWA_CP_TILES(9) GRAWA_CP_TILES(10) GRAWA_CP_TILES(11) GRAWA_CP_TILES(12)
+        GRAWA_CP_TILES(13) GRAWA_CP_TILES(14) GRAWA_CP_TILES(15)
+    }
+#undef GRAWA_CP_TILES
+}
+
+// Where every block works the weights out for itself instead of a launch of its own doing it once.  The extra work
+// grows with the blocks and the workers, what it saves is one launch (us per LGRAWA update, with the launch and
+// without): 4 workers x 270 k columns 16.1 / 13.7, 8 x 270 k 16.0 / 14.6, 4 x 600 k 15.8 / 13.9; a draw at
+// 16 x 270 k (20.5 / 20.1); slower from 4 x 1.2 M (20.3 / 20.8) on, 16 x 600 k 31.6 / 33.8.
+#define GRAWA_TILES_MAX_CELLS 10240 // cells times workers
+bool grawa_pull_from_tiles(const grawa_plan *p)
+{
+    return p->K <= 15 && p->n_cells * p->K <= GRAWA_TILES_MAX_CELLS;
+}
+
 hipError_t grawa_launch_center_pull(const grawa_plan *p, float *x, int64_t ldx, const float *beta,
                                     int per_layer, float lambda, const void *g_sgd, int64_t ldg_sgd,
                                     grawa_dtype_t dt, float lr, int fuse_sgd, float *center_out, float rho,
-                                    int moving, hipStream_t s, hipEvent_t e0, hipEvent_t e1)
+                                    int moving, float *weights_out, hipStream_t s, hipEvent_t e0, hipEvent_t e1)
 {
+    TileWeights tw = {};
+    if (!beta) {
+        int group = GRAWA_WAVE;
+        while (group * p->K > GRAWA_WAVE) group >>= 1;
+        tw = TileWeights{p->d_partials, p->n_tiles, p->d_layer_tile0, p->d_layer_tile1, weights_out, p->d_flags, group};
+    }
     // Streaming accesses pay off only when the arrays do not fit the last-level cache anyway.
-    bool nt = (int64_t)p->K * p->P * 4 > GRAWA_STREAMING_MIN_BYTES && rows_line_aligned(x, ldx, 4) &&
+    bool nt = beta && (int64_t)p->K * p->P * 4 > GRAWA_STREAMING_MIN_BYTES && rows_line_aligned(x, ldx, 4) &&
               (!center_out || rows_line_aligned(center_out, 0, 4));
     if (fuse_sgd) nt = nt && rows_line_aligned(g_sgd, ldg_sgd, dt == GRAWA_BF16 ? 2 : 4);
-    if (!fuse_sgd) {
-        if (nt) dispatch_cp<false, float, true>(p, x, ldx, nullptr, 0, 0.f, beta, per_layer, lambda, center_out, rho, moving, s, e0, e1);
-        else dispatch_cp<false, float, false>(p, x, ldx, nullptr, 0, 0.f, beta, per_layer, lambda, center_out, rho, moving, s, e0, e1);
-    } else if (dt == GRAWA_BF16) {
-        if (nt) dispatch_cp<true, uint16_t, true>(p, x, ldx, g_sgd, ldg_sgd, lr, beta, per_layer, lambda, center_out, rho, moving, s, e0, e1);
-        else dispatch_cp<true, uint16_t, false>(p, x, ldx, g_sgd, ldg_sgd, lr, beta, per_layer, lambda, center_out, rho, moving, s, e0, e1);
-    } else {
-        if (nt) dispatch_cp<true, float, true>(p, x, ldx, g_sgd, ldg_sgd, lr, beta, per_layer, lambda, center_out, rho, moving, s, e0, e1);
-        else dispatch_cp<true, float, false>(p, x, ldx, g_sgd, ldg_sgd, lr, beta, per_layer, lambda, center_out, rho, moving, s, e0, e1);
-    }
+    const void *g = g_sgd;
+    const int64_t ldg = ldg_sgd;
+#define GRAWA_CP_GO(SGD, GT)                                                 \
+    do {                                                                     \
+        if (!beta) dispatch_cp_tiles<SGD, GT>(GRAWA_CP_PASS);                \
+        else if (nt) dispatch_cp<SGD, GT, true>(GRAWA_CP_PASS);              \
+        else dispatch_cp<SGD, GT, false>(GRAWA_CP_PASS);                     \
+    } while (0)
+    if (!fuse_sgd) GRAWA_CP_GO(false, float);
+    else if (dt == GRAWA_BF16) GRAWA_CP_GO(true, uint16_t);
+    else GRAWA_CP_GO(true, float);
+#undef GRAWA_CP_GO
     return hipGetLastError();
 }

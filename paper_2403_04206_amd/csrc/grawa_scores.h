@@ -1,0 +1,117 @@
+// From tile sums to scores and weights on the device (gfx950, wave64): the weight formula, and the pieces that
+// let one launch do what needs a second one otherwise.
+//
+// Values pass between blocks of one launch (which may run on different XCDs, each with an L2 of its own) only
+// through device-scope atomic read-modify-writes, which always act on the latest value.  The thread that hands
+// a value over waits for its acknowledgement before it counts its block in, and the block that arrives last
+// reads after its count has returned.  No block ever waits for another: one that is not last leaves, so nothing
+// depends on which blocks are resident and nothing can hang.  Which block comes last varies from run to run;
+// what it adds and in which order does not, so results are bit-reproducible.  Release and acquire fences at
+// device scope would do instead of the read-modify-writes, but write back and invalidate a whole L2 per block
+// (one acquire per layer alone: 16 us instead of 8 for the norm pass of a 270 k-parameter model).
+#pragma once
+#include "grawa_device.h"
+
+__device__ __forceinline__ void hand_over(double *p, double v)
+{
+    (void)__hip_atomic_exchange(reinterpret_cast<unsigned long long *>(p), (unsigned long long)__double_as_longlong(v),
+                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double take_over(double *p)
+{
+    return __longlong_as_double((long long)__hip_atomic_fetch_add(reinterpret_cast<unsigned long long *>(p), 0ull,
+                                                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+
+// Counts the block in; true in every thread of the block that is the n-th.  What the block publishes was
+// handed over by thread 0 before the call.  The last arriver leaves the counter at zero for the next call.
+// `sh` is one word of LDS.
+__device__ __forceinline__ bool last_to_arrive(unsigned *counter, unsigned n, unsigned *sh)
+{
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        const unsigned before = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const bool last = before == n - 1;
+        if (last) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        *sh = last ? 1u : 0u;
+    }
+    __syncthreads();
+    return *sh != 0u;
+}
+
+// Weights of one group of K scores held in LDS (sA[k], k < K): beta_k proportional to
+// 1/A_k, summing to one, evaluated as (A_min/A_k) / sum_j (A_min/A_j) so that nothing
+// overflows.  Scores of exactly zero share the weight equally and take all of it (the
+// limit A -> 0+).  Called by ONE full wave (all 64 lanes); lanes stride over the workers.
+// A score that is +inf or NaN sets `bit` in the plan's flag word (flags may be null).
+__device__ __forceinline__ void group_weights(const double *sA, int K, float *beta, int64_t stride,
+                                              float *beta_user, unsigned *flags, unsigned bit)
+{
+    const int lane = threadIdx.x & (GRAWA_WAVE - 1);
+    double mn = INFINITY, nz = 0.0, bad = 0.0;
+    for (int k = lane; k < K; k += GRAWA_WAVE) {
+        const double a = sA[k];
+        mn = fmin(mn, a);
+        nz += (a == 0.0) ? 1.0 : 0.0;
+        bad += isfinite(a) ? 0.0 : 1.0;
+    }
+    const double a_min = wave_min(mn);
+    const double n_zero = wave_sum(nz);
+    if (flags && wave_sum(bad) > 0.0 && lane == 0) atomicOr(flags, bit);
+    double z = 0.0;
+    if (n_zero == 0.0)
+        for (int k = lane; k < K; k += GRAWA_WAVE) z += a_min / sA[k];
+    const double zsum = wave_sum(z);
+    for (int k = lane; k < K; k += GRAWA_WAVE) {
+        const double a = sA[k];
+        double b;
+        if (n_zero > 0.0)
+            b = (a == 0.0) ? 1.0 / n_zero : 0.0;
+        else
+            b = (a_min / a) / zsum;
+        beta[(int64_t)k * stride] = (float)b;
+        if (beta_user) beta_user[(int64_t)k * stride] = (float)b;
+    }
+}
+
+// The same weights for one layer straight from its tile sums, by one full wave (K <= 64): `group` = the largest
+// power of two not above 64 / K lanes share a worker's tiles t0 .. t1 - 1.  out[k] (LDS) receives beta_k;
+// beta_user[k * L] too if not null, and a score that is not finite is flagged then.
+__device__ __forceinline__ void wave_layer_weights(const double *__restrict__ partials, int64_t pitch, int t0, int t1,
+                                                   int K, int group, float *out, bool owner, float *beta_user, int L,
+                                                   unsigned *flags)
+{
+    const int lane = threadIdx.x & (GRAWA_WAVE - 1);
+    const int k = lane / group, i = lane % group;
+    const bool active = k < K, head = active && i == 0;
+    const double *p = partials + (int64_t)(active ? k : 0) * pitch;
+    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+    int t = t0 + i;
+    for (; t + 3 * group < t1; t += 4 * group) {
+        s0 += p[t];
+        s1 += p[t + group];
+        s2 += p[t + 2 * group];
+        s3 += p[t + 3 * group];
+    }
+    for (; t < t1; t += group) s0 += p[t];
+    double s = (s0 + s1) + (s2 + s3);
+    for (int m = 1; m < group; m <<= 1) s += __shfl_xor(s, m, GRAWA_WAVE);
+    const double a = sqrt(s);
+    const double a_min = wave_min(active ? a : (double)INFINITY);
+    const double n_zero = wave_sum(head && a == 0.0 ? 1.0 : 0.0);
+    const double z = wave_sum(head && n_zero == 0.0 ? a_min / a : 0.0);
+    if (head) {
+        const double b = n_zero > 0.0 ? (a == 0.0 ? 1.0 / n_zero : 0.0) : (a_min / a) / z;
+        out[k] = (float)b;
+        if (owner && beta_user) beta_user[(int64_t)k * L] = (float)b;
+        if (owner && flags && !isfinite(a)) atomicOr(flags, GRAWA_NONFINITE_LAYER_SCORE);
+    }
+}
+
+// Running estimate of Appendix G for one (worker, layer): g_mvg <- gamma g_mvg + (1 - gamma) g_cur.
+__device__ __forceinline__ void estimate_step(double *mvg, double norm, double gamma, unsigned *flags)
+{
+    *mvg = gamma * *mvg + (1.0 - gamma) * norm;
+    if (flags && !isfinite(norm)) atomicOr(flags, GRAWA_NONFINITE_LAYER_SCORE);
+}

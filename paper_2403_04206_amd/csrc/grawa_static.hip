@@ -1,7 +1,7 @@
 // LGRAWA update for callers that cannot allocate device memory (code under HIP graph capture,
 // tight serving loops, harnesses that forbid hipMalloc): the same kernels as grawa_lgrawa_update,
 // with the plan's workspace replaced by a fixed array that lives in the library's device image.
-// The index maps a plan builds on the host are built here by two small kernels from layer
+// The index maps a plan builds on the host are built here by one small kernel from layer
 // offsets that already sit in device memory, so the call enqueues kernels and nothing else.
 #include <cstring>
 #include <mutex>
@@ -48,87 +48,79 @@ inline size_t round256(size_t n) { return (n + 255) & ~size_t(255); }
 // them, which keeps every access in range whatever they hold.
 __device__ __forceinline__ int64_t clamp_off(int64_t v, int64_t lo, int64_t hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
-#define GRAWA_SCAN_BLOCK 1024
-
-// grid 1, block 1024.  layer_tile0[l] = number of norm-pass tiles before layer l when every layer
-// is cut at the multiples of T (the same cut the host-side plan makes); layer_tile0[L] = total.
-// Nothing exceeds `bound`, the tile count the host sized the partials for.
-__global__ __launch_bounds__(GRAWA_SCAN_BLOCK) void k_static_layer_tiles(const int64_t *__restrict__ off, int L,
-                                                                          int64_t P, int T, int64_t bound,
-                                                                          int32_t *__restrict__ layer_tile0)
+// Tile slots.  Every layer is cut at the multiples of T = 2^shift (the same cut the host-side plan makes).
+// The piece of layer l in the aligned stretch j of T columns gets slot j + l: going along the row, every new piece
+// starts a new stretch, a new layer or both, so slots never repeat and those of a layer are consecutive, and a
+// slot is found without a count of the pieces before it.  Slots skipped where a layer starts on a multiple of T
+// become tiles of length 0, whose blocks add nothing.  No slot exceeds P / T + L - 1.
+__device__ __forceinline__ int64_t first_slot(const int64_t *off, int l, int64_t P, int shift)
 {
-    __shared__ int64_t sm[GRAWA_SCAN_BLOCK];
-    __shared__ int64_t carry;
-    const int tid = threadIdx.x;
-    if (tid == 0) carry = 0;
-    __syncthreads();
-    for (int base = 0; base < L; base += GRAWA_SCAN_BLOCK) {
-        const int l = base + tid;
-        int64_t cnt = 0;
-        if (l < L) {
-            const int64_t a = clamp_off(off[l], 0, P), b = clamp_off(off[l + 1], a, P);
-            if (b > a) cnt = (b - 1) / T - a / T + 1;
-        }
-        sm[tid] = cnt;
-        __syncthreads();
-        for (int d = 1; d < GRAWA_SCAN_BLOCK; d <<= 1) { // inclusive scan
-            const int64_t v = tid >= d ? sm[tid - d] : 0;
-            __syncthreads();
-            sm[tid] += v;
-            __syncthreads();
-        }
-        const int64_t before = carry + sm[tid] - cnt;
-        if (l < L) layer_tile0[l] = (int32_t)(before < bound ? before : bound);
-        __syncthreads();
-        if (tid == GRAWA_SCAN_BLOCK - 1) carry += sm[tid];
-        __syncthreads();
-    }
-    if (tid == 0) layer_tile0[L] = (int32_t)(carry < bound ? carry : bound);
+    return (clamp_off(off[l], 0, P) >> shift) + l;
 }
 
-// Largest l in [0, L-1] with key[l] <= v (key[0] <= v assumed; key non-decreasing).
-template <typename T> __device__ __forceinline__ int last_not_above(const T *__restrict__ key, int L, int64_t v)
+// One entry of each of the maps per thread; `off` may be LDS or global memory.
+__device__ __forceinline__ void static_maps_entry(const int64_t *off, int64_t i, int64_t n, int L, int64_t P, int shift,
+                                                  int64_t bound, GrawaTile *__restrict__ tiles, int64_t n_cells,
+                                                  int32_t *__restrict__ cell_layer, int32_t *__restrict__ tile_begin,
+                                                  int32_t *__restrict__ tile_end)
 {
-    int lo = 0, hi = L - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if ((int64_t)key[mid] <= v) lo = mid;
-        else hi = mid - 1;
-    }
-    return lo;
-}
-
-// grid ceil(max(bound, n_cells)/256), block 256.  Thread i writes tile i of the norm pass (tiles
-// past the real total get length 0: their blocks add nothing) and the layer of 256-column cell i
-// of the center+pull pass (the layer itself if the cell lies in one layer, else the complement of
-// the layer of its first column).
-__global__ __launch_bounds__(GRAWA_BLOCK) void k_static_maps(const int64_t *__restrict__ off, int L, int64_t P, int T,
-                                                             int64_t bound, const int32_t *__restrict__ layer_tile0,
-                                                             GrawaTile *__restrict__ tiles, int64_t n_cells,
-                                                             int32_t *__restrict__ cell_layer)
-{
-    const int64_t i = (int64_t)blockIdx.x * GRAWA_BLOCK + threadIdx.x;
     if (i < bound) {
-        GrawaTile t = {0, 0, 0};
-        if (i < layer_tile0[L]) {
-            const int l = last_not_above(layer_tile0, L, i);
-            const int64_t a = clamp_off(off[l], 0, P), b = clamp_off(off[l + 1], a, P);
-            const int64_t j = a / T + (i - layer_tile0[l]);
-            int64_t start = j * T, stop = (j + 1) * T;
-            if (start < a) start = a;
-            if (stop > b) stop = b;
-            if (stop < start) stop = start;
-            t.start = start;
-            t.len = (int32_t)(stop - start);
-            t.layer = l;
+        int lo = 0, hi = L - 1; // the last layer whose first slot is not above i
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (first_slot(off, mid, P, shift) <= i) lo = mid;
+            else hi = mid - 1;
         }
+        const int64_t a = clamp_off(off[lo], 0, P), b = clamp_off(off[lo + 1], a, P);
+        const int64_t j = i - lo;
+        int64_t start = j << shift, stop = (j + 1) << shift;
+        if (start < a) start = a;
+        if (stop > b) stop = b;
+        if (stop < start) stop = start;
+        GrawaTile t;
+        t.start = start;
+        t.len = (int32_t)(stop - start);
+        t.layer = lo;
         tiles[i] = t;
     }
     if (i < n_cells) {
         const int64_t first = i * GRAWA_CELL;
         const int64_t last = (first + GRAWA_CELL < P ? first + GRAWA_CELL : P) - 1;
-        const int l = last_not_above(off, L, first);
-        cell_layer[i] = off[l + 1] > last ? (int32_t)l : ~(int32_t)l;
+        int lo = 0, hi = L - 1; // the last layer that starts at or before `first`
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (off[mid] <= first) lo = mid;
+            else hi = mid - 1;
+        }
+        cell_layer[i] = off[lo + 1] > last ? (int32_t)lo : ~(int32_t)lo;
+    }
+    for (int64_t l = i; l < L; l += n) {
+        const int64_t a = clamp_off(off[l], 0, P), b = clamp_off(off[l + 1], a, P);
+        tile_begin[l] = (int32_t)((a >> shift) + l);
+        tile_end[l] = b > a ? (int32_t)(((b - 1) >> shift) + l + 1) : (int32_t)((a >> shift) + l);
+    }
+}
+
+// grid ceil(max(bound, n_cells)/256), block 256.  Tile i of the norm pass, the layer of 256-column cell i of
+// the center+pull pass (the layer itself if the cell lies in one layer, else the complement of
+// the layer of its first column) and the tile range of every layer.  The searches run in LDS when the
+// offsets fit (two launches with a prefix sum and searches in global memory took 6.1 us on the device for 59 layers).
+#define GRAWA_MAP_LDS_OFFSETS 2048
+__global__ __launch_bounds__(GRAWA_BLOCK) void k_static_maps(const int64_t *__restrict__ off, int L, int64_t P, int shift,
+                                                             int64_t bound, GrawaTile *__restrict__ tiles,
+                                                             int64_t n_cells, int32_t *__restrict__ cell_layer,
+                                                             int32_t *__restrict__ tile_begin,
+                                                             int32_t *__restrict__ tile_end)
+{
+    __shared__ int64_t sm[GRAWA_MAP_LDS_OFFSETS];
+    const int64_t i = (int64_t)blockIdx.x * GRAWA_BLOCK + threadIdx.x;
+    const int64_t n = (int64_t)gridDim.x * GRAWA_BLOCK;
+    if (L + 1 <= GRAWA_MAP_LDS_OFFSETS) {
+        for (int l = threadIdx.x; l <= L; l += GRAWA_BLOCK) sm[l] = off[l];
+        __syncthreads();
+        static_maps_entry(sm, i, n, L, P, shift, bound, tiles, n_cells, cell_layer, tile_begin, tile_end);
+    } else {
+        static_maps_entry(off, i, n, L, P, shift, bound, tiles, n_cells, cell_layer, tile_begin, tile_end);
     }
 }
 
@@ -181,25 +173,23 @@ extern "C" grawa_status_t grawa_lgrawa_update_static(int K, int64_t P, int L, co
     p.d_tiles = reinterpret_cast<GrawaTile *>(w); w += b_tiles;
     p.d_layer_tile0 = reinterpret_cast<int32_t *>(w); w += b_lt0;
     p.d_partials = reinterpret_cast<double *>(w); w += b_part;
-    p.d_S = reinterpret_cast<double *>(w); w += b_S;
-    p.d_A = reinterpret_cast<float *>(w); w += b_A;
-    p.d_beta_layer = reinterpret_cast<float *>(w); w += b_A;
-    p.d_beta_model = reinterpret_cast<float *>(w);
+    p.d_layer_tile1 = reinterpret_cast<int32_t *>(w); w += b_S; // 4 L of the 8 K L bytes that the limit counts for S
+    p.d_beta_layer = reinterpret_cast<float *>(w);
 
-    // Nothing in the scratch has to start at zero: the maps, every partial (K x bound) and the
-    // K x L tables are written in full before they are read.
+    // Nothing in the scratch has to start at zero: the maps, every partial that is read and the weights
+    // are written in full before they are read.
     hipStream_t s = static_cast<hipStream_t>(stream);
-    k_static_layer_tiles<<<dim3(1), dim3(GRAWA_SCAN_BLOCK), 0, s>>>(layer_offsets_dev, L, P, T, bound,
-                                                                  p.d_layer_tile0);
-    if (hipGetLastError() != hipSuccess) return GRAWA_ERR_HIP;
     const int64_t n_map = bound > nc ? bound : nc;
     k_static_maps<<<dim3((unsigned)((n_map + GRAWA_BLOCK - 1) / GRAWA_BLOCK)), dim3(GRAWA_BLOCK), 0, s>>>(
-        layer_offsets_dev, L, P, T, bound, p.d_layer_tile0, p.d_tiles, nc, p.d_cell_layer);
+        layer_offsets_dev, L, P, __builtin_ctz((unsigned)T), bound, p.d_tiles, nc, p.d_cell_layer, p.d_layer_tile0,
+        p.d_layer_tile1);
     if (hipGetLastError() != hipSuccess) return GRAWA_ERR_HIP;
     if (grawa_launch_sumsq(&p, g, ldg, dt, s, nullptr, nullptr) != hipSuccess) return GRAWA_ERR_HIP;
-    if (grawa_launch_finalize_layers(&p, nullptr, weights_out, s, 0, 0.0) != hipSuccess) return GRAWA_ERR_HIP;
-    if (grawa_launch_center_pull(&p, x, ldx, p.d_beta_layer, 1, lambda, nullptr, 0, GRAWA_F32, 0.f, 0, center_out,
-                                 0.f, 0, s, nullptr, nullptr) != hipSuccess)
+    const bool from_tiles = grawa_pull_from_tiles(&p);
+    if (!from_tiles && grawa_launch_finalize_layers(&p, GRAWA_GOAL_LAYER_WEIGHTS, nullptr, weights_out, s) != hipSuccess)
+        return GRAWA_ERR_HIP;
+    if (grawa_launch_center_pull(&p, x, ldx, from_tiles ? nullptr : p.d_beta_layer, 1, lambda, nullptr, 0, GRAWA_F32,
+                                 0.f, 0, center_out, 0.f, 0, weights_out, s, nullptr, nullptr) != hipSuccess)
         return GRAWA_ERR_HIP;
     return GRAWA_OK;
 }

@@ -1,0 +1,116 @@
+"""GPU parity where a launch does the work of two: per-layer weights taken straight from the tile sums inside the
+center+pull pass (small problems), the model-level weights inside the finalize launch, and the running estimate
+inside the scored step.  Layouts: one layer, layers of one column, cells with more layers than the per-cell table
+holds, layers of many tiles; both sides of each size rule; non-finite scores; the same plan called repeatedly."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import grawa_oracle as orc
+from paper_2403_04206_amd import grawa, workloads as W
+from parity_util import TIGHT, assert_params_close, assert_table_close
+from test_gpu_local import scale_of
+from test_gpu_parity import run_variant
+from test_zz_no_alloc import both_ways
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+LAYOUTS = {
+    "one layer": [70001],
+    "ones": [1] * 700,                                   # 256 layers in a cell: beyond the per-cell table
+    "mixed": [1] * 63 + [300, 2, 2, 252, 4097, 1, 1, 20001, 255, 1],
+    "tiles": [36864, 1, 8192, 2048, 2047],
+}
+
+
+@pytest.mark.parametrize("name", sorted(LAYOUTS))
+@pytest.mark.parametrize("K,dtype", [(1, "f32"), (2, "bf16"), (3, "f32"), (7, "f32"), (8, "bf16"), (12, "f32"), (15, "f32")])
+def test_weights_inside_the_pull(name, K, dtype):
+    w, x, g = W.make_small(2000 + K, K, LAYOUTS[name], grad_dtype=dtype, ld_pad=8 if K == 3 else 0, device=DEV)
+    run_variant(w, x, g, "lgrawa", 0.3)
+    run_variant(w, x, g, "lgrawa", 0.25, fused=True, lr=0.1, want_center=False)
+    run_variant(w, x, g, "mgrawa", 0.3)
+    run_variant(w, x, g, "flat", 0.3)
+    both_ways(w, x, g, 0.4)
+
+
+@pytest.mark.parametrize("K,cells", [(4, 2560), (4, 2561), (15, 682), (15, 683)])
+def test_either_side_of_the_size_rule(K, cells):
+    P = cells * 256
+    w, x, g = W.make_small(2100 + cells, K, [P // 3, 77, P - P // 3 - 77], device=DEV)
+    run_variant(w, x, g, "lgrawa", 0.3)
+    both_ways(w, x, g, 0.4)
+
+
+def test_zero_and_non_finite_scores_inside_the_pull():
+    w, x, g = W.make_small(2200, 4, [40, 9000, 17, 64, 1, 1], device=DEV)
+    off, P = w.offsets, w.P
+    g[1:, off[0]:off[1]] = 0                            # only worker 0 has a gradient in layer 0
+    g[:, off[2]:off[3]] = 0
+    run_variant(w, x, g, "lgrawa", 0.5)
+    g[1, off[1] + 5] = float("inf")
+    g[3, off[3] + 1] = float("nan")
+    ref = orc.lgrawa_update(W.to_numpy_params(x), W.to_numpy_grads(g), off, 0.5)
+    wts = torch.empty((4, w.L), device=DEV)
+    with grawa.Plan(4, P, off) as plan:
+        plan.lgrawa_update(x[:, :P], g[:, :P], 0.5, weights_out=wts)
+        assert plan.nonfinite() == grawa.NONFINITE_LAYER_SCORE
+    got = wts.cpu().numpy()
+    np.testing.assert_array_equal(np.isnan(got), np.isnan(ref["beta"]))
+    fin = np.isfinite(ref["beta"])
+    assert_table_close(np.where(fin, got, 0), np.where(fin, ref["beta"], 0), TIGHT, "beta")
+
+
+@pytest.mark.parametrize("K,sizes", [(4, LAYOUTS["mixed"]), (8, [270000]), (8, [280001]), (2, [1] * 700), (15, [2048, 1, 60000])])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_estimate_inside_the_scored_step(K, sizes, dtype):
+    # 8 x 270 000 columns is the last that takes one launch, 8 x 280 001 takes two
+    w, x, g = W.make_small(2300 + K, K, sizes, grad_dtype=dtype, device=DEV)
+    P, lr, lam, gamma = w.P, 0.05, 0.3, 0.9
+    xh, gh = W.to_numpy_params(x), W.to_numpy_grads(g)
+    est = torch.empty((K, w.L), device=DEV)
+    cen = torch.empty(W.round_up(P, 4), device=DEV)
+    with grawa.Plan(K, P, w.offsets) as plan:
+        for rep in range(20):                            # the arrival counters are left at zero by every call
+            xg = x.clone()
+            for _ in range(3):
+                plan.local_step_scored(xg[:, :P], g[:, :P], lr, gamma)
+            plan.local_lgrawa_update(xg[:, :P], lam, center_out=cen, est_out=est)
+            if rep == 0:
+                first = (xg.clone(), cen[:P].clone(), est.clone())
+            else:                                        # and no result depends on which block came last
+                assert torch.equal(xg, first[0]) and torch.equal(cen[:P], first[1]) and torch.equal(est, first[2])
+    ref = orc.local_grawa_round(xh, [gh] * 3, w.offsets, lr, lam, gamma, "lgrawa")
+    assert_table_close(est.cpu().numpy(), ref["g_est"], TIGHT, "g_est")
+    assert_params_close(first[0].cpu().numpy()[:, :P], ref["x"], w.offsets, TIGHT, "x", scale_of(xh, P, [gh] * 3, lr))
+
+
+def test_model_weights_repeatedly():
+    # the last block of the finalize launch forms the model weights: the same bits every time, fresh inputs each call
+    w, x, g = W.make_small(2400, 6, [1] * 200 + [5000, 33, 70000], device=DEV)
+    P = w.P
+    wts = torch.empty(6, device=DEV)
+    with grawa.Plan(6, P, w.offsets) as plan:
+        for rep in range(30):
+            k = rep % 6
+            g2 = g.roll(k, 0).contiguous()
+            plan.mgrawa_update(x.clone()[:, :P], g2[:, :P], 0.1, weights_out=wts)
+            if rep == 0:
+                first = wts.clone()
+            torch.testing.assert_close(wts, first.roll(k, 0), rtol=1e-6, atol=0)
+
+
+@pytest.mark.parametrize("losses,leader", [([3.0, 1.0, 1.0, 2.0], 1), ([float("nan"), 1.0, 0.5], 0), ([2.0, float("nan"), 1.0], 2),
+                                          ([float("inf")] * 3, 0), ([float("inf"), float("nan"), float("inf")], 0),
+                                          ([float("nan")] * 3, 0), ([float("inf"), 5.0, float("-inf")], 2), ([0.0, -0.0], 0)])
+def test_leader_rule(losses, leader):
+    K = len(losses)
+    w, x, _ = W.make_small(2500, K, [300], device=DEV)
+    lead = torch.full((1,), -1, dtype=torch.int32, device=DEV)
+    for pad in (0, 70):                                  # with 70 more workers: several per lane
+        ls = torch.tensor(losses + [float("inf")] * pad, device=DEV)
+        w, x, _ = W.make_small(2500, K + pad, [300], device=DEV)
+        with grawa.Plan(K + pad, 300, w.offsets) as plan:
+            plan.lsgd_update(x[:, :300], ls, 0.3, leader_out=lead)
+        assert int(lead.item()) == leader
