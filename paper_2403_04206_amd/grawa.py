@@ -90,9 +90,17 @@ def _check(status: int, where: str):
 
 
 def _stream(stream=None):
-    if stream is None:
-        stream = torch.cuda.current_stream()
+    if stream is None:  # the handle of torch's current stream, without making a Stream object (2.9 us); the calls
+        # that come here hold CUDA tensors, so torch's CUDA state is set up
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return C.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+
+
+def _stream_no_tensors(stream=None):
+    return _stream(torch.cuda.current_stream() if stream is None else stream)
+
+
+_NULL = C.c_void_p(0)
 
 
 def _ptr(t):
@@ -106,69 +114,80 @@ def _on_device(t) -> bool:
     return t.is_cuda or not _REQUIRE_DEVICE
 
 
-def _covers(t, rows: int, cols: int, what: str):
-    """The memory behind a [rows, >= cols] view with row stride t.stride(0) must hold the last row too."""
-    if rows < 1 or cols < 1:
-        raise ValueError("%s: empty" % what)
-    need = (rows - 1) * (t.stride(0) if t.dim() == 2 else 0) + cols
-    have = t.untyped_storage().nbytes() // t.element_size() - t.storage_offset()
+def _covers(t, need: int, what: str):
+    """The memory behind a view must hold `need` elements from the view's start."""
+    have = t.untyped_storage().nbytes() // t.itemsize - t.storage_offset()
     if need > have:
         raise ValueError("%s: the tensor's storage holds %d elements from its start, the call reads %d" %
                          (what, have, need))
 
 
+# The checks below run on every call and their cost is the larger part of a small update's: each attribute of a
+# tensor is asked for once.
+def _rows(t, rows, cols, K, P, ld, what: str):
+    """A [rows, cols] view with row stride ld (unit column stride) as [K, >= P], rows not overlapping."""
+    if K is None:
+        K = rows
+    if P is None:
+        P = cols
+    if rows != K or cols < P:
+        raise ValueError("%s has shape %r, expected [%d, >= %d]" % (what, (rows, cols), K, P))
+    if K > 1 and ld < P:
+        raise ValueError("%s: row stride %d is shorter than the %d columns used" % (what, ld, P))
+    if K < 1 or P < 1:
+        raise ValueError("%s: empty" % what)
+    _covers(t, (K - 1) * ld + P, what)
+
+
 def _params(x: torch.Tensor, K=None, P=None, what="x"):
     """float32 [K, >= P], unit column stride, rows not overlapping; returns (pointer, row stride)."""
-    if x.dtype != torch.float32 or x.dim() != 2 or x.stride(1) != 1 or not _on_device(x):
-        raise TypeError("%s must be a float32 CUDA tensor [K, P] with unit column stride" % what)
-    K = x.shape[0] if K is None else K
-    P = x.shape[1] if P is None else P
-    if x.shape[0] != K or x.shape[1] < P:
-        raise ValueError("%s has shape %r, expected [%d, >= %d]" % (what, tuple(x.shape), K, P))
-    if K > 1 and x.stride(0) < P:
-        raise ValueError("%s: row stride %d is shorter than the %d columns used" % (what, x.stride(0), P))
-    _covers(x, K, P, what)
-    return x.data_ptr(), x.stride(0)
+    if x.dtype is torch.float32 and x.ndim == 2 and (x.is_cuda or not _REQUIRE_DEVICE):
+        ld, unit = x.stride()
+        if unit == 1:
+            rows, cols = x.shape
+            _rows(x, rows, cols, K, P, ld, what)
+            return x.data_ptr(), ld
+    raise TypeError("%s must be a float32 CUDA tensor [K, P] with unit column stride" % what)
 
 
 def _grads(g: torch.Tensor, K=None, P=None, what="g"):
     """float32 or bfloat16 [K, >= P]; returns (pointer, row stride, dtype code)."""
-    if g.dim() != 2 or g.stride(1) != 1 or not _on_device(g):
-        raise TypeError("%s must be a CUDA tensor [K, P] with unit column stride" % what)
-    if g.dtype == torch.float32:
-        dt = F32
-    elif g.dtype == torch.bfloat16:
-        dt = BF16
-    else:
-        raise TypeError("%s must be float32 or bfloat16" % what)
-    K = g.shape[0] if K is None else K
-    P = g.shape[1] if P is None else P
-    if g.shape[0] != K or g.shape[1] < P:
-        raise ValueError("%s has shape %r, expected [%d, >= %d]" % (what, tuple(g.shape), K, P))
-    if K > 1 and g.stride(0) < P:
-        raise ValueError("%s: row stride %d is shorter than the %d columns used" % (what, g.stride(0), P))
-    _covers(g, K, P, what)
-    return g.data_ptr(), g.stride(0), dt
+    if g.ndim == 2 and (g.is_cuda or not _REQUIRE_DEVICE):
+        ld, unit = g.stride()
+        if unit == 1:
+            dtype = g.dtype
+            if dtype is torch.float32:
+                dt = F32
+            elif dtype is torch.bfloat16:
+                dt = BF16
+            else:
+                raise TypeError("%s must be float32 or bfloat16" % what)
+            rows, cols = g.shape
+            _rows(g, rows, cols, K, P, ld, what)
+            return g.data_ptr(), ld, dt
+    raise TypeError("%s must be a CUDA tensor [K, P] with unit column stride" % what)
 
 
 def _vector(t, n: int, what: str, dtype=torch.float32, optional=True):
     """A contiguous 1-D tensor of at least n elements (a center, the losses, the leader index), or None."""
     if t is None:
         if optional:
-            return C.c_void_p(0)
+            return _NULL
         raise TypeError("%s is required" % what)
     if t.dtype != dtype or t.dim() != 1 or t.stride(0) != 1 or not _on_device(t):
         raise TypeError("%s must be a contiguous 1-D %s CUDA tensor" % (what, str(dtype).replace("torch.", "")))
     if t.numel() < n:
         raise ValueError("%s holds %d elements, the call needs %d" % (what, t.numel(), n))
-    _covers(t, 1, n, what)
+    if n < 1:
+        raise ValueError("%s: empty" % what)
+    _covers(t, n, what)
     return C.c_void_p(t.data_ptr())
 
 
 def _table(t, shape, what: str):
     """A contiguous float32 tensor of exactly `shape` (weights, norms, estimates), or None."""
     if t is None:
-        return C.c_void_p(0)
+        return _NULL
     if t.dtype != torch.float32 or not t.is_contiguous() or not _on_device(t):
         raise TypeError("%s must be a contiguous float32 CUDA tensor" % what)
     if tuple(t.shape) != tuple(shape):
@@ -300,7 +319,7 @@ class Plan:
                "grawa_local_mgrawa_update")
 
     def local_scores_reset(self, stream=None):
-        _check(lib().grawa_local_scores_reset(self._h, _stream(stream)), "grawa_local_scores_reset")
+        _check(lib().grawa_local_scores_reset(self._h, _stream_no_tensors(stream)), "grawa_local_scores_reset")
 
     # -- competing centers (Appendix F) ---------------------------------------------
     def easgd_update(self, x, lam, rho, center, stream=None):
@@ -319,7 +338,7 @@ class Plan:
     def nonfinite(self, clear=True, stream=None):
         """grawa_plan_nonfinite: the NONFINITE_* bits seen since the last clear (waits for the stream)."""
         f = C.c_uint()
-        _check(lib().grawa_plan_nonfinite(self._h, C.byref(f), 1 if clear else 0, _stream(stream)),
+        _check(lib().grawa_plan_nonfinite(self._h, C.byref(f), 1 if clear else 0, _stream_no_tensors(stream)),
                "grawa_plan_nonfinite")
         return f.value
 
