@@ -122,9 +122,7 @@ __global__ __launch_bounds__(GRAWA_CELL) void k_row_step(float *__restrict__ x, 
                 if (PROX) v = fmaf(w, vec_get<V>(cv[u], e) - v, v);
                 vec_set<V>(o, e, v);
             }
-            XV *xp = reinterpret_cast<XV *>(xr + c);
-            if (NT) __builtin_nontemporal_store(o, xp);
-            else *xp = o;
+            st_lane<NT, XV>(uniform_base(xr + (int64_t)m * GRAWA_ROW_BLOCK), (threadIdx.x + u * GRAWA_CELL) * (V * 4u), o);
         } else if (V > 1 && c < P) { // the vector that holds the row's last columns
 #pragma unroll
             for (int e = 0; e < V; ++e)
@@ -218,15 +216,10 @@ __global__ __launch_bounds__(GRAWA_CELL) void k_nesterov(float *__restrict__ x, 
                 vec_set<V>(bo, c, b);
                 vec_set<V>(xo, c, fmaf(-lr, fmaf(momentum, b, d), xc));
             }
-            XV *xp = reinterpret_cast<XV *>(xr + j * V);
-            XV *bp = reinterpret_cast<XV *>(br + j * V);
-            if (NT) {
-                __builtin_nontemporal_store(xo, xp);
-                __builtin_nontemporal_store(bo, bp);
-            } else {
-                *xp = xo;
-                *bp = bo;
-            }
+            const int64_t c0 = (int64_t)blockIdx.x * (GRAWA_CELL * U * V);
+            const unsigned o = (threadIdx.x + u * GRAWA_CELL) * (V * 4u);
+            st_lane<NT, XV>(uniform_base(xr + c0), o, xo);
+            st_lane<NT, XV>(uniform_base(br + c0), o, bo);
         }
     }
     if (blockIdx.x == 0 && threadIdx.x < (unsigned)(P - nvec * V)) {
