@@ -183,6 +183,15 @@ template <bool NT> struct GradVec<float, 1, NT> {
     static __device__ __forceinline__ void load(const float *p, float (&f)[1]) { f[0] = NT ? __builtin_nontemporal_load(p) : *p; }
 };
 template <bool NT> struct GradVec<float, 4, NT> {
+    static __device__ __forceinline__ void lane(uint64_t base, unsigned off, float (&f)[4])
+    {
+        typedef float v4f __attribute__((ext_vector_type(4)));
+        const v4f w = ld_lane<NT, v4f>(base, off);
+        f[0] = w.x;
+        f[1] = w.y;
+        f[2] = w.z;
+        f[3] = w.w;
+    }
     static __device__ __forceinline__ void load(const float *p, float (&f)[4])
     {
         typedef float v4f __attribute__((ext_vector_type(4)));
@@ -210,6 +219,14 @@ template <bool NT> struct GradVec<uint16_t, 2, NT> {
     }
 };
 template <bool NT> struct GradVec<uint16_t, 4, NT> {
+    static __device__ __forceinline__ void lane(uint64_t base, unsigned off, float (&f)[4])
+    {
+        const v2u w = ld_lane<NT, v2u>(base, off);
+        f[0] = bf16_lo(w.x);
+        f[1] = bf16_hi(w.x);
+        f[2] = bf16_lo(w.y);
+        f[3] = bf16_hi(w.y);
+    }
     static __device__ __forceinline__ void load(const uint16_t *p, float (&f)[4])
     {
         const v2u *q = reinterpret_cast<const v2u *>(p);

@@ -192,6 +192,114 @@ __global__ __launch_bounds__(GRAWA_CELL) __attribute__((amdgpu_waves_per_eu(1, W
     }
 }
 
+// Wide form, for arrays beyond the last-level cache whose rows do not start on line boundaries (a plain [K, P]
+// tensor).  grid ceil(P/1024), block 256: a lane owns four adjacent columns (16-byte accesses are always aligned:
+// the ABI asks for it), a wave 1 KiB per row and the block 4 KiB, so that one line in 32 instead of one in 8 is shared
+// with another block; loads cached, so that the lines the waves of a block share are fetched once; stores streaming.
+// Otherwise as the plain form; a wave's 256 columns are one cell.  Measured on 1.2 to 2 GB of random values, pitch
+// 16 bytes off a line, TB/s, plain form / this one (WPE in grawa_waves_wide): K = 2 5.46/6.27, 3 5.73/6.26, 4 5.71/5.96,
+// 6 5.53/5.52, 8 5.39/5.35, 10 5.36/5.25, 12 4.94/5.29, 16 4.86/5.45, 20 4.68/5.48; with the SGD step 2 5.60/6.28,
+// 4 5.69/5.97, 8 5.52/5.45, 12 5.29/5.58, 16 5.35/5.67; bf16 gradients 4 5.34/6.08, 16 5.16/5.48.
+template <int K, bool SGD, typename GT, int WPE>
+__global__ __launch_bounds__(GRAWA_BLOCK) __attribute__((amdgpu_waves_per_eu(1, WPE))) void k_center_pull_wide(
+    float *__restrict__ x, int64_t ldx, const GT *__restrict__ g, int64_t ldg, float lr,
+    const float *__restrict__ beta, int64_t beta_stride, const int32_t *__restrict__ cell_layer,
+    const int64_t *__restrict__ off, int L, int64_t P, float lambda,
+    float *__restrict__ center_out, float rho, int moving)
+{
+    constexpr int V = 4;
+    typedef typename FloatVec<V>::T XV;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / GRAWA_WAVE));
+    const int64_t cell = (int64_t)blockIdx.x * V + wave; // wave-uniform
+    const int64_t cell0 = cell * GRAWA_CELL;
+    if (cell0 >= P) return;
+    const unsigned lane = threadIdx.x & (GRAWA_WAVE - 1);
+    const int64_t col = cell0 + lane * V;
+    const int n = col + V <= P ? V : (col < P ? (int)(P - col) : 0); // columns of this lane inside the row
+    float *xb = x + cell0;
+    const GT *gb = g + cell0;
+    const unsigned xoff = lane * (V * 4u), goff = lane * (V * (unsigned)sizeof(GT));
+
+    XV v[K];
+    XV cprev = XV{};
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] = XV{};
+    if (n == V) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) v[k] = ld_lane<false, XV>(uniform_base(xb + (int64_t)k * ldx), xoff);
+        if constexpr (SGD) {
+            float f[K][V];
+#pragma unroll
+            for (int k = 0; k < K; ++k) GradVec<GT, V, false>::lane(uniform_base(gb + (int64_t)k * ldg), goff, f[k]);
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+#pragma unroll
+                for (int e = 0; e < V; ++e) vec_set<V>(v[k], e, fmaf(-lr, f[k][e], vec_get<V>(v[k], e)));
+        }
+        if (moving) cprev = ld_lane<false, XV>(uniform_base(center_out + cell0), xoff);
+    } else if (n > 0) { // the lane that holds the row's last columns
+#pragma unroll
+        for (int e = 0; e < V; ++e)
+            if (e < n) {
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    float t = xb[(int64_t)k * ldx + lane * V + e];
+                    if (SGD) t = fmaf(-lr, Grad<GT>::one(gb + (int64_t)k * ldg + lane * V + e), t);
+                    vec_set<V>(v[k], e, t);
+                }
+                if (moving) vec_set<V>(cprev, e, center_out[col + e]);
+            }
+    }
+
+    const int info = cell_layer ? cell_layer[cell] : 0;
+    XV c = XV{};
+    if (info >= 0) { // one layer for the whole cell: weights through scalar loads
+        const uint64_t bb = uniform_base(beta + info);
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const float w = ld_uniform_f32(bb, (int64_t)k * beta_stride);
+#pragma unroll
+            for (int e = 0; e < V; ++e) vec_set<V>(c, e, fmaf(w, vec_get<V>(v[k], e), vec_get<V>(c, e)));
+        }
+    } else { // the cell holds a layer boundary: each column looks up its own layer
+#pragma unroll
+        for (int e = 0; e < V; ++e)
+            if (e < n) {
+                const float *b = beta + layer_of(off, ~info, L, col + e);
+                float t = 0.f;
+#pragma unroll
+                for (int k = 0; k < K; ++k) t = fmaf(b[(int64_t)k * beta_stride], vec_get<V>(v[k], e), t);
+                vec_set<V>(c, e, t);
+            }
+    }
+    if (moving) {
+#pragma unroll
+        for (int e = 0; e < V; ++e)
+            vec_set<V>(c, e, fmaf(rho, vec_get<V>(c, e) - vec_get<V>(cprev, e), vec_get<V>(cprev, e)));
+    }
+    if (n == V) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            XV o = v[k];
+#pragma unroll
+            for (int e = 0; e < V; ++e)
+                vec_set<V>(o, e, fmaf(lambda, vec_get<V>(c, e) - vec_get<V>(v[k], e), vec_get<V>(v[k], e)));
+            st_lane<true, XV>(uniform_base(xb + (int64_t)k * ldx), xoff, o);
+        }
+        if (center_out) st_lane<true, XV>(uniform_base(center_out + cell0), xoff, c);
+    } else if (n > 0) {
+#pragma unroll
+        for (int e = 0; e < V; ++e)
+            if (e < n) {
+#pragma unroll
+                for (int k = 0; k < K; ++k)
+                    xb[(int64_t)k * ldx + lane * V + e] =
+                        fmaf(lambda, vec_get<V>(c, e) - vec_get<V>(v[k], e), vec_get<V>(v[k], e));
+                if (center_out) center_out[col + e] = vec_get<V>(c, e);
+            }
+    }
+}
+
 // Row-split form: the rows of a 256-column cell are divided over S groups of waves.  grid ceil(P/256),
 // block S * 256 / V.  A lane owns V adjacent columns of its group's rows: Q of them, and one more for the
 // first K - S Q groups when REM (K is then S Q + 1 .. S Q + S - 1).  Each group forms its part of the
@@ -390,6 +498,24 @@ template <int K, bool SGD, typename GT, bool NT, bool TILES> static void launch_
                           GRAWA_CP_CELLS, (const int64_t *)p->d_off, p->L, p->P, lambda, center_out, rho, moving, tw);
 }
 
+// The wide form's cap (best of 2, 3, 4 and 8 waves for K <= 5; one too many costs 3 to 5 %, and more than it gains over
+// the plain form), and the worker counts it is used for: where it is at least as fast as the plain form.
+constexpr int grawa_waves_wide(int k, bool sgd)
+{
+    if (k == 2) return sgd ? 3 : 4;
+    if (k == 3) return sgd ? 2 : 3;
+    return k <= 5 ? 2 : 1;
+}
+static bool wide_is_faster(int k) { return k >= 2 && (k <= 5 || (k >= 12 && k <= 23)); }
+
+template <int K, bool SGD, typename GT> static void launch_wide(GRAWA_CP_ARGS)
+{
+    (void)tw;
+    hipExtLaunchKernelGGL((k_center_pull_wide<K, SGD, GT, grawa_waves_wide(K, SGD)>), dim3((unsigned)((p->n_cells + 3) / 4)),
+                          dim3(GRAWA_BLOCK), 0, s, e0, e1, 0, x, ldx, (const GT *)g, ldg, lr, beta, GRAWA_CP_STRIDE,
+                          GRAWA_CP_CELLS, (const int64_t *)p->d_off, p->L, p->P, lambda, center_out, rho, moving);
+}
+
 template <int Q, bool REM, int S, int V, bool SGD, typename GT, bool NT> static void launch_split(GRAWA_CP_ARGS)
 {
     hipExtLaunchKernelGGL((k_center_pull_split<Q, REM, S, V, SGD, GT, NT>), dim3((unsigned)p->n_cells),
@@ -429,6 +555,18 @@ template <bool SGD, typename GT, bool NT> static void dispatch_cp(GRAWA_CP_ARGS)
 #undef GRAWA_CP_SPLIT
 }
 
+template <bool SGD, typename GT> static void dispatch_cp_wide(GRAWA_CP_ARGS)
+{
+#define GRAWA_CP_WIDE(N) \
+    case N: launch_wide<N, SGD, GT>(GRAWA_CP_PASS); return;
+    switch (p->K) { // wide_is_faster()
+        GRAWA_CP_WIDE(2) GRAWA_CP_WIDE(3) GRAWA_CP_WIDE(4) GRAWA_CP_WIDE(5) GRAWA_CP_WIDE(12) GRAWA_CP_WIDE(13)
+        GRAWA_CP_WIDE(14) GRAWA_CP_WIDE(15) GRAWA_CP_WIDE(16) GRAWA_CP_WIDE(17) GRAWA_CP_WIDE(18) GRAWA_CP_WIDE(19)
+        GRAWA_CP_WIDE(20) GRAWA_CP_WIDE(21) GRAWA_CP_WIDE(22) GRAWA_CP_WIDE(23)
+    }
+#undef GRAWA_CP_WIDE
+}
+
 // Weights straight from the tile sums: K <= 15 (grawa_pull_from_tiles), cached accesses.
 template <bool SGD, typename GT> static void dispatch_cp_tiles(GRAWA_CP_ARGS)
 {
@@ -464,15 +602,17 @@ hipError_t grawa_launch_center_pull(const grawa_plan *p, float *x, int64_t ldx, 
         tw = TileWeights{p->d_partials, p->n_tiles, p->d_layer_tile0, p->d_layer_tile1, weights_out, p->d_flags, group};
     }
     // Streaming accesses pay off only when the arrays do not fit the last-level cache anyway.
-    bool nt = beta && (int64_t)p->K * p->P * 4 > GRAWA_STREAMING_MIN_BYTES && rows_line_aligned(x, ldx, 4) &&
-              (!center_out || rows_line_aligned(center_out, 0, 4));
+    const bool large = beta && (int64_t)p->K * p->P * 4 > GRAWA_STREAMING_MIN_BYTES;
+    bool nt = large && rows_line_aligned(x, ldx, 4) && (!center_out || rows_line_aligned(center_out, 0, 4));
     if (fuse_sgd) nt = nt && rows_line_aligned(g_sgd, ldg_sgd, dt == GRAWA_BF16 ? 2 : 4);
+    const bool wide = large && !nt && wide_is_faster(p->K);
     const void *g = g_sgd;
     const int64_t ldg = ldg_sgd;
 #define GRAWA_CP_GO(SGD, GT)                                                 \
     do {                                                                     \
         if (!beta) dispatch_cp_tiles<SGD, GT>(GRAWA_CP_PASS);                \
         else if (nt) dispatch_cp<SGD, GT, true>(GRAWA_CP_PASS);              \
+        else if (wide) dispatch_cp_wide<SGD, GT>(GRAWA_CP_PASS);             \
         else dispatch_cp<SGD, GT, false>(GRAWA_CP_PASS);                     \
     } while (0)
     if (!fuse_sgd) GRAWA_CP_GO(false, float);
