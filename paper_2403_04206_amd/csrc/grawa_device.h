@@ -250,7 +250,17 @@ template <int V> __device__ __forceinline__ void vec_set(typename FloatVec<V>::T
     else v[c] = f;
 }
 
-#define GRAWA_STREAMING_MIN_BYTES ((int64_t)512 << 20)
+// From what size of x (K P floats) on a pass streams past the caches.  The lines lie where the pass is faster on
+// arrays that the caches do not hold when it starts, as after a backward pass.  Cached against streaming, us, on three
+// such sets in turn (in brackets: one set again and again, which the 256 MB last-level cache partly holds):
+//   pull            MGRAWA, 4 workers,  80 MB x: 43.0/42.5 (38/39), 120 MB: 75/69, 187 MB: 102.8/93.2 (87.2/90.5)
+//   Nesterov step   8 workers, x 80 MB: 1.13 x faster (0.9), 120 MB 1.13 (1.06), 160 MB 1.15 (1.15)
+//   step with center or scores: 80 MB 1.04 to 1.21 (0.98 to 1.12), 160 MB 1.22 (1.12); 40 MB 0.96
+//   plain SGD step: 187 MB 100.5/90.2 alone, but the pull that follows finds x in the cache after a cached one: step
+//   and EASGD phase 158.4/164.0; 400 MB 211/189 alone, 344/347 with the phase.
+#define GRAWA_STREAMING_MIN_BYTES ((int64_t)128 << 20)
+#define GRAWA_STREAMING_MIN_ROW_BYTES ((int64_t)64 << 20)
+#define GRAWA_STREAMING_MIN_SGD_BYTES ((int64_t)256 << 20)
 
 // Streaming accesses are used only when no cache line is shared between two rows or written
 // in two parts: base pointers and row pitches are multiples of 128 bytes.

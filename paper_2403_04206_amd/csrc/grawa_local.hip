@@ -271,8 +271,8 @@ static hipError_t launch_row_step(const grawa_plan *p, float *x, int64_t ldx, co
     const int64_t n_groups = (nb + group - 1) / group;
     if (K > 65535 || n_groups > 65535 || group >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)group, (unsigned)K, (unsigned)n_groups), block(GRAWA_CELL);
-    const bool nt = (int64_t)K * P * 4 > GRAWA_STREAMING_MIN_BYTES && rows_line_aligned(x, ldx, 4) &&
-                    rows_line_aligned(g, ldg, dt == GRAWA_BF16 ? 2 : 4);
+    const bool nt = (int64_t)K * P * 4 > (prox || p ? GRAWA_STREAMING_MIN_ROW_BYTES : GRAWA_STREAMING_MIN_SGD_BYTES) &&
+                    rows_line_aligned(x, ldx, 4) && rows_line_aligned(g, ldg, dt == GRAWA_BF16 ? 2 : 4);
     RowScores a = {};
     int score = 0;
     if (p) {

@@ -196,11 +196,13 @@ __global__ __launch_bounds__(GRAWA_CELL) __attribute__((amdgpu_waves_per_eu(1, W
 // tensor).  grid ceil(P/1024), block 256: a lane owns four adjacent columns (16-byte accesses are always aligned:
 // the ABI asks for it), a wave 1 KiB per row and the block 4 KiB, so that one line in 32 instead of one in 8 is shared
 // with another block; loads cached, so that the lines the waves of a block share are fetched once; stores streaming.
-// Otherwise as the plain form; a wave's 256 columns are one cell.  Measured on 1.2 to 2 GB of random values, pitch
+// Otherwise as the plain form; a wave's 256 columns are one cell.  With streaming loads (LNT) the form also serves
+// line-aligned rows of one or two workers, where a 4-byte load per row and lane leaves too little in flight: K = 1
+// 3.64 -> 6.69 TB/s, K = 2 5.71 -> 6.64, with the SGD step on bf16 gradients 5.77 -> 6.46.  Off the line grid: measured on 1.2 to 2 GB of random values, pitch
 // 16 bytes off a line, TB/s, plain form / this one (WPE in grawa_waves_wide): K = 2 5.46/6.27, 3 5.73/6.26, 4 5.71/5.96,
 // 6 5.53/5.52, 8 5.39/5.35, 10 5.36/5.25, 12 4.94/5.29, 16 4.86/5.45, 20 4.68/5.48; with the SGD step 2 5.60/6.28,
 // 4 5.69/5.97, 8 5.52/5.45, 12 5.29/5.58, 16 5.35/5.67; bf16 gradients 4 5.34/6.08, 16 5.16/5.48.
-template <int K, bool SGD, typename GT, int WPE>
+template <int K, bool SGD, typename GT, bool LNT, int WPE>
 __global__ __launch_bounds__(GRAWA_BLOCK) __attribute__((amdgpu_waves_per_eu(1, WPE))) void k_center_pull_wide(
     float *__restrict__ x, int64_t ldx, const GT *__restrict__ g, int64_t ldg, float lr,
     const float *__restrict__ beta, int64_t beta_stride, const int32_t *__restrict__ cell_layer,
@@ -226,17 +228,17 @@ __global__ __launch_bounds__(GRAWA_BLOCK) __attribute__((amdgpu_waves_per_eu(1, 
     for (int k = 0; k < K; ++k) v[k] = XV{};
     if (n == V) {
 #pragma unroll
-        for (int k = 0; k < K; ++k) v[k] = ld_lane<false, XV>(uniform_base(xb + (int64_t)k * ldx), xoff);
+        for (int k = 0; k < K; ++k) v[k] = ld_lane<LNT, XV>(uniform_base(xb + (int64_t)k * ldx), xoff);
         if constexpr (SGD) {
             float f[K][V];
 #pragma unroll
-            for (int k = 0; k < K; ++k) GradVec<GT, V, false>::lane(uniform_base(gb + (int64_t)k * ldg), goff, f[k]);
+            for (int k = 0; k < K; ++k) GradVec<GT, V, LNT>::lane(uniform_base(gb + (int64_t)k * ldg), goff, f[k]);
 #pragma unroll
             for (int k = 0; k < K; ++k)
 #pragma unroll
                 for (int e = 0; e < V; ++e) vec_set<V>(v[k], e, fmaf(-lr, f[k][e], vec_get<V>(v[k], e)));
         }
-        if (moving) cprev = ld_lane<false, XV>(uniform_base(center_out + cell0), xoff);
+        if (moving) cprev = ld_lane<LNT, XV>(uniform_base(center_out + cell0), xoff);
     } else if (n > 0) { // the lane that holds the row's last columns
 #pragma unroll
         for (int e = 0; e < V; ++e)
@@ -473,14 +475,19 @@ __global__ __launch_bounds__(GRAWA_CELL) void k_center_pull_any(
 // launchers
 // ---------------------------------------------------------------------------------
 
-// Waves per SIMD the plain form is capped at, from sweeps of this kernel over K and
-// the cap on the part, on arrays of 3 to 11 GB holding random values (best throughput at roughly
-// 24-48 row loads in flight per SIMD).  The values matter: arrays of zeros stream about 4 % faster
-// on this part and shift some of the optima, so sweeps over cleared memory mislead.
-constexpr int grawa_waves_for(int k, bool sgd)
+// Waves per SIMD the plain form is capped at, from sweeps of this kernel over K and the cap on the part, on arrays
+// of 1 to 2 GB holding random values and three row lengths (best throughput at roughly 24 to 36 four-byte row
+// loads in flight per SIMD; a two-byte load counts half).  The best caps, TB/s at the best and one wave more:
+// K = 4 6.71 (8), 6 6.66/6.57, 8 6.57/6.46, 12 6.41/6.28, 22 6.16/5.95; with the fp32 SGD step
+// 4 6.60/6.57, 8 6.43/6.30, 12 6.13/6.07, 16 6.04/5.73; with bf16 gradients 4 6.73/6.68, 8 6.51/6.43 (one wave
+// fewer: 6.09), 12 6.28/6.25 (one fewer: 5.61), 16 5.96/5.92.
+// The values matter: arrays of zeros stream about 4 % faster on this part and shift some of the optima, so
+// sweeps over cleared memory mislead.
+constexpr int grawa_waves_for(int k, bool sgd, bool bf16)
 {
-    if (sgd) return k <= 3 ? 8 : k <= 5 ? 5 : k <= 7 ? 4 : k <= 11 ? 3 : 2;
-    return k <= 4 ? 8 : k == 5 ? 5 : k <= 8 ? 4 : k <= 16 ? 3 : 2;
+    if (sgd && bf16) return k <= 3 ? 8 : k == 4 ? 7 : k == 5 ? 6 : k == 6 ? 5 : k <= 11 ? 4 : k <= 16 ? 3 : 2;
+    if (sgd) return k <= 2 ? 8 : k == 3 ? 7 : k <= 5 ? 5 : k <= 7 ? 4 : k <= 11 ? 3 : 2;
+    return k <= 4 ? 8 : k == 5 ? 6 : k == 6 ? 5 : k <= 8 ? 4 : k <= 16 ? 3 : 2;
 }
 
 #define GRAWA_CP_ARGS                                                                                                 \
@@ -493,25 +500,26 @@ constexpr int grawa_waves_for(int k, bool sgd)
 
 template <int K, bool SGD, typename GT, bool NT, bool TILES> static void launch_plain(GRAWA_CP_ARGS)
 {
-    hipExtLaunchKernelGGL((k_center_pull<K, SGD, GT, NT, grawa_waves_for(K, SGD), TILES>), dim3((unsigned)p->n_cells),
+    hipExtLaunchKernelGGL((k_center_pull<K, SGD, GT, NT, grawa_waves_for(K, SGD, sizeof(GT) == 2), TILES>), dim3((unsigned)p->n_cells),
                           dim3(GRAWA_CELL), 0, s, e0, e1, 0, x, ldx, (const GT *)g, ldg, lr, beta, GRAWA_CP_STRIDE,
                           GRAWA_CP_CELLS, (const int64_t *)p->d_off, p->L, p->P, lambda, center_out, rho, moving, tw);
 }
 
 // The wide form's cap (best of 2, 3, 4 and 8 waves for K <= 5; one too many costs 3 to 5 %, and more than it gains over
 // the plain form), and the worker counts it is used for: where it is at least as fast as the plain form.
-constexpr int grawa_waves_wide(int k, bool sgd)
+constexpr int grawa_waves_wide(int k, bool sgd /* fp32 gradients */)
 {
+    if (k == 1) return 8;
     if (k == 2) return sgd ? 3 : 4;
     if (k == 3) return sgd ? 2 : 3;
     return k <= 5 ? 2 : 1;
 }
-static bool wide_is_faster(int k) { return k >= 2 && (k <= 5 || (k >= 12 && k <= 23)); }
+static bool wide_is_faster(int k) { return k <= 5 || (k >= 12 && k <= 23); }
 
-template <int K, bool SGD, typename GT> static void launch_wide(GRAWA_CP_ARGS)
+template <int K, bool SGD, typename GT, bool LNT> static void launch_wide(GRAWA_CP_ARGS)
 {
     (void)tw;
-    hipExtLaunchKernelGGL((k_center_pull_wide<K, SGD, GT, grawa_waves_wide(K, SGD)>), dim3((unsigned)((p->n_cells + 3) / 4)),
+    hipExtLaunchKernelGGL((k_center_pull_wide<K, SGD, GT, LNT, grawa_waves_wide(K, SGD && sizeof(GT) == 4)>), dim3((unsigned)((p->n_cells + 3) / 4)),
                           dim3(GRAWA_BLOCK), 0, s, e0, e1, 0, x, ldx, (const GT *)g, ldg, lr, beta, GRAWA_CP_STRIDE,
                           GRAWA_CP_CELLS, (const int64_t *)p->d_off, p->L, p->P, lambda, center_out, rho, moving);
 }
@@ -535,6 +543,17 @@ template <bool SGD, typename GT, bool NT> static void dispatch_cp(GRAWA_CP_ARGS)
         if (p->K % 8 == 0) launch_split<N, false, 8, 2, SGD, GT, NT>(GRAWA_CP_PASS); \
         else launch_split<N, true, 8, 2, SGD, GT, NT>(GRAWA_CP_PASS);                \
         return;
+    if constexpr (NT) {
+        if (p->K == 1) {
+            launch_wide<1, SGD, GT, true>(GRAWA_CP_PASS);
+            return;
+        }
+        if constexpr (!SGD || sizeof(GT) == 2)
+            if (p->K == 2) {
+                launch_wide<2, SGD, GT, true>(GRAWA_CP_PASS);
+                return;
+            }
+    }
     switch (p->K) {
         GRAWA_CP_PLAIN(1) GRAWA_CP_PLAIN(2) GRAWA_CP_PLAIN(3) GRAWA_CP_PLAIN(4) GRAWA_CP_PLAIN(5) GRAWA_CP_PLAIN(6)
         GRAWA_CP_PLAIN(7) GRAWA_CP_PLAIN(8) GRAWA_CP_PLAIN(9) GRAWA_CP_PLAIN(10) GRAWA_CP_PLAIN(11) GRAWA_CP_PLAIN(12)
@@ -558,9 +577,9 @@ template <bool SGD, typename GT, bool NT> static void dispatch_cp(GRAWA_CP_ARGS)
 template <bool SGD, typename GT> static void dispatch_cp_wide(GRAWA_CP_ARGS)
 {
 #define GRAWA_CP_WIDE(N) \
-    case N: launch_wide<N, SGD, GT>(GRAWA_CP_PASS); return;
+    case N: launch_wide<N, SGD, GT, false>(GRAWA_CP_PASS); return;
     switch (p->K) { // wide_is_faster()
-        GRAWA_CP_WIDE(2) GRAWA_CP_WIDE(3) GRAWA_CP_WIDE(4) GRAWA_CP_WIDE(5) GRAWA_CP_WIDE(12) GRAWA_CP_WIDE(13)
+        GRAWA_CP_WIDE(1) GRAWA_CP_WIDE(2) GRAWA_CP_WIDE(3) GRAWA_CP_WIDE(4) GRAWA_CP_WIDE(5) GRAWA_CP_WIDE(12) GRAWA_CP_WIDE(13)
         GRAWA_CP_WIDE(14) GRAWA_CP_WIDE(15) GRAWA_CP_WIDE(16) GRAWA_CP_WIDE(17) GRAWA_CP_WIDE(18) GRAWA_CP_WIDE(19)
         GRAWA_CP_WIDE(20) GRAWA_CP_WIDE(21) GRAWA_CP_WIDE(22) GRAWA_CP_WIDE(23)
     }

@@ -1,5 +1,6 @@
-"""GPU parity of large arrays whose rows do not start on cache-line boundaries (a plain [K, P] tensor): the wide
-center+pull form at the first and last worker counts of its range, beside the forms on either side of it."""
+"""GPU parity of the wide center+pull form on arrays beyond the last-level cache: rows that do not start on cache-line
+boundaries (a plain [K, P] tensor) at the first and last worker counts of its range, beside the forms on either
+side of it, and line-aligned rows of one and two workers."""
 import pytest
 import torch
 
@@ -12,13 +13,15 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-@pytest.mark.parametrize("K,dtype,fused,tail", [(2, "f32", False, 1), (5, "bf16", True, 3), (6, "f32", False, 2), (12, "f32", True, 0),
-                                                (23, "bf16", False, 2), (23, "f32", True, 1), (24, "f32", False, 1)])
-def test_large_rows_off_the_line_grid(K, dtype, fused, tail):
+@pytest.mark.parametrize("K,dtype,fused,tail,pad", [(1, "f32", False, 3, 8), (2, "f32", False, 1, 8), (5, "bf16", True, 3, 8),
+                                                    (6, "f32", False, 2, 8), (12, "f32", True, 0, 8), (23, "bf16", False, 2, 8),
+                                                    (23, "f32", True, 1, 8), (24, "f32", False, 1, 8), (1, "bf16", True, 1, 0),
+                                                    (1, "f32", True, 2, 0), (2, "f32", False, 3, 0), (2, "bf16", True, 1, 0)])
+def test_wide_form(K, dtype, fused, tail, pad):
     P = (530 << 20) // (4 * K) // 1024 * 1024 + 1024 - 300 + tail       # the last block is partly empty, its last lane too
     w = W.Workload("tight_K%d" % K, K, [P // 3, 1, 5, P - P // 3 - 6], grad_dtype=dtype, lam=0.1, lr=0.1, seed=(5, K))
-    x, g = W.make_inputs(w, device=DEV, ld_pad=8)
-    assert x.stride(0) % 32
+    x, g = W.make_inputs(w, device=DEV, ld_pad=pad)
+    assert bool(x.stride(0) % 32) == bool(pad)
     x0, lr = x.clone(), w.lr if fused else 0.0
     cen = torch.empty(W.round_up(P, 4), device=DEV)
     wts = torch.empty((K, w.L), device=DEV)
