@@ -3,8 +3,8 @@
 // part of the update; every step runs in the kernels of grawa_norms.hip, grawa_pull.hip and grawa_local.hip.
 #include <cmath>
 #include <cstring>
+#include <memory>
 #include <new>
-#include <vector>
 
 #include "grawa_internal.h"
 
@@ -144,7 +144,22 @@ static grawa_status_t plan_create_impl(grawa_plan_t **out, int K, int64_t P, int
     const int64_t nrb = (int64_t)m.block_rtile0.size() - 1;
     const int64_t nc = (int64_t)m.cell_layer.size();
 
-    const std::vector<float> uniform((size_t)K, 1.f / (float)K);
+    const size_t b_off = round256(sizeof(int64_t) * ((size_t)L + 1));
+    const size_t b_cells = round256(sizeof(int32_t) * (size_t)nc);
+    const size_t b_tiles = round256(sizeof(GrawaTile) * (size_t)nt);
+    const size_t b_rtiles = round256(sizeof(GrawaTile) * (size_t)nrt);
+    const size_t b_lt0 = round256(sizeof(int32_t) * ((size_t)L + 1));
+    const size_t b_brt0 = round256(sizeof(int32_t) * ((size_t)nrb + 1));
+    const size_t b_part = round256(sizeof(double) * (size_t)K * (size_t)(nrt > nt ? nrt : nt));
+    const size_t b_S = round256(sizeof(double) * (size_t)K * (size_t)L);
+    const size_t b_bl = round256(sizeof(float) * (size_t)K * (size_t)L);
+    const size_t b_bm = round256(sizeof(float) * (size_t)K);
+    const size_t b_mvg = b_S;
+    const size_t b_ckl = round256(sizeof(unsigned) * (size_t)K * (size_t)L);
+    const size_t b_t = 256;
+    const size_t b_zeroed = b_part + b_S + b_bl + b_bm + b_mvg + b_ckl + b_t;
+    const size_t b_host = b_off + b_cells + b_tiles + b_lt0 + b_rtiles + b_lt0 + b_brt0 + b_bm;
+    const std::unique_ptr<char[]> host(new char[b_host]); // may throw: before anything that would have to be freed
 
     grawa_plan *p = new (std::nothrow) grawa_plan();
     if (!p) return GRAWA_ERR_WORKSPACE;
@@ -160,22 +175,7 @@ static grawa_status_t plan_create_impl(grawa_plan_t **out, int K, int64_t P, int
         delete p;
         return GRAWA_ERR_HIP;
     }
-
-    const size_t b_off = round256(sizeof(int64_t) * ((size_t)L + 1));
-    const size_t b_cells = round256(sizeof(int32_t) * (size_t)nc);
-    const size_t b_tiles = round256(sizeof(GrawaTile) * (size_t)nt);
-    const size_t b_rtiles = round256(sizeof(GrawaTile) * (size_t)nrt);
-    const size_t b_lt0 = round256(sizeof(int32_t) * ((size_t)L + 1));
-    const size_t b_brt0 = round256(sizeof(int32_t) * ((size_t)nrb + 1));
-    const size_t b_part = round256(sizeof(double) * (size_t)K * (size_t)(nrt > nt ? nrt : nt));
-    const size_t b_S = round256(sizeof(double) * (size_t)K * (size_t)L);
-    const size_t b_bl = round256(sizeof(float) * (size_t)K * (size_t)L);
-    const size_t b_bm = round256(sizeof(float) * (size_t)K);
-    const size_t b_mvg = b_S;
-    const size_t b_ckl = round256(sizeof(unsigned) * (size_t)K * (size_t)L);
-    const size_t b_t = 256;
-    const size_t b_zeroed = b_part + b_S + b_bl + b_bm + b_mvg + b_ckl + b_t;
-    p->ws_bytes = b_off + b_cells + b_tiles + b_lt0 + b_rtiles + b_lt0 + b_brt0 + b_bm + b_zeroed;
+    p->ws_bytes = b_host + b_zeroed;
     if (hipMalloc(&p->ws, p->ws_bytes) != hipSuccess) {
         (void)hipGetLastError();
         delete p;
@@ -201,14 +201,22 @@ static grawa_status_t plan_create_impl(grawa_plan_t **out, int K, int64_t P, int
     p->d_flags = reinterpret_cast<unsigned *>(w + 64);
     p->d_cnt_all = reinterpret_cast<unsigned *>(w + 128);
 
-    if (hipMemcpy(p->d_off, off, sizeof(int64_t) * ((size_t)L + 1), hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(p->d_cell_layer, m.cell_layer.data(), sizeof(int32_t) * (size_t)nc, hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(p->d_tiles, m.tiles.data(), sizeof(GrawaTile) * (size_t)nt, hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(p->d_layer_tile0, m.layer_tile0.data(), sizeof(int32_t) * ((size_t)L + 1), hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(p->d_rtiles, m.rtiles.data(), sizeof(GrawaTile) * (size_t)nrt, hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(p->d_layer_rtile0, m.layer_rtile0.data(), sizeof(int32_t) * ((size_t)L + 1), hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(p->d_block_rtile0, m.block_rtile0.data(), sizeof(int32_t) * ((size_t)nrb + 1), hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(p->d_beta_uniform, uniform.data(), sizeof(float) * (size_t)K, hipMemcpyHostToDevice) != hipSuccess ||
+    // Everything before the partials comes from the host, in one copy.
+    char *at = host.get();
+    const auto put = [&](const void *src, size_t bytes, size_t room) {
+        std::memcpy(at, src, bytes);
+        at += room;
+    };
+    put(off, sizeof(int64_t) * ((size_t)L + 1), b_off);
+    put(m.cell_layer.data(), sizeof(int32_t) * (size_t)nc, b_cells);
+    put(m.tiles.data(), sizeof(GrawaTile) * (size_t)nt, b_tiles);
+    put(m.layer_tile0.data(), sizeof(int32_t) * ((size_t)L + 1), b_lt0);
+    put(m.rtiles.data(), sizeof(GrawaTile) * (size_t)nrt, b_rtiles);
+    put(m.layer_rtile0.data(), sizeof(int32_t) * ((size_t)L + 1), b_lt0);
+    put(m.block_rtile0.data(), sizeof(int32_t) * ((size_t)nrb + 1), b_brt0);
+    float *uniform = reinterpret_cast<float *>(at);
+    for (int k = 0; k < K; ++k) uniform[k] = 1.f / (float)K;
+    if (hipMemcpy(p->ws, host.get(), b_host, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemset(p->d_partials, 0, b_zeroed) != hipSuccess) {
         (void)hipFree(p->ws);
         delete p;

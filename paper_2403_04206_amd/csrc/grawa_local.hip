@@ -76,8 +76,8 @@ __device__ __forceinline__ void row_tile_done(const RowScores &a, unsigned k, in
 // block_tile0[m] .. block_tile0[m+1]-1 lie in aligned block m, each inside one layer).  Nearly
 // every block holds one tile; a block that contains layer boundaries reduces once per tile.
 // The last P % V columns of a row are handled element by element.
-template <typename GT, int V, int U, bool NT, bool PROX, int SCORE>
-__global__ __launch_bounds__(GRAWA_CELL) void k_row_step(float *__restrict__ x, int64_t ldx,
+template <typename GT, int V, int U, bool LNT, bool SNT, bool PROX, int SCORE>
+__global__ __launch_bounds__(GRAWA_CELL) __attribute__((amdgpu_waves_per_eu(1, PROX && !SCORE ? 7 : 8))) void k_row_step(float *__restrict__ x, int64_t ldx,
                                                          const GT *__restrict__ g, int64_t ldg, float lr,
                                                          const float *__restrict__ center, float w, int64_t P,
                                                          unsigned n_blocks, const RowScores a)
@@ -97,8 +97,8 @@ __global__ __launch_bounds__(GRAWA_CELL) void k_row_step(float *__restrict__ x, 
         const int64_t c = c0 + (int64_t)u * (GRAWA_CELL * V);
         if (c + V <= P) {
             const XV *xp = reinterpret_cast<const XV *>(xr + c);
-            xv[u] = NT ? __builtin_nontemporal_load(xp) : *xp;
-            GradVec<GT, V, NT>::load(gr + c, gf[u]);
+            xv[u] = LNT ? __builtin_nontemporal_load(xp) : *xp;
+            GradVec<GT, V, LNT>::load(gr + c, gf[u]);
             if (PROX) cv[u] = *reinterpret_cast<const XV *>(center + c); // cached: shared by the K rows
         } else {
 #pragma unroll
@@ -122,7 +122,7 @@ __global__ __launch_bounds__(GRAWA_CELL) void k_row_step(float *__restrict__ x, 
                 if (PROX) v = fmaf(w, vec_get<V>(cv[u], e) - v, v);
                 vec_set<V>(o, e, v);
             }
-            st_lane<NT, XV>(uniform_base(xr + (int64_t)m * GRAWA_ROW_BLOCK), (threadIdx.x + u * GRAWA_CELL) * (V * 4u), o);
+            st_lane<SNT, XV>(uniform_base(xr + (int64_t)m * GRAWA_ROW_BLOCK), (threadIdx.x + u * GRAWA_CELL) * (V * 4u), o);
         } else if (V > 1 && c < P) { // the vector that holds the row's last columns
 #pragma unroll
             for (int e = 0; e < V; ++e)
@@ -165,9 +165,12 @@ __global__ __launch_bounds__(GRAWA_CELL) void k_row_step(float *__restrict__ x, 
 // Nesterov-momentum SGD step
 // ---------------------------------------------------------------------------------
 
-// Vector shape of the Nesterov step: fp32 gradients V = 1, U = 4; bf16 V = 2, U = 2 (measured
-// 6.3-6.4 TB/s for both; bf16 at V = 4, U = 4 5.6: more bytes in flight per lane cost bandwidth at
-// full occupancy, and 2-byte loads (V = 1) waste requests).
+// Vector shape of the Nesterov step: fp32 gradients V = 1, U = 4; bf16 V = 2, U = 2 (bf16 at V = 4, U = 4
+// 5.6 TB/s: more bytes in flight per lane cost bandwidth at full occupancy, and 2-byte loads (V = 1) waste
+// requests).  Waves per SIMD: bf16 6 (36.5 M columns x 8 workers 795 us; 5: 810, 7: 810, 8: 825), fp32 8 (889; 6: 914).
+// Large rows off the cache-line grid with bf16 gradients: V = 4, cached loads and streaming stores (47 M elements,
+// 4 workers 152.5 -> 132.5 us, 400 M, 3 workers 1345 -> 1307); with fp32 gradients from 512 MB on (400 M, 3 workers
+// 1478 -> 1453; 25 M 92.5 -> 94.6).
 #define GRAWA_SGD_V_F32 1
 #define GRAWA_SGD_U_F32 4
 #define GRAWA_SGD_V_BF16 2
@@ -177,8 +180,8 @@ __global__ __launch_bounds__(GRAWA_CELL) void k_row_step(float *__restrict__ x, 
 // block 256*V columns apart; the last P % V columns of a row take a scalar path.  One step of SGD with Nesterov momentum and weight decay
 // (the local optimizer of Appendix B.2.2), buf = momentum buffer [K][ldb], zero before the first step:
 //     d = g + wd x ;  buf <- momentum buf + d ;  x <- x - lr (d + momentum buf).
-template <typename GT, int V, int U, bool NT>
-__global__ __launch_bounds__(GRAWA_CELL) void k_nesterov(float *__restrict__ x, int64_t ldx,
+template <typename GT, int V, int U, bool LNT, bool SNT>
+__global__ __launch_bounds__(GRAWA_CELL) __attribute__((amdgpu_waves_per_eu(1, sizeof(GT) == 2 ? 6 : 8))) void k_nesterov(float *__restrict__ x, int64_t ldx,
                                                          const GT *__restrict__ g, int64_t ldg,
                                                          float *__restrict__ buf, int64_t ldb, int64_t P,
                                                          float lr, float momentum, float wd)
@@ -197,9 +200,9 @@ __global__ __launch_bounds__(GRAWA_CELL) void k_nesterov(float *__restrict__ x, 
         if (j < nvec) {
             const XV *xp = reinterpret_cast<const XV *>(xr + j * V);
             const XV *bp = reinterpret_cast<const XV *>(br + j * V);
-            xv[u] = NT ? __builtin_nontemporal_load(xp) : *xp;
-            bv[u] = NT ? __builtin_nontemporal_load(bp) : *bp;
-            GradVec<GT, V, NT>::load(gr + j * V, gf[u]);
+            xv[u] = LNT ? __builtin_nontemporal_load(xp) : *xp;
+            bv[u] = LNT ? __builtin_nontemporal_load(bp) : *bp;
+            GradVec<GT, V, LNT>::load(gr + j * V, gf[u]);
         }
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -218,8 +221,8 @@ __global__ __launch_bounds__(GRAWA_CELL) void k_nesterov(float *__restrict__ x, 
             }
             const int64_t c0 = (int64_t)blockIdx.x * (GRAWA_CELL * U * V);
             const unsigned o = (threadIdx.x + u * GRAWA_CELL) * (V * 4u);
-            st_lane<NT, XV>(uniform_base(xr + c0), o, xo);
-            st_lane<NT, XV>(uniform_base(br + c0), o, bo);
+            st_lane<SNT, XV>(uniform_base(xr + c0), o, xo);
+            st_lane<SNT, XV>(uniform_base(br + c0), o, bo);
         }
     }
     if (blockIdx.x == 0 && threadIdx.x < (unsigned)(P - nvec * V)) {
@@ -260,6 +263,11 @@ __global__ __launch_bounds__(GRAWA_COPY_BLOCK) void k_stream_copy(v4u *__restric
 // V = 4, U = 1 with the proximity step or the scores; bf16 V = 2, U = 2 for the plain step, else
 // V = 4, U = 1 (each the fastest measured for its case on arrays of random values; the spread
 // between shapes is 3-10 %).
+// Large rows off the cache-line grid (wide): 16-byte lanes, cached loads, so that the lines two waves share are
+// fetched once, and streaming stores.  Against cached accesses, us, 400 M elements x 4 bytes, 12 workers, rows 32
+// bytes off a line: with the center fp32 946 -> 894, bf16 811 -> 726; a round of two scored steps and the communication
+// 2556 -> 2448, 2266 -> 2100.  The plain step only from 512 MB on: at 360 MB the pull that follows would lose
+// the part of x a cached step leaves in the cache (step and LSGD phase 330 -> 349).
 static hipError_t launch_row_step(const grawa_plan *p, float *x, int64_t ldx, const void *g, int64_t ldg,
                                   grawa_dtype_t dt, float lr, const float *center, float w, int K, int64_t P,
                                   double gamma, hipStream_t s)
@@ -271,8 +279,11 @@ static hipError_t launch_row_step(const grawa_plan *p, float *x, int64_t ldx, co
     const int64_t n_groups = (nb + group - 1) / group;
     if (K > 65535 || n_groups > 65535 || group >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)group, (unsigned)K, (unsigned)n_groups), block(GRAWA_CELL);
-    const bool nt = (int64_t)K * P * 4 > (prox || p ? GRAWA_STREAMING_MIN_ROW_BYTES : GRAWA_STREAMING_MIN_SGD_BYTES) &&
-                    rows_line_aligned(x, ldx, 4) && rows_line_aligned(g, ldg, dt == GRAWA_BF16 ? 2 : 4);
+    const bool aligned = rows_line_aligned(x, ldx, 4) && rows_line_aligned(g, ldg, dt == GRAWA_BF16 ? 2 : 4);
+    const int64_t bytes = (int64_t)K * P * 4;
+    const bool plain = !prox && !p;
+    const bool nt = aligned && bytes > (plain ? GRAWA_STREAMING_MIN_SGD_BYTES : GRAWA_STREAMING_MIN_ROW_BYTES);
+    const bool wide = !aligned && bytes > (plain ? 2 * GRAWA_STREAMING_MIN_SGD_BYTES : GRAWA_STREAMING_MIN_ROW_BYTES);
     RowScores a = {};
     int score = 0;
     if (p) {
@@ -280,13 +291,14 @@ static hipError_t launch_row_step(const grawa_plan *p, float *x, int64_t ldx, co
                       p->d_mvg, gamma, p->d_local_t, p->d_flags};
         score = nb * K <= GRAWA_FUSE_MAX_ROW_BLOCKS ? 2 : 1;
     }
-#define GRAWA_RS_GO(GT, V, U, NT, PROX, SCORE)                                                                   \
-    k_row_step<GT, V, U, NT, PROX, SCORE><<<grid, block, 0, s>>>(x, ldx, (const GT *)g, ldg, lr, center, w, P, \
-                                                                 (unsigned)nb, a)
-#define GRAWA_RS_NT(GT, V, U, PROX, SCORE)              \
-    do {                                                \
-        if (nt) GRAWA_RS_GO(GT, V, U, true, PROX, SCORE); \
-        else GRAWA_RS_GO(GT, V, U, false, PROX, SCORE);   \
+#define GRAWA_RS_GO(GT, V, U, LNT, SNT, PROX, SCORE)                                                                   \
+    k_row_step<GT, V, U, LNT, SNT, PROX, SCORE><<<grid, block, 0, s>>>(x, ldx, (const GT *)g, ldg, lr, center, w, P, \
+                                                                       (unsigned)nb, a)
+#define GRAWA_RS_NT(GT, V, U, PROX, SCORE)                          \
+    do {                                                            \
+        if (nt) GRAWA_RS_GO(GT, V, U, true, true, PROX, SCORE);     \
+        else if (wide) GRAWA_RS_GO(GT, 4, 1, false, true, PROX, SCORE); \
+        else GRAWA_RS_GO(GT, V, U, false, false, PROX, SCORE);      \
     } while (0)
 #define GRAWA_RS_SCORE(GT, SCORE)                     \
     do {                                              \
@@ -328,21 +340,22 @@ hipError_t grawa_launch_row_step_scored(const grawa_plan *p, float *x, int64_t l
 hipError_t grawa_launch_nesterov(float *x, int64_t ldx, const void *g, int64_t ldg, grawa_dtype_t dt, float *buf,
                                  int64_t ldb, int K, int64_t P, float lr, float momentum, float wd, hipStream_t s)
 {
-    const int64_t per_block = dt == GRAWA_BF16 ? GRAWA_CELL * GRAWA_SGD_U_BF16 * GRAWA_SGD_V_BF16
-                                               : GRAWA_CELL * GRAWA_SGD_U_F32 * GRAWA_SGD_V_F32;
-    int64_t gx = (P + per_block - 1) / per_block;
-    if (gx < 1) gx = 1;
-    const dim3 grid((unsigned)gx, (unsigned)K), block(GRAWA_CELL);
-    const bool nt = (int64_t)K * P * 4 > GRAWA_STREAMING_MIN_BYTES && rows_line_aligned(x, ldx, 4) &&
-                    rows_line_aligned(buf, ldb, 4) && rows_line_aligned(g, ldg, dt == GRAWA_BF16 ? 2 : 4);
-#define GRAWA_NAG_GO(GT, V, U, NT) \
-    k_nesterov<GT, V, U, NT><<<grid, block, 0, s>>>(x, ldx, (const GT *)g, ldg, buf, ldb, P, lr, momentum, wd)
+    const int64_t bytes = (int64_t)K * P * 4;
+    const bool large = bytes > GRAWA_STREAMING_MIN_BYTES;
+    const bool nt = large && rows_line_aligned(x, ldx, 4) && rows_line_aligned(buf, ldb, 4) &&
+                    rows_line_aligned(g, ldg, dt == GRAWA_BF16 ? 2 : 4);
+#define GRAWA_NAG_GO(GT, V, U, LNT, SNT)                                                                          \
+    k_nesterov<GT, V, U, LNT, SNT><<<dim3((unsigned)((P + GRAWA_CELL * (U) * (V) - 1) / (GRAWA_CELL * (U) * (V))), \
+                                          (unsigned)K), dim3(GRAWA_CELL), 0, s>>>(                               \
+        x, ldx, (const GT *)g, ldg, buf, ldb, P, lr, momentum, wd)
     if (dt == GRAWA_BF16) {
-        if (nt) GRAWA_NAG_GO(uint16_t, GRAWA_SGD_V_BF16, GRAWA_SGD_U_BF16, true);
-        else GRAWA_NAG_GO(uint16_t, GRAWA_SGD_V_BF16, GRAWA_SGD_U_BF16, false);
+        if (nt) GRAWA_NAG_GO(uint16_t, GRAWA_SGD_V_BF16, GRAWA_SGD_U_BF16, true, true);
+        else if (large) GRAWA_NAG_GO(uint16_t, 4, 1, false, true);
+        else GRAWA_NAG_GO(uint16_t, GRAWA_SGD_V_BF16, GRAWA_SGD_U_BF16, false, false);
     } else {
-        if (nt) GRAWA_NAG_GO(float, GRAWA_SGD_V_F32, GRAWA_SGD_U_F32, true);
-        else GRAWA_NAG_GO(float, GRAWA_SGD_V_F32, GRAWA_SGD_U_F32, false);
+        if (nt) GRAWA_NAG_GO(float, GRAWA_SGD_V_F32, GRAWA_SGD_U_F32, true, true);
+        else if (bytes > 4 * GRAWA_STREAMING_MIN_BYTES) GRAWA_NAG_GO(float, 4, 1, false, true);
+        else GRAWA_NAG_GO(float, GRAWA_SGD_V_F32, GRAWA_SGD_U_F32, false, false);
     }
 #undef GRAWA_NAG_GO
     return hipGetLastError();
