@@ -5,6 +5,7 @@
 #include <cstring>
 #include <memory>
 #include <new>
+#include <vector>
 
 #include "grawa_internal.h"
 
@@ -159,7 +160,9 @@ static grawa_status_t plan_create_impl(grawa_plan_t **out, int K, int64_t P, int
     const size_t b_t = 256;
     const size_t b_zeroed = b_part + b_S + b_bl + b_bm + b_mvg + b_ckl + b_t;
     const size_t b_host = b_off + b_cells + b_tiles + b_lt0 + b_rtiles + b_lt0 + b_brt0 + b_bm;
-    const std::unique_ptr<char[]> host(new char[b_host]); // may throw: before anything that would have to be freed
+    // These may throw: before anything that would have to be freed.
+    const std::vector<float> uniform((size_t)K, 1.f / (float)K);
+    const std::unique_ptr<char[]> host(b_host <= ((size_t)1 << 20) ? new char[b_host] : nullptr);
 
     grawa_plan *p = new (std::nothrow) grawa_plan();
     if (!p) return GRAWA_ERR_WORKSPACE;
@@ -201,10 +204,12 @@ static grawa_status_t plan_create_impl(grawa_plan_t **out, int K, int64_t P, int
     p->d_flags = reinterpret_cast<unsigned *>(w + 64);
     p->d_cnt_all = reinterpret_cast<unsigned *>(w + 128);
 
-    // Everything before the partials comes from the host, in one copy.
-    char *at = host.get();
+    // Everything before the partials comes from the host: small maps in one copy, large ones from where they are.
+    size_t at = 0;
+    bool ok = true;
     const auto put = [&](const void *src, size_t bytes, size_t room) {
-        std::memcpy(at, src, bytes);
+        if (host) std::memcpy(host.get() + at, src, bytes);
+        else ok = ok && hipMemcpy(static_cast<char *>(p->ws) + at, src, bytes, hipMemcpyHostToDevice) == hipSuccess;
         at += room;
     };
     put(off, sizeof(int64_t) * ((size_t)L + 1), b_off);
@@ -214,10 +219,9 @@ static grawa_status_t plan_create_impl(grawa_plan_t **out, int K, int64_t P, int
     put(m.rtiles.data(), sizeof(GrawaTile) * (size_t)nrt, b_rtiles);
     put(m.layer_rtile0.data(), sizeof(int32_t) * ((size_t)L + 1), b_lt0);
     put(m.block_rtile0.data(), sizeof(int32_t) * ((size_t)nrb + 1), b_brt0);
-    float *uniform = reinterpret_cast<float *>(at);
-    for (int k = 0; k < K; ++k) uniform[k] = 1.f / (float)K;
-    if (hipMemcpy(p->ws, host.get(), b_host, hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemset(p->d_partials, 0, b_zeroed) != hipSuccess) {
+    put(uniform.data(), sizeof(float) * (size_t)K, b_bm);
+    if (host) ok = hipMemcpy(p->ws, host.get(), b_host, hipMemcpyHostToDevice) == hipSuccess;
+    if (!ok || hipMemset(p->d_partials, 0, b_zeroed) != hipSuccess) {
         (void)hipFree(p->ws);
         delete p;
         return GRAWA_ERR_HIP;

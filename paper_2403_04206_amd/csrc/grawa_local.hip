@@ -122,7 +122,10 @@ __global__ __launch_bounds__(GRAWA_CELL) __attribute__((amdgpu_waves_per_eu(1, P
                 if (PROX) v = fmaf(w, vec_get<V>(cv[u], e) - v, v);
                 vec_set<V>(o, e, v);
             }
-            st_lane<SNT, XV>(uniform_base(xr + (int64_t)m * GRAWA_ROW_BLOCK), (threadIdx.x + u * GRAWA_CELL) * (V * 4u), o);
+            if (SNT)
+                st_lane<true, XV>(uniform_base(xr + (int64_t)m * GRAWA_ROW_BLOCK), (threadIdx.x + u * GRAWA_CELL) * (V * 4u), o);
+            else
+                *reinterpret_cast<XV *>(xr + c) = o;
         } else if (V > 1 && c < P) { // the vector that holds the row's last columns
 #pragma unroll
             for (int e = 0; e < V; ++e)
@@ -219,10 +222,15 @@ __global__ __launch_bounds__(GRAWA_CELL) __attribute__((amdgpu_waves_per_eu(1, s
                 vec_set<V>(bo, c, b);
                 vec_set<V>(xo, c, fmaf(-lr, fmaf(momentum, b, d), xc));
             }
-            const int64_t c0 = (int64_t)blockIdx.x * (GRAWA_CELL * U * V);
-            const unsigned o = (threadIdx.x + u * GRAWA_CELL) * (V * 4u);
-            st_lane<SNT, XV>(uniform_base(xr + c0), o, xo);
-            st_lane<SNT, XV>(uniform_base(br + c0), o, bo);
+            if (SNT) {
+                const int64_t c0 = (int64_t)blockIdx.x * (GRAWA_CELL * U * V);
+                const unsigned o = (threadIdx.x + u * GRAWA_CELL) * (V * 4u);
+                st_lane<true, XV>(uniform_base(xr + c0), o, xo);
+                st_lane<true, XV>(uniform_base(br + c0), o, bo);
+            } else {
+                *reinterpret_cast<XV *>(xr + j * V) = xo;
+                *reinterpret_cast<XV *>(br + j * V) = bo;
+            }
         }
     }
     if (blockIdx.x == 0 && threadIdx.x < (unsigned)(P - nvec * V)) {
