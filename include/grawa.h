@@ -291,7 +291,7 @@ grawa_status_t grawa_lsgd_update(grawa_plan_t *plan, float *x, int64_t ldx, cons
  *   x, g, lambda, center_out, weights_out: as in grawa_lgrawa_update.
  * Limits: K <= GRAWA_MAX_WORKERS, and the workspace must fit the array:
  *   4*ceil(P/256) + (16 + 8K)*(P/T + L + 1) + 16*K*L + 4K + 4L bytes (each part
- *   rounded up to 256) <= 32 MiB, T the tile length a plan would pick (2048 ..
+ *   rounded up to 256) <= 32 MiB, T the tile length a plan would pick (4096 ..
  *   16384); the largest benchmark configuration (P = 354 M, K = 8) needs 7 MiB.
  *   Beyond that:
  *   GRAWA_ERR_UNSUPPORTED, nothing launched.

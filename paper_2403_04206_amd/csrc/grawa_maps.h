@@ -30,7 +30,7 @@ struct GrawaHostMaps {
     std::vector<int32_t> cell_layer;    // [ceil(P/256)] layer of a cell, or ~(first layer) if it holds a boundary
 };
 
-// Norm-pass tile length for a problem: as long as possible while leaving ~8192 blocks.
+// Norm-pass tile length for a problem: as long as possible while leaving ~4096 blocks.
 int grawa_default_tile_elems(int K, int64_t P);
 
 // 0: offsets are valid (off[0] = 0, strictly increasing, off[L] = P, 1 <= L <= P); 1 otherwise.

@@ -24,6 +24,27 @@
 // norms as a float64 evaluation up to the order of the additions.  The pass needs under a
 // fifth of the fp64 rate at full HBM speed, so this costs no time.
 #define GRAWA_SUMSQ_U 8
+
+// The last, partial trip of up to N loads per lane: a lane past the end loads a clamped (valid) address and
+// discards the value.
+template <typename GT, int N>
+__device__ __forceinline__ void sumsq_rest(const GT *body, int j0, int nvec, double (&acc)[GRAWA_SUMSQ_U])
+{
+    if (j0 >= nvec) return;
+    typename Grad<GT>::Vec8 q[N];
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+        const int j = j0 + u * GRAWA_BLOCK;
+        q[u] = Grad<GT>::load8(body + (int64_t)(j < nvec ? j : j0) * Grad<GT>::VEC8);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+        const double r = Grad<GT>::sumsq8(q[u], 0.0);
+        acc[u] += (j0 + u * GRAWA_BLOCK < nvec) ? r : 0.0;
+    }
+}
+
 template <typename GT>
 __global__ __launch_bounds__(GRAWA_BLOCK) __attribute__((amdgpu_waves_per_eu(1, 4))) void k_sumsq(
     const GT *__restrict__ g, int64_t ldg, const GrawaTile *__restrict__ tiles, int64_t n_tiles,
@@ -53,8 +74,7 @@ __global__ __launch_bounds__(GRAWA_BLOCK) __attribute__((amdgpu_waves_per_eu(1, 
         acc[1] = sq_add(Grad<GT>::one(row + b_al + (tid - GRAWA_WAVE)), 0.0);
     }
 
-    // Body: all loads of a trip are issued before any is used.  Full trips need no bounds
-    // checks; the last, partial trip loads a clamped (valid) address and discards the value.
+    // Body: all loads of a trip are issued before any is used.  Full trips need no bounds checks.
     const int nvec = (int)((b_al - a_al) / V);
     const GT *body = row + a_al;
     typename Grad<GT>::Vec8 q[GRAWA_SUMSQ_U];
@@ -66,19 +86,13 @@ __global__ __launch_bounds__(GRAWA_BLOCK) __attribute__((amdgpu_waves_per_eu(1, 
 #pragma unroll
         for (int u = 0; u < GRAWA_SUMSQ_U; ++u) acc[u] = Grad<GT>::sumsq8(q[u], acc[u]);
     }
-    if (j0 < nvec) {
-#pragma unroll
-        for (int u = 0; u < GRAWA_SUMSQ_U; ++u) {
-            const int j = j0 + u * GRAWA_BLOCK;
-            q[u] = Grad<GT>::load8(body + (int64_t)(j < nvec ? j : j0) * V);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int u = 0; u < GRAWA_SUMSQ_U; ++u) {
-            const double r = Grad<GT>::sumsq8(q[u], 0.0);
-            acc[u] += (j0 + u * GRAWA_BLOCK < nvec) ? r : 0.0;
-        }
-    }
+    // What is left is less than a trip: a trip of as few loads as hold it (block-uniform), so that a short tile does
+    // not load, convert and discard values.
+    const int left = nvec - (j0 - tid);
+    if (left > 4 * GRAWA_BLOCK) sumsq_rest<GT, 8>(body, j0, nvec, acc);
+    else if (left > 2 * GRAWA_BLOCK) sumsq_rest<GT, 4>(body, j0, nvec, acc);
+    else if (left > GRAWA_BLOCK) sumsq_rest<GT, 2>(body, j0, nvec, acc);
+    else sumsq_rest<GT, 1>(body, j0, nvec, acc);
 
     __shared__ double sm[GRAWA_BLOCK / GRAWA_WAVE];
     double lane = 0.0;
