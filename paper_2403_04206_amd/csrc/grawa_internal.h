@@ -38,8 +38,7 @@ struct grawa_plan {
     float *d_beta_layer;    // [K][L] per-layer weights
     float *d_beta_model;    // [K] model-level weights
     float *d_beta_uniform;  // [K] 1/K each (EASGD), written once
-    unsigned *d_cnt_kl;     // [K][L] arrivals of the tiles of a (worker, layer); every counter is 0 between calls
-    unsigned *d_cnt_all;    // [1] arrivals of the layers
+    unsigned *d_cnt_all;    // [1] arrivals of the layers; 0 between calls
     double *d_mvg;          // [K][L] moving average of the layer norms (running estimate, Appendix G)
     int64_t *d_local_t;     // device: local steps since the last communication (what the kernels use)
     unsigned *d_flags;      // device: GRAWA_NONFINITE_* bits, sticky until read-and-cleared (may be null)

@@ -7,7 +7,7 @@
 //   k_stream_copy  plain copy (measurement aid)
 // All are read-modify-write streams with no reuse: global loads and stores kept in flight, one
 // row (worker) per block, which is the access shape that streams fastest on this part.
-#include "grawa_scores.h"
+#include "grawa_device.h"
 
 // ---------------------------------------------------------------------------------
 // local step, row by row
@@ -16,54 +16,20 @@
 #define GRAWA_ROW_BLOCK 1024 // columns per block
 #define GRAWA_ROW_GROUP 4096 // column blocks of one row launched back to back (4 Mi columns)
 
-// Where the tile sums of a scored step go.
+// Where the tile sums of a scored step go: to k_estimate.  (Updating the estimate inside this launch, by the block
+// that brings the last tile of a (worker, layer), was tried: its device-scope traffic costs more than the launch from
+// about 1000 blocks or 30 tiles per layer on, 4 steps and the communication on 8 workers 117 us instead of 45.)
 struct RowScores {
     const GrawaTile *tiles;      // 1024-column tiles, and the first one of every aligned block of 1024 columns
     const int32_t *block_tile0;
-    const int32_t *layer_tile0;  // [L+1]
-    int L;
     double *partials;            // [K][n_tiles]
     int64_t n_tiles;
-    unsigned *cnt_kl;            // [K][L]
-    double *mvg;                 // [K][L]
-    double gamma;
-    int64_t *local_t;
-    unsigned *flags;
 };
-
-// Tile t of worker k is summed up (acc: one part per thread).  SCORE 1: the sum is left for k_estimate.
-// SCORE 2: the block that brings the last tile of (worker, layer) adds the layer's tiles and updates the estimate.
-template <int SCORE>
-__device__ __forceinline__ void row_tile_done(const RowScores &a, unsigned k, int t, double acc, double *sm,
-                                              unsigned *sh_last)
-{
-    double tot = block_sum<GRAWA_BLOCK>(acc, sm);
-    double *row = a.partials + (int64_t)k * a.n_tiles;
-    if constexpr (SCORE == 1) {
-        if (threadIdx.x == 0) row[t] = tot;
-        return;
-    }
-    const int l = a.tiles[t].layer;
-    const int first = a.layer_tile0[l], end = a.layer_tile0[l + 1];
-    const int64_t at = (int64_t)k * a.L + l;
-    if (end - first > 1) {
-        if (threadIdx.x == 0) hand_over(row + t, tot);
-        if (!last_to_arrive(a.cnt_kl + at, (unsigned)(end - first), sh_last)) return;
-        double s = 0.0;
-        for (int j = first + (int)threadIdx.x; j < end; j += GRAWA_BLOCK) s += take_over(row + j);
-        tot = block_sum<GRAWA_BLOCK>(s, sm);
-    }
-    if (threadIdx.x == 0) {
-        estimate_step(a.mvg + at, sqrt(tot), a.gamma, a.flags);
-        if (at == 0) *a.local_t += 1;
-    }
-}
 
 // One block = one aligned block of 1024 columns of one worker; V * U * 256 = 1024, a lane handles U
 // vectors of V adjacent columns.  All loads are issued at once, then
 //     x <- x - lr g ;   PROX: x <- x + w (c - x), c the stored center, w = mu/tau ;
-//     SCORE: sum over each tile of g^2 in fp64, from the values in registers; 1: left in partials[k][tile] for
-//     k_estimate, 2: taken up to the running estimate inside this launch (see row_tile_done).
+//     SCORE: partials[k][tile] = sum over the tile of g^2 in fp64, from the values in registers.
 // grid (group, K, n_groups): the column blocks are cut into groups of gridDim.x; blocks are started
 // with x fastest, so within a group the blocks of worker 0 come first, then worker 1, ..., and no
 // index arithmetic is needed to find a block's place.  Blocks that run together therefore stream one
@@ -76,7 +42,7 @@ __device__ __forceinline__ void row_tile_done(const RowScores &a, unsigned k, in
 // block_tile0[m] .. block_tile0[m+1]-1 lie in aligned block m, each inside one layer).  Nearly
 // every block holds one tile; a block that contains layer boundaries reduces once per tile.
 // The last P % V columns of a row are handled element by element.
-template <typename GT, int V, int U, bool LNT, bool SNT, bool PROX, int SCORE>
+template <typename GT, int V, int U, bool LNT, bool SNT, bool PROX, bool SCORE>
 __global__ __launch_bounds__(GRAWA_CELL) __attribute__((amdgpu_waves_per_eu(1, PROX && !SCORE ? 7 : 8))) void k_row_step(float *__restrict__ x, int64_t ldx,
                                                          const GT *__restrict__ g, int64_t ldg, float lr,
                                                          const float *__restrict__ center, float w, int64_t P,
@@ -137,16 +103,17 @@ __global__ __launch_bounds__(GRAWA_CELL) __attribute__((amdgpu_waves_per_eu(1, P
                 }
         }
     }
-    if constexpr (SCORE != 0) {
+    if constexpr (SCORE) {
         __shared__ double sm[GRAWA_BLOCK / GRAWA_WAVE];
-        __shared__ unsigned sh_last;
+        double *out = a.partials + (int64_t)k * a.n_tiles;
         if (r1 - r0 == 1) { // the usual case: the whole block lies in one tile
             double acc = 0.0; // squares and sums in fp64: exact squares at any gradient magnitude
 #pragma unroll
             for (int u = 0; u < U; ++u)
 #pragma unroll
                 for (int e = 0; e < V; ++e) acc = sq_add(gf[u][e], acc);
-            row_tile_done<SCORE>(a, k, r0, acc, sm, &sh_last);
+            const double tot = block_sum<GRAWA_BLOCK>(acc, sm);
+            if (threadIdx.x == 0) out[r0] = tot;
         } else {
             for (int t = r0; t < r1; ++t) {
                 const int64_t lo = a.tiles[t].start, hi = lo + a.tiles[t].len;
@@ -158,7 +125,8 @@ __global__ __launch_bounds__(GRAWA_CELL) __attribute__((amdgpu_waves_per_eu(1, P
                         const int64_t c = c0 + (int64_t)u * (GRAWA_CELL * V) + e;
                         acc = (c >= lo && c < hi) ? sq_add(gf[u][e], acc) : acc;
                     }
-                row_tile_done<SCORE>(a, k, t, acc, sm, &sh_last);
+                const double tot = block_sum<GRAWA_BLOCK>(acc, sm);
+                if (threadIdx.x == 0) out[t] = tot;
             }
         }
     }
@@ -261,11 +229,6 @@ __global__ __launch_bounds__(GRAWA_COPY_BLOCK) void k_stream_copy(v4u *__restric
 // launchers
 // ---------------------------------------------------------------------------------
 
-// Up to here the scored step finishes the estimate in its own launch: the launch it saves is worth more than the
-// device-scope traffic of its blocks (us of a round of 4 scored steps and the communication, two launches a step /
-// one: 1056 blocks 67.8 / 59.1, 2112 65.2 / 57.9, 2344 64.9 / 67.6, 4224 66.4 / 78.9, 15 632 189 / 278).
-#define GRAWA_FUSE_MAX_ROW_BLOCKS 2200
-
 // center == nullptr: no proximity step.  p == nullptr: no scores; otherwise the plan's 1024-column tile map and
 // workspace take them.  Vector shapes: fp32 gradients V = 1, U = 4 for the plain step,
 // V = 4, U = 1 with the proximity step or the scores; bf16 V = 2, U = 2 for the plain step, else
@@ -292,13 +255,7 @@ static hipError_t launch_row_step(const grawa_plan *p, float *x, int64_t ldx, co
     const bool plain = !prox && !p;
     const bool nt = aligned && bytes > (plain ? GRAWA_STREAMING_MIN_SGD_BYTES : GRAWA_STREAMING_MIN_ROW_BYTES);
     const bool wide = !aligned && bytes > (plain ? 2 * GRAWA_STREAMING_MIN_SGD_BYTES : GRAWA_STREAMING_MIN_ROW_BYTES);
-    RowScores a = {};
-    int score = 0;
-    if (p) {
-        a = RowScores{p->d_rtiles, p->d_block_rtile0, p->d_layer_rtile0, p->L, p->d_partials, p->n_rtiles, p->d_cnt_kl,
-                      p->d_mvg, gamma, p->d_local_t, p->d_flags};
-        score = nb * K <= GRAWA_FUSE_MAX_ROW_BLOCKS ? 2 : 1;
-    }
+    const RowScores a = p ? RowScores{p->d_rtiles, p->d_block_rtile0, p->d_partials, p->n_rtiles} : RowScores{};
 #define GRAWA_RS_GO(GT, V, U, LNT, SNT, PROX, SCORE)                                                                   \
     k_row_step<GT, V, U, LNT, SNT, PROX, SCORE><<<grid, block, 0, s>>>(x, ldx, (const GT *)g, ldg, lr, center, w, P, \
                                                                        (unsigned)nb, a)
@@ -308,27 +265,21 @@ static hipError_t launch_row_step(const grawa_plan *p, float *x, int64_t ldx, co
         else if (wide) GRAWA_RS_GO(GT, 4, 1, false, true, PROX, SCORE); \
         else GRAWA_RS_GO(GT, V, U, false, false, PROX, SCORE);      \
     } while (0)
-#define GRAWA_RS_SCORE(GT, SCORE)                     \
-    do {                                              \
-        if (prox) GRAWA_RS_NT(GT, 4, 1, true, SCORE); \
-        else GRAWA_RS_NT(GT, 4, 1, false, SCORE);     \
-    } while (0)
     if (dt == GRAWA_BF16) {
-        if (score == 2) GRAWA_RS_SCORE(uint16_t, 2);
-        else if (score == 1) GRAWA_RS_SCORE(uint16_t, 1);
-        else if (prox) GRAWA_RS_NT(uint16_t, 4, 1, true, 0);
-        else GRAWA_RS_NT(uint16_t, 2, 2, false, 0);
+        if (prox && p) GRAWA_RS_NT(uint16_t, 4, 1, true, true);
+        else if (prox) GRAWA_RS_NT(uint16_t, 4, 1, true, false);
+        else if (p) GRAWA_RS_NT(uint16_t, 4, 1, false, true);
+        else GRAWA_RS_NT(uint16_t, 2, 2, false, false);
     } else {
-        if (score == 2) GRAWA_RS_SCORE(float, 2);
-        else if (score == 1) GRAWA_RS_SCORE(float, 1);
-        else if (prox) GRAWA_RS_NT(float, 4, 1, true, 0);
-        else GRAWA_RS_NT(float, 1, 4, false, 0);
+        if (prox && p) GRAWA_RS_NT(float, 4, 1, true, true);
+        else if (prox) GRAWA_RS_NT(float, 4, 1, true, false);
+        else if (p) GRAWA_RS_NT(float, 4, 1, false, true);
+        else GRAWA_RS_NT(float, 1, 4, false, false);
     }
-#undef GRAWA_RS_SCORE
 #undef GRAWA_RS_NT
 #undef GRAWA_RS_GO
     const hipError_t e = hipGetLastError();
-    if (e != hipSuccess || score != 1) return e;
+    if (e != hipSuccess || !p) return e;
     return grawa_launch_estimate(p, gamma, s);
 }
 

@@ -228,7 +228,11 @@ __global__ __launch_bounds__(GRAWA_EST_BLOCK) void k_estimate(const double *__re
             for (int u = 0; u < 8; ++u) s[u] += p[t + u * GRAWA_EST_BLOCK];
         for (; t < t1; t += GRAWA_EST_BLOCK) s[0] += p[t];
         const double tot = block_sum<GRAWA_EST_BLOCK>(((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7])), sm);
-        if (threadIdx.x == 0) estimate_step(mvg + (int64_t)k * L + l, sqrt(tot), gamma, flags);
+        if (threadIdx.x == 0) {
+            const double norm = sqrt(tot);
+            mvg[(int64_t)k * L + l] = gamma * mvg[(int64_t)k * L + l] + (1.0 - gamma) * norm;
+            if (flags && !isfinite(norm)) atomicOr(flags, GRAWA_NONFINITE_LAYER_SCORE);
+        }
     }
     if (l == 0 && blockIdx.y == 0 && threadIdx.x == 0) *local_t += 1;
 }

@@ -108,10 +108,3 @@ __device__ __forceinline__ void wave_layer_weights(const double *__restrict__ pa
         if (owner && flags && !isfinite(a)) atomicOr(flags, GRAWA_NONFINITE_LAYER_SCORE);
     }
 }
-
-// Running estimate of Appendix G for one (worker, layer): g_mvg <- gamma g_mvg + (1 - gamma) g_cur.
-__device__ __forceinline__ void estimate_step(double *mvg, double norm, double gamma, unsigned *flags)
-{
-    *mvg = gamma * *mvg + (1.0 - gamma) * norm;
-    if (flags && !isfinite(norm)) atomicOr(flags, GRAWA_NONFINITE_LAYER_SCORE);
-}

@@ -1,6 +1,6 @@
 """GPU parity where a launch does the work of two: per-layer weights taken straight from the tile sums inside the
-center+pull pass (small problems), the model-level weights inside the finalize launch, and the running estimate
-inside the scored step.  Layouts: one layer, layers of one column, cells with more layers than the per-cell table
+center+pull pass (small problems), the model-level weights inside the finalize launch, and the reset of the running
+estimate inside the weights launch.  Layouts: one layer, layers of one column, cells with more layers than the per-cell table
 holds, layers of many tiles; both sides of each size rule; non-finite scores; the same plan called repeatedly."""
 import numpy as np
 import pytest
@@ -64,15 +64,14 @@ def test_zero_and_non_finite_scores_inside_the_pull():
 
 @pytest.mark.parametrize("K,sizes", [(4, LAYOUTS["mixed"]), (8, [270000]), (8, [280001]), (2, [1] * 700), (15, [2048, 1, 60000])])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-def test_estimate_inside_the_scored_step(K, sizes, dtype):
-    # 8 x 270 000 columns is the last that takes one launch, 8 x 280 001 takes two
+def test_estimate_and_its_reset(K, sizes, dtype):
     w, x, g = W.make_small(2300 + K, K, sizes, grad_dtype=dtype, device=DEV)
     P, lr, lam, gamma = w.P, 0.05, 0.3, 0.9
     xh, gh = W.to_numpy_params(x), W.to_numpy_grads(g)
     est = torch.empty((K, w.L), device=DEV)
     cen = torch.empty(W.round_up(P, 4), device=DEV)
     with grawa.Plan(K, P, w.offsets) as plan:
-        for rep in range(20):                            # the arrival counters are left at zero by every call
+        for rep in range(20):                            # the estimate, t and the arrival counter are left at zero
             xg = x.clone()
             for _ in range(3):
                 plan.local_step_scored(xg[:, :P], g[:, :P], lr, gamma)
