@@ -205,33 +205,50 @@ __global__ __launch_bounds__(GRAWA_FIN_BLOCK) void k_finalize_layers(
 // Appendix G, g_mvg <- gamma g_mvg + (1 - gamma) g_cur, t <- t + 1.  Block (l, y) adds the tiles of layer l for
 // workers y, y + gridDim.y, ....  The tiles of this step are short: with one block per layer the 50 000 tiles
 // of the largest layer of the 350 M transformer for each of 8 workers took 72 us.
+// WAVES (rows to 2^20 columns): grid (L, ceil(K / 8)), every wave takes a worker of its own, since starting L K blocks
+// takes longer than the sums.  Steps and communication, against one block per layer for all workers, 250 layers of
+// 170 k columns and 15 workers: L K blocks 35.1 us for 32.3 (one step), a wave per worker 44.5 us for 46.7 (two
+// steps); from 2^20 columns on the blocks are the shorter chain (8 workers, 1 or 3 layers, 1.1 M columns: 66.4 us for 70.9).
 // The counter lives on the device so that a recorded and replayed call still counts.
 #define GRAWA_EST_BLOCK 512
 #define GRAWA_EST_ROWS 64
+#define GRAWA_EST_WAVES (GRAWA_EST_BLOCK / GRAWA_WAVE)
+#define GRAWA_EST_WAVES_MAX_P ((int64_t)1 << 20)
+template <bool WAVES>
 __global__ __launch_bounds__(GRAWA_EST_BLOCK) void k_estimate(const double *__restrict__ partials, int64_t n_tiles,
                                                               const int32_t *__restrict__ layer_tile0, int K, int L,
                                                               double *__restrict__ mvg, double gamma,
                                                               int64_t *__restrict__ local_t,
                                                               unsigned *__restrict__ flags)
 {
-    __shared__ double sm[GRAWA_EST_BLOCK / GRAWA_WAVE];
     const int l = blockIdx.x;
     const int t0 = layer_tile0[l], t1 = layer_tile0[l + 1];
-    for (int k = blockIdx.y; k < K; k += gridDim.y) {
-        const double *p = partials + (int64_t)k * n_tiles;
-        double s[8];
+    const auto step = [&](int k, double tot) {
+        const double norm = sqrt(tot);
+        mvg[(int64_t)k * L + l] = gamma * mvg[(int64_t)k * L + l] + (1.0 - gamma) * norm;
+        if (flags && !isfinite(norm)) atomicOr(flags, GRAWA_NONFINITE_LAYER_SCORE);
+    };
+    if constexpr (WAVES) {
+        const int lane = threadIdx.x & (GRAWA_WAVE - 1);
+        const int k = (int)blockIdx.y * GRAWA_EST_WAVES + (int)(threadIdx.x / GRAWA_WAVE);
+        if (k < K) {
+            const double tot = wave_strided_sum(partials + (int64_t)k * n_tiles, t0, t1, lane, GRAWA_WAVE);
+            if (lane == 0) step(k, tot);
+        }
+    } else {
+        __shared__ double sm[GRAWA_EST_WAVES];
+        for (int k = blockIdx.y; k < K; k += gridDim.y) {
+            const double *p = partials + (int64_t)k * n_tiles;
+            double s[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) s[u] = 0.0;
-        int t = t0 + (int)threadIdx.x;
-        for (; t + 7 * GRAWA_EST_BLOCK < t1; t += 8 * GRAWA_EST_BLOCK)
+            for (int u = 0; u < 8; ++u) s[u] = 0.0;
+            int t = t0 + (int)threadIdx.x;
+            for (; t + 7 * GRAWA_EST_BLOCK < t1; t += 8 * GRAWA_EST_BLOCK)
 #pragma unroll
-            for (int u = 0; u < 8; ++u) s[u] += p[t + u * GRAWA_EST_BLOCK];
-        for (; t < t1; t += GRAWA_EST_BLOCK) s[0] += p[t];
-        const double tot = block_sum<GRAWA_EST_BLOCK>(((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7])), sm);
-        if (threadIdx.x == 0) {
-            const double norm = sqrt(tot);
-            mvg[(int64_t)k * L + l] = gamma * mvg[(int64_t)k * L + l] + (1.0 - gamma) * norm;
-            if (flags && !isfinite(norm)) atomicOr(flags, GRAWA_NONFINITE_LAYER_SCORE);
+                for (int u = 0; u < 8; ++u) s[u] += p[t + u * GRAWA_EST_BLOCK];
+            for (; t < t1; t += GRAWA_EST_BLOCK) s[0] += p[t];
+            const double tot = block_sum<GRAWA_EST_BLOCK>(((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7])), sm);
+            if (threadIdx.x == 0) step(k, tot);
         }
     }
     if (l == 0 && blockIdx.y == 0 && threadIdx.x == 0) *local_t += 1;
@@ -369,9 +386,15 @@ hipError_t grawa_launch_finalize_layers(const grawa_plan *p, int goal, float *no
 
 hipError_t grawa_launch_estimate(const grawa_plan *p, double gamma, hipStream_t s)
 {
-    const unsigned rows = p->K < GRAWA_EST_ROWS ? (unsigned)p->K : (unsigned)GRAWA_EST_ROWS;
-    k_estimate<<<dim3((unsigned)p->L, rows), dim3(GRAWA_EST_BLOCK), 0, s>>>(
-        p->d_partials, p->n_rtiles, p->d_layer_rtile0, p->K, p->L, p->d_mvg, gamma, p->d_local_t, p->d_flags);
+    const int64_t rows = p->P <= GRAWA_EST_WAVES_MAX_P ? (p->K + GRAWA_EST_WAVES - 1) / GRAWA_EST_WAVES
+                                                       : (p->K < GRAWA_EST_ROWS ? p->K : GRAWA_EST_ROWS);
+    const dim3 grid((unsigned)p->L, (unsigned)rows), block(GRAWA_EST_BLOCK);
+    if (p->P <= GRAWA_EST_WAVES_MAX_P)
+        k_estimate<true><<<grid, block, 0, s>>>(p->d_partials, p->n_rtiles, p->d_layer_rtile0, p->K, p->L, p->d_mvg, gamma,
+                                                p->d_local_t, p->d_flags);
+    else
+        k_estimate<false><<<grid, block, 0, s>>>(p->d_partials, p->n_rtiles, p->d_layer_rtile0, p->K, p->L, p->d_mvg, gamma,
+                                                 p->d_local_t, p->d_flags);
     return hipGetLastError();
 }
 
