@@ -7,6 +7,7 @@
 // 256-byte piece of every row (one 32-bit element per lane per row), blocks are small and many,
 // and accesses are non-temporal -- provided every row starts on a 128-byte boundary, so that no
 // cache line is written in two parts.  There is no dense contraction, hence no matrix-core code.
+#include "grawa_route.h"
 #include "grawa_scores.h"
 
 // ---------------------------------------------------------------------------------
@@ -302,8 +303,8 @@ __global__ __launch_bounds__(GRAWA_BLOCK) __attribute__((amdgpu_waves_per_eu(1, 
     }
 }
 
-// Row-split form: the rows of a 256-column cell are divided over S groups of waves.  grid ceil(P/256),
-// block S * 256 / V.  A lane owns V adjacent columns of its group's rows: Q of them, and one more for the
+// Row-split form: the rows of a 256-column cell are divided over S groups of waves.  grid: one block per cell, in rows
+// of blocks (grawa_split_grid), block S * 256 / V.  A lane owns V adjacent columns of its group's rows: Q of them, and one more for the
 // first K - S Q groups when REM (K is then S Q + 1 .. S Q + S - 1).  Each group forms its part of the
 // center, the parts are added in group order through LDS, every group pulls and stores its own rows.  A
 // wave touches one piece of 256 V bytes per row, the block starts its loads, and after the barrier its
@@ -326,7 +327,10 @@ __global__ __launch_bounds__(S *GRAWA_CELL / V) void k_center_pull_split(
     constexpr int LANES = GRAWA_CELL / V; // lanes of a group
     constexpr int R = REM ? Q + 1 : Q;    // register slots per lane
     static_assert(LANES % GRAWA_WAVE == 0, "a group is made of whole waves");
-    const int64_t cell0 = (int64_t)blockIdx.x * GRAWA_CELL; // wave-uniform
+    static_assert(S * LANES == GRAWA_SPLIT_THREADS, "the grid is chosen for this many threads");
+    const int64_t cell = (int64_t)blockIdx.y * gridDim.x + blockIdx.x; // wave-uniform
+    const int64_t cell0 = cell * GRAWA_CELL;
+    if (cell0 >= P) return; // past the last cell (whole block leaves, before any barrier)
     const int group = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / LANES)); // wave-uniform
     const unsigned lane = threadIdx.x % LANES;
     const int rem = REM ? K - S * Q : 0;
@@ -379,7 +383,7 @@ __global__ __launch_bounds__(S *GRAWA_CELL / V) void k_center_pull_split(
             if (n < V && e < n) vec_set<V>(cprev, e, center_out[col + e]);
     }
 
-    const int info = cell_layer ? cell_layer[blockIdx.x] : 0;
+    const int info = cell_layer ? cell_layer[cell] : 0;
     XV c = XV{};
     if (info >= 0) { // one layer for the whole cell: weights through scalar loads
         const uint64_t bb = uniform_base(beta + info + (int64_t)k0 * beta_stride);
@@ -526,8 +530,10 @@ template <int K, bool SGD, typename GT, bool LNT> static void launch_wide(GRAWA_
 
 template <int Q, bool REM, int S, int V, bool SGD, typename GT, bool NT> static void launch_split(GRAWA_CP_ARGS)
 {
-    hipExtLaunchKernelGGL((k_center_pull_split<Q, REM, S, V, SGD, GT, NT>), dim3((unsigned)p->n_cells),
-                          dim3(S * GRAWA_CELL / V), 0, s, e0, e1, 0, x, ldx, (const GT *)g, ldg, lr, beta,
+    unsigned gx, gy;
+    grawa_split_grid(p->n_cells, &gx, &gy);
+    hipExtLaunchKernelGGL((k_center_pull_split<Q, REM, S, V, SGD, GT, NT>), dim3(gx, gy),
+                          dim3(GRAWA_SPLIT_THREADS), 0, s, e0, e1, 0, x, ldx, (const GT *)g, ldg, lr, beta,
                           GRAWA_CP_STRIDE, GRAWA_CP_CELLS, (const int64_t *)p->d_off, p->L, p->K, p->P, lambda,
                           center_out, rho, moving);
 }

@@ -4,7 +4,7 @@ layer boundaries inside cells, cached and streaming accesses."""
 import pytest
 import torch
 
-from paper_2403_04206_amd import workloads as W
+from paper_2403_04206_amd import grawa, workloads as W
 from test_gpu_full_configs import run_workload
 from test_gpu_parity import run_variant
 
@@ -32,3 +32,31 @@ def test_row_split_streaming(K, dtype, fused):
                    variants=("lgrawa",), seed=(4, K))
     run_workload(w, "lgrawa", "chunks", 40 + K)
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("K", [16, 24])
+def test_row_split_second_row_of_blocks(K):
+    # 2^18 cells are one row of blocks; one column more starts a second row, whose last block holds no cell when their
+    # number is odd.  The caller's weights, so that x is the only large array.
+    for P in ((1 << 26) + 1, (1 << 26) + 256 + 1):
+        x = torch.empty((K, W.round_up(P, 256)), device=DEV).normal_(0.0, 0.05, generator=torch.Generator(device=DEV).manual_seed(K))
+        x0 = x.clone()
+        off = [0, P // 2 + 3, P]
+        beta = torch.rand((K, 2), device=DEV, generator=torch.Generator(device=DEV).manual_seed(P))
+        cen = torch.empty(W.round_up(P, 4), device=DEV)
+        with grawa.Plan(K, P, off) as plan:
+            plan.center_pull(x[:, :P], beta, 0.25, center_out=cen)
+            torch.cuda.synchronize()
+        step = 1 << 22
+        for a in range(0, P, step):
+            b = min(P, a + step)
+            xd = x0[:, a:b].double()
+            cut = min(max(off[1], a), b)
+            c = torch.cat([(beta[:, :1].double() * xd[:, :cut - a]).sum(0), (beta[:, 1:].double() * xd[:, cut - a:]).sum(0)])
+            # K products and sums of at most 0.5 in all, each rounded to 24 bits, and the pull
+            bound = (K + 3) * 2.0 ** -24 * (xd.abs().max() * (1.0 + beta.double().sum(0).max()))
+            assert float((cen[a:b].double() - c).abs().max()) <= float(bound)
+            assert float((x[:, a:b].double() - (xd + 0.25 * (c - xd))).abs().max()) <= float(bound)
+        assert torch.equal(x[:, P:], x0[:, P:])
+        del x, x0, cen
+        torch.cuda.empty_cache()
