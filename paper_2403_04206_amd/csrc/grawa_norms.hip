@@ -184,12 +184,11 @@ __global__ __launch_bounds__(GRAWA_FIN_BLOCK) void k_finalize_layers(
         if (wave == 0) group_weights(sA, K, beta + l, L, beta_user ? beta_user + l : nullptr, flags, GRAWA_NONFINITE_LAYER_SCORE);
         return;
     }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // every thread's hand-over is acknowledged
     if (!last_to_arrive(cnt_all, (unsigned)L, &sh_last)) return;
     for (int k = wave; k < K; k += GRAWA_FIN_WAVES) {
         double *p = S + (int64_t)k * L;
         double s = 0.0;
-        for (int j = lane; j < L; j += GRAWA_WAVE) {
+        for (int j = lane; j < L; j += GRAWA_WAVE) { // the block's own values too
             const double v = take_over(p + j);
             s += goal == GRAWA_GOAL_MODEL_SUM ? sqrt(v) : v;
         }

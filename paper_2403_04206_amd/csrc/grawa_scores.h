@@ -2,8 +2,8 @@
 // let one launch do what needs a second one otherwise.
 //
 // Values pass between blocks of one launch (which may run on different XCDs, each with an L2 of its own) only
-// through device-scope atomic read-modify-writes, which always act on the latest value.  The thread that hands
-// a value over waits for its acknowledgement before it counts its block in, and the block that arrives last
+// through device-scope atomic read-modify-writes, which always act on the latest value.  A thread that hands
+// a value over waits for the exchange to return before its block counts itself in, and the block that arrives last
 // reads after its count has returned.  No block ever waits for another: one that is not last leaves, so nothing
 // depends on which blocks are resident and nothing can hang.  Which block comes last varies from run to run;
 // what it adds and in which order does not, so results are bit-reproducible.  Release and acquire fences at
@@ -12,25 +12,30 @@
 #pragma once
 #include "grawa_device.h"
 
+// The values below pass through registers that the compiler cannot see through: an exchange whose result is unused
+// may be lowered to a plain store, and the addition of a known zero is lowered to a plain load.
 __device__ __forceinline__ void hand_over(double *p, double v)
 {
-    (void)__hip_atomic_exchange(reinterpret_cast<unsigned long long *>(p), (unsigned long long)__double_as_longlong(v),
-                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned long long before =
+        __hip_atomic_exchange(reinterpret_cast<unsigned long long *>(p), (unsigned long long)__double_as_longlong(v),
+                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("" ::"v"(before) : "memory"); // also: the exchange has been performed from here on
 }
 __device__ __forceinline__ double take_over(double *p)
 {
-    return __longlong_as_double((long long)__hip_atomic_fetch_add(reinterpret_cast<unsigned long long *>(p), 0ull,
+    unsigned long long zero = 0ull;
+    asm volatile("" : "+v"(zero)::"memory");
+    return __longlong_as_double((long long)__hip_atomic_fetch_add(reinterpret_cast<unsigned long long *>(p), zero,
                                                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 }
 
 // Counts the block in; true in every thread of the block that is the n-th.  What the block publishes was
-// handed over by thread 0 before the call.  The last arriver leaves the counter at zero for the next call.
+// handed over, by any of its threads, before the call.  The last arriver leaves the counter at zero for the next call.
 // `sh` is one word of LDS.
 __device__ __forceinline__ bool last_to_arrive(unsigned *counter, unsigned n, unsigned *sh)
 {
     __syncthreads();
     if (threadIdx.x == 0) {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         const unsigned before = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const bool last = before == n - 1;
         if (last) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
