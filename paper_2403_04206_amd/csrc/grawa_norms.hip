@@ -2,6 +2,7 @@
 //
 //   k_sumsq            per (tile, worker) sum of squares of the gradient   [eq. (3), (5)]
 //   k_finalize_layers  tile sums -> ||G||_F, per-layer or model-level weights [eq. (2)-(7)]
+//   k_finalize_model   ||G||_F -> model-level weights, many layers         [eq. (2)-(4)]
 //   k_estimate         tile sums of a scored step -> running norm estimate [App. G]
 //   k_local_weights    weights from the running norm estimate              [App. G]
 //   k_leader_weights   LSGD (leader) weights                               [App. F]
@@ -9,6 +10,7 @@
 // The norm pass is a read-only stream: it runs fastest with several non-temporal loads per
 // lane in flight and a capped occupancy.  Squares and sums are fp64 throughout, added in a
 // fixed order (no atomics), so results are bit-reproducible.
+#include "grawa_route.h"
 #include "grawa_scores.h"
 
 // ---------------------------------------------------------------------------------
@@ -126,13 +128,35 @@ __device__ __forceinline__ double wave_strided_sum(const double *__restrict__ p,
     return wave_sum((s0 + s1) + (s2 + s3));
 }
 
+// Score of every worker (the sum of its layer norms, or the norm of the flattened gradient) from S[k][l], then the K
+// weights, by one block of 1024.
+template <typename Read>
+__device__ __forceinline__ void model_weights(double *S, int K, int L, int goal, Read read, double *sA, float *beta,
+                                              float *beta_user, unsigned *flags)
+{
+    const int lane = threadIdx.x & (GRAWA_WAVE - 1);
+    const int wave = threadIdx.x / GRAWA_WAVE;
+    for (int k = wave; k < K; k += GRAWA_FIN_WAVES) {
+        double *p = S + (int64_t)k * L;
+        double s = 0.0;
+        for (int l = lane; l < L; l += GRAWA_WAVE) {
+            const double v = read(p + l);
+            s += goal == GRAWA_GOAL_MODEL_SUM ? sqrt(v) : v;
+        }
+        s = wave_sum(s);
+        if (goal == GRAWA_GOAL_MODEL_FLAT) s = sqrt(s);
+        if (lane == 0) sA[k] = s;
+    }
+    __syncthreads();
+    if (wave == 0) group_weights(sA, K, beta, 1, beta_user, flags, GRAWA_NONFINITE_MODEL_SCORE);
+}
+
 // grid L, block 1024 (16 waves).  Block l adds the tile partials of layer l for every worker
 // and turns the K layer norms into the K per-layer weights.  With K >= 16 every wave takes
 // workers w, w+16, ...; with fewer workers 16/K waves share one worker's tiles and their
 // results are added in wave order.  All sums are fp64 in a fixed order.
-// Model level (goal): the blocks hand their squared norms S[k][l] over, and the last one forms every worker's
-// score (the sum of its layer norms, or the norm of the flattened gradient) and the K weights; as a kernel of its
-// own that last step took 4.7 us and a launch.
+// Model level (goal): the blocks hand their squared norms S[k][l] over, and the last one forms the model-level weights;
+// cnt_all null: S is only stored, for k_finalize_model (grawa_model_weights_by_last_block).
 __global__ __launch_bounds__(GRAWA_FIN_BLOCK) void k_finalize_layers(
     const double *__restrict__ partials, int64_t n_tiles, const int32_t *__restrict__ tile_begin,
     const int32_t *__restrict__ tile_end, int K, int L, int goal, double *__restrict__ S, float *__restrict__ A_user,
@@ -173,7 +197,8 @@ __global__ __launch_bounds__(GRAWA_FIN_BLOCK) void k_finalize_layers(
     for (int k = threadIdx.x; k < K; k += GRAWA_FIN_BLOCK) {
         const double s = sA[k];
         const double a = sqrt(s);
-        if (model) hand_over(S + (int64_t)k * L + l, s);
+        if (model && cnt_all) hand_over(S + (int64_t)k * L + l, s);
+        else if (model) S[(int64_t)k * L + l] = s;
         if (A_user) A_user[(int64_t)k * L + l] = (float)a;
         if (goal != GRAWA_GOAL_LAYER_WEIGHTS && flags && !isfinite(a)) atomicOr(flags, GRAWA_NONFINITE_LAYER_SCORE);
         sA[k] = a;
@@ -184,20 +209,18 @@ __global__ __launch_bounds__(GRAWA_FIN_BLOCK) void k_finalize_layers(
         if (wave == 0) group_weights(sA, K, beta + l, L, beta_user ? beta_user + l : nullptr, flags, GRAWA_NONFINITE_LAYER_SCORE);
         return;
     }
-    if (!last_to_arrive(cnt_all, (unsigned)L, &sh_last)) return;
-    for (int k = wave; k < K; k += GRAWA_FIN_WAVES) {
-        double *p = S + (int64_t)k * L;
-        double s = 0.0;
-        for (int j = lane; j < L; j += GRAWA_WAVE) { // the block's own values too
-            const double v = take_over(p + j);
-            s += goal == GRAWA_GOAL_MODEL_SUM ? sqrt(v) : v;
-        }
-        s = wave_sum(s);
-        if (goal == GRAWA_GOAL_MODEL_FLAT) s = sqrt(s);
-        if (lane == 0) sA[k] = s;
-    }
-    __syncthreads();
-    if (wave == 0) group_weights(sA, K, beta, 1, beta_user, flags, GRAWA_NONFINITE_MODEL_SCORE);
+    if (!cnt_all || !last_to_arrive(cnt_all, (unsigned)L, &sh_last)) return;
+    model_weights(S, K, L, goal, [](double *p) { return take_over(p); }, sA, beta, beta_user, flags);
+}
+
+// grid 1, block 1024: the model-level weights from the squared layer norms.
+__global__ __launch_bounds__(GRAWA_FIN_BLOCK) void k_finalize_model(double *__restrict__ S, int K, int L, int goal,
+                                                                    float *__restrict__ beta,
+                                                                    float *__restrict__ beta_user,
+                                                                    unsigned *__restrict__ flags)
+{
+    __shared__ double sA[GRAWA_MAX_WORKERS];
+    model_weights(S, K, L, goal, [](double *p) { return *p; }, sA, beta, beta_user, flags);
 }
 
 // grid (L, min(K, GRAWA_EST_ROWS)), block 512: the tile sums of a scored local step -> running estimate of
@@ -377,9 +400,15 @@ hipError_t grawa_launch_sumsq(const grawa_plan *p, const void *g, int64_t ldg, g
 hipError_t grawa_launch_finalize_layers(const grawa_plan *p, int goal, float *norms_user, float *beta_user,
                                         hipStream_t s)
 {
+    const bool model = goal >= GRAWA_GOAL_MODEL_SUM;
+    const bool apart = model && !grawa_model_weights_by_last_block(p->L);
+    float *beta = model ? p->d_beta_model : p->d_beta_layer;
     k_finalize_layers<<<dim3((unsigned)p->L), dim3(GRAWA_FIN_BLOCK), 0, s>>>(
-        p->d_partials, p->n_tiles, p->d_layer_tile0, p->d_layer_tile1, p->K, p->L, goal, p->d_S, norms_user,
-        goal == GRAWA_GOAL_LAYER_WEIGHTS ? p->d_beta_layer : p->d_beta_model, beta_user, p->d_cnt_all, p->d_flags);
+        p->d_partials, p->n_tiles, p->d_layer_tile0, p->d_layer_tile1, p->K, p->L, goal, p->d_S, norms_user, beta,
+        beta_user, apart ? nullptr : p->d_cnt_all, p->d_flags);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !apart) return e;
+    k_finalize_model<<<dim3(1), dim3(GRAWA_FIN_BLOCK), 0, s>>>(p->d_S, p->K, p->L, goal, beta, beta_user, p->d_flags);
     return hipGetLastError();
 }
 

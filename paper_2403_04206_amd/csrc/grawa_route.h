@@ -19,4 +19,14 @@ static inline void grawa_split_grid(int64_t n_cells, unsigned *gx, unsigned *gy)
     *gx = (unsigned)((n_cells + rows - 1) / rows);
 }
 
+// Model-level weights: by the last block of the launch that forms the layer norms, or by a launch of its own.  The last
+// block saves the host a launch (a call of 4 workers that is host-bound: 17 us for 21) and the device nothing; every
+// layer's arrival and every norm handed over cost, so that from about 100 layers on the device loses.  Whole update
+// on the device, us, own launch / last block:
+//   4 workers, 262 k columns:  20 layers 11.5 / 11.5, 60 11.6 / 11.8, 100 12.2 / 12.5, 160 12.2 / 13.8, 1000 22.4 / 32.5
+//   16 workers, 200 k:         20 16.5 / 16.2, 60 17.1 / 17.1, 100 18.2 / 19.0, 160 20.4 / 21.5, 1000 41.5 / 52.1
+//   64 workers, 200 k:         20 40.1 / 39.8, 60 44.3 / 44.3, 100 48.9 / 49.8, 160 57.2 / 58.4, 1000 152 / 164
+#define GRAWA_LAST_BLOCK_MAX_LAYERS 100
+static inline bool grawa_model_weights_by_last_block(int L) { return L <= GRAWA_LAST_BLOCK_MAX_LAYERS; }
+
 #endif

@@ -1,5 +1,6 @@
 // Prints the launch shapes that the host-side rules of paper_2403_04206_amd/csrc/grawa_route.h give (no GPU toolchain).
 //   split <n_cells>...   -> per line: n_cells grid_x grid_y threads
+//   model <L>...         -> per line: L, 1 if the last block of the norms' launch forms the model-level weights
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -16,6 +17,10 @@ int main(int argc, char **argv)
             grawa_split_grid(n, &gx, &gy);
             std::printf("%lld %u %u %d\n", n, gx, gy, GRAWA_SPLIT_THREADS);
         }
+        return 0;
+    }
+    if (!std::strcmp(argv[1], "model")) {
+        for (int i = 2; i < argc; ++i) std::printf("%s %d\n", argv[i], grawa_model_weights_by_last_block(std::atoi(argv[i])));
         return 0;
     }
     return 2;

@@ -100,6 +100,21 @@ def test_model_weights_repeatedly():
             torch.testing.assert_close(wts, first.roll(k, 0), rtol=1e-6, atol=0)
 
 
+@pytest.mark.parametrize("L", [1, 99, 100, 101, 700, 5000])
+@pytest.mark.parametrize("K", [3, 16, 33])
+def test_model_weights_by_layer_count(K, L):
+    # either side of the layer count from which the model-level weights are a launch of their own
+    w, x, g = W.make_small(2450 + L, K, [1 + (i * 37) % 23 for i in range(L)], device=DEV)
+    run_variant(w, x, g, "mgrawa", 0.3)
+    run_variant(w, x, g, "flat", 0.3)
+    g[0, w.offsets[L // 2]] = float("inf")
+    wts = torch.empty(K, device=DEV)
+    with grawa.Plan(K, w.P, w.offsets) as plan:
+        plan.mgrawa_update(x.clone()[:, :w.P], g[:, :w.P], 0.3, weights_out=wts)
+        assert plan.nonfinite() == grawa.NONFINITE_LAYER_SCORE | grawa.NONFINITE_MODEL_SCORE
+    assert float(wts[0]) == 0.0 and abs(float(wts.double().sum()) - 1.0) < K * 2.0 ** -24
+
+
 @pytest.mark.parametrize("losses,leader", [([3.0, 1.0, 1.0, 2.0], 1), ([float("nan"), 1.0, 0.5], 0), ([2.0, float("nan"), 1.0], 2),
                                           ([float("inf")] * 3, 0), ([float("inf"), float("nan"), float("inf")], 0),
                                           ([float("nan")] * 3, 0), ([float("inf"), 5.0, float("-inf")], 2), ([0.0, -0.0], 0)])

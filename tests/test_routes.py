@@ -29,3 +29,8 @@ def test_row_split_grid_within_the_launch_limit(driver):
         assert gx * threads < 1 << 32 and gy < 1 << 16
         assert n <= gx * gy < n + gy                     # every cell, and less than one block per row for nothing
         assert gy == 1 or n > 1 << 18
+
+
+def test_no_arrivals_with_many_layers(driver):
+    # one arrival per layer on one address: bounded by a rule on the layer count, whatever else the problem is
+    assert driver("model", 1, 62, 100, 101, 161, 291, 100000) == [[1, 1], [62, 1], [100, 1], [101, 0], [161, 0], [291, 0], [100000, 0]]
