@@ -156,8 +156,9 @@ static grawa_status_t plan_create_impl(grawa_plan_t **out, int K, int64_t P, int
     const size_t b_bl = round256(sizeof(float) * (size_t)K * (size_t)L);
     const size_t b_bm = round256(sizeof(float) * (size_t)K);
     const size_t b_mvg = b_S;
-    const size_t b_t = 256;
-    const size_t b_zeroed = b_part + b_S + b_bl + b_bm + b_mvg + b_t;
+    const size_t b_t = round256(sizeof(int64_t) * (size_t)L);
+    const size_t b_words = 256; // flag word, arrival counter
+    const size_t b_zeroed = b_part + b_S + b_bl + b_bm + b_mvg + b_t + b_words;
     const size_t b_host = b_off + b_cells + b_tiles + b_lt0 + b_rtiles + b_lt0 + b_brt0 + b_bm;
     // These may throw: before anything that would have to be freed.
     const std::vector<float> uniform((size_t)K, 1.f / (float)K);
@@ -198,8 +199,8 @@ static grawa_status_t plan_create_impl(grawa_plan_t **out, int K, int64_t P, int
     p->d_beta_layer = reinterpret_cast<float *>(w); w += b_bl;
     p->d_beta_model = reinterpret_cast<float *>(w); w += b_bm;
     p->d_mvg = reinterpret_cast<double *>(w); w += b_mvg;
-    p->d_local_t = reinterpret_cast<int64_t *>(w);
-    p->d_flags = reinterpret_cast<unsigned *>(w + 64);
+    p->d_local_t = reinterpret_cast<int64_t *>(w); w += b_t;
+    p->d_flags = reinterpret_cast<unsigned *>(w);
     p->d_cnt_all = reinterpret_cast<unsigned *>(w + 128);
 
     // Everything before the partials comes from the host: small maps in one copy, large ones from where they are.

@@ -40,7 +40,7 @@ struct grawa_plan {
     float *d_beta_uniform;  // [K] 1/K each (EASGD), written once
     unsigned *d_cnt_all;    // [1] arrivals of the layers; 0 between calls
     double *d_mvg;          // [K][L] moving average of the layer norms (running estimate, Appendix G)
-    int64_t *d_local_t;     // device: local steps since the last communication (what the kernels use)
+    int64_t *d_local_t;     // [L], all equal: local steps since the last communication (what the kernels use)
     unsigned *d_flags;      // device: GRAWA_NONFINITE_* bits, sticky until read-and-cleared (may be null)
     int64_t local_t;        // host mirror of the counter as of the last enqueued call (argument checks only)
     double local_gamma;     // momentum of the running estimate used so far (0 = none yet)

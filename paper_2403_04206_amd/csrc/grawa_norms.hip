@@ -231,7 +231,7 @@ __global__ __launch_bounds__(GRAWA_FIN_BLOCK) void k_finalize_model(double *__re
 // takes longer than the sums.  Steps and communication, against one block per layer for all workers, 250 layers of
 // 170 k columns and 15 workers: L K blocks 35.1 us for 32.3 (one step), a wave per worker 44.5 us for 46.7 (two
 // steps); from 2^20 columns on the blocks are the shorter chain (8 workers, 1 or 3 layers, 1.1 M columns: 66.4 us for 70.9).
-// The counter lives on the device so that a recorded and replayed call still counts.
+// The counts t (one per layer, see k_local_weights) live on the device so that a recorded and replayed call still counts.
 #define GRAWA_EST_BLOCK 512
 #define GRAWA_EST_ROWS 64
 #define GRAWA_EST_WAVES (GRAWA_EST_BLOCK / GRAWA_WAVE)
@@ -273,7 +273,7 @@ __global__ __launch_bounds__(GRAWA_EST_BLOCK) void k_estimate(const double *__re
             if (threadIdx.x == 0) step(k, tot);
         }
     }
-    if (l == 0 && blockIdx.y == 0 && threadIdx.x == 0) *local_t += 1;
+    if (blockIdx.y == 0 && threadIdx.x == 0) local_t[l] += 1;
 }
 
 // Weights from the running norm estimate g_est = gamma g_mvg / (1 - gamma^t) (Appendix G), t =
@@ -282,35 +282,35 @@ __global__ __launch_bounds__(GRAWA_EST_BLOCK) void k_estimate(const double *__re
 // is the sum of its layer estimates (eq. (3) applied to the estimates), then eq. (4).  est_user (float
 // [K][L], may be null) receives g_est.  With t = 0 (no step was counted) the estimates are taken
 // as zero, which the zero-norm rule turns into the plain average.
+// Every layer has a count t of its own (all equal), so that the block that reads one also resets it and no block
+// needs to know of the others: one count for all needs the blocks to arrive at a counter, which from some thousand layers
+// on takes longer than the reset as a launch of its own.
 #define GRAWA_LW_BLOCK 256
 __global__ __launch_bounds__(GRAWA_LW_BLOCK) void k_local_weights(double *__restrict__ mvg, double gamma,
                                                                   int64_t *__restrict__ local_t, int K, int L,
                                                                   int per_layer, float *__restrict__ beta,
                                                                   float *__restrict__ beta_user,
                                                                   float *__restrict__ est_user,
-                                                                  unsigned *__restrict__ flags,
-                                                                  unsigned *__restrict__ cnt_all)
+                                                                  unsigned *__restrict__ flags)
 {
     __shared__ double sA[GRAWA_MAX_WORKERS];
-    __shared__ unsigned sh_last;
     const int lane = threadIdx.x & (GRAWA_WAVE - 1);
     const int wave = threadIdx.x / GRAWA_WAVE;
-    const int64_t t = *local_t;
+    const int l0 = per_layer ? (int)blockIdx.x : 0;
+    const int64_t t = local_t[l0];
     const double scale = t > 0 ? gamma / (1.0 - pow(gamma, (double)t)) : 0.0;
     if (per_layer) {
-        const int l = blockIdx.x;
         for (int k = threadIdx.x; k < K; k += GRAWA_LW_BLOCK) {
-            const int64_t at = (int64_t)k * L + l;
+            const int64_t at = (int64_t)k * L + l0;
             const double e = scale * mvg[at];
             sA[k] = e;
             if (est_user) est_user[at] = (float)e;
             mvg[at] = 0.0;
         }
-        __syncthreads();
+        __syncthreads(); // also: every thread has read t
+        if (threadIdx.x == 0) local_t[l0] = 0;
         if (wave == 0)
-            group_weights(sA, K, beta + l, L, beta_user ? beta_user + l : nullptr, flags, GRAWA_NONFINITE_LAYER_SCORE);
-        // every block has read t (its value is in the weights above) before it counts itself in
-        if (last_to_arrive(cnt_all, (unsigned)L, &sh_last) && threadIdx.x == 0) *local_t = 0;
+            group_weights(sA, K, beta + l0, L, beta_user ? beta_user + l0 : nullptr, flags, GRAWA_NONFINITE_LAYER_SCORE);
     } else {
         for (int k = wave; k < K; k += GRAWA_LW_BLOCK / GRAWA_WAVE) {
             double s = 0.0;
@@ -325,18 +325,18 @@ __global__ __launch_bounds__(GRAWA_LW_BLOCK) void k_local_weights(double *__rest
             if (lane == 0) sA[k] = s;
         }
         __syncthreads(); // also: every thread has read t
-        if (threadIdx.x == 0) *local_t = 0;
+        for (int l = threadIdx.x; l < L; l += GRAWA_LW_BLOCK) local_t[l] = 0;
         if (wave == 0) group_weights(sA, K, beta, 1, beta_user, flags, GRAWA_NONFINITE_MODEL_SCORE);
     }
 }
 
 // g_mvg <- 0 and t <- 0 (an explicit reset).
 __global__ __launch_bounds__(GRAWA_BLOCK) void k_zero_estimate(double *__restrict__ p, int64_t n,
-                                                               int64_t *__restrict__ local_t)
+                                                               int64_t *__restrict__ local_t, int L)
 {
     const int64_t i = (int64_t)blockIdx.x * GRAWA_BLOCK + threadIdx.x;
     if (i < n) p[i] = 0.0;
-    if (i == 0) *local_t = 0;
+    if (i < L) local_t[i] = 0;
 }
 
 // flag word <- 0
@@ -431,7 +431,7 @@ hipError_t grawa_launch_local_weights(const grawa_plan *p, double gamma, int per
 {
     k_local_weights<<<dim3(per_layer ? (unsigned)p->L : 1u), dim3(GRAWA_LW_BLOCK), 0, s>>>(
         p->d_mvg, gamma, p->d_local_t, p->K, p->L, per_layer, per_layer ? p->d_beta_layer : p->d_beta_model,
-        beta_user, est_user, p->d_flags, p->d_cnt_all);
+        beta_user, est_user, p->d_flags);
     return hipGetLastError();
 }
 
@@ -439,7 +439,7 @@ hipError_t grawa_launch_zero_estimate(const grawa_plan *p, hipStream_t s)
 {
     const int64_t n = (int64_t)p->K * p->L;
     k_zero_estimate<<<dim3((unsigned)((n + GRAWA_BLOCK - 1) / GRAWA_BLOCK)), dim3(GRAWA_BLOCK), 0, s>>>(p->d_mvg, n,
-                                                                                                    p->d_local_t);
+                                                                                                    p->d_local_t, p->L);
     return hipGetLastError();
 }
 

@@ -100,6 +100,26 @@ def test_model_weights_repeatedly():
             torch.testing.assert_close(wts, first.roll(k, 0), rtol=1e-6, atol=0)
 
 
+@pytest.mark.parametrize("K,L", [(3, 1), (5, 40), (2, 3000), (17, 300)])
+def test_step_count_of_every_layer(K, L):
+    # gamma^t enters g_est: rounds of different lengths, ended by either communication or a reset, on one plan
+    w, x, g = W.make_small(2350 + L, K, [1 + (i * 29) % 17 for i in range(L)], device=DEV)
+    P, gamma = w.P, 0.7
+    gh = W.to_numpy_grads(g)
+    est = torch.empty((K, L), device=DEV)
+    with grawa.Plan(K, P, w.offsets) as plan:
+        for t, end in ((2, "l"), (1, "m"), (3, "reset"), (4, "l"), (1, "l"), (3, "m"), (2, "m")):
+            scores = orc.LocalScores(K, L, gamma)
+            for _ in range(t):
+                plan.local_step_scored(x[:, :P], g[:, :P], 0.0, gamma)
+                scores.step(gh, w.offsets)
+            if end == "reset":
+                plan.local_scores_reset()
+                continue
+            (plan.local_lgrawa_update if end == "l" else plan.local_mgrawa_update)(x[:, :P], 0.1, est_out=est)
+            assert_table_close(est.cpu().numpy(), scores.g_est, TIGHT, "g_est after %d steps" % t)
+
+
 @pytest.mark.parametrize("L", [1, 99, 100, 101, 700, 5000])
 @pytest.mark.parametrize("K", [3, 16, 33])
 def test_model_weights_by_layer_count(K, L):
