@@ -285,8 +285,12 @@ __global__ __launch_bounds__(GRAWA_EST_BLOCK) void k_estimate(const double *__re
 // Every layer has a count t of its own (all equal), so that the block that reads one also resets it and no block
 // needs to know of the others: one count for all needs the blocks to arrive at a counter, which from some thousand layers
 // on takes longer than the reset as a launch of its own.
-#define GRAWA_LW_BLOCK 256
-__global__ __launch_bounds__(GRAWA_LW_BLOCK) void k_local_weights(double *__restrict__ mvg, double gamma,
+// Block: 256 per layer (starting the blocks is what takes the time), 1024 for the one of the model level, where a wave
+// takes a worker at a time (256 threads there: 4 waves, 16 workers and 3000 layers of 300 k columns 108 us the step and
+// the communication, with 1024 threads 64; the launch apart that reset the estimate before: 75).
+#define GRAWA_LW_BLOCK_LAYER 256
+#define GRAWA_LW_BLOCK_MODEL 1024
+__global__ __launch_bounds__(GRAWA_LW_BLOCK_MODEL) void k_local_weights(double *__restrict__ mvg, double gamma,
                                                                   int64_t *__restrict__ local_t, int K, int L,
                                                                   int per_layer, float *__restrict__ beta,
                                                                   float *__restrict__ beta_user,
@@ -295,12 +299,12 @@ __global__ __launch_bounds__(GRAWA_LW_BLOCK) void k_local_weights(double *__rest
 {
     __shared__ double sA[GRAWA_MAX_WORKERS];
     const int lane = threadIdx.x & (GRAWA_WAVE - 1);
-    const int wave = threadIdx.x / GRAWA_WAVE;
+    const int wave = threadIdx.x / GRAWA_WAVE, waves = (int)blockDim.x / GRAWA_WAVE;
     const int l0 = per_layer ? (int)blockIdx.x : 0;
     const int64_t t = local_t[l0];
     const double scale = t > 0 ? gamma / (1.0 - pow(gamma, (double)t)) : 0.0;
     if (per_layer) {
-        for (int k = threadIdx.x; k < K; k += GRAWA_LW_BLOCK) {
+        for (int k = threadIdx.x; k < K; k += blockDim.x) {
             const int64_t at = (int64_t)k * L + l0;
             const double e = scale * mvg[at];
             sA[k] = e;
@@ -312,20 +316,30 @@ __global__ __launch_bounds__(GRAWA_LW_BLOCK) void k_local_weights(double *__rest
         if (wave == 0)
             group_weights(sA, K, beta + l0, L, beta_user ? beta_user + l0 : nullptr, flags, GRAWA_NONFINITE_LAYER_SCORE);
     } else {
-        for (int k = wave; k < K; k += GRAWA_LW_BLOCK / GRAWA_WAVE) {
+        for (int k = wave; k < K; k += waves) {
+            double *row = mvg + (int64_t)k * L;
+            float *est = est_user ? est_user + (int64_t)k * L : nullptr;
             double s = 0.0;
-            for (int l = lane; l < L; l += GRAWA_WAVE) {
-                const int64_t at = (int64_t)k * L + l;
-                const double e = scale * mvg[at];
+            const auto take = [&](int l, double v) {
+                const double e = scale * v;
                 s += e;
-                if (est_user) est_user[at] = (float)e;
-                mvg[at] = 0.0;
+                if (est) est[l] = (float)e;
+                row[l] = 0.0;
+            };
+            int l = lane;
+            for (; l + 3 * GRAWA_WAVE < L; l += 4 * GRAWA_WAVE) { // four loads in flight: none may pass the stores
+                const double v0 = row[l], v1 = row[l + GRAWA_WAVE], v2 = row[l + 2 * GRAWA_WAVE], v3 = row[l + 3 * GRAWA_WAVE];
+                take(l, v0);
+                take(l + GRAWA_WAVE, v1);
+                take(l + 2 * GRAWA_WAVE, v2);
+                take(l + 3 * GRAWA_WAVE, v3);
             }
+            for (; l < L; l += GRAWA_WAVE) take(l, row[l]);
             s = wave_sum(s);
             if (lane == 0) sA[k] = s;
         }
         __syncthreads(); // also: every thread has read t
-        for (int l = threadIdx.x; l < L; l += GRAWA_LW_BLOCK) local_t[l] = 0;
+        for (int l = threadIdx.x; l < L; l += blockDim.x) local_t[l] = 0;
         if (wave == 0) group_weights(sA, K, beta, 1, beta_user, flags, GRAWA_NONFINITE_MODEL_SCORE);
     }
 }
@@ -429,7 +443,7 @@ hipError_t grawa_launch_estimate(const grawa_plan *p, double gamma, hipStream_t 
 hipError_t grawa_launch_local_weights(const grawa_plan *p, double gamma, int per_layer, float *beta_user,
                                       float *est_user, hipStream_t s)
 {
-    k_local_weights<<<dim3(per_layer ? (unsigned)p->L : 1u), dim3(GRAWA_LW_BLOCK), 0, s>>>(
+    k_local_weights<<<dim3(per_layer ? (unsigned)p->L : 1u), dim3(per_layer ? GRAWA_LW_BLOCK_LAYER : GRAWA_LW_BLOCK_MODEL), 0, s>>>(
         p->d_mvg, gamma, p->d_local_t, p->K, p->L, per_layer, per_layer ? p->d_beta_layer : p->d_beta_model,
         beta_user, est_user, p->d_flags);
     return hipGetLastError();
