@@ -16,16 +16,6 @@
 #define GRAWA_ROW_BLOCK 1024 // columns per block
 #define GRAWA_ROW_GROUP 4096 // column blocks of one row launched back to back (4 Mi columns)
 
-// Where the tile sums of a scored step go: to k_estimate.  (Updating the estimate inside this launch, by the block
-// that brings the last tile of a (worker, layer), was tried: its device-scope traffic costs more than the launch from
-// about 1000 blocks or 30 tiles per layer on, 4 steps and the communication on 8 workers 117 us instead of 45.)
-struct RowScores {
-    const GrawaTile *tiles;      // 1024-column tiles, and the first one of every aligned block of 1024 columns
-    const int32_t *block_tile0;
-    double *partials;            // [K][n_tiles]
-    int64_t n_tiles;
-};
-
 // One block = one aligned block of 1024 columns of one worker; V * U * 256 = 1024, a lane handles U
 // vectors of V adjacent columns.  All loads are issued at once, then
 //     x <- x - lr g ;   PROX: x <- x + w (c - x), c the stored center, w = mu/tau ;
@@ -40,13 +30,21 @@ struct RowScores {
 // blocks in flight spread over all K rows (5.8-6.0).
 // SCORE: only after its loads are issued does a block consult the 1024-column tile map (tiles
 // block_tile0[m] .. block_tile0[m+1]-1 lie in aligned block m, each inside one layer).  Nearly
-// every block holds one tile; a block that contains layer boundaries reduces once per tile.
+// every block holds one tile; a block that contains layer boundaries reduces once per tile.  The tile sums go to
+// k_estimate.  (Updating the estimate inside this launch, by the block that brings the last tile of a (worker, layer), was
+// tried: its device-scope traffic costs more than the launch from about 1000 blocks or 30 tiles per layer on, 4 steps and
+// the communication on 8 workers 117 us instead of 45.)  The maps are parameters of their own, each __restrict__: as
+// members of a struct they may alias the stores, and a block with many tiles then reads them by vector loads that wait for
+// its stores (64 workers, 300 k columns, 5000 layers: this kernel 141 us for 114).
 // The last P % V columns of a row are handled element by element.
 template <typename GT, int V, int U, bool LNT, bool SNT, bool PROX, bool SCORE>
 __global__ __launch_bounds__(GRAWA_CELL) __attribute__((amdgpu_waves_per_eu(1, PROX && !SCORE ? 7 : 8))) void k_row_step(float *__restrict__ x, int64_t ldx,
                                                          const GT *__restrict__ g, int64_t ldg, float lr,
                                                          const float *__restrict__ center, float w, int64_t P,
-                                                         unsigned n_blocks, const RowScores a)
+                                                         unsigned n_blocks,
+                                                         const GrawaTile *__restrict__ tiles,
+                                                         const int32_t *__restrict__ block_tile0, int64_t n_tiles,
+                                                         double *__restrict__ partials)
 {
     static_assert(V * U * GRAWA_CELL == GRAWA_ROW_BLOCK, "one trip covers one aligned block of columns");
     typedef typename FloatVec<V>::T XV;
@@ -73,8 +71,8 @@ __global__ __launch_bounds__(GRAWA_CELL) __attribute__((amdgpu_waves_per_eu(1, P
     }
     int r0 = 0, r1 = 1;
     if (SCORE) {
-        r0 = a.block_tile0[m];
-        r1 = a.block_tile0[m + 1];
+        r0 = block_tile0[m];
+        r1 = block_tile0[m + 1];
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -105,7 +103,7 @@ __global__ __launch_bounds__(GRAWA_CELL) __attribute__((amdgpu_waves_per_eu(1, P
     }
     if constexpr (SCORE) {
         __shared__ double sm[GRAWA_BLOCK / GRAWA_WAVE];
-        double *out = a.partials + (int64_t)k * a.n_tiles;
+        double *out = partials + (int64_t)k * n_tiles;
         if (r1 - r0 == 1) { // the usual case: the whole block lies in one tile
             double acc = 0.0; // squares and sums in fp64: exact squares at any gradient magnitude
 #pragma unroll
@@ -116,7 +114,7 @@ __global__ __launch_bounds__(GRAWA_CELL) __attribute__((amdgpu_waves_per_eu(1, P
             if (threadIdx.x == 0) out[r0] = tot;
         } else {
             for (int t = r0; t < r1; ++t) {
-                const int64_t lo = a.tiles[t].start, hi = lo + a.tiles[t].len;
+                const int64_t lo = tiles[t].start, hi = lo + tiles[t].len;
                 double acc = 0.0;
 #pragma unroll
                 for (int u = 0; u < U; ++u)
@@ -255,10 +253,14 @@ static hipError_t launch_row_step(const grawa_plan *p, float *x, int64_t ldx, co
     const bool plain = !prox && !p;
     const bool nt = aligned && bytes > (plain ? GRAWA_STREAMING_MIN_SGD_BYTES : GRAWA_STREAMING_MIN_ROW_BYTES);
     const bool wide = !aligned && bytes > (plain ? 2 * GRAWA_STREAMING_MIN_SGD_BYTES : GRAWA_STREAMING_MIN_ROW_BYTES);
-    const RowScores a = p ? RowScores{p->d_rtiles, p->d_block_rtile0, p->d_partials, p->n_rtiles} : RowScores{};
+    const GrawaTile *tiles = p ? p->d_rtiles : nullptr;
+    const int32_t *block_tile0 = p ? p->d_block_rtile0 : nullptr;
+    double *partials = p ? p->d_partials : nullptr;
+    const int64_t n_tiles = p ? p->n_rtiles : 0;
 #define GRAWA_RS_GO(GT, V, U, LNT, SNT, PROX, SCORE)                                                                   \
     k_row_step<GT, V, U, LNT, SNT, PROX, SCORE><<<grid, block, 0, s>>>(x, ldx, (const GT *)g, ldg, lr, center, w, P, \
-                                                                       (unsigned)nb, a)
+                                                                       (unsigned)nb, tiles, block_tile0, n_tiles,  \
+                                                                       partials)
 #define GRAWA_RS_NT(GT, V, U, PROX, SCORE)                          \
     do {                                                            \
         if (nt) GRAWA_RS_GO(GT, V, U, true, true, PROX, SCORE);     \
