@@ -174,6 +174,10 @@ static grawa_status_t plan_create_impl(grawa_plan_t **out, int K, int64_t P, int
     p->n_tiles = nt;
     p->n_rtiles = nrt;
     p->n_cells = nc;
+    for (int l = 0; l < L; ++l) {
+        const int64_t n = m.layer_rtile0[(size_t)l + 1] - m.layer_rtile0[(size_t)l];
+        if (n > p->max_rtiles) p->max_rtiles = n;
+    }
     if (hipGetDevice(&p->device) != hipSuccess) {
         delete p;
         return GRAWA_ERR_HIP;

@@ -32,6 +32,7 @@ struct grawa_plan {
     int32_t *d_layer_rtile0; // [L+1]
     int32_t *d_block_rtile0; // [ceil(P/1024)+1] first short tile of every aligned block of 1024 columns
     int64_t n_rtiles;
+    int64_t max_rtiles;     // most short tiles of a layer
     int32_t *d_cell_layer;  // [n_cells] layer of a 256-column cell, or ~(first layer) if it holds a boundary
     double *d_partials;     // [K][n_tiles] per-tile sums of squares
     double *d_S;            // [K][L] squared Frobenius norms

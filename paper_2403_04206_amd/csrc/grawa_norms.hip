@@ -223,57 +223,63 @@ __global__ __launch_bounds__(GRAWA_FIN_BLOCK) void k_finalize_model(double *__re
     model_weights(S, K, L, goal, [](double *p) { return *p; }, sA, beta, beta_user, flags);
 }
 
-// grid (L, min(K, GRAWA_EST_ROWS)), block 512: the tile sums of a scored local step -> running estimate of
-// Appendix G, g_mvg <- gamma g_mvg + (1 - gamma) g_cur, t <- t + 1.  Block (l, y) adds the tiles of layer l for
-// workers y, y + gridDim.y, ....  The tiles of this step are short: with one block per layer the 50 000 tiles
-// of the largest layer of the 350 M transformer for each of 8 workers took 72 us.
-// WAVES (rows to 2^20 columns): grid (L, ceil(K / 8)), every wave takes a worker of its own, since starting L K blocks
-// takes longer than the sums.  Steps and communication, against one block per layer for all workers, 250 layers of
-// 170 k columns and 15 workers: L K blocks 35.1 us for 32.3 (one step), a wave per worker 44.5 us for 46.7 (two
-// steps); from 2^20 columns on the blocks are the shorter chain (8 workers, 1 or 3 layers, 1.1 M columns: 66.4 us for 70.9).
+// grid (L, y) and block from grawa_estimate_shape: the tile sums of a scored local step -> running estimate of
+// Appendix G, g_mvg <- gamma g_mvg + (1 - gamma) g_cur, t <- t + 1.  The tiles of this step are short (1024 columns).
+// A layer of up to GRAWA_EST_WAVE_TILES of them is a wave's work for one worker; of a longer one the whole block adds
+// the tiles of one worker at a time (the 50 000 tiles of the largest layer of the 350 M transformer for each of 8 workers
+// took one block 72 us).
 // The counts t (one per layer, see k_local_weights) live on the device so that a recorded and replayed call still counts.
-#define GRAWA_EST_BLOCK 512
-#define GRAWA_EST_ROWS 64
-#define GRAWA_EST_WAVES (GRAWA_EST_BLOCK / GRAWA_WAVE)
-#define GRAWA_EST_WAVES_MAX_P ((int64_t)1 << 20)
-template <bool WAVES>
-__global__ __launch_bounds__(GRAWA_EST_BLOCK) void k_estimate(const double *__restrict__ partials, int64_t n_tiles,
-                                                              const int32_t *__restrict__ layer_tile0, int K, int L,
-                                                              double *__restrict__ mvg, double gamma,
-                                                              int64_t *__restrict__ local_t,
-                                                              unsigned *__restrict__ flags)
+__global__ __launch_bounds__(GRAWA_EST_MAX_THREADS) void k_estimate(const double *__restrict__ partials, int64_t n_tiles,
+                                                                    const int32_t *__restrict__ layer_tile0, int K, int L,
+                                                                    double *__restrict__ mvg, double gamma,
+                                                                    int64_t *__restrict__ local_t,
+                                                                    unsigned *__restrict__ flags)
 {
-    const int l = blockIdx.x;
+    __shared__ double sm[GRAWA_MAX_WORKERS];
+    const int l = blockIdx.x, y = blockIdx.y, rows = gridDim.y, threads = blockDim.x;
     const int t0 = layer_tile0[l], t1 = layer_tile0[l + 1];
+    const int lane = threadIdx.x & (GRAWA_WAVE - 1);
+    const int wave = threadIdx.x / GRAWA_WAVE, waves = threads / GRAWA_WAVE;
     const auto step = [&](int k, double tot) {
         const double norm = sqrt(tot);
         mvg[(int64_t)k * L + l] = gamma * mvg[(int64_t)k * L + l] + (1.0 - gamma) * norm;
         if (flags && !isfinite(norm)) atomicOr(flags, GRAWA_NONFINITE_LAYER_SCORE);
     };
-    if constexpr (WAVES) {
-        const int lane = threadIdx.x & (GRAWA_WAVE - 1);
-        const int k = (int)blockIdx.y * GRAWA_EST_WAVES + (int)(threadIdx.x / GRAWA_WAVE);
-        if (k < K) {
+    if (t1 - t0 <= GRAWA_EST_WAVE_TILES || K > 4 * rows) {
+        // The sums first, then every worker's update by a thread of its own, side by side.
+        int n = wave;
+        for (int k = y * waves + wave; k < K; k += rows * waves, n += waves) {
             const double tot = wave_strided_sum(partials + (int64_t)k * n_tiles, t0, t1, lane, GRAWA_WAVE);
-            if (lane == 0) step(k, tot);
+            if (lane == 0) sm[n] = tot;
+        }
+        __syncthreads();
+        for (int j = threadIdx.x; j < K; j += threads) {
+            const int k = (j / waves * rows + y) * waves + j % waves;
+            if (k < K) step(k, sm[j]);
         }
     } else {
-        __shared__ double sm[GRAWA_EST_WAVES];
-        for (int k = blockIdx.y; k < K; k += gridDim.y) {
+        for (int k = y; k < K; k += rows) {
             const double *p = partials + (int64_t)k * n_tiles;
             double s[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) s[u] = 0.0;
             int t = t0 + (int)threadIdx.x;
-            for (; t + 7 * GRAWA_EST_BLOCK < t1; t += 8 * GRAWA_EST_BLOCK)
+            for (; t + 7 * threads < t1; t += 8 * threads)
 #pragma unroll
-                for (int u = 0; u < 8; ++u) s[u] += p[t + u * GRAWA_EST_BLOCK];
-            for (; t < t1; t += GRAWA_EST_BLOCK) s[0] += p[t];
-            const double tot = block_sum<GRAWA_EST_BLOCK>(((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7])), sm);
-            if (threadIdx.x == 0) step(k, tot);
+                for (int u = 0; u < 8; ++u) s[u] += p[t + u * threads];
+            for (; t < t1; t += threads) s[0] += p[t];
+            const double part = wave_sum(((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7])));
+            __syncthreads(); // the last worker's sums have been read
+            if (lane == 0) sm[wave] = part;
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                double tot = 0.0;
+                for (int i = 0; i < waves; ++i) tot += sm[i];
+                step(k, tot);
+            }
         }
     }
-    if (blockIdx.y == 0 && threadIdx.x == 0) local_t[l] += 1;
+    if (y == 0 && threadIdx.x == 0) local_t[l] += 1;
 }
 
 // Weights from the running norm estimate g_est = gamma g_mvg / (1 - gamma^t) (Appendix G), t =
@@ -428,15 +434,10 @@ hipError_t grawa_launch_finalize_layers(const grawa_plan *p, int goal, float *no
 
 hipError_t grawa_launch_estimate(const grawa_plan *p, double gamma, hipStream_t s)
 {
-    const int64_t rows = p->P <= GRAWA_EST_WAVES_MAX_P ? (p->K + GRAWA_EST_WAVES - 1) / GRAWA_EST_WAVES
-                                                       : (p->K < GRAWA_EST_ROWS ? p->K : GRAWA_EST_ROWS);
-    const dim3 grid((unsigned)p->L, (unsigned)rows), block(GRAWA_EST_BLOCK);
-    if (p->P <= GRAWA_EST_WAVES_MAX_P)
-        k_estimate<true><<<grid, block, 0, s>>>(p->d_partials, p->n_rtiles, p->d_layer_rtile0, p->K, p->L, p->d_mvg, gamma,
-                                                p->d_local_t, p->d_flags);
-    else
-        k_estimate<false><<<grid, block, 0, s>>>(p->d_partials, p->n_rtiles, p->d_layer_rtile0, p->K, p->L, p->d_mvg, gamma,
-                                                 p->d_local_t, p->d_flags);
+    int rows, threads;
+    grawa_estimate_shape(p->K, p->L, p->max_rtiles, &rows, &threads);
+    k_estimate<<<dim3((unsigned)p->L, (unsigned)rows), dim3((unsigned)threads), 0, s>>>(
+        p->d_partials, p->n_rtiles, p->d_layer_rtile0, p->K, p->L, p->d_mvg, gamma, p->d_local_t, p->d_flags);
     return hipGetLastError();
 }
 

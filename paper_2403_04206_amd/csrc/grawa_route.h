@@ -29,4 +29,27 @@ static inline void grawa_split_grid(int64_t n_cells, unsigned *gx, unsigned *gy)
 #define GRAWA_LAST_BLOCK_MAX_LAYERS 100
 static inline bool grawa_model_weights_by_last_block(int L) { return L <= GRAWA_LAST_BLOCK_MAX_LAYERS; }
 
+// Launch of the running estimate: y rows of blocks per layer and threads of a block.  max_tiles: the most 1024-column
+// tiles that a layer has.  Layers of up to GRAWA_EST_WAVE_TILES tiles take a wave per worker, or, where there are many
+// layers (GRAWA_EST_BLOCKS blocks fill the chip), a wave per few workers: starting a wave costs more than such a sum.
+// A longer layer takes a block of 512 threads per worker, as long as that keeps the launch within
+// GRAWA_EST_LONG_BLOCKS blocks for all layers.  Scored step and estimate on the device, us, one block of 1024 per layer /
+// a block per layer and worker from 2^20 columns on, a wave below / this:
+//   8 workers, 1.05 M columns:   250 layers 24.0 / 24.7 / 22.5, 5000 layers 57.5 / 78.6 / 37.5
+//   15 workers, 1.05 M:          1000 layers 40.3 / 53.5 / 36.6
+//   64 workers, 300 k:           1000 layers 55.6 / 70.6 / 55.5;  1.05 M, 5000 layers 223 / 586 / 196
+#define GRAWA_EST_MAX_THREADS 1024
+#define GRAWA_EST_WAVE_TILES 1024
+#define GRAWA_EST_BLOCKS 512
+#define GRAWA_EST_LONG_BLOCKS 4096
+static inline void grawa_estimate_shape(int K, int L, int64_t max_tiles, int *rows, int *threads)
+{
+    const bool longest = max_tiles > GRAWA_EST_WAVE_TILES;
+    const int waves = longest ? 8 : K < 16 ? K : 16;
+    const int all = (K + waves - 1) / waves, fill = (longest ? GRAWA_EST_LONG_BLOCKS : GRAWA_EST_BLOCKS) / L;
+    const int want = longest ? K : all;
+    *rows = fill < 1 ? 1 : fill < want ? fill : want;
+    *threads = waves * 64;
+}
+
 #endif

@@ -1,6 +1,7 @@
 // Prints the launch shapes that the host-side rules of paper_2403_04206_amd/csrc/grawa_route.h give (no GPU toolchain).
 //   split <n_cells>...   -> per line: n_cells grid_x grid_y threads
 //   model <L>...         -> per line: L, 1 if the last block of the norms' launch forms the model-level weights
+//   estimate <K> <L> <max_tiles> ... -> per triple: the triple, rows, threads
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -21,6 +22,14 @@ int main(int argc, char **argv)
     }
     if (!std::strcmp(argv[1], "model")) {
         for (int i = 2; i < argc; ++i) std::printf("%s %d\n", argv[i], grawa_model_weights_by_last_block(std::atoi(argv[i])));
+        return 0;
+    }
+    if (!std::strcmp(argv[1], "estimate")) {
+        for (int i = 2; i + 2 < argc; i += 3) {
+            int rows = 0, threads = 0;
+            grawa_estimate_shape(std::atoi(argv[i]), std::atoi(argv[i + 1]), std::atoll(argv[i + 2]), &rows, &threads);
+            std::printf("%s %s %s %d %d\n", argv[i], argv[i + 1], argv[i + 2], rows, threads);
+        }
         return 0;
     }
     return 2;

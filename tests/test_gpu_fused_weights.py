@@ -120,6 +120,29 @@ def test_step_count_of_every_layer(K, L):
             assert_table_close(est.cpu().numpy(), scores.g_est, TIGHT, "g_est after %d steps" % t)
 
 
+@pytest.mark.parametrize("K,sizes", [
+    (3, [1 << 20]), (3, [(1 << 20) + 1]),                # 1024 tiles: the most that a wave adds; one more
+    (3, [5, (1 << 20) + 1019, 7]),                       # a layer cut off the tile grid, 1026 tiles
+    (1, [(1 << 20) + 5000, 3, 1]), (17, [3, (1 << 20) + 2000]),
+    (66, [1 << 20, 9]), (66, [3, (1 << 20) + 3000]),     # more workers than waves: further trips over the workers
+    (70, [11] * 700), (33, [2] * 600 + [40000]), (2, [3] * 5000),
+    (5, [2] * 4100 + [(1 << 20) + 1100]),                # many layers beside a long one
+])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_estimate_shapes(K, sizes, dtype):
+    w, x, g = W.make_small(2360 + K, K, sizes, grad_dtype=dtype, device=DEV)
+    P, gamma = w.P, 0.9
+    est = torch.empty((K, w.L), device=DEV)
+    scores = orc.LocalScores(K, w.L, gamma)
+    scores.step(W.to_numpy_grads(g), w.offsets)
+    with grawa.Plan(K, P, w.offsets) as plan:
+        for _ in range(2):
+            plan.local_step_scored(x[:, :P], g[:, :P], 0.01, gamma)
+            plan.local_lgrawa_update(x[:, :P], 0.1, est_out=est)
+            worst = assert_table_close(est.cpu().numpy(), scores.g_est, TIGHT, "g_est")
+            assert worst < 2e-7                          # fp64 sums, one rounding to the float32 table
+
+
 @pytest.mark.parametrize("L", [1, 99, 100, 101, 700, 5000])
 @pytest.mark.parametrize("K", [3, 16, 33])
 def test_model_weights_by_layer_count(K, L):

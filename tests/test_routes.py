@@ -34,3 +34,13 @@ def test_row_split_grid_within_the_launch_limit(driver):
 def test_no_arrivals_with_many_layers(driver):
     # one arrival per layer on one address: bounded by a rule on the layer count, whatever else the problem is
     assert driver("model", 1, 62, 100, 101, 161, 291, 100000) == [[1, 1], [62, 1], [100, 1], [101, 0], [161, 0], [291, 0], [100000, 0]]
+
+
+def test_estimate_launch(driver):
+    cases = [(K, L, T) for K in (1, 3, 8, 15, 16, 17, 64, 1024) for L in (1, 60, 511, 512, 513, 5000, 1 << 20)
+             for T in (1, 1024, 1025, 50000)]
+    for (K, L, T, rows, threads) in driver("estimate", *[v for c in cases for v in c]):
+        assert 64 <= threads <= 1024 and threads % 64 == 0 and 1 <= rows <= K
+        assert rows == 1 or rows * L <= (512 if T <= 1024 else 4096)
+        assert T > 1024 or (rows - 1) * (threads // 64) < K              # no row of blocks without a worker
+        assert L * threads < 1 << 32
