@@ -35,8 +35,8 @@ static inline bool grawa_model_weights_by_last_block(int L) { return L <= GRAWA_
 // A longer layer takes a block of 512 threads per worker, as long as that keeps the launch within
 // GRAWA_EST_LONG_BLOCKS blocks for all layers.  Scored step and estimate on the device, us, one block of 1024 per layer /
 // a block per layer and worker from 2^20 columns on, a wave below / this:
-//   8 workers, 1.05 M columns:   250 layers 24.0 / 24.7 / 22.5, 5000 layers 57.5 / 78.6 / 37.5
-//   15 workers, 1.05 M:          1000 layers 40.3 / 53.5 / 36.6
+//   8 workers, 1.05 M columns:   250 layers 24.4 / 24.7 / 23.3, 5000 layers 57.5 / 78.6 / 37.5
+//   15 workers, 1.05 M:          1000 layers 40.2 / 53.5 / 38.3
 //   64 workers, 300 k:           1000 layers 55.6 / 70.6 / 55.5;  1.05 M, 5000 layers 223 / 586 / 196
 #define GRAWA_EST_MAX_THREADS 1024
 #define GRAWA_EST_WAVE_TILES 1024
