@@ -24,7 +24,7 @@ __device__ __forceinline__ int layer_of(const int64_t *__restrict__ off, int lay
 // Per-layer weights straight from the tile sums of the norm pass, computed by every block for the layers of its own
 // cell (TILES).  A small update is a chain of short launches, and this one drops a link: for 270 k parameters and
 // 4 workers the weights as a launch of their own took 4.0 us plus the boundary.  The loads of x are in flight
-// meanwhile.  K <= 64; every wave of the block takes one layer at a time; the layer's first cell writes weights_out.
+// meanwhile.  The cell that a layer starts in writes its row of weights_out.
 struct TileWeights {
     const double *partials;
     int64_t pitch;
@@ -34,17 +34,21 @@ struct TileWeights {
     int group;                            // lanes per worker: the largest power of two not above 64 / K
 };
 
-#define GRAWA_CELL_BETAS 2048  // weights of one cell kept in LDS
-#define GRAWA_CELL_LAYERS 64   // layers of one cell kept in LDS; beyond either, every lane works for itself
-struct CellWeights {
-    float beta[GRAWA_CELL_BETAS]; // [layer of the cell][K]
-    int start[GRAWA_CELL_LAYERS]; // first column of the layer, relative to the cell
+template <int K> struct CellWeights {
+    float beta[GRAWA_CELL * K]; // [layer of the cell][K]
+    int start[GRAWA_CELL];      // first column of the layer, relative to the cell
 };
 
-// Fills `sh` for the cell at column cell0 whose first layer is l0; returns the number of layers, or 0 if they do not
-// fit.  Called by the whole block; ends with a barrier.
-__device__ __forceinline__ int cell_weights(const TileWeights &w, const int64_t *__restrict__ off, int L, int K,
-                                            int64_t P, int64_t cell0, int l0, bool boundary, int waves, CellWeights &sh)
+// Fills `sh` for the cell at column cell0 whose first layer is l0; returns the number of layers.  Called by the whole
+// block (4 waves); ends with a barrier.  The first and the last layer of the cell may have tiles in other cells, any
+// number of them: a wave for each.  The layers between have all their columns in the cell, so one tile each (tiles are
+// cut at multiples of at least 4096): a lane for each, with the loads of its K workers in flight together.  So a cell
+// takes two rounds at most, for 3 layers as for 256 (a wave per layer in turn took 16 rounds, and lanes that walked
+// all tiles of their layer more: 4 workers, 600 k columns, of which the first 60 or 100 are layers of their own, update on the
+// device 24.6 and 174 us; with the weights as a launch 17.3 and 21.8; now 11.4 and 11.7).
+template <int K>
+__device__ __forceinline__ int cell_weights(const TileWeights &w, const int64_t *__restrict__ off, int L, int64_t P,
+                                            int64_t cell0, int l0, bool boundary, CellWeights<K> &sh)
 {
     const int lane = threadIdx.x & (GRAWA_WAVE - 1);
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / GRAWA_WAVE));
@@ -56,62 +60,32 @@ __device__ __forceinline__ int cell_weights(const TileWeights &w, const int64_t 
             nl += __popcll(in);
             if (in != ~0ull) break;
         }
+        if (nl > GRAWA_CELL) nl = GRAWA_CELL; // only with offsets that break the rules
+        if ((int)threadIdx.x < nl) sh.start[threadIdx.x] = threadIdx.x ? (int)(off[l0 + (int)threadIdx.x] - cell0) : 0;
     }
-    if (nl > GRAWA_CELL_LAYERS || nl * K > GRAWA_CELL_BETAS) return 0;
-    if (wave == 0 && lane < nl) sh.start[lane] = lane ? (int)(off[l0 + lane] - cell0) : 0;
-    for (int i = wave; i < nl; i += waves) {
-        const int l = l0 + i;
+    if (wave == 0 || (wave == 1 && nl > 1)) {
+        const int i = wave == 0 ? 0 : nl - 1, l = l0 + i;
         wave_layer_weights(w.partials, w.pitch, w.tile_begin[l], w.tile_end[l], K, w.group, sh.beta + i * K,
                            off[l] >= cell0, w.weights_out ? w.weights_out + l : nullptr, L, w.flags);
+    } else if (wave >= 2) {
+        for (int i = 1 + (int)threadIdx.x - 2 * GRAWA_WAVE; i < nl - 1; i += GRAWA_CELL - 2 * GRAWA_WAVE) {
+            const int l = l0 + i;
+            lane_layer_weights<K>(w.partials, w.pitch, w.tile_begin[l], w.tile_end[l], sh.beta + i * K,
+                                  w.weights_out ? w.weights_out + l : nullptr, L, w.flags);
+        }
     }
     __syncthreads();
     return nl;
 }
 
 // Which of the nl layers of the cell column `col` (relative to the cell) lies in.
-__device__ __forceinline__ int cell_layer_of(const CellWeights &sh, int nl, int col)
+template <int K> __device__ __forceinline__ int cell_layer_of(const CellWeights<K> &sh, int nl, int col)
 {
     int i = 0;
-    for (int j = 1; j < nl; ++j) i += sh.start[j] <= col ? 1 : 0;
+    for (int step = nl > 1 ? 1 << (31 - __builtin_clz(nl - 1)) : 0; step; step >>= 1)
+        if (i + step < nl && sh.start[i + step] <= col) i += step;
     return i;
 }
-
-// One lane's own way to the weights of layer l (cells with more layers than the table above holds).
-struct LaneWeights {
-    const double *p;
-    int64_t pitch;
-    int t0, t1;
-    double a_min, n_zero, z;
-    __device__ __forceinline__ double score(int k) const
-    {
-        double s = 0.0;
-        for (int t = t0; t < t1; ++t) s += p[(int64_t)k * pitch + t];
-        return sqrt(s);
-    }
-    __device__ __forceinline__ LaneWeights(const TileWeights &w, int l, int K)
-        : p(w.partials), pitch(w.pitch), t0(w.tile_begin[l]), t1(w.tile_end[l]), a_min(INFINITY), n_zero(0.0), z(0.0)
-    {
-        for (int k = 0; k < K; ++k) {
-            const double a = score(k);
-            a_min = fmin(a_min, a);
-            n_zero += a == 0.0 ? 1.0 : 0.0;
-        }
-        if (n_zero == 0.0)
-            for (int k = 0; k < K; ++k) z += a_min / score(k);
-    }
-    __device__ __forceinline__ float beta(int k) const
-    {
-        const double a = score(k);
-        return (float)(n_zero > 0.0 ? (a == 0.0 ? 1.0 / n_zero : 0.0) : (a_min / a) / z);
-    }
-    __device__ __forceinline__ void publish(const TileWeights &w, int l, int K, int L) const
-    {
-        for (int k = 0; k < K; ++k) {
-            if (w.weights_out) w.weights_out[(int64_t)k * L + l] = beta(k);
-            if (w.flags && !isfinite(score(k))) atomicOr(w.flags, GRAWA_NONFINITE_LAYER_SCORE);
-        }
-    }
-};
 
 // Plain form, K <= 23 (16 without the SGD step excepted).  grid ceil(P/256), block 256: a lane owns one
 // column.  It loads x[k][i] for its K workers (all loads in flight together; with SGD also g[k][i] and
@@ -160,20 +134,11 @@ __global__ __launch_bounds__(GRAWA_CELL) __attribute__((amdgpu_waves_per_eu(1, W
     const int info = cell_layer ? cell_layer[blockIdx.x] : 0;
     float c = 0.f;
     if constexpr (TILES) {
-        __shared__ CellWeights cw;
-        const int l0 = info >= 0 ? info : ~info;
-        const int nl = cell_weights(tw, off, L, K, P, cell0, l0, info < 0, GRAWA_CELL / GRAWA_WAVE, cw);
-        if (nl > 0) {
-            const float *b = cw.beta + (nl > 1 ? cell_layer_of(cw, nl, (int)col) * K : 0);
+        __shared__ CellWeights<K> cw;
+        const int nl = cell_weights<K>(tw, off, L, P, cell0, info >= 0 ? info : ~info, info < 0, cw);
+        const float *b = cw.beta + cell_layer_of<K>(cw, nl, (int)col) * K;
 #pragma unroll
-            for (int k = 0; k < K; ++k) c = fmaf(b[k], v[k], c);
-        } else if (ok) {
-            const int l = layer_of(off, l0, L, cell0 + col);
-            const LaneWeights lw(tw, l, K);
-#pragma unroll
-            for (int k = 0; k < K; ++k) c = fmaf(lw.beta(k), v[k], c);
-            if (off[l] == cell0 + col) lw.publish(tw, l, K, L);
-        }
+        for (int k = 0; k < K; ++k) c = fmaf(b[k], v[k], c);
     } else if (info >= 0) { // one layer for the whole cell: weights through scalar loads
         const uint64_t bb = uniform_base(beta + info);
 #pragma unroll

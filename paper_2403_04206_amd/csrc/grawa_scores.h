@@ -113,3 +113,36 @@ __device__ __forceinline__ void wave_layer_weights(const double *__restrict__ pa
         if (owner && flags && !isfinite(a)) atomicOr(flags, GRAWA_NONFINITE_LAYER_SCORE);
     }
 }
+
+// The same by one lane, for a layer of few tiles; the whole row of weights.
+template <int K>
+__device__ __forceinline__ void lane_layer_weights(const double *__restrict__ partials, int64_t pitch, int t0, int t1,
+                                                   float *out, float *beta_user, int L, unsigned *flags)
+{
+    double a[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) a[k] = 0.0;
+    for (int t = t0; t < t1; ++t)
+#pragma unroll
+        for (int k = 0; k < K; ++k) a[k] += partials[(int64_t)k * pitch + t];
+    double a_min = INFINITY, n_zero = 0.0, z = 0.0;
+    bool bad = false;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        a[k] = sqrt(a[k]);
+        a_min = fmin(a_min, a[k]);
+        n_zero += a[k] == 0.0 ? 1.0 : 0.0;
+        bad = bad || !isfinite(a[k]);
+    }
+    if (n_zero == 0.0) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) z += a_min / a[k];
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const float b = (float)(n_zero > 0.0 ? (a[k] == 0.0 ? 1.0 / n_zero : 0.0) : (a_min / a[k]) / z);
+        out[k] = b;
+        if (beta_user) beta_user[(int64_t)k * L] = b;
+    }
+    if (flags && bad) atomicOr(flags, GRAWA_NONFINITE_LAYER_SCORE);
+}

@@ -1,7 +1,7 @@
 """GPU parity where a launch does the work of two: per-layer weights taken straight from the tile sums inside the
 center+pull pass (small problems), the model-level weights inside the finalize launch, and the reset of the running
-estimate inside the weights launch.  Layouts: one layer, layers of one column, cells with more layers than the per-cell table
-holds, layers of many tiles; both sides of each size rule; non-finite scores; the same plan called repeatedly."""
+estimate inside the weights launch.  Layouts: one layer, layers of one column, cells full of layers beside long ones,
+layers of many tiles; both sides of each size rule; non-finite scores; the same plan called repeatedly."""
 import numpy as np
 import pytest
 import torch
@@ -18,7 +18,9 @@ DEV = "cuda:0"
 
 LAYOUTS = {
     "one layer": [70001],
-    "ones": [1] * 700,                                   # 256 layers in a cell: beyond the per-cell table
+    "ones": [1] * 700,                                   # 256 layers in a cell
+    "clustered": [40000] + [1] * 63 + [1] * 255 + [30001],   # full cells beside long layers, first and last of a cell
+    "around 64": [193] + [1] * 63 + [9000] + [4] * 66 + [256, 256, 1, 255, 2, 254],
     "mixed": [1] * 63 + [300, 2, 2, 252, 4097, 1, 1, 20001, 255, 1],
     "tiles": [36864, 1, 8192, 2048, 2047],
 }
