@@ -570,15 +570,7 @@ template <bool SGD, typename GT> static void dispatch_cp_tiles(GRAWA_CP_ARGS)
 #undef GRAWA_CP_TILES
 }
 
-// Where every block works the weights out for itself instead of a launch of its own doing it once.  The extra work
-// grows with the blocks and the workers, what it saves is one launch (us per LGRAWA update, with the launch and
-// without): 4 workers x 270 k columns 16.1 / 13.7, 8 x 270 k 16.0 / 14.6, 4 x 600 k 15.8 / 13.9; a draw at
-// 16 x 270 k (20.5 / 20.1); slower from 4 x 1.2 M (20.3 / 20.8) on, 16 x 600 k 31.6 / 33.8.
-#define GRAWA_TILES_MAX_CELLS 10240 // cells times workers
-bool grawa_pull_from_tiles(const grawa_plan *p)
-{
-    return p->K <= 15 && p->n_cells * p->K <= GRAWA_TILES_MAX_CELLS;
-}
+bool grawa_pull_from_tiles(const grawa_plan *p) { return grawa_weights_in_pull(p->K, p->n_cells); }
 
 hipError_t grawa_launch_center_pull(const grawa_plan *p, float *x, int64_t ldx, const float *beta,
                                     int per_layer, float lambda, const void *g_sgd, int64_t ldg_sgd,

@@ -19,6 +19,22 @@ static inline void grawa_split_grid(int64_t n_cells, unsigned *gx, unsigned *gy)
     *gx = (unsigned)((n_cells + rows - 1) / rows);
 }
 
+// Per-layer weights: worked out by every block of the pull for the layers of its own cell, or by a launch of their own.
+// The work in the pull grows with the blocks, with the tiles of the longest layer (with one layer, each of the blocks
+// adds all tiles of it) and with the workers; what it saves is one launch.  With fewer than 4 workers the lanes of a wave
+// share few sums, and the line is that of 4 workers.  Whole update on the device, us, a launch / in the pull, one layer
+// and 60 layers: 1 worker, 400 k columns 8.6 / 7.3 and 9.5 / 7.5, 655 k 9.1 / 9.4 and 9.8 / 8.9, 2.6 M 12.8 / 19.2 and
+// 13.3 / 16.8; 2 workers, 655 k 9.9 / 9.7 and 10.4 / 9.4, 1.3 M 11.8 / 14.1 and 12.6 / 12.8; 4 workers, 400 k
+// 10.2 / 8.6 and 10.9 / 8.6, 655 k 11.3 / 11.6 and 12.2 / 11.0; 15 workers, 175 k 11.4 / 10.0 and 13.9 / 13.1.
+// Without the launch the host saves 1 to 4 us of a call as well.  Slower from 4 x 1.2 M (20.3 / 20.8) and 16 x 600 k
+// (31.6 / 33.8) on.
+#define GRAWA_TILES_MAX_WORKERS 15
+#define GRAWA_TILES_MAX_CELLS 10240 // cells times workers
+static inline bool grawa_weights_in_pull(int K, int64_t n_cells)
+{
+    return K <= GRAWA_TILES_MAX_WORKERS && n_cells * (K < 4 ? 4 : K) <= GRAWA_TILES_MAX_CELLS;
+}
+
 // Model-level weights: by the last block of the launch that forms the layer norms, or by a launch of its own.  The last
 // block saves the host a launch (a call of 4 workers that is host-bound: 17 us for 21) and the device nothing; every
 // layer's arrival and every norm handed over cost, so that from about 100 layers on the device loses.  Whole update

@@ -1,6 +1,7 @@
 // Prints the launch shapes that the host-side rules of paper_2403_04206_amd/csrc/grawa_route.h give (no GPU toolchain).
 //   split <n_cells>...   -> per line: n_cells grid_x grid_y threads
 //   model <L>...         -> per line: L, 1 if the last block of the norms' launch forms the model-level weights
+//   tiles <K> <n_cells>... -> per pair: the pair, 1 if the pull forms the per-layer weights
 //   estimate <K> <L> <max_tiles> ... -> per triple: the triple, rows, threads
 #include <cstdio>
 #include <cstdlib>
@@ -22,6 +23,11 @@ int main(int argc, char **argv)
     }
     if (!std::strcmp(argv[1], "model")) {
         for (int i = 2; i < argc; ++i) std::printf("%s %d\n", argv[i], grawa_model_weights_by_last_block(std::atoi(argv[i])));
+        return 0;
+    }
+    if (!std::strcmp(argv[1], "tiles")) {
+        for (int i = 2; i + 1 < argc; i += 2)
+            std::printf("%s %s %d\n", argv[i], argv[i + 1], grawa_weights_in_pull(std::atoi(argv[i]), std::atoll(argv[i + 1])));
         return 0;
     }
     if (!std::strcmp(argv[1], "estimate")) {

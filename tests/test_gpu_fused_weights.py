@@ -37,7 +37,7 @@ def test_weights_inside_the_pull(name, K, dtype):
     both_ways(w, x, g, 0.4)
 
 
-@pytest.mark.parametrize("K,cells", [(4, 2560), (4, 2561), (15, 682), (15, 683)])
+@pytest.mark.parametrize("K,cells", [(1, 2560), (1, 2561), (2, 2560), (2, 2561), (4, 2560), (4, 2561), (15, 682), (15, 683)])
 def test_either_side_of_the_size_rule(K, cells):
     P = cells * 256
     w, x, g = W.make_small(2100 + cells, K, [P // 3, 77, P - P // 3 - 77], device=DEV)

@@ -44,3 +44,11 @@ def test_estimate_launch(driver):
         assert rows == 1 or rows * L <= (512 if T <= 1024 else 4096)
         assert T > 1024 or (rows - 1) * (threads // 64) < K              # no row of blocks without a worker
         assert L * threads < 1 << 32
+
+
+def test_weights_in_the_pull(driver):
+    # every block adds the tiles of its layers: bounded by the blocks alone where there are few workers
+    on = [(1, 2560), (2, 2560), (4, 2560), (8, 1280), (15, 682)]
+    off = [(1, 2561), (1, 10240), (2, 2561), (2, 5120), (3, 2561), (4, 2561), (8, 1281), (15, 683), (16, 1)]
+    assert all(r[2] == 1 for r in driver("tiles", *[v for c in on for v in c]))
+    assert all(r[2] == 0 for r in driver("tiles", *[v for c in off for v in c]))
