@@ -39,7 +39,7 @@ struct grawa_plan {
     float *d_beta_layer;    // [K][L] per-layer weights
     float *d_beta_model;    // [K] model-level weights
     float *d_beta_uniform;  // [K] 1/K each (EASGD), written once
-    unsigned *d_cnt_all;    // [1] arrivals of the layers; 0 between calls
+    unsigned *d_cnt_all;    // [1] arrivals of the layers, cleared by the norm pass of the call
     double *d_mvg;          // [K][L] moving average of the layer norms (running estimate, Appendix G)
     int64_t *d_local_t;     // [L], all equal: local steps since the last communication (what the kernels use)
     unsigned *d_flags;      // device: GRAWA_NONFINITE_* bits, sticky until read-and-cleared (may be null)

@@ -17,7 +17,8 @@
 // gradient norms: per-tile sums of squares
 // ---------------------------------------------------------------------------------
 
-// grid (n_tiles, K), block 256.  partials[k][tile] = sum over the tile of g[k][i]^2.
+// grid (n_tiles, K), block 256.  partials[k][tile] = sum over the tile of g[k][i]^2.  Also clears the arrival counter
+// of the launch that follows (null where none arrives).
 // Each lane issues 8 independent 8-byte streaming loads per trip and keeps one accumulator
 // per load; with the occupancy capped at 4 waves per SIMD this shape measured fastest for a
 // read-only stream on this part (7.3-7.4 TB/s; 16-byte loads at full occupancy 6.9-7.0).
@@ -50,7 +51,7 @@ __device__ __forceinline__ void sumsq_rest(const GT *body, int j0, int nvec, dou
 template <typename GT>
 __global__ __launch_bounds__(GRAWA_BLOCK) __attribute__((amdgpu_waves_per_eu(1, 4))) void k_sumsq(
     const GT *__restrict__ g, int64_t ldg, const GrawaTile *__restrict__ tiles, int64_t n_tiles,
-    double *__restrict__ partials)
+    double *__restrict__ partials, unsigned *__restrict__ cnt_all)
 {
     constexpr int V = Grad<GT>::VEC8;
     const GrawaTile t = tiles[blockIdx.x];
@@ -102,6 +103,7 @@ __global__ __launch_bounds__(GRAWA_BLOCK) __attribute__((amdgpu_waves_per_eu(1, 
     for (int u = 0; u < GRAWA_SUMSQ_U; ++u) lane += acc[u];
     const double total = block_sum<GRAWA_BLOCK>(lane, sm);
     if (tid == 0) partials[(int64_t)k * n_tiles + blockIdx.x] = total;
+    if (cnt_all && tid == 0 && k == 0 && blockIdx.x == 0) *cnt_all = 0u;
 }
 
 // ---------------------------------------------------------------------------------
@@ -410,10 +412,10 @@ hipError_t grawa_launch_sumsq(const grawa_plan *p, const void *g, int64_t ldg, g
     const dim3 grid((unsigned)p->n_tiles, (unsigned)p->K), block(GRAWA_BLOCK);
     if (dt == GRAWA_BF16)
         hipExtLaunchKernelGGL(k_sumsq<uint16_t>, grid, block, 0, s, e0, e1, 0, (const uint16_t *)g, ldg,
-                              (const GrawaTile *)p->d_tiles, p->n_tiles, p->d_partials);
+                              (const GrawaTile *)p->d_tiles, p->n_tiles, p->d_partials, p->d_cnt_all);
     else
         hipExtLaunchKernelGGL(k_sumsq<float>, grid, block, 0, s, e0, e1, 0, (const float *)g, ldg,
-                              (const GrawaTile *)p->d_tiles, p->n_tiles, p->d_partials);
+                              (const GrawaTile *)p->d_tiles, p->n_tiles, p->d_partials, p->d_cnt_all);
     return hipGetLastError();
 }
 

@@ -30,16 +30,15 @@ __device__ __forceinline__ double take_over(double *p)
 }
 
 // Counts the block in; true in every thread of the block that is the n-th.  What the block publishes was
-// handed over, by any of its threads, before the call.  The last arriver leaves the counter at zero for the next call.
+// handed over, by any of its threads, before the call.  The launch before this one has set the counter to zero (k_sumsq),
+// so that nothing a launch leaves behind, complete or not, reaches the next call.
 // `sh` is one word of LDS.
 __device__ __forceinline__ bool last_to_arrive(unsigned *counter, unsigned n, unsigned *sh)
 {
     __syncthreads();
     if (threadIdx.x == 0) {
         const unsigned before = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const bool last = before == n - 1;
-        if (last) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        *sh = last ? 1u : 0u;
+        *sh = before == n - 1 ? 1u : 0u;
     }
     __syncthreads();
     return *sh != 0u;

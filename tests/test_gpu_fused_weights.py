@@ -2,6 +2,8 @@
 center+pull pass (small problems), the model-level weights inside the finalize launch, and the reset of the running
 estimate inside the weights launch.  Layouts: one layer, layers of one column, cells full of layers beside long ones,
 layers of many tiles; both sides of each size rule; non-finite scores; the same plan called repeatedly."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -158,6 +160,34 @@ def test_model_weights_by_layer_count(K, L):
         plan.mgrawa_update(x.clone()[:, :w.P], g[:, :w.P], 0.3, weights_out=wts)
         assert plan.nonfinite() == grawa.NONFINITE_LAYER_SCORE | grawa.NONFINITE_MODEL_SCORE
     assert float(wts[0]) == 0.0 and abs(float(wts.double().sum()) - 1.0) < K * 2.0 ** -24
+
+
+def test_model_weights_with_arrivals_left_behind():
+    # a call starts from a counter of its own, whatever an earlier one left: the test writes the plan's counter
+    K, sizes = 5, [300] * 40
+    w, x, g = W.make_small(2460, K, sizes, device=DEV)
+    P = w.P
+    ref, wts = torch.empty(K, device=DEV), torch.empty(K, device=DEV)
+    with grawa.Plan(K, P, w.offsets) as plan:
+        plan.mgrawa_update(x.clone()[:, :P], g[:, :P], 0.1, weights_out=ref)
+    for left in (1, 7, 39, 4000000000):
+        with grawa.Plan(K, P, w.offsets) as plan:
+            # struct grawa_plan: ... void *ws at 48, size_t ws_bytes at 56; the last 256 bytes of ws: flag word, counter at 128
+            ws, n = (ctypes.c_uint64.from_address(plan._h.value + o).value for o in (48, 56))
+            copy = grawa.lib().hipMemcpy
+            copy.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_int]
+            word = ctypes.c_uint32(0)
+            bad = g.clone()
+            bad[0, 0] = float("inf")
+            plan.mgrawa_update(x.clone()[:, :P], bad[:, :P], 0.1)
+            torch.cuda.synchronize()
+            assert copy(ctypes.byref(word), ws + n - 256, 4, 2) == 0
+            assert word.value == plan.nonfinite() == 3   # that is the flag word: the layout is as this test assumes
+            word.value = left
+            assert copy(ws + n - 128, ctypes.byref(word), 4, 1) == 0
+            for _ in range(2):
+                plan.mgrawa_update(x.clone()[:, :P], g[:, :P], 0.1, weights_out=wts)
+                assert torch.equal(wts, ref)
 
 
 @pytest.mark.parametrize("losses,leader", [([3.0, 1.0, 1.0, 2.0], 1), ([float("nan"), 1.0, 0.5], 0), ([2.0, float("nan"), 1.0], 2),
