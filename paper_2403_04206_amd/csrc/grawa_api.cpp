@@ -437,13 +437,13 @@ grawa_status_t local_update(grawa_plan_t *p, float *x, int64_t ldx, int per_laye
     DeviceGuard guard(p->device);
     if (!guard.ok) return GRAWA_ERR_HIP;
     GRAWA_TRY_HIP(grawa_launch_local_weights(p, p->local_gamma, per_layer, weights_out, est_out, s));
+    p->local_t = 0; // the weights have consumed the estimate: also if the launch below fails
     const bool prof = prof_active(p);
     hipEvent_t *ev = prof ? p->ev + 4 * (size_t)p->profile_n : nullptr;
     GRAWA_TRY_HIP(grawa_launch_center_pull(p, x, ldx, per_layer ? p->d_beta_layer : p->d_beta_model, per_layer,
                                            lambda, nullptr, 0, GRAWA_F32, 0.f, 0, center_out, 0.f, 0, nullptr, s,
                                            prof ? ev[2] : nullptr, prof ? ev[3] : nullptr));
     if (prof) prof_commit(p, false);
-    p->local_t = 0;
     return GRAWA_OK;
 }
 } // namespace
