@@ -475,7 +475,7 @@ template <int K, bool SGD, typename GT, bool NT, bool TILES> static void launch_
 }
 
 // The wide form's cap (best of 2, 3, 4 and 8 waves for K <= 5; one too many costs 3 to 5 %, and more than it gains over
-// the plain form), and the worker counts it is used for: where it is at least as fast as the plain form.
+// the plain form).  It is used for the worker counts where it is at least as fast as the plain form (GRAWA_WIDE_COUNTS).
 constexpr int grawa_waves_wide(int k, bool sgd /* fp32 gradients */)
 {
     if (k == 1) return 8;
@@ -483,7 +483,6 @@ constexpr int grawa_waves_wide(int k, bool sgd /* fp32 gradients */)
     if (k == 3) return sgd ? 2 : 3;
     return k <= 5 ? 2 : 1;
 }
-static bool wide_is_faster(int k) { return k <= 5 || (k >= 12 && k <= 23); }
 
 template <int K, bool SGD, typename GT, bool LNT> static void launch_wide(GRAWA_CP_ARGS)
 {
@@ -505,26 +504,20 @@ template <int Q, bool REM, int S, int V, bool SGD, typename GT, bool NT> static 
 
 // One plain kernel per worker count up to 23 (fully unrolled); 24..71 workers share the row-split
 // kernels by K / 8; beyond that the two-sweep kernel.
-template <bool SGD, typename GT, bool NT> static void dispatch_cp(GRAWA_CP_ARGS)
+template <bool SGD, typename GT, bool NT> static hipError_t dispatch_cp(GRAWA_CP_ARGS)
 {
-#define GRAWA_CP_PLAIN(N) \
-    case N: launch_plain<N, SGD, GT, NT, false>(GRAWA_CP_PASS); return;
+    // Line-aligned streaming rows of one worker, and of two unless fused with fp32 gradients: the wide form.
+    constexpr int WIDE_TO = !NT ? 0 : SGD && sizeof(GT) == 4 ? 1 : 2;
+#define GRAWA_CP_PLAIN(N)                                                                       \
+    case N:                                                                                     \
+        if constexpr (N <= WIDE_TO) launch_wide<N, SGD, GT, true>(GRAWA_CP_PASS);               \
+        else launch_plain<N, SGD, GT, NT, false>(GRAWA_CP_PASS);                                \
+        return hipGetLastError();
 #define GRAWA_CP_SPLIT(N)                                                            \
     case N:                                                                          \
         if (p->K % 8 == 0) launch_split<N, false, 8, 2, SGD, GT, NT>(GRAWA_CP_PASS); \
         else launch_split<N, true, 8, 2, SGD, GT, NT>(GRAWA_CP_PASS);                \
-        return;
-    if constexpr (NT) {
-        if (p->K == 1) {
-            launch_wide<1, SGD, GT, true>(GRAWA_CP_PASS);
-            return;
-        }
-        if constexpr (!SGD || sizeof(GT) == 2)
-            if (p->K == 2) {
-                launch_wide<2, SGD, GT, true>(GRAWA_CP_PASS);
-                return;
-            }
-    }
+        return hipGetLastError();
     switch (p->K) {
         GRAWA_CP_PLAIN(1) GRAWA_CP_PLAIN(2) GRAWA_CP_PLAIN(3) GRAWA_CP_PLAIN(4) GRAWA_CP_PLAIN(5) GRAWA_CP_PLAIN(6)
         GRAWA_CP_PLAIN(7) GRAWA_CP_PLAIN(8) GRAWA_CP_PLAIN(9) GRAWA_CP_PLAIN(10) GRAWA_CP_PLAIN(11) GRAWA_CP_PLAIN(12)
@@ -533,7 +526,7 @@ template <bool SGD, typename GT, bool NT> static void dispatch_cp(GRAWA_CP_ARGS)
     case 16:
         if constexpr (SGD) launch_plain<16, SGD, GT, NT, false>(GRAWA_CP_PASS);
         else launch_split<4, false, 4, 1, SGD, GT, NT>(GRAWA_CP_PASS);
-        return;
+        return hipGetLastError();
     }
     switch (p->K / 8) {
         GRAWA_CP_SPLIT(3) GRAWA_CP_SPLIT(4) GRAWA_CP_SPLIT(5) GRAWA_CP_SPLIT(6) GRAWA_CP_SPLIT(7) GRAWA_CP_SPLIT(8)
@@ -541,32 +534,32 @@ template <bool SGD, typename GT, bool NT> static void dispatch_cp(GRAWA_CP_ARGS)
     hipExtLaunchKernelGGL((k_center_pull_any<SGD, GT>), dim3((unsigned)p->n_cells), dim3(GRAWA_CELL), 0, s, e0, e1, 0, x,
                           ldx, (const GT *)g, ldg, lr, beta, GRAWA_CP_STRIDE, GRAWA_CP_CELLS,
                           (const int64_t *)p->d_off, p->L, p->K, p->P, lambda, center_out, rho, moving);
+    return hipGetLastError();
 #undef GRAWA_CP_PLAIN
 #undef GRAWA_CP_SPLIT
 }
 
-template <bool SGD, typename GT> static void dispatch_cp_wide(GRAWA_CP_ARGS)
+// Rows off the line grid (GRAWA_WIDE_COUNTS).  A worker count without a kernel is an error, never a call that does nothing.
+template <bool SGD, typename GT> static hipError_t dispatch_cp_wide(GRAWA_CP_ARGS)
 {
 #define GRAWA_CP_WIDE(N) \
-    case N: launch_wide<N, SGD, GT, false>(GRAWA_CP_PASS); return;
-    switch (p->K) { // wide_is_faster()
-        GRAWA_CP_WIDE(1) GRAWA_CP_WIDE(2) GRAWA_CP_WIDE(3) GRAWA_CP_WIDE(4) GRAWA_CP_WIDE(5) GRAWA_CP_WIDE(12) GRAWA_CP_WIDE(13)
-        GRAWA_CP_WIDE(14) GRAWA_CP_WIDE(15) GRAWA_CP_WIDE(16) GRAWA_CP_WIDE(17) GRAWA_CP_WIDE(18) GRAWA_CP_WIDE(19)
-        GRAWA_CP_WIDE(20) GRAWA_CP_WIDE(21) GRAWA_CP_WIDE(22) GRAWA_CP_WIDE(23)
+    case N: launch_wide<N, SGD, GT, false>(GRAWA_CP_PASS); return hipGetLastError();
+    switch (p->K) {
+        GRAWA_WIDE_COUNTS(GRAWA_CP_WIDE)
     }
+    return hipErrorInvalidValue;
 #undef GRAWA_CP_WIDE
 }
 
-// Weights straight from the tile sums: K <= 15 (grawa_pull_from_tiles), cached accesses.
-template <bool SGD, typename GT> static void dispatch_cp_tiles(GRAWA_CP_ARGS)
+// Weights straight from the tile sums (GRAWA_TILES_COUNTS), cached accesses.
+template <bool SGD, typename GT> static hipError_t dispatch_cp_tiles(GRAWA_CP_ARGS)
 {
 #define GRAWA_CP_TILES(N) \
-    case N: launch_plain<N, SGD, GT, false, true>(GRAWA_CP_PASS); return;
+    case N: launch_plain<N, SGD, GT, false, true>(GRAWA_CP_PASS); return hipGetLastError();
     switch (p->K) {
-        GRAWA_CP_TILES(1) GRAWA_CP_TILES(2) GRAWA_CP_TILES(3) GRAWA_CP_TILES(4) GRAWA_CP_TILES(5) GRAWA_CP_TILES(6)
-        GRAWA_CP_TILES(7) GRAWA_CP_TILES(8) GRAWA_CP_TILES(9) GRAWA_CP_TILES(10) GRAWA_CP_TILES(11) GRAWA_CP_TILES(12)
-        GRAWA_CP_TILES(13) GRAWA_CP_TILES(14) GRAWA_CP_TILES(15)
+        GRAWA_TILES_COUNTS(GRAWA_CP_TILES)
     }
+    return hipErrorInvalidValue;
 #undef GRAWA_CP_TILES
 }
 
@@ -587,19 +580,15 @@ hipError_t grawa_launch_center_pull(const grawa_plan *p, float *x, int64_t ldx, 
     const bool large = beta && (int64_t)p->K * p->P * 4 > GRAWA_STREAMING_MIN_BYTES;
     bool nt = large && rows_line_aligned(x, ldx, 4) && (!center_out || rows_line_aligned(center_out, 0, 4));
     if (fuse_sgd) nt = nt && rows_line_aligned(g_sgd, ldg_sgd, dt == GRAWA_BF16 ? 2 : 4);
-    const bool wide = large && !nt && wide_is_faster(p->K);
+    const bool wide = large && !nt && grawa_wide_has_kernel(p->K);
     const void *g = g_sgd;
     const int64_t ldg = ldg_sgd;
-#define GRAWA_CP_GO(SGD, GT)                                                 \
-    do {                                                                     \
-        if (!beta) dispatch_cp_tiles<SGD, GT>(GRAWA_CP_PASS);                \
-        else if (nt) dispatch_cp<SGD, GT, true>(GRAWA_CP_PASS);              \
-        else if (wide) dispatch_cp_wide<SGD, GT>(GRAWA_CP_PASS);             \
-        else dispatch_cp<SGD, GT, false>(GRAWA_CP_PASS);                     \
-    } while (0)
-    if (!fuse_sgd) GRAWA_CP_GO(false, float);
-    else if (dt == GRAWA_BF16) GRAWA_CP_GO(true, uint16_t);
-    else GRAWA_CP_GO(true, float);
+#define GRAWA_CP_GO(SGD, GT)                                                      \
+    (!beta  ? dispatch_cp_tiles<SGD, GT>(GRAWA_CP_PASS)                           \
+     : nt   ? dispatch_cp<SGD, GT, true>(GRAWA_CP_PASS)                           \
+     : wide ? dispatch_cp_wide<SGD, GT>(GRAWA_CP_PASS)                            \
+            : dispatch_cp<SGD, GT, false>(GRAWA_CP_PASS))
+    if (!fuse_sgd) return GRAWA_CP_GO(false, float);
+    return dt == GRAWA_BF16 ? GRAWA_CP_GO(true, uint16_t) : GRAWA_CP_GO(true, float);
 #undef GRAWA_CP_GO
-    return hipGetLastError();
 }

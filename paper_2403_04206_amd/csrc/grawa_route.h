@@ -19,6 +19,28 @@ static inline void grawa_split_grid(int64_t n_cells, unsigned *gx, unsigned *gy)
     *gx = (unsigned)((n_cells + rows - 1) / rows);
 }
 
+// The worker counts that have a kernel of the wide form, and of the form with the weights from the tile sums.  The rules
+// below and the dispatch (grawa_pull.hip) are made from the same lists.
+#define GRAWA_WIDE_COUNTS(X) \
+    X(1) X(2) X(3) X(4) X(5) X(12) X(13) X(14) X(15) X(16) X(17) X(18) X(19) X(20) X(21) X(22) X(23)
+#define GRAWA_TILES_COUNTS(X) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15)
+#define GRAWA_COUNT_TRUE(N) \
+    case N: return true;
+static inline bool grawa_wide_has_kernel(int K)
+{
+    switch (K) {
+        GRAWA_WIDE_COUNTS(GRAWA_COUNT_TRUE)
+    }
+    return false;
+}
+static inline bool grawa_tiles_has_kernel(int K)
+{
+    switch (K) {
+        GRAWA_TILES_COUNTS(GRAWA_COUNT_TRUE)
+    }
+    return false;
+}
+
 // Per-layer weights: worked out by every block of the pull for the layers of its own cell, or by a launch of their own.
 // The work in the pull grows with the blocks, with the tiles of the longest layer (with one layer, each of the blocks
 // adds all tiles of it) and with the workers; what it saves is one launch.  With fewer than 4 workers the lanes of a wave
@@ -28,11 +50,10 @@ static inline void grawa_split_grid(int64_t n_cells, unsigned *gx, unsigned *gy)
 // 10.2 / 8.6 and 10.9 / 8.6, 655 k 11.3 / 11.6 and 12.2 / 11.0; 15 workers, 175 k 11.4 / 10.0 and 13.9 / 13.1.
 // Without the launch the host saves 1 to 4 us of a call as well.  Slower from 4 x 1.2 M (20.3 / 20.8) and 16 x 600 k
 // (31.6 / 33.8) on.
-#define GRAWA_TILES_MAX_WORKERS 15
 #define GRAWA_TILES_MAX_CELLS 10240 // cells times workers
 static inline bool grawa_weights_in_pull(int K, int64_t n_cells)
 {
-    return K <= GRAWA_TILES_MAX_WORKERS && n_cells * (K < 4 ? 4 : K) <= GRAWA_TILES_MAX_CELLS;
+    return grawa_tiles_has_kernel(K) && n_cells * (K < 4 ? 4 : K) <= GRAWA_TILES_MAX_CELLS;
 }
 
 // Model-level weights: by the last block of the launch that forms the layer norms, or by a launch of its own.  The last

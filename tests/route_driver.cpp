@@ -1,6 +1,7 @@
 // Prints the launch shapes that the host-side rules of paper_2403_04206_amd/csrc/grawa_route.h give (no GPU toolchain).
 //   split <n_cells>...   -> per line: n_cells grid_x grid_y threads
 //   model <L>...         -> per line: L, 1 if the last block of the norms' launch forms the model-level weights
+//   counts <K>...        -> per line: K, 1 if the wide form has a kernel for it, 1 if the weights-in-the-pull form has
 //   tiles <K> <n_cells>... -> per pair: the pair, 1 if the pull forms the per-layer weights
 //   estimate <K> <L> <max_tiles> ... -> per triple: the triple, rows, threads
 #include <cstdio>
@@ -23,6 +24,11 @@ int main(int argc, char **argv)
     }
     if (!std::strcmp(argv[1], "model")) {
         for (int i = 2; i < argc; ++i) std::printf("%s %d\n", argv[i], grawa_model_weights_by_last_block(std::atoi(argv[i])));
+        return 0;
+    }
+    if (!std::strcmp(argv[1], "counts")) {
+        for (int i = 2; i < argc; ++i)
+            std::printf("%s %d %d\n", argv[i], grawa_wide_has_kernel(std::atoi(argv[i])), grawa_tiles_has_kernel(std::atoi(argv[i])));
         return 0;
     }
     if (!std::strcmp(argv[1], "tiles")) {

@@ -52,3 +52,19 @@ def test_weights_in_the_pull(driver):
     off = [(1, 2561), (1, 10240), (2, 2561), (2, 5120), (3, 2561), (4, 2561), (8, 1281), (15, 683), (16, 1)]
     assert all(r[2] == 1 for r in driver("tiles", *[v for c in on for v in c]))
     assert all(r[2] == 0 for r in driver("tiles", *[v for c in off for v in c]))
+
+
+def test_no_route_without_a_kernel(driver):
+    # the rules that send a call to the wide or the weights-in-the-pull form know no other counts than their dispatch
+    have = {k: (wide, tiles) for k, wide, tiles in driver("counts", *range(1, 1025))}
+    assert [k for k in have if have[k][0]] == [1, 2, 3, 4, 5] + list(range(12, 24))
+    assert [k for k in have if have[k][1]] == list(range(1, 16))
+    assert all(r[2] == have[r[0]][1] for r in driver("tiles", *[v for k in range(1, 1025) for v in (k, 1)]))
+
+
+def test_a_missing_kernel_is_an_error():
+    src = open(os.path.join(ROOT, "paper_2403_04206_amd", "csrc", "grawa_pull.hip")).read()
+    for name, counts in (("dispatch_cp_wide", "GRAWA_WIDE_COUNTS"), ("dispatch_cp_tiles", "GRAWA_TILES_COUNTS")):
+        body = src[src.index("static hipError_t %s(" % name):]
+        body = body[:body.index("\n}\n")]
+        assert counts in body and "return hipErrorInvalidValue;" in body
