@@ -197,9 +197,21 @@ def test_leader_rule(losses, leader):
     K = len(losses)
     w, x, _ = W.make_small(2500, K, [300], device=DEV)
     lead = torch.full((1,), -1, dtype=torch.int32, device=DEV)
-    for pad in (0, 70):                                  # with 70 more workers: several per lane
+    for pad in (0, 1, 5, 6, 13, 61, 70):                 # more workers: to either side of a scan by every lane; several per lane
         ls = torch.tensor(losses + [float("inf")] * pad, device=DEV)
         w, x, _ = W.make_small(2500, K + pad, [300], device=DEV)
         with grawa.Plan(K + pad, 300, w.offsets) as plan:
             plan.lsgd_update(x[:, :300], ls, 0.3, leader_out=lead)
         assert int(lead.item()) == leader
+
+
+@pytest.mark.parametrize("K", [1, 2, 3, 4, 5, 8, 9, 33, 63, 64, 65, 200])
+def test_leader_at_every_place(K):
+    w, x, _ = W.make_small(2550, K, [40], device=DEV)
+    lead = torch.full((K,), -1, dtype=torch.int32, device=DEV)
+    with grawa.Plan(K, 40, w.offsets) as plan:
+        for k in range(K):
+            ls = torch.rand(K, device=DEV) + 1.0
+            ls[k:] = 0.5                                 # the first of the smallest
+            plan.lsgd_update(x.clone()[:, :40], ls, 0.3, leader_out=lead[k:k + 1])
+    assert lead.cpu().tolist() == list(range(K))
