@@ -89,10 +89,17 @@ def _check(status: int, where: str):
         raise GrawaError(status, where)
 
 
+# The handle of torch's current stream without making a Stream object (2.9 us).  Neither function is public: where torch
+# does not have them, the Stream object it is.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream=None):
-    if stream is None:  # the handle of torch's current stream, without making a Stream object (2.9 us); the calls
-        # that come here hold CUDA tensors, so torch's CUDA state is set up
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if stream is None:
+        if _raw_stream is not None and _raw_device is not None:  # the calls that come here hold CUDA tensors, so torch's
+            return _raw_stream(_raw_device())                    # CUDA state is set up
+        stream = torch.cuda.current_stream()
     return C.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
 
 

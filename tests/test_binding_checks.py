@@ -164,3 +164,17 @@ def test_planless_steps_check_their_shapes(plan):
         grawa.lgrawa_update_static(x, g, torch.zeros(L + 1, dtype=torch.int32), 0.1)    # offsets must be int64
     with pytest.raises(ValueError):
         grawa.lgrawa_update_static(x, g, torch.zeros(L + 1, dtype=torch.int64), 0.1, weights_out=torch.zeros((K, L + 1)))
+
+
+def test_current_stream_with_and_without_the_private_functions(monkeypatch):
+    class Stream:
+        cuda_stream = 7
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream())
+    monkeypatch.setattr(grawa, "_raw_device", lambda: 2)
+    monkeypatch.setattr(grawa, "_raw_stream", lambda device: 40 + device)
+    assert grawa._stream() == 42
+    for name in ("_raw_stream", "_raw_device"):
+        with monkeypatch.context() as m:
+            m.setattr(grawa, name, None)
+            assert grawa._stream().value == 7
+    assert grawa._stream(Stream()).value == 7 and grawa._stream(9).value == 9
