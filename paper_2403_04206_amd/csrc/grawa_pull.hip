@@ -21,6 +21,75 @@ __device__ __forceinline__ int layer_of(const int64_t *__restrict__ off, int lay
     return layer;
 }
 
+// The layers of V adjacent columns from `col` on; the start of the next layer is loaded only where a column reaches it.
+// Columns past the row get the layer of its last column (their weights are loaded and not used).
+template <int V>
+__device__ __forceinline__ void layers_of(const int64_t *__restrict__ off, int layer, int L, int64_t col, int64_t P,
+                                          int (&layers)[V])
+{
+    int64_t next = layer + 1 < L ? off[layer + 1] : P;
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+        const int64_t i = col + e < P ? col + e : P - 1;
+        while (layer + 1 < L && next <= i) {
+            ++layer;
+            next = layer + 1 < L ? off[layer + 1] : P;
+        }
+        layers[e] = layer;
+    }
+}
+
+// Center of the V columns from `col` of a cell that holds layer boundaries, over R rows of v (rows for which has(k) is
+// false excepted), weights beta[k * stride + layer].  c must be 0.  A cell of few layers goes through them one by one, the
+// weights by scalar loads, and every column keeps the sum of its own layer; with more layers every column fetches its own
+// weights, all of them loaded before one is used.  (Every column fetching its own, one after the other: pull of 4 rows of
+// 10 M columns off the line grid, 3000 layers 52.6 -> 73.4 us against the one-column form, 100 000 layers 60.3 -> 129;
+// now 58 and 69, which is what streaming a 160 MB array that was in the cache costs: 30 M columns 168 -> 166 and 198 -> 197.)  Lanes past the row take part and are not used.
+#define GRAWA_FEW_LAYERS 8
+template <int R, int V, bool FEW, typename Has>
+__device__ __forceinline__ void center_by_layer(const float *beta, int64_t stride, const int64_t *__restrict__ off, int L,
+                                                int64_t P, int64_t cell0, int first, int64_t col, const Has &has,
+                                                const typename FloatVec<V>::T (&v)[R], typename FloatVec<V>::T &c)
+{
+    const int64_t end = cell0 + GRAWA_CELL < P ? cell0 + GRAWA_CELL : P;
+    const int l0 = __builtin_amdgcn_readfirstlane(first);
+    const __attribute__((address_space(4))) int64_t *starts = (const __attribute__((address_space(4))) int64_t *)uniform_base(off);
+    if (FEW && (l0 + GRAWA_FEW_LAYERS >= L || starts[l0 + GRAWA_FEW_LAYERS] >= end)) {
+        int64_t start = cell0;
+        for (int l = l0;; ++l) {
+            const uint64_t bb = uniform_base(beta + l);
+            typename FloatVec<V>::T t = typename FloatVec<V>::T{};
+#pragma unroll
+            for (int k = 0; k < R; ++k)
+                if (has(k)) {
+                    const float w = ld_uniform_f32(bb, (int64_t)k * stride);
+#pragma unroll
+                    for (int e = 0; e < V; ++e) vec_set<V>(t, e, fmaf(w, vec_get<V>(v[k], e), vec_get<V>(t, e)));
+                }
+#pragma unroll
+            for (int e = 0; e < V; ++e)
+                if (col + e >= start) vec_set<V>(c, e, vec_get<V>(t, e));
+            if (l + 1 >= L) break;
+            start = starts[l + 1];
+            if (start >= end) break;
+        }
+        return;
+    }
+    int layers[V];
+    layers_of<V>(off, l0, L, col, P, layers);
+    float w[R][V];
+#pragma unroll
+    for (int k = 0; k < R; ++k)
+#pragma unroll
+        for (int e = 0; e < V; ++e) w[k][e] = has(k) ? beta[(int64_t)k * stride + layers[e]] : 0.f;
+#pragma unroll
+    for (int k = 0; k < R; ++k)
+        if (has(k)) {
+#pragma unroll
+            for (int e = 0; e < V; ++e) vec_set<V>(c, e, fmaf(w[k][e], vec_get<V>(v[k], e), vec_get<V>(c, e)));
+        }
+}
+
 // Per-layer weights straight from the tile sums of the norm pass, computed by every block for the layers of its own
 // cell (TILES).  A small update is a chain of short launches, and this one drops a link: for 270 k parameters and
 // 4 workers the weights as a launch of their own took 4.0 us plus the boundary.  The loads of x are in flight
@@ -229,16 +298,8 @@ __global__ __launch_bounds__(GRAWA_BLOCK) __attribute__((amdgpu_waves_per_eu(1, 
 #pragma unroll
             for (int e = 0; e < V; ++e) vec_set<V>(c, e, fmaf(w, vec_get<V>(v[k], e), vec_get<V>(c, e)));
         }
-    } else { // the cell holds a layer boundary: each column looks up its own layer
-#pragma unroll
-        for (int e = 0; e < V; ++e)
-            if (e < n) {
-                const float *b = beta + layer_of(off, ~info, L, col + e);
-                float t = 0.f;
-#pragma unroll
-                for (int k = 0; k < K; ++k) t = fmaf(b[(int64_t)k * beta_stride], vec_get<V>(v[k], e), t);
-                vec_set<V>(c, e, t);
-            }
+    } else { // the cell holds a layer boundary
+        center_by_layer<K, V, true>(beta, beta_stride, off, L, P, cell0, ~info, col, [](int) { return true; }, v, c);
     }
     if (moving) {
 #pragma unroll
@@ -359,17 +420,9 @@ __global__ __launch_bounds__(S *GRAWA_CELL / V) void k_center_pull_split(
 #pragma unroll
                 for (int e = 0; e < V; ++e) vec_set<V>(c, e, fmaf(w, vec_get<V>(v[k], e), vec_get<V>(c, e)));
             }
-    } else { // the cell holds a layer boundary: each column looks up its own layer
-#pragma unroll
-        for (int e = 0; e < V; ++e)
-            if (e < n) {
-                const float *b = beta + layer_of(off, ~info, L, col + e) + (int64_t)k0 * beta_stride;
-                float t = 0.f;
-#pragma unroll
-                for (int k = 0; k < R; ++k)
-                    if (k < Q || more) t = fmaf(b[(int64_t)k * beta_stride], vec_get<V>(v[k], e), t);
-                vec_set<V>(c, e, t);
-            }
+    } else { // the cell holds a layer boundary
+        center_by_layer<R, V, false>(beta + (int64_t)k0 * beta_stride, beta_stride, off, L, P, cell0, ~info, col,
+                              [&](int k) { return k < Q || more; }, v, c);
     }
     __shared__ XV part[S][LANES];
     part[group][lane] = c;

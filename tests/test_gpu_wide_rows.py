@@ -13,6 +13,36 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
+@pytest.mark.parametrize("K,pad", [(1, 0), (2, 8), (4, 8), (16, 8)])
+def test_wide_form_with_layers_in_every_cell(K, pad):
+    # cells of 2, 8, 9 and 256 layers and one that ends with the row: weights by scalar loads, and by column
+    P = (140 << 20) // (4 * K) // 256 * 256 + 129
+    sizes = [100, 412] + [32] * 8 + [29] * 8 + [24] + [1] * 256 + [7] * 500 + [300] * 2000
+    sizes += [P - sum(sizes) - 130, 120, 10]
+    off = torch.tensor([0] + sizes).cumsum(0).tolist()
+    L = len(sizes)
+    gen = torch.Generator(device=DEV).manual_seed(K)
+    x = torch.empty((K, W.round_up(P, 256) + pad), device=DEV).normal_(0.0, 0.05, generator=gen)
+    x0 = x.clone()
+    beta = torch.rand((K, L), device=DEV, generator=gen)
+    cen = torch.empty(W.round_up(P, 4), device=DEV)
+    with grawa.Plan(K, P, off) as plan:
+        plan.center_pull(x[:, :P], beta, 0.25, center_out=cen)
+        torch.cuda.synchronize()
+    layer = torch.repeat_interleave(torch.arange(L, device=DEV), torch.tensor(sizes, device=DEV))
+    c = torch.zeros(P, dtype=torch.float64, device=DEV)
+    for k in range(K):
+        c += beta[k].double()[layer] * x0[k, :P].double()
+    # K products and sums of magnitude at most max|x| sum(beta), each rounded to 24 bits, and the pull
+    bound = (K + 3) * 2.0 ** -24 * float(x0.abs().max()) * (1.0 + K)
+    assert float((cen[:P].double() - c).abs().max()) <= bound
+    for k in range(K):
+        xd = x0[k, :P].double()
+        assert float((x[k, :P].double() - (xd + 0.25 * (c - xd))).abs().max()) <= bound
+    assert torch.equal(x[:, P:], x0[:, P:])
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("K,dtype,fused,tail,pad", [(1, "f32", False, 3, 8), (2, "f32", False, 1, 8), (5, "bf16", True, 3, 8),
                                                     (6, "f32", False, 2, 8), (12, "f32", True, 0, 8), (23, "bf16", False, 2, 8),
                                                     (23, "f32", True, 1, 8), (24, "f32", False, 1, 8), (1, "bf16", True, 1, 0),
