@@ -156,7 +156,7 @@ template <int K> __device__ __forceinline__ int cell_layer_of(const CellWeights<
     return i;
 }
 
-// Plain form, K <= 23 (16 without the SGD step excepted).  grid ceil(P/256), block 256: a lane owns one
+// Plain form, K <= 23 (16 without the SGD step excepted), on few cells to 32 (grawa_plain_form).  grid ceil(P/256), block 256: a lane owns one
 // column.  It loads x[k][i] for its K workers (all loads in flight together; with SGD also g[k][i] and
 // applies x - lr g), forms c = sum_k beta_k x_k and writes x_k + lambda (c - x_k) back, so every
 // parameter is read once and written once.  A wave touches one 256-byte piece per row.
@@ -555,8 +555,8 @@ template <int Q, bool REM, int S, int V, bool SGD, typename GT, bool NT> static 
                           center_out, rho, moving);
 }
 
-// One plain kernel per worker count up to 23 (fully unrolled); 24..71 workers share the row-split
-// kernels by K / 8; beyond that the two-sweep kernel.
+// One plain kernel per worker count up to 23, on few cells up to 32 (fully unrolled); the rest up to 71 workers share the
+// row-split kernels by K / 8; beyond that the two-sweep kernel.
 template <bool SGD, typename GT, bool NT> static hipError_t dispatch_cp(GRAWA_CP_ARGS)
 {
     // Line-aligned streaming rows of one worker, and of two unless fused with fp32 gradients: the wide form.
@@ -581,6 +581,11 @@ template <bool SGD, typename GT, bool NT> static hipError_t dispatch_cp(GRAWA_CP
         else launch_split<4, false, 4, 1, SGD, GT, NT>(GRAWA_CP_PASS);
         return hipGetLastError();
     }
+    if constexpr (!NT) // never as large as the streaming passes
+        if (grawa_plain_form(p->K, p->n_cells)) switch (p->K) {
+                GRAWA_CP_PLAIN(24) GRAWA_CP_PLAIN(25) GRAWA_CP_PLAIN(26) GRAWA_CP_PLAIN(27) GRAWA_CP_PLAIN(28)
+                GRAWA_CP_PLAIN(29) GRAWA_CP_PLAIN(30) GRAWA_CP_PLAIN(31) GRAWA_CP_PLAIN(32)
+            }
     switch (p->K / 8) {
         GRAWA_CP_SPLIT(3) GRAWA_CP_SPLIT(4) GRAWA_CP_SPLIT(5) GRAWA_CP_SPLIT(6) GRAWA_CP_SPLIT(7) GRAWA_CP_SPLIT(8)
     }

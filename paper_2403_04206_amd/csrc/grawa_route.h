@@ -56,6 +56,19 @@ static inline bool grawa_weights_in_pull(int K, int64_t n_cells)
     return grawa_tiles_has_kernel(K) && n_cells * (K < 4 ? 4 : K) <= GRAWA_TILES_MAX_CELLS;
 }
 
+// The one-column-per-lane (plain) form serves up to 23 workers, and up to 32 on few cells: there a block of the row-split form,
+// with its barrier and four times the threads, is the longer chain.  Split against plain, time of the pull by per-layer
+// weights, 24 / 28 / 32 workers, 1 layer, 40 layers and 500: 5 k columns 1.04 1.16 1.30 / 1.07 1.21 1.29 / 1.00 1.18 1.31,
+// 105 k 1.09 1.17 1.30 / 1.10 1.20 1.30 / 1.06 1.15 1.30, 200 k 1.10 1.07 1.14 / 1.11 1.10 1.16 / 1.07 1.01 1.10,
+// 300 k 1.07 1.02 1.05 / 1.03 0.96 0.96 / 0.98 0.92 0.92, 1 M 1.01 0.98 0.92 / 1.01 0.99 0.94 / 1.00 0.99 0.96.
+#define GRAWA_PLAIN_MAX_WORKERS 23
+#define GRAWA_PLAIN_FEW_CELLS 1024
+#define GRAWA_PLAIN_FEW_CELLS_MAX_WORKERS 32
+static inline bool grawa_plain_form(int K, int64_t n_cells)
+{
+    return K <= (n_cells <= GRAWA_PLAIN_FEW_CELLS ? GRAWA_PLAIN_FEW_CELLS_MAX_WORKERS : GRAWA_PLAIN_MAX_WORKERS);
+}
+
 // Model-level weights: by the last block of the launch that forms the layer norms, or by a launch of its own.  The last
 // block saves the host a launch (a call of 4 workers that is host-bound: 17 us for 21) and the device nothing; every
 // layer's arrival and every norm handed over cost, so that from about 100 layers on the device loses.  Whole update

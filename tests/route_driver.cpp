@@ -2,6 +2,7 @@
 //   split <n_cells>...   -> per line: n_cells grid_x grid_y threads
 //   model <L>...         -> per line: L, 1 if the last block of the norms' launch forms the model-level weights
 //   counts <K>...        -> per line: K, 1 if the wide form has a kernel for it, 1 if the weights-in-the-pull form has
+//   plain <K> <n_cells>... -> per pair: the pair, 1 if the one-column-per-lane form serves it
 //   tiles <K> <n_cells>... -> per pair: the pair, 1 if the pull forms the per-layer weights
 //   estimate <K> <L> <max_tiles> ... -> per triple: the triple, rows, threads
 #include <cstdio>
@@ -29,6 +30,11 @@ int main(int argc, char **argv)
     if (!std::strcmp(argv[1], "counts")) {
         for (int i = 2; i < argc; ++i)
             std::printf("%s %d %d\n", argv[i], grawa_wide_has_kernel(std::atoi(argv[i])), grawa_tiles_has_kernel(std::atoi(argv[i])));
+        return 0;
+    }
+    if (!std::strcmp(argv[1], "plain")) {
+        for (int i = 2; i + 1 < argc; i += 2)
+            std::printf("%s %s %d\n", argv[i], argv[i + 1], grawa_plain_form(std::atoi(argv[i]), std::atoll(argv[i + 1])));
         return 0;
     }
     if (!std::strcmp(argv[1], "tiles")) {

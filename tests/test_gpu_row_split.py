@@ -24,6 +24,21 @@ def test_row_split_worker_counts(K, dtype, ld_pad):
     run_variant(w, x, g, "lgrawa", 0.25, fused=True, lr=0.1)
 
 
+@pytest.mark.parametrize("K", [24, 25, 31, 32, 33, 40])
+@pytest.mark.parametrize("cells", [1024, 1025])
+def test_either_side_of_few_cells(K, cells):
+    # up to 1024 cells the plain form serves up to 32 workers; cells with one, two, a few and many layers
+    P = cells * 256 - 3
+    many = [5] * 100 + [1] * 30
+    sizes = [P // 2] + many + [P - P // 2 - sum(many) - 2000, 2000]
+    w, x, g = W.make_small(1500 + K, K, sizes, device=DEV)
+    run_variant(w, x, g, "lgrawa", 0.3)
+    run_variant(w, x, g, "mgrawa", 0.3)
+    _, _, gb = W.make_small(1600 + K, K, sizes, grad_dtype="bf16", device=DEV)
+    wb = W.Workload("bf16", K, sizes, grad_dtype="bf16", seed=(7, K))
+    run_variant(wb, x, gb, "lgrawa", 0.25, fused=True, lr=0.1)
+
+
 @pytest.mark.parametrize("K,dtype,fused", [(24, "f32", False), (43, "bf16", True), (33, "f32", True)])
 def test_row_split_streaming(K, dtype, fused):
     # arrays over 512 MB on line-aligned rows: the streaming instantiations

@@ -62,6 +62,12 @@ def test_no_route_without_a_kernel(driver):
     assert all(r[2] == have[r[0]][1] for r in driver("tiles", *[v for k in range(1, 1025) for v in (k, 1)]))
 
 
+def test_plain_form_counts(driver):
+    # each count the rule names has a kernel: 1..15 and 17..32 (16 has its own form), and 32 only on few cells
+    rows = driver("plain", *[v for k in (1, 23, 24, 32, 33, 64) for n in (1, 1024, 1025, 1 << 24) for v in (k, n)])
+    assert [r[2] for r in rows] == [1] * 8 + [1, 1, 0, 0] * 2 + [0] * 8
+
+
 def test_a_missing_kernel_is_an_error():
     src = open(os.path.join(ROOT, "paper_2403_04206_amd", "csrc", "grawa_pull.hip")).read()
     for name, counts in (("dispatch_cp_wide", "GRAWA_WIDE_COUNTS"), ("dispatch_cp_tiles", "GRAWA_TILES_COUNTS")):
