@@ -19,7 +19,7 @@ struct GrawaTile {
 
 #define GRAWA_ROW_TILE 1024 // columns per tile of the scored local step
 #define GRAWA_CELL_COLS 256 // columns per cell of the center+pull pass
-#define GRAWA_MAX_TILES ((int64_t)1 << 24) // tiles or cells: keeps grid.x * 256 below 2^32 (larger blocks: grawa_route.h)
+#define GRAWA_MAX_TILES ((int64_t)1 << 24) // tiles or cells: keeps grid.x * 256 below 2^32 (larger blocks: grawa_split_blocks)
 
 struct GrawaHostMaps {
     std::vector<GrawaTile> tiles;       // norm pass: layers cut at the multiples of tile_elems

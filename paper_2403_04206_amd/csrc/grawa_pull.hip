@@ -329,8 +329,8 @@ __global__ __launch_bounds__(GRAWA_BLOCK) __attribute__((amdgpu_waves_per_eu(1, 
     }
 }
 
-// Row-split form: the rows of a 256-column cell are divided over S groups of waves.  grid: one block per cell, in rows
-// of blocks (grawa_split_grid), block S * 256 / V.  A lane owns V adjacent columns of its group's rows: Q of them, and one more for the
+// Row-split form: the rows of a 256-column cell are divided over S groups of waves.  grid: one block per cell from
+// first_cell on (grawa_split_blocks), block S * 256 / V.  A lane owns V adjacent columns of its group's rows: Q of them, and one more for the
 // first K - S Q groups when REM (K is then S Q + 1 .. S Q + S - 1).  Each group forms its part of the
 // center, the parts are added in group order through LDS, every group pulls and stores its own rows.  A
 // wave touches one piece of 256 V bytes per row, the block starts its loads, and after the barrier its
@@ -347,16 +347,15 @@ __global__ __launch_bounds__(S *GRAWA_CELL / V) void k_center_pull_split(
     float *__restrict__ x, int64_t ldx, const GT *__restrict__ g, int64_t ldg, float lr,
     const float *__restrict__ beta, int64_t beta_stride, const int32_t *__restrict__ cell_layer,
     const int64_t *__restrict__ off, int L, int K, int64_t P, float lambda,
-    float *__restrict__ center_out, float rho, int moving)
+    float *__restrict__ center_out, float rho, int moving, unsigned first_cell)
 {
     typedef typename FloatVec<V>::T XV;
     constexpr int LANES = GRAWA_CELL / V; // lanes of a group
     constexpr int R = REM ? Q + 1 : Q;    // register slots per lane
     static_assert(LANES % GRAWA_WAVE == 0, "a group is made of whole waves");
     static_assert(S * LANES == GRAWA_SPLIT_THREADS, "the grid is chosen for this many threads");
-    const int64_t cell = (int64_t)blockIdx.y * gridDim.x + blockIdx.x; // wave-uniform
-    const int64_t cell0 = cell * GRAWA_CELL;
-    if (cell0 >= P) return; // past the last cell (whole block leaves, before any barrier)
+    const unsigned cell = first_cell + blockIdx.x; // wave-uniform; below 2^24
+    const int64_t cell0 = (int64_t)cell * GRAWA_CELL;
     const int group = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / LANES)); // wave-uniform
     const unsigned lane = threadIdx.x % LANES;
     const int rem = REM ? K - S * Q : 0;
@@ -547,12 +546,14 @@ template <int K, bool SGD, typename GT, bool LNT> static void launch_wide(GRAWA_
 
 template <int Q, bool REM, int S, int V, bool SGD, typename GT, bool NT> static void launch_split(GRAWA_CP_ARGS)
 {
-    unsigned gx, gy;
-    grawa_split_grid(p->n_cells, &gx, &gy);
-    hipExtLaunchKernelGGL((k_center_pull_split<Q, REM, S, V, SGD, GT, NT>), dim3(gx, gy),
-                          dim3(GRAWA_SPLIT_THREADS), 0, s, e0, e1, 0, x, ldx, (const GT *)g, ldg, lr, beta,
-                          GRAWA_CP_STRIDE, GRAWA_CP_CELLS, (const int64_t *)p->d_off, p->L, p->K, p->P, lambda,
-                          center_out, rho, moving);
+    for (int64_t at = 0; at < p->n_cells;) { // one launch but for the longest rows
+        const int64_t n = grawa_split_blocks(p->n_cells, at);
+        hipExtLaunchKernelGGL((k_center_pull_split<Q, REM, S, V, SGD, GT, NT>), dim3((unsigned)n),
+                              dim3(GRAWA_SPLIT_THREADS), 0, s, at == 0 ? e0 : nullptr, at + n == p->n_cells ? e1 : nullptr, 0,
+                              x, ldx, (const GT *)g, ldg, lr, beta, GRAWA_CP_STRIDE, GRAWA_CP_CELLS,
+                              (const int64_t *)p->d_off, p->L, p->K, p->P, lambda, center_out, rho, moving, (unsigned)at);
+        at += n;
+    }
 }
 
 // One plain kernel per worker count up to 23, on few cells up to 32 (fully unrolled); the rest up to 71 workers share the

@@ -1,5 +1,5 @@
 // Prints the launch shapes that the host-side rules of paper_2403_04206_amd/csrc/grawa_route.h give (no GPU toolchain).
-//   split <n_cells>...   -> per line: n_cells grid_x grid_y threads
+//   split <n_cells>...   -> per launch: n_cells, first cell, blocks, threads
 //   model <L>...         -> per line: L, 1 if the last block of the norms' launch forms the model-level weights
 //   counts <K>...        -> per line: K, 1 if the wide form has a kernel for it, 1 if the weights-in-the-pull form has
 //   plain <K> <n_cells>... -> per pair: the pair, 1 if the one-column-per-lane form serves it
@@ -16,10 +16,9 @@ int main(int argc, char **argv)
     if (argc < 2) return 2;
     if (!std::strcmp(argv[1], "split")) {
         for (int i = 2; i < argc; ++i) {
-            const long long n = std::atoll(argv[i]);
-            unsigned gx = 0, gy = 0;
-            grawa_split_grid(n, &gx, &gy);
-            std::printf("%lld %u %u %d\n", n, gx, gy, GRAWA_SPLIT_THREADS);
+            const int64_t n = std::atoll(argv[i]);
+            for (int64_t at = 0; at < n; at += grawa_split_blocks(n, at))
+                std::printf("%lld %lld %lld %d\n", (long long)n, (long long)at, (long long)grawa_split_blocks(n, at), GRAWA_SPLIT_THREADS);
         }
         return 0;
     }

@@ -50,9 +50,8 @@ def test_row_split_streaming(K, dtype, fused):
 
 
 @pytest.mark.parametrize("K", [16, 24])
-def test_row_split_second_row_of_blocks(K):
-    # 2^18 cells are one row of blocks; one column more starts a second row, whose last block holds no cell when their
-    # number is odd.  The caller's weights, so that x is the only large array.
+def test_row_split_second_launch(K):
+    # 2^18 cells are one launch; one column more starts a second.  The caller's weights, so that x is the only large array.
     for P in ((1 << 26) + 1, (1 << 26) + 256 + 1):
         x = torch.empty((K, W.round_up(P, 256)), device=DEV).normal_(0.0, 0.05, generator=torch.Generator(device=DEV).manual_seed(K))
         x0 = x.clone()

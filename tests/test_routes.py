@@ -24,11 +24,15 @@ def driver(tmp_path_factory):
 
 def test_row_split_grid_within_the_launch_limit(driver):
     P = [1, 256, 257, (1 << 26) - 1, 1 << 26, (1 << 26) + 1, (1 << 30) - 256, 1 << 30, (1 << 30) + 1, (1 << 31) + 5, (1 << 32) - 512]
-    cells = [(p + 255) // 256 for p in P]
-    for n, gx, gy, threads in driver("split", *cells):
-        assert gx * threads < 1 << 32 and gy < 1 << 16
-        assert n <= gx * gy < n + gy                     # every cell, and less than one block per row for nothing
-        assert gy == 1 or n > 1 << 18
+    cells = sorted({(p + 255) // 256 for p in P})
+    rows = driver("split", *cells)
+    for n in cells:
+        launches = [r for r in rows if r[0] == n]
+        assert all(blocks >= 1 and blocks * threads < 1 << 32 for _, _, blocks, threads in launches)
+        assert [r[1] for r in launches] == [sum(r[2] for r in launches[:i]) for i in range(len(launches))]   # no gap
+        assert sum(r[2] for r in launches) == n          # every cell once
+        assert len(launches) == 1 or n > 1 << 18
+
 
 
 def test_no_arrivals_with_many_layers(driver):
