@@ -9,7 +9,8 @@
 //
 // The norm pass is a read-only stream: it runs fastest with several non-temporal loads per
 // lane in flight and a capped occupancy.  Squares and sums are fp64 throughout, added in a
-// fixed order (no atomics), so results are bit-reproducible.
+// fixed order (no sum is formed by atomics; how norms pass between the blocks of a launch: grawa_scores.h),
+// so results are bit-reproducible.
 #include "grawa_route.h"
 #include "grawa_scores.h"
 
@@ -89,8 +90,9 @@ __global__ __launch_bounds__(GRAWA_BLOCK) __attribute__((amdgpu_waves_per_eu(1, 
 #pragma unroll
         for (int u = 0; u < GRAWA_SUMSQ_U; ++u) acc[u] = Grad<GT>::sumsq8(q[u], acc[u]);
     }
-    // What is left is less than a trip: a trip of as few loads as hold it (block-uniform), so that a short tile does
-    // not load, convert and discard values.
+    // What is left is less than a trip: a trip of as few loads as hold it, so that a short tile does not load, convert and
+    // discard values.  (All lanes of a block take the same one, except that with more than 7 loads left the lanes that
+    // have all 8 took them as a full trip above and have nothing left.)
     const int left = nvec - (j0 - tid);
     if (left > 4 * GRAWA_BLOCK) sumsq_rest<GT, 8>(body, j0, nvec, acc);
     else if (left > 2 * GRAWA_BLOCK) sumsq_rest<GT, 4>(body, j0, nvec, acc);

@@ -168,9 +168,8 @@ template <int K> __device__ __forceinline__ int cell_layer_of(const CellWeights<
 // The pull is x + lambda (c - x), one fma, which leaves a single worker exactly unchanged.
 // moving != 0 (EASGD, Appendix F): center_out holds the previous center c0 on entry and the
 // center used and stored is c0 + rho (c - c0).
-// WPE caps the waves per SIMD: the form is fastest with roughly 32-48 row loads in flight per
-// SIMD (K x WPE); more only queues requests to K far-apart rows and costs DRAM efficiency
-// (measured: K = 16 at 3 waves 6.1 TB/s, at 8 waves 5.7; K = 8 at 4 waves 6.5, at 8 waves 6.2).
+// WPE caps the waves per SIMD (grawa_waves_for): more only queues requests to K far-apart rows and costs DRAM
+// efficiency (measured: K = 16 at 3 waves 6.1 TB/s, at 8 waves 5.7; K = 8 at 4 waves 6.5, at 8 waves 6.2).
 template <int K, bool SGD, typename GT, bool NT, int WPE, bool TILES>
 __global__ __launch_bounds__(GRAWA_CELL) __attribute__((amdgpu_waves_per_eu(1, WPE))) void k_center_pull(
     float *__restrict__ x, int64_t ldx, const GT *__restrict__ g, int64_t ldg, float lr,
@@ -233,10 +232,14 @@ __global__ __launch_bounds__(GRAWA_CELL) __attribute__((amdgpu_waves_per_eu(1, W
 // with another block; loads cached, so that the lines the waves of a block share are fetched once; stores streaming.
 // Otherwise as the plain form; a wave's 256 columns are one cell.  With streaming loads (LNT) the form also serves
 // line-aligned rows of one or two workers, where a 4-byte load per row and lane leaves too little in flight: K = 1
-// 3.64 -> 6.69 TB/s, K = 2 5.71 -> 6.64, with the SGD step on bf16 gradients 5.77 -> 6.46.  Off the line grid: measured on 1.2 to 2 GB of random values, pitch
-// 16 bytes off a line, TB/s, plain form / this one (WPE in grawa_waves_wide): K = 2 5.46/6.27, 3 5.73/6.26, 4 5.71/5.96,
+// 3.64 -> 6.69 TB/s, K = 2 5.71 -> 6.64, with the SGD step on bf16 gradients 5.77 -> 6.46.
+// Off the line grid: measured on 1.2 to 2 GB of random values, pitch 16 bytes off a line, TB/s, plain form / this one (WPE in grawa_waves_wide): K = 2 5.46/6.27, 3 5.73/6.26, 4 5.71/5.96,
 // 6 5.53/5.52, 8 5.39/5.35, 10 5.36/5.25, 12 4.94/5.29, 16 4.86/5.45, 20 4.68/5.48; with the SGD step 2 5.60/6.28,
 // 4 5.69/5.97, 8 5.52/5.45, 12 5.29/5.58, 16 5.35/5.67; bf16 gradients 4 5.34/6.08, 16 5.16/5.48.
+// These are passes in a row over several arrays.  The plain form's cached stores leave up to 256 MB in the last-level
+// cache, which a later pass has to write back; after a read of other memory a single pass of it looks faster than it is.
+// One LGRAWA update, and a read of 1 GB after it, plain / wide: 4 workers, 75 M columns 597 / 613 and 313 / 277 us,
+// 12 workers, 25.6 M 624 / 632 and 310 / 277, 16 workers, 18 M 591 / 593 and 313 / 275, 23 workers, 13 M 654 / 635 and 314 / 276.
 template <int K, bool SGD, typename GT, bool LNT, int WPE>
 __global__ __launch_bounds__(GRAWA_BLOCK) __attribute__((amdgpu_waves_per_eu(1, WPE))) void k_center_pull_wide(
     float *__restrict__ x, int64_t ldx, const GT *__restrict__ g, int64_t ldg, float lr,

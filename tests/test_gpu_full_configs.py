@@ -1,5 +1,5 @@
 """GPU parity at the full benchmark sizes (configurations 1-4), in the launch configuration
-the benchmark times (streaming accesses above 512 MB, i.e. configurations 2-4).
+the benchmark times (streaming accesses of the pull above 128 MB of parameters, i.e. all four).
 
 The norm and weight tables are compared in full (the CPU reference streams every gradient
 element), and so are the pulled parameters and the center: EVERY element of x (K x P) and of the

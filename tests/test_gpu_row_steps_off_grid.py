@@ -1,4 +1,5 @@
-"""GPU parity of the row-by-row local steps on arrays beyond the caches, on line-aligned rows and on rows that are not:
+"""GPU parity of the row-by-row local steps on arrays beyond the caches, on line-aligned rows and on rows that are not,
+every element of them:
 steps with and without the center and the scores, the Nesterov step; odd row ends, a layer boundary inside a block."""
 import numpy as np
 import pytest
@@ -10,7 +11,7 @@ from parity_util import TIGHT, assert_params_close, assert_table_close, grads_to
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
-COLS = 1 << 16                                           # columns compared at each end and around the boundary
+COLS = 1 << 16                                           # columns compared with the oracle at each end and around the boundary
 
 
 def windows(P, at):
@@ -68,12 +69,31 @@ def test_large_row_steps(step, dtype, pad):
             if prox:
                 sc = np.maximum(sc, np.abs(ch))
         assert_params_close(x[:, a:b].cpu().numpy(), ref, [0, b - a], TIGHT, "x [%d,%d)" % (a, b), sc)
-    # everywhere: the update moved every element by what plain torch arithmetic says, in fp32
-    d = x0[:, :P] - lr * g[:, :P].float()
-    if prox:
-        d = d + (mu / tau) * (cen[:P] - d)
-    if step != "nesterov":
-        scale = float(d.abs().max()) + float(x0[:, :P].abs().max())
-        assert float((x[:, :P] - d).abs().max()) <= 4 * 2.0 ** -24 * 2 * scale
+    # everywhere, element by element against the same formulas in float64.  Each result is one to three fused
+    # multiply-adds of terms of magnitude at most |x| + lr (|g| + |buf|) (with weight decay and momentum, each below 2 of
+    # it), rounded to 24 bits each; the center enters with weight mu / tau.
+    chunk = 1 << 24
+    for k in range(K):
+        for a in range(0, P, chunk):
+            b = min(P, a + chunk)
+            xs, gs = x0[k, a:b].double(), g[k, a:b].double()
+            size = xs.abs() + lr * gs.abs()
+            if step == "nesterov":
+                m, wd = float(np.float32(0.9)), float(np.float32(5e-4))
+                d = gs + wd * xs
+                bs = m * buf0[k, a:b].double() + d
+                want = xs - float(np.float32(lr)) * (d + m * bs)
+                bsize = buf0[k, a:b].double().abs() + gs.abs() + wd * xs.abs()
+                assert bool(((buf[k, a:b].double() - bs).abs() <= 3 * 2.0 ** -24 * bsize).all())
+                size = xs.abs() + 4 * lr * bsize
+            else:
+                want = xs - float(np.float32(lr)) * gs
+                if prox:
+                    w_c = float(np.float32(mu) / np.float32(tau))
+                    want = want + w_c * (cen[a:b].double() - want)
+                    size = size + w_c * cen[a:b].double().abs()
+            assert bool(((x[k, a:b].double() - want).abs() <= 4 * 2.0 ** -24 * size).all())
+    if buf is not None:
+        assert torch.equal(buf[:, P:], buf0[:, P:])
     assert torch.equal(x[:, P:], x0[:, P:])
     torch.cuda.empty_cache()
