@@ -75,23 +75,24 @@ def test_estimate_and_its_reset(K, sizes, dtype):
     est = torch.empty((K, w.L), device=DEV)
     cen = torch.empty(W.round_up(P, 4), device=DEV)
     with grawa.Plan(K, P, w.offsets) as plan:
-        for rep in range(20):                            # the estimate, t and the arrival counter are left at zero
+        for rep in range(20):                            # the estimate and every layer's t are left at zero
             xg = x.clone()
             for _ in range(3):
                 plan.local_step_scored(xg[:, :P], g[:, :P], lr, gamma)
             plan.local_lgrawa_update(xg[:, :P], lam, center_out=cen, est_out=est)
             if rep == 0:
                 first = (xg.clone(), cen[:P].clone(), est.clone())
-            else:                                        # and no result depends on which block came last
+            else:                                        # and every round gives the same bits
                 assert torch.equal(xg, first[0]) and torch.equal(cen[:P], first[1]) and torch.equal(est, first[2])
     ref = orc.local_grawa_round(xh, [gh] * 3, w.offsets, lr, lam, gamma, "lgrawa")
     assert_table_close(est.cpu().numpy(), ref["g_est"], TIGHT, "g_est")
     assert_params_close(first[0].cpu().numpy()[:, :P], ref["x"], w.offsets, TIGHT, "x", scale_of(xh, P, [gh] * 3, lr))
 
 
-def test_model_weights_repeatedly():
-    # the last block of the finalize launch forms the model weights: the same bits every time, fresh inputs each call
-    w, x, g = W.make_small(2400, 6, [1] * 200 + [5000, 33, 70000], device=DEV)
+@pytest.mark.parametrize("short", [97, 200])  # 100 layers: by the last block of the finalize launch; 203: a launch of their own
+def test_model_weights_repeatedly(short):
+    # the same bits every time, fresh inputs each call
+    w, x, g = W.make_small(2400, 6, [1] * short + [5000, 33, 70000], device=DEV)
     P = w.P
     wts = torch.empty(6, device=DEV)
     with grawa.Plan(6, P, w.offsets) as plan:
