@@ -175,6 +175,10 @@ def test_model_weights_with_arrivals_left_behind():
         with grawa.Plan(K, P, w.offsets) as plan:
             # struct grawa_plan: ... void *ws at 48, size_t ws_bytes at 56; the last 256 bytes of ws: flag word, counter at 128
             ws, n = (ctypes.c_uint64.from_address(plan._h.value + o).value for o in (48, 56))
+            at = plan._h.value                           # seen on the host first: an address that is not ws never reaches the device
+            assert [ctypes.c_int32.from_address(at + o).value for o in (0, 4)] == [K, w.L]
+            assert ctypes.c_int64.from_address(at + 8).value == P
+            assert ctypes.c_uint64.from_address(at + 64).value == ws and n % 256 == 0 and 256 < n < 1 << 20  # d_off: the first part
             copy = grawa.lib().hipMemcpy
             copy.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_int]
             word = ctypes.c_uint32(0)
