@@ -255,19 +255,11 @@ template <int V> __device__ __forceinline__ void vec_set(typename FloatVec<V>::T
 // such sets in turn (in brackets: one set again and again, which the 256 MB last-level cache partly holds):
 //   pull            MGRAWA, 4 workers,  80 MB x: 43.0/42.5 (38/39), 120 MB: 75/69, 187 MB: 102.8/93.2 (87.2/90.5)
 //   Nesterov step   8 workers, x 80 MB: 1.13 x faster (0.9), 120 MB 1.13 (1.06), 160 MB 1.15 (1.15)
-//   step with the center, aligned rows: 80 MB 1.02 to 1.17, 160 MB 1.22 (1.12); 40 MB 0.96
+//   step with center or scores: 80 MB 1.04 to 1.21 (0.98 to 1.12), 160 MB 1.22 (1.12); 40 MB 0.96
 //   plain SGD step: 187 MB 100.5/90.2 alone, but the pull that follows finds x in the cache after a cached one: step
 //   and EASGD phase 158.4/164.0; 400 MB 211/189 alone, 344/347 with the phase.
-// A scored step without the center, and any step off the line grid, takes the common line: below it a call that follows
-// one on the same x, or a pass that has read x and written g, finds them in the cache.  Scored step of 4 and 12 workers after
-// such a pass, which for every worker also reads and writes 64 MB of other memory, cached/streaming: 70 MB 34.9/38.3 and
-// 35.7/36.9, 100 MB 46.3/52.6 and 48.3/48.2, 140 MB 71.4/58.4 and 66.8/55.7; off the grid 70 MB 35.9/40.1, 100 MB 50.9/53.7,
-// 140 MB 75.8/63.7.  Two such steps and the communication, 8 workers: 70 MB 101.8/107.3, 95 MB 131.2/139.7, 200 MB
-// 268.8/259.7.  With the center on aligned rows, 70 MB: 4 workers 40.4/38.2, 12 workers 38.8/40.4.
-// A pull of an array of 134 to 250 MB that a small iteration leaves in the cache is slower for it (4 workers, 140 MB 59.6
-// cached, 65.7 with nothing else touched between, 61.8/60.3 with 64 MB per worker).
 #define GRAWA_STREAMING_MIN_BYTES ((int64_t)128 << 20)
-#define GRAWA_STREAMING_MIN_CENTER_BYTES ((int64_t)64 << 20)
+#define GRAWA_STREAMING_MIN_ROW_BYTES ((int64_t)64 << 20)
 #define GRAWA_STREAMING_MIN_SGD_BYTES ((int64_t)256 << 20)
 
 // Streaming accesses are used only when no cache line is shared between two rows or written

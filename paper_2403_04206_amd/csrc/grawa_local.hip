@@ -251,10 +251,8 @@ static hipError_t launch_row_step(const grawa_plan *p, float *x, int64_t ldx, co
     const bool aligned = rows_line_aligned(x, ldx, 4) && rows_line_aligned(g, ldg, dt == GRAWA_BF16 ? 2 : 4);
     const int64_t bytes = (int64_t)K * P * 4;
     const bool plain = !prox && !p;
-    const bool nt = aligned && bytes > (plain  ? GRAWA_STREAMING_MIN_SGD_BYTES
-                                        : prox ? GRAWA_STREAMING_MIN_CENTER_BYTES
-                                               : GRAWA_STREAMING_MIN_BYTES);
-    const bool wide = !aligned && bytes > (plain ? 2 * GRAWA_STREAMING_MIN_SGD_BYTES : GRAWA_STREAMING_MIN_BYTES);
+    const bool nt = aligned && bytes > (plain ? GRAWA_STREAMING_MIN_SGD_BYTES : GRAWA_STREAMING_MIN_ROW_BYTES);
+    const bool wide = !aligned && bytes > (plain ? 2 * GRAWA_STREAMING_MIN_SGD_BYTES : GRAWA_STREAMING_MIN_ROW_BYTES);
     const GrawaTile *tiles = p ? p->d_rtiles : nullptr;
     const int32_t *block_tile0 = p ? p->d_block_rtile0 : nullptr;
     double *partials = p ? p->d_partials : nullptr;
