@@ -255,9 +255,15 @@ template <int V> __device__ __forceinline__ void vec_set(typename FloatVec<V>::T
 // such sets in turn (in brackets: one set again and again, which the 256 MB last-level cache partly holds):
 //   pull            MGRAWA, 4 workers,  80 MB x: 43.0/42.5 (38/39), 120 MB: 75/69, 187 MB: 102.8/93.2 (87.2/90.5)
 //   Nesterov step   8 workers, x 80 MB: 1.13 x faster (0.9), 120 MB 1.13 (1.06), 160 MB 1.15 (1.15)
-//   step with center or scores: 80 MB 1.04 to 1.21 (0.98 to 1.12), 160 MB 1.22 (1.12); 40 MB 0.96
+//   step with center or scores: 80 MB 1.04 to 1.21 (0.98 to 1.12), 160 MB 1.22 (1.12); 40 MB 0.96.  Scored, aligned rows, 4
+//   and 52 workers: 90 MB 56.3/49.6 and 55.0/49.1 (45.7/49.2 and 44.7/48.7), after a pass over x, g and 256 MB of other memory
+//   67.6/52.0 and 67.3/50.8.  With the center, off the line grid: 90 MB 58.2/53.7 and 49.9/44.9 (49.6/49.9 and 41.1/42.8),
+//   after such a pass 72.1/71.8 and 62.0/61.1.  What the line costs: a step that finds its arrays in the cache, two scored steps
+//   and the communication, 8 workers, 95 MB 131/140; one scored step after a pass that leaves them there, 70 MB 34.9/38.3.
 //   plain SGD step: 187 MB 100.5/90.2 alone, but the pull that follows finds x in the cache after a cached one: step
 //   and EASGD phase 158.4/164.0; 400 MB 211/189 alone, 344/347 with the phase.
+// A pull of an array of 134 to 250 MB that a small iteration leaves in the cache is slower for its line (4 workers, 140 MB
+// 59.6/65.7 with nothing else touched between, 61.8/60.3 with 64 MB per worker).
 #define GRAWA_STREAMING_MIN_BYTES ((int64_t)128 << 20)
 #define GRAWA_STREAMING_MIN_ROW_BYTES ((int64_t)64 << 20)
 #define GRAWA_STREAMING_MIN_SGD_BYTES ((int64_t)256 << 20)
