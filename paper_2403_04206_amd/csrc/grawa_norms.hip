@@ -229,13 +229,13 @@ __global__ __launch_bounds__(GRAWA_FIN_BLOCK) void k_finalize_model(double *__re
 
 // grid (L, y) and block from grawa_estimate_shape: the tile sums of a scored local step -> running estimate of
 // Appendix G, g_mvg <- gamma g_mvg + (1 - gamma) g_cur, t <- t + 1.  The tiles of this step are short (1024 columns).
-// A layer of up to GRAWA_EST_WAVE_TILES of them is a wave's work for one worker; of a longer one the whole block adds
+// A layer of up to wave_tiles of them is a wave's work for one worker; of a longer one the whole block adds
 // the tiles of one worker at a time (the 50 000 tiles of the largest layer of the 350 M transformer for each of 8 workers
 // took one block 72 us).
 // The counts t (one per layer, see k_local_weights) live on the device so that a recorded and replayed call still counts.
 __global__ __launch_bounds__(GRAWA_EST_MAX_THREADS) void k_estimate(const double *__restrict__ partials, int64_t n_tiles,
                                                                     const int32_t *__restrict__ layer_tile0, int K, int L,
-                                                                    double *__restrict__ mvg, double gamma,
+                                                                    int wave_tiles, double *__restrict__ mvg, double gamma,
                                                                     int64_t *__restrict__ local_t,
                                                                     unsigned *__restrict__ flags)
 {
@@ -249,7 +249,7 @@ __global__ __launch_bounds__(GRAWA_EST_MAX_THREADS) void k_estimate(const double
         mvg[(int64_t)k * L + l] = gamma * mvg[(int64_t)k * L + l] + (1.0 - gamma) * norm;
         if (flags && !isfinite(norm)) atomicOr(flags, GRAWA_NONFINITE_LAYER_SCORE);
     };
-    if (t1 - t0 <= GRAWA_EST_WAVE_TILES || K > 4 * rows) {
+    if (t1 - t0 <= wave_tiles || K > 4 * rows) {
         // The sums first, then every worker's update by a thread of its own, side by side.
         int n = wave;
         for (int k = y * waves + wave; k < K; k += rows * waves, n += waves) {
@@ -455,10 +455,10 @@ hipError_t grawa_launch_finalize_layers(const grawa_plan *p, int goal, float *no
 
 hipError_t grawa_launch_estimate(const grawa_plan *p, double gamma, hipStream_t s)
 {
-    int rows, threads;
-    grawa_estimate_shape(p->K, p->L, p->max_rtiles, &rows, &threads);
+    int rows, threads, wave_tiles;
+    grawa_estimate_shape(p->K, p->L, p->max_rtiles, &rows, &threads, &wave_tiles);
     k_estimate<<<dim3((unsigned)p->L, (unsigned)rows), dim3((unsigned)threads), 0, s>>>(
-        p->d_partials, p->n_rtiles, p->d_layer_rtile0, p->K, p->L, p->d_mvg, gamma, p->d_local_t, p->d_flags);
+        p->d_partials, p->n_rtiles, p->d_layer_rtile0, p->K, p->L, wave_tiles, p->d_mvg, gamma, p->d_local_t, p->d_flags);
     return hipGetLastError();
 }
 

@@ -86,14 +86,23 @@ static inline bool grawa_model_weights_by_last_block(int L) { return L <= GRAWA_
 //   8 workers, 1.05 M columns:   250 layers 24.4 / 24.7 / 23.3, 5000 layers 57.5 / 78.6 / 37.5
 //   15 workers, 1.05 M:          1000 layers 40.2 / 53.5 / 38.3
 //   64 workers, 300 k:           1000 layers 55.6 / 70.6 / 55.5;  1.05 M, 5000 layers 223 / 586 / 196
+// With few sums (GRAWA_EST_FEW_BLOCKS) nothing but the longest one counts: the block per worker already from 129 tiles
+// on, and waves in blocks of 8.  A block or wave as above / the rule for many / this: 7 workers, 2.1 M
+// columns, 11 layers 29.8 / 31.0 / 29.9; 8 workers, 1.1 M, 3 layers 20.3 / 21.2 / 20.5; 31 workers, 252 k, 6 layers
+// 19.2 / 19.9 / 19.5; from 256 tiles on 30.0, 20.6 and 19.9.
 #define GRAWA_EST_MAX_THREADS 1024
 #define GRAWA_EST_WAVE_TILES 1024
 #define GRAWA_EST_BLOCKS 512
 #define GRAWA_EST_LONG_BLOCKS 4096
-static inline void grawa_estimate_shape(int K, int L, int64_t max_tiles, int *rows, int *threads)
+#define GRAWA_EST_FEW_BLOCKS 512
+#define GRAWA_EST_WAVE_TILES_FEW 128
+static inline void grawa_estimate_shape(int K, int L, int64_t max_tiles, int *rows, int *threads, int *wave_tiles)
 {
-    const bool longest = max_tiles > GRAWA_EST_WAVE_TILES;
-    const int waves = longest ? 8 : K < 16 ? K : 16;
+    const bool few = (int64_t)K * L <= GRAWA_EST_FEW_BLOCKS;
+    *wave_tiles = few ? GRAWA_EST_WAVE_TILES_FEW : GRAWA_EST_WAVE_TILES;
+    const bool longest = max_tiles > *wave_tiles;
+    const int most = few ? 8 : 16;
+    const int waves = longest ? 8 : K < most ? K : most;
     const int all = (K + waves - 1) / waves, fill = (longest ? GRAWA_EST_LONG_BLOCKS : GRAWA_EST_BLOCKS) / L;
     const int want = longest ? K : all;
     *rows = fill < 1 ? 1 : fill < want ? fill : want;

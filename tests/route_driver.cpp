@@ -43,9 +43,9 @@ int main(int argc, char **argv)
     }
     if (!std::strcmp(argv[1], "estimate")) {
         for (int i = 2; i + 2 < argc; i += 3) {
-            int rows = 0, threads = 0;
-            grawa_estimate_shape(std::atoi(argv[i]), std::atoi(argv[i + 1]), std::atoll(argv[i + 2]), &rows, &threads);
-            std::printf("%s %s %s %d %d\n", argv[i], argv[i + 1], argv[i + 2], rows, threads);
+            int rows = 0, threads = 0, wave_tiles = 0;
+            grawa_estimate_shape(std::atoi(argv[i]), std::atoi(argv[i + 1]), std::atoll(argv[i + 2]), &rows, &threads, &wave_tiles);
+            std::printf("%s %s %s %d %d %d\n", argv[i], argv[i + 1], argv[i + 2], rows, threads, wave_tiles);
         }
         return 0;
     }

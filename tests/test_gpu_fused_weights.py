@@ -126,7 +126,9 @@ def test_step_count_of_every_layer(K, L):
 
 
 @pytest.mark.parametrize("K,sizes", [
-    (3, [1 << 20]), (3, [(1 << 20) + 1]),                # 1024 tiles: the most that a wave adds; one more
+    (3, [1 << 17]), (3, [(1 << 17) + 1]),                # 128 tiles: the most that a wave adds where there are few sums; one more
+    (3, [1] * 170 + [1 << 20]), (3, [1] * 170 + [(1 << 20) + 1025]),  # more than 512 sums: up to 1024 tiles
+    (16, [1] * 31 + [1 << 17]), (9, [(1 << 17) + 1500, 5]), (3, [1 << 20]), (3, [(1 << 20) + 1]),
     (3, [5, (1 << 20) + 1019, 7]),                       # a layer cut off the tile grid, 1026 tiles
     (1, [(1 << 20) + 5000, 3, 1]), (17, [3, (1 << 20) + 2000]),
     (66, [1 << 20, 9]), (66, [3, (1 << 20) + 3000]),     # more workers than waves: further trips over the workers

@@ -42,11 +42,12 @@ def test_no_arrivals_with_many_layers(driver):
 
 def test_estimate_launch(driver):
     cases = [(K, L, T) for K in (1, 3, 8, 15, 16, 17, 64, 1024) for L in (1, 60, 511, 512, 513, 5000, 1 << 20)
-             for T in (1, 1024, 1025, 50000)]
-    for (K, L, T, rows, threads) in driver("estimate", *[v for c in cases for v in c]):
+             for T in (1, 128, 129, 1024, 1025, 50000)]
+    for (K, L, T, rows, threads, most) in driver("estimate", *[v for c in cases for v in c]):
         assert 64 <= threads <= 1024 and threads % 64 == 0 and 1 <= rows <= K
-        assert rows == 1 or rows * L <= (512 if T <= 1024 else 4096)
-        assert T > 1024 or (rows - 1) * (threads // 64) < K              # no row of blocks without a worker
+        assert rows == 1 or rows * L <= (512 if T <= most else 4096)
+        assert most == (128 if K * L <= 512 else 1024)
+        assert T > most or (rows - 1) * (threads // 64) < K              # no row of blocks without a worker
         assert L * threads < 1 << 32
 
 
