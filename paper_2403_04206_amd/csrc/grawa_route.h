@@ -58,9 +58,10 @@ static inline bool grawa_weights_in_pull(int K, int64_t n_cells)
 // with its barrier and four times the threads, is the longer chain.  Split against plain, time of the pull by per-layer
 // weights, 24 / 28 / 32 workers, 1 layer, 40 layers and 500: 5 k columns 1.04 1.16 1.30 / 1.07 1.21 1.29 / 1.00 1.18 1.31,
 // 105 k 1.09 1.17 1.30 / 1.10 1.20 1.30 / 1.06 1.15 1.30, 200 k 1.10 1.07 1.14 / 1.11 1.10 1.16 / 1.07 1.01 1.10,
-// 300 k 1.07 1.02 1.05 / 1.03 0.96 0.96 / 0.98 0.92 0.92, 1 M 1.01 0.98 0.92 / 1.01 0.99 0.94 / 1.00 0.99 0.96.
+// 300 k 1.07 1.02 1.05 / 1.03 0.96 0.96 / 0.98 0.92 0.92, 1 M 1.01 0.98 0.92 / 1.01 0.99 0.94 / 1.00 0.99 0.96.  In a local
+// round of 31 workers on 252 k columns (985 cells) the split form is 0.4 us faster, so the line lies at 800 cells.
 #define GRAWA_PLAIN_MAX_WORKERS 23
-#define GRAWA_PLAIN_FEW_CELLS 1024
+#define GRAWA_PLAIN_FEW_CELLS 800
 #define GRAWA_PLAIN_FEW_CELLS_MAX_WORKERS 32
 static inline bool grawa_plain_form(int K, int64_t n_cells)
 {

@@ -25,9 +25,9 @@ def test_row_split_worker_counts(K, dtype, ld_pad):
 
 
 @pytest.mark.parametrize("K", [24, 25, 31, 32, 33, 40])
-@pytest.mark.parametrize("cells", [1024, 1025])
+@pytest.mark.parametrize("cells", [800, 801])
 def test_either_side_of_few_cells(K, cells):
-    # up to 1024 cells the plain form serves up to 32 workers; cells with one, two, a few and many layers
+    # up to 800 cells the plain form serves up to 32 workers; cells with one, two, a few and many layers
     P = cells * 256 - 3
     many = [5] * 100 + [1] * 30
     sizes = [P // 2] + many + [P - P // 2 - sum(many) - 2000, 2000]
