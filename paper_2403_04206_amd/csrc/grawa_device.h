@@ -92,21 +92,25 @@ template <bool NT, typename T> __device__ __forceinline__ T ld_lane(uint64_t bas
     const GRAWA_GLOBAL T *p = (const GRAWA_GLOBAL T *)(base + byte_off);
     return NT ? __builtin_nontemporal_load(p) : *p;
 }
-// Streaming store (NT): written through the L2 (device scope, sc1) on top of the non-temporal hint, instead of being
-// left to the L2's replacement.  Only the buffer form lets both bits be asked for.  Against the hint alone, random
-// values: pull of 12 rows of 102 MB 6.31 -> 6.43 TB/s (plain stores 5.55), LGRAWA of the 350 M transformer with
-// 8 workers 4411 -> 4279 us, Nesterov step of 36.5 M columns x 8 workers 922 -> 889 us; 0 to 2 % elsewhere.
-#define GRAWA_STORE_SC1_NT 18
-template <bool NT, typename T> __device__ __forceinline__ void st_lane(uint64_t base, unsigned byte_off, T v)
+// Stores.  STREAM: written through the L2 (device scope, sc1) on top of the non-temporal hint, instead of being left to the
+// L2's replacement; for rows whose lines are written whole.  Only the buffer form lets both bits be asked for.  Against the
+// hint alone, random values: pull of 12 rows of 102 MB 6.31 -> 6.43 TB/s (plain stores 5.55), LGRAWA of the 350 M
+// transformer with 8 workers 4411 -> 4279 us, Nesterov step of 36.5 M columns x 8 workers 922 -> 889 us; 0 to 2 % elsewhere.
+// MERGE: the hint alone.  For rows off the line grid: where a wave's piece ends inside a line, the L2 holds that part
+// until the neighbour's part has come, while STREAM sends both parts on as writes of their own.  8 rows of 50 M
+// columns, 32 bytes off a line, streaming loads, TB/s, STREAM / MERGE: step with center and scores fp32 5.88 / 6.08, bf16 5.76 / 6.00,
+// plain step 5.90 / 6.13.
+enum { GRAWA_ST_CACHED = 0, GRAWA_ST_MERGE = 2, GRAWA_ST_STREAM = 18 }; // the cache bits of the buffer store
+template <int ST, typename T> __device__ __forceinline__ void st_lane(uint64_t base, unsigned byte_off, T v)
 {
-    if constexpr (NT) {
+    if constexpr (ST != GRAWA_ST_CACHED) {
         __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>(base), 0, -1, 0x00020000);
         if constexpr (sizeof(T) == 4)
-            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, (int)byte_off, 0, GRAWA_STORE_SC1_NT);
+            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, (int)byte_off, 0, ST);
         else if constexpr (sizeof(T) == 8)
-            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2u, v), r, (int)byte_off, 0, GRAWA_STORE_SC1_NT);
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2u, v), r, (int)byte_off, 0, ST);
         else
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), r, (int)byte_off, 0, GRAWA_STORE_SC1_NT);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), r, (int)byte_off, 0, ST);
     } else {
         *(GRAWA_GLOBAL T *)(base + byte_off) = v;
     }

@@ -37,7 +37,7 @@
 // members of a struct they may alias the stores, and a block with many tiles then reads them by vector loads that wait for
 // its stores (64 workers, 300 k columns, 5000 layers: this kernel 141 us for 114).
 // The last P % V columns of a row are handled element by element.
-template <typename GT, int V, int U, bool LNT, bool SNT, bool PROX, bool SCORE>
+template <typename GT, int V, int U, bool LNT, int ST, bool PROX, bool SCORE>
 __global__ __launch_bounds__(GRAWA_CELL) __attribute__((amdgpu_waves_per_eu(1, PROX && !SCORE ? 7 : 8))) void k_row_step(float *__restrict__ x, int64_t ldx,
                                                          const GT *__restrict__ g, int64_t ldg, float lr,
                                                          const float *__restrict__ center, float w, int64_t P,
@@ -86,8 +86,8 @@ __global__ __launch_bounds__(GRAWA_CELL) __attribute__((amdgpu_waves_per_eu(1, P
                 if (PROX) v = fmaf(w, vec_get<V>(cv[u], e) - v, v);
                 vec_set<V>(o, e, v);
             }
-            if (SNT)
-                st_lane<true, XV>(uniform_base(xr + (int64_t)m * GRAWA_ROW_BLOCK), (threadIdx.x + u * GRAWA_CELL) * (V * 4u), o);
+            if (ST)
+                st_lane<ST, XV>(uniform_base(xr + (int64_t)m * GRAWA_ROW_BLOCK), (threadIdx.x + u * GRAWA_CELL) * (V * 4u), o);
             else
                 *reinterpret_cast<XV *>(xr + c) = o;
         } else if (V > 1 && c < P) { // the vector that holds the row's last columns
@@ -137,9 +137,12 @@ __global__ __launch_bounds__(GRAWA_CELL) __attribute__((amdgpu_waves_per_eu(1, P
 // Vector shape of the Nesterov step: fp32 gradients V = 1, U = 4; bf16 V = 2, U = 2 (bf16 at V = 4, U = 4
 // 5.6 TB/s: more bytes in flight per lane cost bandwidth at full occupancy, and 2-byte loads (V = 1) waste
 // requests).  Waves per SIMD: bf16 6 (36.5 M columns x 8 workers 795 us; 5: 810, 7: 810, 8: 825), fp32 8 (889; 6: 914).
-// Large rows off the cache-line grid with bf16 gradients: V = 4, cached loads and streaming stores (47 M elements,
-// 4 workers 152.5 -> 132.5 us, 400 M, 3 workers 1345 -> 1307); with fp32 gradients from 512 MB on (400 M, 3 workers
-// 1478 -> 1453; 25 M 92.5 -> 94.6).
+// Large rows off the cache-line grid: V = 4, streaming loads and stores that the L2 merges (GRAWA_ST_MERGE); with bf16 gradients
+// up to 192 MB cached loads and stores written through, which find part of the arrays in the cache.  Three sets in turn, us:
+// fp32 against cached accesses with V = 1, 140 MB 126 -> 119, 400 MB 361 -> 348, 1.5 GB 1367 -> 1335; bf16, the form up to 192 MB
+// against the one beyond, 3 and 16 workers: 140 MB 100 / 106 and 93 / 103, 180 MB 136 / 137 and 130 / 134, 260 MB 208 / 200 and
+// 201 / 194, 1.5 GB 1216 / 1163.
+#define GRAWA_NAG_CACHED_LOADS_BYTES ((int64_t)192 << 20)
 #define GRAWA_SGD_V_F32 1
 #define GRAWA_SGD_U_F32 4
 #define GRAWA_SGD_V_BF16 2
@@ -149,7 +152,7 @@ __global__ __launch_bounds__(GRAWA_CELL) __attribute__((amdgpu_waves_per_eu(1, P
 // block 256*V columns apart; the last P % V columns of a row take a scalar path.  One step of SGD with Nesterov momentum and weight decay
 // (the local optimizer of Appendix B.2.2), buf = momentum buffer [K][ldb], zero before the first step:
 //     d = g + wd x ;  buf <- momentum buf + d ;  x <- x - lr (d + momentum buf).
-template <typename GT, int V, int U, bool LNT, bool SNT>
+template <typename GT, int V, int U, bool LNT, int ST>
 __global__ __launch_bounds__(GRAWA_CELL) __attribute__((amdgpu_waves_per_eu(1, sizeof(GT) == 2 ? 6 : 8))) void k_nesterov(float *__restrict__ x, int64_t ldx,
                                                          const GT *__restrict__ g, int64_t ldg,
                                                          float *__restrict__ buf, int64_t ldb, int64_t P,
@@ -188,11 +191,11 @@ __global__ __launch_bounds__(GRAWA_CELL) __attribute__((amdgpu_waves_per_eu(1, s
                 vec_set<V>(bo, c, b);
                 vec_set<V>(xo, c, fmaf(-lr, fmaf(momentum, b, d), xc));
             }
-            if (SNT) {
+            if (ST) {
                 const int64_t c0 = (int64_t)blockIdx.x * (GRAWA_CELL * U * V);
                 const unsigned o = (threadIdx.x + u * GRAWA_CELL) * (V * 4u);
-                st_lane<true, XV>(uniform_base(xr + c0), o, xo);
-                st_lane<true, XV>(uniform_base(br + c0), o, bo);
+                st_lane<ST, XV>(uniform_base(xr + c0), o, xo);
+                st_lane<ST, XV>(uniform_base(br + c0), o, bo);
             } else {
                 *reinterpret_cast<XV *>(xr + j * V) = xo;
                 *reinterpret_cast<XV *>(br + j * V) = bo;
@@ -232,11 +235,16 @@ __global__ __launch_bounds__(GRAWA_COPY_BLOCK) void k_stream_copy(v4u *__restric
 // V = 4, U = 1 with the proximity step or the scores; bf16 V = 2, U = 2 for the plain step, else
 // V = 4, U = 1 (each the fastest measured for its case on arrays of random values; the spread
 // between shapes is 3-10 %).
-// Large rows off the cache-line grid (wide): 16-byte lanes, cached loads, so that the lines two waves share are
-// fetched once, and streaming stores.  Against cached accesses, us, 400 M elements x 4 bytes, 12 workers, rows 32
-// bytes off a line: with the center fp32 946 -> 894, bf16 811 -> 726; a round of two scored steps and the communication
-// 2556 -> 2448, 2266 -> 2100.  The plain step only from 512 MB on: at 360 MB the pull that follows would lose
-// the part of x a cached step leaves in the cache (step and LSGD phase 330 -> 349).
+// Large rows off the cache-line grid (wide): 16-byte lanes, streaming loads, and stores that the L2 merges (GRAWA_ST_MERGE).
+// Against cached loads with stores written through (the form before), three sets of arrays in turn, us, 3 and 16 workers,
+// rows 4 or 12 bytes off a line: with the center fp32 100 MB 58.7 -> 51.8, 200 MB 120 -> 103, 1.5 GB 879 -> 815; bf16 200 MB
+// 97.4 -> 89.8 and 99.4 -> 87.1, 1.5 GB 729 -> 705; scored step with the center and the communication fp32 70 MB 79.9 -> 72.8,
+// 400 MB 378 -> 357, bf16 100 MB 97.7 -> 94.2 and 100.0 -> 93.1.  With the center and bf16 gradients the old form stays up to
+// 128 MB, where its loads find part of the arrays in the cache: 3 workers 70 MB 32.2 / 33.8, 100 MB 44.0 / 45.8, 16 workers
+// 70 MB 35.9 / 36.5 (100 MB 49.8 / 45.5).
+// The plain step only from 512 MB on: below, the pull that follows would lose the part of x a cached step leaves in the
+// cache (step and LSGD phase, bf16, 3 and 16 workers: 300 MB 210 / 222 and 216 / 229, 520 MB 364 / 376 and 388 / 402, 800 MB
+// 609 / 596 and 638 / 626).
 static hipError_t launch_row_step(const grawa_plan *p, float *x, int64_t ldx, const void *g, int64_t ldg,
                                   grawa_dtype_t dt, float lr, const float *center, float w, int K, int64_t P,
                                   double gamma, hipStream_t s)
@@ -257,18 +265,19 @@ static hipError_t launch_row_step(const grawa_plan *p, float *x, int64_t ldx, co
     const int32_t *block_tile0 = p ? p->d_block_rtile0 : nullptr;
     double *partials = p ? p->d_partials : nullptr;
     const int64_t n_tiles = p ? p->n_rtiles : 0;
-#define GRAWA_RS_GO(GT, V, U, LNT, SNT, PROX, SCORE)                                                                   \
-    k_row_step<GT, V, U, LNT, SNT, PROX, SCORE><<<grid, block, 0, s>>>(x, ldx, (const GT *)g, ldg, lr, center, w, P, \
+#define GRAWA_RS_GO(GT, V, U, LNT, ST, PROX, SCORE)                                                                    \
+    k_row_step<GT, V, U, LNT, ST, PROX, SCORE><<<grid, block, 0, s>>>(x, ldx, (const GT *)g, ldg, lr, center, w, P, \
                                                                        (unsigned)nb, tiles, block_tile0, n_tiles,  \
                                                                        partials)
 #define GRAWA_RS_NT(GT, V, U, PROX, SCORE)                          \
     do {                                                            \
-        if (nt) GRAWA_RS_GO(GT, V, U, true, true, PROX, SCORE);     \
-        else if (wide) GRAWA_RS_GO(GT, 4, 1, false, true, PROX, SCORE); \
-        else GRAWA_RS_GO(GT, V, U, false, false, PROX, SCORE);      \
+        if (nt) GRAWA_RS_GO(GT, V, U, true, GRAWA_ST_STREAM, PROX, SCORE);       \
+        else if (wide) GRAWA_RS_GO(GT, 4, 1, true, GRAWA_ST_MERGE, PROX, SCORE); \
+        else GRAWA_RS_GO(GT, V, U, false, GRAWA_ST_CACHED, PROX, SCORE);         \
     } while (0)
     if (dt == GRAWA_BF16) {
         if (prox && p) GRAWA_RS_NT(uint16_t, 4, 1, true, true);
+        else if (prox && wide && bytes <= GRAWA_STREAMING_MIN_BYTES) GRAWA_RS_GO(uint16_t, 4, 1, false, GRAWA_ST_STREAM, true, false);
         else if (prox) GRAWA_RS_NT(uint16_t, 4, 1, true, false);
         else if (p) GRAWA_RS_NT(uint16_t, 4, 1, false, true);
         else GRAWA_RS_NT(uint16_t, 2, 2, false, false);
@@ -305,18 +314,19 @@ hipError_t grawa_launch_nesterov(float *x, int64_t ldx, const void *g, int64_t l
     const bool large = bytes > GRAWA_STREAMING_MIN_BYTES;
     const bool nt = large && rows_line_aligned(x, ldx, 4) && rows_line_aligned(buf, ldb, 4) &&
                     rows_line_aligned(g, ldg, dt == GRAWA_BF16 ? 2 : 4);
-#define GRAWA_NAG_GO(GT, V, U, LNT, SNT)                                                                          \
-    k_nesterov<GT, V, U, LNT, SNT><<<dim3((unsigned)((P + GRAWA_CELL * (U) * (V) - 1) / (GRAWA_CELL * (U) * (V))), \
-                                          (unsigned)K), dim3(GRAWA_CELL), 0, s>>>(                               \
+#define GRAWA_NAG_GO(GT, V, U, LNT, ST)                                                                          \
+    k_nesterov<GT, V, U, LNT, ST><<<dim3((unsigned)((P + GRAWA_CELL * (U) * (V) - 1) / (GRAWA_CELL * (U) * (V))), \
+                                         (unsigned)K), dim3(GRAWA_CELL), 0, s>>>(                               \
         x, ldx, (const GT *)g, ldg, buf, ldb, P, lr, momentum, wd)
     if (dt == GRAWA_BF16) {
-        if (nt) GRAWA_NAG_GO(uint16_t, GRAWA_SGD_V_BF16, GRAWA_SGD_U_BF16, true, true);
-        else if (large) GRAWA_NAG_GO(uint16_t, 4, 1, false, true);
-        else GRAWA_NAG_GO(uint16_t, GRAWA_SGD_V_BF16, GRAWA_SGD_U_BF16, false, false);
+        if (nt) GRAWA_NAG_GO(uint16_t, GRAWA_SGD_V_BF16, GRAWA_SGD_U_BF16, true, GRAWA_ST_STREAM);
+        else if (large && bytes <= GRAWA_NAG_CACHED_LOADS_BYTES) GRAWA_NAG_GO(uint16_t, 4, 1, false, GRAWA_ST_STREAM);
+        else if (large) GRAWA_NAG_GO(uint16_t, 4, 1, true, GRAWA_ST_MERGE);
+        else GRAWA_NAG_GO(uint16_t, GRAWA_SGD_V_BF16, GRAWA_SGD_U_BF16, false, GRAWA_ST_CACHED);
     } else {
-        if (nt) GRAWA_NAG_GO(float, GRAWA_SGD_V_F32, GRAWA_SGD_U_F32, true, true);
-        else if (bytes > 4 * GRAWA_STREAMING_MIN_BYTES) GRAWA_NAG_GO(float, 4, 1, false, true);
-        else GRAWA_NAG_GO(float, GRAWA_SGD_V_F32, GRAWA_SGD_U_F32, false, false);
+        if (nt) GRAWA_NAG_GO(float, GRAWA_SGD_V_F32, GRAWA_SGD_U_F32, true, GRAWA_ST_STREAM);
+        else if (large) GRAWA_NAG_GO(float, 4, 1, true, GRAWA_ST_MERGE);
+        else GRAWA_NAG_GO(float, GRAWA_SGD_V_F32, GRAWA_SGD_U_F32, false, GRAWA_ST_CACHED);
     }
 #undef GRAWA_NAG_GO
     return hipGetLastError();

@@ -221,8 +221,8 @@ __global__ __launch_bounds__(GRAWA_CELL) __attribute__((amdgpu_waves_per_eu(1, W
     if (ok) {
 #pragma unroll
         for (int k = 0; k < K; ++k)
-            st_lane<NT, float>(uniform_base(xb + (int64_t)k * ldx), xoff, fmaf(lambda, c - v[k], v[k]));
-        if (center_out) st_lane<NT, float>(uniform_base(center_out + cell0), xoff, c);
+            st_lane<NT ? GRAWA_ST_STREAM : GRAWA_ST_CACHED, float>(uniform_base(xb + (int64_t)k * ldx), xoff, fmaf(lambda, c - v[k], v[k]));
+        if (center_out) st_lane<NT ? GRAWA_ST_STREAM : GRAWA_ST_CACHED, float>(uniform_base(center_out + cell0), xoff, c);
     }
 }
 
@@ -316,9 +316,9 @@ __global__ __launch_bounds__(GRAWA_BLOCK) __attribute__((amdgpu_waves_per_eu(1, 
 #pragma unroll
             for (int e = 0; e < V; ++e)
                 vec_set<V>(o, e, fmaf(lambda, vec_get<V>(c, e) - vec_get<V>(v[k], e), vec_get<V>(v[k], e)));
-            st_lane<true, XV>(uniform_base(xb + (int64_t)k * ldx), xoff, o);
+            st_lane<GRAWA_ST_STREAM, XV>(uniform_base(xb + (int64_t)k * ldx), xoff, o);
         }
-        if (center_out) st_lane<true, XV>(uniform_base(center_out + cell0), xoff, c);
+        if (center_out) st_lane<GRAWA_ST_STREAM, XV>(uniform_base(center_out + cell0), xoff, c);
     } else if (n > 0) {
 #pragma unroll
         for (int e = 0; e < V; ++e)
@@ -445,9 +445,9 @@ __global__ __launch_bounds__(S *GRAWA_CELL / V) void k_center_pull_split(
 #pragma unroll
                 for (int e = 0; e < V; ++e)
                     vec_set<V>(o, e, fmaf(lambda, vec_get<V>(c, e) - vec_get<V>(v[k], e), vec_get<V>(v[k], e)));
-                st_lane<NT, XV>(uniform_base(xb + (int64_t)k * ldx), xoff, o);
+                st_lane<NT ? GRAWA_ST_STREAM : GRAWA_ST_CACHED, XV>(uniform_base(xb + (int64_t)k * ldx), xoff, o);
             }
-        if (center_out && group == 0) st_lane<NT, XV>(uniform_base(center_out + cell0), xoff, c);
+        if (center_out && group == 0) st_lane<NT ? GRAWA_ST_STREAM : GRAWA_ST_CACHED, XV>(uniform_base(center_out + cell0), xoff, c);
     } else if (n > 0) {
 #pragma unroll
         for (int e = 0; e < V; ++e)
