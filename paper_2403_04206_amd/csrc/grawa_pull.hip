@@ -226,21 +226,19 @@ __global__ __launch_bounds__(GRAWA_CELL) __attribute__((amdgpu_waves_per_eu(1, W
     }
 }
 
-// Wide form, for arrays beyond the last-level cache whose rows do not start on line boundaries (a plain [K, P]
-// tensor).  grid ceil(P/1024), block 256: a lane owns four adjacent columns (16-byte accesses are always aligned:
+// Wide form, up to 5 workers and with the fp32 SGD step 12 to 23, for arrays beyond the last-level cache whose rows do not start on line boundaries (a plain
+// [K, P] tensor).  grid ceil(P/1024), block 256: a lane owns four adjacent columns (16-byte accesses are always aligned:
 // the ABI asks for it), a wave 1 KiB per row and the block 4 KiB, so that one line in 32 instead of one in 8 is shared
-// with another block; loads cached, so that the lines the waves of a block share are fetched once; stores streaming.
-// Otherwise as the plain form; a wave's 256 columns are one cell.  With streaming loads (LNT) the form also serves
-// line-aligned rows of one or two workers, where a 4-byte load per row and lane leaves too little in flight: K = 1
-// 3.64 -> 6.69 TB/s, K = 2 5.71 -> 6.64, with the SGD step on bf16 gradients 5.77 -> 6.46.
-// Off the line grid: measured on 1.2 to 2 GB of random values, pitch 16 bytes off a line, TB/s, plain form / this one (WPE in grawa_waves_wide): K = 2 5.46/6.27, 3 5.73/6.26, 4 5.71/5.96,
-// 6 5.53/5.52, 8 5.39/5.35, 10 5.36/5.25, 12 4.94/5.29, 16 4.86/5.45, 20 4.68/5.48; with the SGD step 2 5.60/6.28,
-// 4 5.69/5.97, 8 5.52/5.45, 12 5.29/5.58, 16 5.35/5.67; bf16 gradients 4 5.34/6.08, 16 5.16/5.48.
+// with another block.  Otherwise as the plain form; a wave's 256 columns are one cell.  With streaming loads and stores written
+// through (LNT, GRAWA_ST_STREAM) it also serves line-aligned rows of one or two workers, where a 4-byte load per row and lane
+// leaves too little in flight: K = 1 3.64 -> 6.69 TB/s, K = 2 5.71 -> 6.64, with the SGD step on bf16 gradients 5.77 -> 6.46.
+// Off the line grid: measured on 1.2 to 2 GB of random values, pitch 16 bytes off a line, TB/s, plain form / this one (WPE in
+// grawa_waves_wide), cached loads: K = 2 5.46/6.27, 3 5.73/6.26, 4 5.71/5.96; with the SGD step 2 5.60/6.28, 4 5.69/5.97,
+// 12 5.29/5.58, 16 5.35/5.67.
 // These are passes in a row over several arrays.  The plain form's cached stores leave up to 256 MB in the last-level
 // cache, which a later pass has to write back; after a read of other memory a single pass of it looks faster than it is.
-// One LGRAWA update, and a read of 1 GB after it, plain / wide: 4 workers, 75 M columns 597 / 613 and 313 / 277 us,
-// 12 workers, 25.6 M 624 / 632 and 310 / 277, 16 workers, 18 M 591 / 593 and 313 / 275, 23 workers, 13 M 654 / 635 and 314 / 276.
-template <int K, bool SGD, typename GT, bool LNT, int WPE>
+// One LGRAWA update, and a read of 1 GB after it, 4 workers, 75 M columns, plain / wide: 597 / 613 and 313 / 277 us.
+template <int K, bool SGD, typename GT, bool LNT, int ST, int WPE>
 __global__ __launch_bounds__(GRAWA_BLOCK) __attribute__((amdgpu_waves_per_eu(1, WPE))) void k_center_pull_wide(
     float *__restrict__ x, int64_t ldx, const GT *__restrict__ g, int64_t ldg, float lr,
     const float *__restrict__ beta, int64_t beta_stride, const int32_t *__restrict__ cell_layer,
@@ -316,9 +314,9 @@ __global__ __launch_bounds__(GRAWA_BLOCK) __attribute__((amdgpu_waves_per_eu(1, 
 #pragma unroll
             for (int e = 0; e < V; ++e)
                 vec_set<V>(o, e, fmaf(lambda, vec_get<V>(c, e) - vec_get<V>(v[k], e), vec_get<V>(v[k], e)));
-            st_lane<GRAWA_ST_STREAM, XV>(uniform_base(xb + (int64_t)k * ldx), xoff, o);
+            st_lane<ST, XV>(uniform_base(xb + (int64_t)k * ldx), xoff, o);
         }
-        if (center_out) st_lane<GRAWA_ST_STREAM, XV>(uniform_base(center_out + cell0), xoff, c);
+        if (center_out) st_lane<ST, XV>(uniform_base(center_out + cell0), xoff, c);
     } else if (n > 0) {
 #pragma unroll
         for (int e = 0; e < V; ++e)
@@ -332,35 +330,48 @@ __global__ __launch_bounds__(GRAWA_BLOCK) __attribute__((amdgpu_waves_per_eu(1, 
     }
 }
 
-// Row-split form: the rows of a 256-column cell are divided over S groups of waves.  grid: one block per cell from
-// first_cell on (grawa_split_blocks), block S * 256 / V.  A lane owns V adjacent columns of its group's rows: Q of them, and one more for the
-// first K - S Q groups when REM (K is then S Q + 1 .. S Q + S - 1).  Each group forms its part of the
-// center, the parts are added in group order through LDS, every group pulls and stores its own rows.  A
-// wave touches one piece of 256 V bytes per row, the block starts its loads, and after the barrier its
-// stores, together.
-// Used for K >= 24 with S = 8, V = 2 (1024 threads), and for K = 16 without the SGD step with S = 4, V = 1.
-// Measured on 4.5 GB of random values, TB/s, this form against the plain one at its best cap: K = 24 5.94/5.85,
-// 28 5.97/5.84, 32 5.89/5.88, 33 5.93/5.78, 44 5.91/5.94, 56 5.59/5.62, 64 5.50/5.52; with the SGD step (fp32)
-// 24 6.00/5.75, 32 5.91/5.44, 33 6.03/5.49, 44 5.56/5.72, 63 5.45/5.53; below 24 the plain form is faster.  One
-// kernel serves eight worker counts, with one guarded row instead of a guard on each: a form that
-// guards every row (its loads then wait for one another) ran at 4.1 TB/s, 2.0 with the SGD step.  Whole MGRAWA update,
-// 11.7 M columns, K = 48, bf16 gradients: 1266 us with that form, 986 with this one.
-template <int Q, bool REM, int S, int V, bool SGD, typename GT, bool NT>
-__global__ __launch_bounds__(S *GRAWA_CELL / V) void k_center_pull_split(
+// Row-split form: the rows of W adjacent 256-column cells are divided over S groups of waves.  grid: one block per W cells
+// from first_cell on (grawa_split_blocks), block S * W * 256 / V = 1024 threads.  A lane owns V adjacent columns of its group's
+// rows: Q of them, and one more for the first K - S Q groups when REM (K is then S Q + 1 .. S Q + S - 1).  Each group forms its
+// part of the center, the parts are added in group order through LDS, every group pulls and stores its own rows.  A wave
+// touches one piece of 256 V bytes per row, the block starts its loads, and after the barrier its stores, together.
+// Two uses:
+// * One cell a block (W = 1), K >= 24 with S = 8, V = 2, and K = 16 without the SGD step with S = 4, V = 1.
+//   Measured on 4.5 GB of random values, TB/s, this form against the plain one at its best cap: K = 24 5.94/5.85,
+//   28 5.97/5.84, 32 5.89/5.88, 33 5.93/5.78, 44 5.91/5.94, 56 5.59/5.62, 64 5.50/5.52; with the SGD step (fp32)
+//   24 6.00/5.75, 32 5.91/5.44, 33 6.03/5.49, 44 5.56/5.72, 63 5.45/5.53; below 24 the plain form is faster.  One
+//   kernel serves eight worker counts, with one guarded row instead of a guard on each: a form that
+//   guards every row (its loads then wait for one another) ran at 4.1 TB/s, 2.0 with the SGD step.  Whole MGRAWA update,
+//   11.7 M columns, K = 48, bf16 gradients: 1266 us with that form, 986 with this one.
+// * Bursts (V = 4, S W = 16, WPE = 4), for large rows off the line grid: one block of 16 waves per CU, so that each CU reads
+//   and then writes W KiB of a row at once and lines are shared at the ends of those pieces only.  What bounds it is the
+//   memory's handling of the parts of lines and of the many rows.  MGRAWA update, arrays of 1.2 GB, us, the forms before / this one:
+//   7 workers 513 / 499, 8 538 / 520, 10 535 / 522, 11 525 / 513, 12 533 / 512, 16 542 / 544, 23 534 / 520, 24 582 / 561, 27 630 / 564,
+//   32 607 / 554, 48 617 / 558, 64 644 / 550; with the fp32 SGD step 10 887 / 833, 32 963 / 877, 48 1013 / 891, 64 1015 / 892;
+//   200 MB 8 to 11 workers 3 to 8 % faster, 30 to 64 2 to 10 %.  Two blocks per CU are slower than the forms before.  Up to 15
+//   workers streaming loads and stores that the L2 merges; beyond, cached loads and stores written through (12 workers 5.81 / 5.99
+//   TB/s against these, 20 workers 5.85 / 5.33).  S: 2 up to 9 workers, 4 up to 23, 8 beyond (10 workers with 2: 540 us, 9 with
+//   4 and the SGD step: 918 for 894).  With the fp32 SGD step the wide form stays for 12 to 23 workers (12, 1.2 GB: 861 / 882, 855 /
+//   848 on rows 32 and 16 bytes off a line; 15 853 / 862, 20 855 / 860).  On line-aligned rows of 40 to 64 workers bursts are no faster.
+template <int Q, bool REM, int S, int V, int W, int WPE, bool SGD, typename GT, bool NT, int ST>
+__global__ __launch_bounds__(S *W *GRAWA_CELL / V) __attribute__((amdgpu_waves_per_eu(4, WPE))) void k_center_pull_split(
     float *__restrict__ x, int64_t ldx, const GT *__restrict__ g, int64_t ldg, float lr,
     const float *__restrict__ beta, int64_t beta_stride, const int32_t *__restrict__ cell_layer,
     const int64_t *__restrict__ off, int L, int K, int64_t P, float lambda,
     float *__restrict__ center_out, float rho, int moving, unsigned first_cell)
 {
     typedef typename FloatVec<V>::T XV;
-    constexpr int LANES = GRAWA_CELL / V; // lanes of a group
+    constexpr int CELL_LANES = GRAWA_CELL / V;
+    constexpr int LANES = W * CELL_LANES; // lanes of a group
     constexpr int R = REM ? Q + 1 : Q;    // register slots per lane
-    static_assert(LANES % GRAWA_WAVE == 0, "a group is made of whole waves");
+    static_assert(CELL_LANES % GRAWA_WAVE == 0, "a cell is made of whole waves");
     static_assert(S * LANES == GRAWA_SPLIT_THREADS, "the grid is chosen for this many threads");
-    const unsigned cell = first_cell + blockIdx.x; // wave-uniform; below 2^24
-    const int64_t cell0 = (int64_t)cell * GRAWA_CELL;
     const int group = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / LANES)); // wave-uniform
-    const unsigned lane = threadIdx.x % LANES;
+    const unsigned at = threadIdx.x % LANES; // the lane's place in its group, and in its cell:
+    const unsigned lane = at % CELL_LANES;
+    unsigned cell = first_cell + blockIdx.x; // wave-uniform; below 2^24 + W
+    if constexpr (W > 1) cell = first_cell + blockIdx.x * W + __builtin_amdgcn_readfirstlane((int)(at / CELL_LANES));
+    const int64_t cell0 = (int64_t)cell * GRAWA_CELL; // W > 1: may lie past the row, whose lanes then take part in the barrier only
     const int rem = REM ? K - S * Q : 0;
     const bool more = REM && group < rem; // this group owns one row more
     const int k0 = group * Q + (REM ? (group < rem ? group : rem) : 0);
@@ -411,7 +422,7 @@ __global__ __launch_bounds__(S *GRAWA_CELL / V) void k_center_pull_split(
             if (n < V && e < n) vec_set<V>(cprev, e, center_out[col + e]);
     }
 
-    const int info = cell_layer ? cell_layer[cell] : 0;
+    const int info = cell_layer && (W == 1 || cell0 < P) ? cell_layer[cell] : 0;
     XV c = XV{};
     if (info >= 0) { // one layer for the whole cell: weights through scalar loads
         const uint64_t bb = uniform_base(beta + info + (int64_t)k0 * beta_stride);
@@ -423,15 +434,15 @@ __global__ __launch_bounds__(S *GRAWA_CELL / V) void k_center_pull_split(
                 for (int e = 0; e < V; ++e) vec_set<V>(c, e, fmaf(w, vec_get<V>(v[k], e), vec_get<V>(c, e)));
             }
     } else { // the cell holds a layer boundary
-        center_by_layer<R, V, false>(beta + (int64_t)k0 * beta_stride, beta_stride, off, L, P, cell0, ~info, col,
+        center_by_layer<R, V, (W > 1)>(beta + (int64_t)k0 * beta_stride, beta_stride, off, L, P, cell0, ~info, col,
                               [&](int k) { return k < Q || more; }, v, c);
     }
     __shared__ XV part[S][LANES];
-    part[group][lane] = c;
+    part[group][at] = c;
     __syncthreads();
-    c = part[0][lane];
+    c = part[0][at];
 #pragma unroll
-    for (int s = 1; s < S; ++s) c += part[s][lane];
+    for (int s = 1; s < S; ++s) c += part[s][at];
     if (moving) {
 #pragma unroll
         for (int e = 0; e < V; ++e)
@@ -445,9 +456,9 @@ __global__ __launch_bounds__(S *GRAWA_CELL / V) void k_center_pull_split(
 #pragma unroll
                 for (int e = 0; e < V; ++e)
                     vec_set<V>(o, e, fmaf(lambda, vec_get<V>(c, e) - vec_get<V>(v[k], e), vec_get<V>(v[k], e)));
-                st_lane<NT ? GRAWA_ST_STREAM : GRAWA_ST_CACHED, XV>(uniform_base(xb + (int64_t)k * ldx), xoff, o);
+                st_lane<ST, XV>(uniform_base(xb + (int64_t)k * ldx), xoff, o);
             }
-        if (center_out && group == 0) st_lane<NT ? GRAWA_ST_STREAM : GRAWA_ST_CACHED, XV>(uniform_base(center_out + cell0), xoff, c);
+        if (center_out && group == 0) st_lane<ST, XV>(uniform_base(center_out + cell0), xoff, c);
     } else if (n > 0) {
 #pragma unroll
         for (int e = 0; e < V; ++e)
@@ -529,8 +540,7 @@ template <int K, bool SGD, typename GT, bool NT, bool TILES> static void launch_
                           GRAWA_CP_CELLS, (const int64_t *)p->d_off, p->L, p->P, lambda, center_out, rho, moving, tw);
 }
 
-// The wide form's cap (best of 2, 3, 4 and 8 waves for K <= 5; one too many costs 3 to 5 %, and more than it gains over
-// the plain form).  It is used for the worker counts where it is at least as fast as the plain form (GRAWA_WIDE_COUNTS).
+// The wide form's cap (best of 2, 3, 4 and 8 waves; one too many costs 3 to 5 %, and more than it gains over the plain form).
 constexpr int grawa_waves_wide(int k, bool sgd /* fp32 gradients */)
 {
     if (k == 1) return 8;
@@ -539,24 +549,43 @@ constexpr int grawa_waves_wide(int k, bool sgd /* fp32 gradients */)
     return k <= 5 ? 2 : 1;
 }
 
-template <int K, bool SGD, typename GT, bool LNT> static void launch_wide(GRAWA_CP_ARGS)
+// The wide form off the line grid: with the fp32 SGD step streaming loads and stores that the L2 merges, else cached loads and
+// stores written through.  LGRAWA with the step, us, cached loads / streaming: 2 workers 140 MB 98.2 / 94.1, 1.2 GB 783 / 775, 4
+// 99.3 / 98.1 and 789 / 787, 5 100.4 / 98.9 and 820 / 798, but 3 1.2 GB 798 / 810; MGRAWA without it 2 477 / 481, 3 482 / 489,
+// 4 491 / 507, 5 489 / 498; with bf16 gradients 140 MB 4 workers 80.3 / 83.2, 5 80.1 / 82.5.
+constexpr bool grawa_wide_merges(int k, bool sgd /* fp32 gradients */) { return sgd && k <= 5 && k != 3; }
+
+template <int K, bool SGD, typename GT, bool LNT, int ST> static void launch_wide(GRAWA_CP_ARGS)
 {
     (void)tw;
-    hipExtLaunchKernelGGL((k_center_pull_wide<K, SGD, GT, LNT, grawa_waves_wide(K, SGD && sizeof(GT) == 4)>), dim3((unsigned)((p->n_cells + 3) / 4)),
+    hipExtLaunchKernelGGL((k_center_pull_wide<K, SGD, GT, LNT, ST, grawa_waves_wide(K, SGD && sizeof(GT) == 4)>), dim3((unsigned)((p->n_cells + 3) / 4)),
                           dim3(GRAWA_BLOCK), 0, s, e0, e1, 0, x, ldx, (const GT *)g, ldg, lr, beta, GRAWA_CP_STRIDE,
                           GRAWA_CP_CELLS, (const int64_t *)p->d_off, p->L, p->P, lambda, center_out, rho, moving);
 }
 
-template <int Q, bool REM, int S, int V, bool SGD, typename GT, bool NT> static void launch_split(GRAWA_CP_ARGS)
+// W cells a block; WPE caps the waves per SIMD.
+template <int Q, bool REM, int S, int V, int W, int WPE, bool SGD, typename GT, bool NT, int ST> static void launch_split(GRAWA_CP_ARGS)
 {
     for (int64_t at = 0; at < p->n_cells;) { // one launch but for the longest rows
         const int64_t n = grawa_split_blocks(p->n_cells, at);
-        hipExtLaunchKernelGGL((k_center_pull_split<Q, REM, S, V, SGD, GT, NT>), dim3((unsigned)n),
+        hipExtLaunchKernelGGL((k_center_pull_split<Q, REM, S, V, W, WPE, SGD, GT, NT, ST>), dim3((unsigned)((n + W - 1) / W)),
                               dim3(GRAWA_SPLIT_THREADS), 0, s, at == 0 ? e0 : nullptr, at + n == p->n_cells ? e1 : nullptr, 0,
                               x, ldx, (const GT *)g, ldg, lr, beta, GRAWA_CP_STRIDE, GRAWA_CP_CELLS,
                               (const int64_t *)p->d_off, p->L, p->K, p->P, lambda, center_out, rho, moving, (unsigned)at);
         at += n;
     }
+}
+
+// Row-split, 8-byte lanes, one cell a block.
+template <int Q, bool REM, bool SGD, typename GT, bool NT> static void launch_cell(GRAWA_CP_ARGS)
+{
+    launch_split<Q, REM, 8, 2, 1, 8, SGD, GT, NT, NT ? GRAWA_ST_STREAM : GRAWA_ST_CACHED>(GRAWA_CP_PASS);
+}
+
+// Row-split, 16-byte lanes, W cells a block and one block per CU: S W = 16 waves, 4 per SIMD.
+template <int Q, bool REM, int S, bool SGD, typename GT, bool NT, int ST> static void launch_burst(GRAWA_CP_ARGS)
+{
+    launch_split<Q, REM, S, 4, 16 / S, 4, SGD, GT, NT, ST>(GRAWA_CP_PASS);
 }
 
 // One plain kernel per worker count up to 23, on few cells up to 32 (fully unrolled); the rest up to 71 workers share the
@@ -567,13 +596,13 @@ template <bool SGD, typename GT, bool NT> static hipError_t dispatch_cp(GRAWA_CP
     constexpr int WIDE_TO = !NT ? 0 : SGD && sizeof(GT) == 4 ? 1 : 2;
 #define GRAWA_CP_PLAIN(N)                                                                       \
     case N:                                                                                     \
-        if constexpr (N <= WIDE_TO) launch_wide<N, SGD, GT, true>(GRAWA_CP_PASS);               \
+        if constexpr (N <= WIDE_TO) launch_wide<N, SGD, GT, true, GRAWA_ST_STREAM>(GRAWA_CP_PASS);               \
         else launch_plain<N, SGD, GT, NT, false>(GRAWA_CP_PASS);                                \
         return hipGetLastError();
-#define GRAWA_CP_SPLIT(N)                                                            \
-    case N:                                                                          \
-        if (p->K % 8 == 0) launch_split<N, false, 8, 2, SGD, GT, NT>(GRAWA_CP_PASS); \
-        else launch_split<N, true, 8, 2, SGD, GT, NT>(GRAWA_CP_PASS);                \
+#define GRAWA_CP_SPLIT(N)                                                     \
+    case N:                                                                   \
+        if (p->K % 8 == 0) launch_cell<N, false, SGD, GT, NT>(GRAWA_CP_PASS); \
+        else launch_cell<N, true, SGD, GT, NT>(GRAWA_CP_PASS);               \
         return hipGetLastError();
     switch (p->K) {
         GRAWA_CP_PLAIN(1) GRAWA_CP_PLAIN(2) GRAWA_CP_PLAIN(3) GRAWA_CP_PLAIN(4) GRAWA_CP_PLAIN(5) GRAWA_CP_PLAIN(6)
@@ -582,7 +611,7 @@ template <bool SGD, typename GT, bool NT> static hipError_t dispatch_cp(GRAWA_CP
         GRAWA_CP_PLAIN(19) GRAWA_CP_PLAIN(20) GRAWA_CP_PLAIN(21) GRAWA_CP_PLAIN(22) GRAWA_CP_PLAIN(23)
     case 16:
         if constexpr (SGD) launch_plain<16, SGD, GT, NT, false>(GRAWA_CP_PASS);
-        else launch_split<4, false, 4, 1, SGD, GT, NT>(GRAWA_CP_PASS);
+        else launch_split<4, false, 4, 1, 1, 8, SGD, GT, NT, NT ? GRAWA_ST_STREAM : GRAWA_ST_CACHED>(GRAWA_CP_PASS);
         return hipGetLastError();
     }
     if constexpr (!NT) // never as large as the streaming passes
@@ -601,16 +630,47 @@ template <bool SGD, typename GT, bool NT> static hipError_t dispatch_cp(GRAWA_CP
 #undef GRAWA_CP_SPLIT
 }
 
-// Rows off the line grid (GRAWA_WIDE_COUNTS).  A worker count without a kernel is an error, never a call that does nothing.
+// Rows off the line grid, 16-byte lanes: up to 5 workers, and with the fp32 SGD step, the wide form, else row-split bursts.  A
+// worker count without a kernel is an error, never a call that does nothing.
 template <bool SGD, typename GT> static hipError_t dispatch_cp_wide(GRAWA_CP_ARGS)
 {
-#define GRAWA_CP_WIDE(N) \
-    case N: launch_wide<N, SGD, GT, false>(GRAWA_CP_PASS); return hipGetLastError();
+    constexpr bool F32_SGD = SGD && sizeof(GT) == 4;
+#define GRAWA_CP_WIDE(N)                                                                                                    \
+    case N:                                                                                                                 \
+        if constexpr (grawa_wide_merges(N, F32_SGD)) launch_wide<N, SGD, GT, true, GRAWA_ST_MERGE>(GRAWA_CP_PASS);          \
+        else if constexpr (N <= 5 || F32_SGD) launch_wide<N, SGD, GT, false, GRAWA_ST_STREAM>(GRAWA_CP_PASS);               \
+        else if constexpr (N < 16) launch_burst<N / 4, (N % 4 != 0), 4, SGD, GT, true, GRAWA_ST_MERGE>(GRAWA_CP_PASS);      \
+        else launch_burst<N / 4, (N % 4 != 0), 4, SGD, GT, false, GRAWA_ST_STREAM>(GRAWA_CP_PASS);                          \
+        return hipGetLastError();
     switch (p->K) {
         GRAWA_WIDE_COUNTS(GRAWA_CP_WIDE)
     }
     return hipErrorInvalidValue;
 #undef GRAWA_CP_WIDE
+}
+
+// Row-split bursts for the worker counts between and beyond those (grawa_burst_form).
+template <bool SGD, typename GT> static hipError_t dispatch_cp_burst(GRAWA_CP_ARGS)
+{
+#define GRAWA_CP_BURST2(N) \
+    case N: launch_burst<N / 2, (N % 2 != 0), 2, SGD, GT, true, GRAWA_ST_MERGE>(GRAWA_CP_PASS); return hipGetLastError();
+#define GRAWA_CP_BURST4(N) \
+    case N: launch_burst<N / 4, (N % 4 != 0), 4, SGD, GT, true, GRAWA_ST_MERGE>(GRAWA_CP_PASS); return hipGetLastError();
+#define GRAWA_CP_BURST8(N)                                                                                     \
+    case N:                                                                                                    \
+        if (p->K % 8 == 0) launch_burst<N, false, 8, SGD, GT, false, GRAWA_ST_STREAM>(GRAWA_CP_PASS);          \
+        else launch_burst<N, true, 8, SGD, GT, false, GRAWA_ST_STREAM>(GRAWA_CP_PASS);                         \
+        return hipGetLastError();
+    switch (p->K) {
+        GRAWA_CP_BURST2(6) GRAWA_CP_BURST2(7) GRAWA_CP_BURST2(8) GRAWA_CP_BURST2(9) GRAWA_CP_BURST4(10) GRAWA_CP_BURST4(11)
+    }
+    switch (p->K / 8) {
+        GRAWA_CP_BURST8(3) GRAWA_CP_BURST8(4) GRAWA_CP_BURST8(5) GRAWA_CP_BURST8(6) GRAWA_CP_BURST8(7) GRAWA_CP_BURST8(8)
+    }
+    return hipErrorInvalidValue;
+#undef GRAWA_CP_BURST2
+#undef GRAWA_CP_BURST4
+#undef GRAWA_CP_BURST8
 }
 
 // Weights straight from the tile sums (GRAWA_TILES_COUNTS), cached accesses.
@@ -643,12 +703,14 @@ hipError_t grawa_launch_center_pull(const grawa_plan *p, float *x, int64_t ldx, 
     bool nt = large && rows_line_aligned(x, ldx, 4) && (!center_out || rows_line_aligned(center_out, 0, 4));
     if (fuse_sgd) nt = nt && rows_line_aligned(g_sgd, ldg_sgd, dt == GRAWA_BF16 ? 2 : 4);
     const bool wide = large && !nt && grawa_wide_has_kernel(p->K);
+    const bool burst = large && !nt && grawa_burst_form(p->K, fuse_sgd && dt != GRAWA_BF16);
     const void *g = g_sgd;
     const int64_t ldg = ldg_sgd;
 #define GRAWA_CP_GO(SGD, GT)                                                      \
     (!beta  ? dispatch_cp_tiles<SGD, GT>(GRAWA_CP_PASS)                           \
      : nt   ? dispatch_cp<SGD, GT, true>(GRAWA_CP_PASS)                           \
      : wide ? dispatch_cp_wide<SGD, GT>(GRAWA_CP_PASS)                            \
+     : burst ? dispatch_cp_burst<SGD, GT>(GRAWA_CP_PASS)                          \
             : dispatch_cp<SGD, GT, false>(GRAWA_CP_PASS))
     if (!fuse_sgd) return GRAWA_CP_GO(false, float);
     return dt == GRAWA_BF16 ? GRAWA_CP_GO(true, uint16_t) : GRAWA_CP_GO(true, float);

@@ -17,8 +17,9 @@ static inline int64_t grawa_split_blocks(int64_t n_cells, int64_t at)
     return n_cells - at < GRAWA_SPLIT_LAUNCH_CELLS ? n_cells - at : GRAWA_SPLIT_LAUNCH_CELLS;
 }
 
-// The worker counts that have a kernel of the wide form, and of the form with the weights from the tile sums.  The rules
-// below and the dispatch (grawa_pull.hip) are made from the same lists.
+// The worker counts that have a kernel of their own for large rows off the line grid (up to 5 the wide form, from 12 on
+// row-split bursts), and of the form with the weights from the tile sums.  The rules below and the dispatch (grawa_pull.hip)
+// are made from the same lists.
 #define GRAWA_WIDE_COUNTS(X) \
     X(1) X(2) X(3) X(4) X(5) X(12) X(13) X(14) X(15) X(16) X(17) X(18) X(19) X(20) X(21) X(22) X(23)
 #define GRAWA_TILES_COUNTS(X) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15)
@@ -30,6 +31,13 @@ static inline bool grawa_wide_has_kernel(int K)
         GRAWA_WIDE_COUNTS(GRAWA_COUNT_TRUE)
     }
     return false;
+}
+// Row-split bursts by K / 2, K / 4 and K / 8 serve the counts between and beyond those.
+// Nine workers with the fp32 SGD step (10 loads of a lane in two groups of waves, 6 in four) keep the plain form: 1.2 GB 866 us
+// for 884 and 890 for 918 (200 MB 150.5 / 146.6).
+static inline bool grawa_burst_form(int K, bool f32_sgd)
+{
+    return K >= 6 && K <= 71 && !grawa_wide_has_kernel(K) && !(K == 9 && f32_sgd);
 }
 static inline bool grawa_tiles_has_kernel(int K)
 {

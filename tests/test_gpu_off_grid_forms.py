@@ -64,3 +64,51 @@ def test_local_steps_either_side_of_a_line(step, dtype, mb):
             close(x[k, :P], x64 - lr64 * (d + m * nb), size + 2 * lr * (b64.abs() + g64.abs()))
             assert (buf[k, P:] == 777.0).all()
         assert (x[k, P:] == 777.0).all()
+
+
+# Each number of wave groups (2, 4, 8) with and without the guarded row, the first and last worker count of each, and the
+# neighbours of the dispatch's lines (5/6, 9/10, 11/12, 15/16, 23/24, 71/72).
+@pytest.mark.parametrize("K", [5, 6, 9, 10, 11, 12, 15, 16, 19, 23, 24, 25, 40, 63, 71, 72])
+@pytest.mark.parametrize("kind", ["pull", "easgd", "f32", "bf16"])
+def test_pull_of_rows_off_the_grid(K, kind):
+    # cells of one layer, of 2 to 8 and of 256, a boundary on a cell's edge; the row ends inside a lane, a cell and a block
+    P = (130 * MB) // (4 * K) // 2048 * 2048 + 2048 + 256 * (K % 5) + 1 + K % 3
+    sizes = [256, 100, 412] + [32] * 8 + [1] * 256 + [300] * 200
+    sizes += [P - sum(sizes) - 130, 120, 10]
+    L, gen = len(sizes), torch.Generator(device=DEV).manual_seed(K)
+    off = torch.tensor([0] + sizes).cumsum(0)
+    x = rows(K, P, torch.float32, gen, 0.05)
+    x0, lam = x.clone(), 0.25
+    cen = torch.full(((P + 7) // 4 * 4,), 777.0, device=DEV)
+    layer = torch.repeat_interleave(torch.arange(L, device=DEV), torch.tensor(sizes, device=DEV))
+    lr = 0.0
+    with grawa.Plan(K, P, off.numpy()) as plan:
+        if kind == "pull":
+            beta = torch.rand((K, L), device=DEV, generator=gen)
+            plan.center_pull(x[:, :P], beta, lam, center_out=cen[:P])
+        elif kind == "easgd":
+            cen[:P].normal_(0.0, 0.05, generator=gen)
+            c0, beta = cen[:P].double(), torch.full((K, L), 1.0 / K, device=DEV)
+            plan.easgd_update(x[:, :P], lam, 0.5, cen[:P])
+        else:
+            lr = 0.1
+            g = rows(K, P, torch.float32 if kind == "f32" else torch.bfloat16, gen, 1.0)
+            beta = torch.zeros((K, L), device=DEV)
+            plan.lgrawa_update_sgd(x[:, :P], g[:, :P], lam, g[:, :P], lr, center_out=cen[:P], weights_out=beta)
+    lr64 = float(torch.tensor(lr))
+    size, c = torch.zeros(P, dtype=torch.float64, device=DEV), torch.zeros(P, dtype=torch.float64, device=DEV)
+    moved = lambda k: x0[k, :P].double() - lr64 * g[k, :P].double() if lr else x0[k, :P].double()
+    for k in range(K):
+        v, b = moved(k), beta[k].double()[layer]
+        c += b * v
+        size = torch.maximum(size, (x0[k, :P].double().abs() + (lr * g[k, :P].double().abs() if lr else 0.0)) * (b * K).clamp_min(1.0))
+    if kind == "easgd":
+        c = c0 + 0.5 * (c - c0)
+        size = torch.maximum(size, c0.abs())
+    # the step, K products and sums and the pull, each rounded to 24 bits of a value no larger than K / K of the largest term
+    tol = (K + 5) * 2.0 ** -24
+    assert float(((cen[:P].double() - c).abs() / size.clamp_min(1e-30)).max()) <= tol
+    for k in range(K):
+        v = moved(k)
+        assert float(((x[k, :P].double() - (v + lam * (c - v))).abs() / size.clamp_min(1e-30)).max()) <= 2 * tol
+    assert (x[:, P:] == 777.0).all() and (cen[P:] == 777.0).all()
