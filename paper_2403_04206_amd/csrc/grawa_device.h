@@ -254,7 +254,7 @@ template <int V> __device__ __forceinline__ void vec_set(typename FloatVec<V>::T
     else v[c] = f;
 }
 
-// From what size of x (K P floats) on a pass streams past the caches.  The lines lie where the pass is faster on
+// From what size of x (K P floats; of x and g in a pull with the SGD step) on a pass streams past the caches.  The lines lie where the pass is faster on
 // arrays that the caches do not hold when it starts, as after a backward pass.  Cached against streaming, us, on three
 // such sets in turn (in brackets: one set again and again, which the 256 MB last-level cache partly holds):
 //   pull            MGRAWA, 4 workers,  80 MB x: 43.0/42.5 (38/39), 120 MB: 75/69, 187 MB: 102.8/93.2 (87.2/90.5)

@@ -510,7 +510,7 @@ __global__ __launch_bounds__(GRAWA_CELL) void k_center_pull_any(
 // launchers
 // ---------------------------------------------------------------------------------
 
-// Waves per SIMD the plain form is capped at, from sweeps of this kernel over K and the cap on the part, on arrays
+// Waves per SIMD the plain form is capped at on large arrays, from sweeps of this kernel over K and the cap on the part, on arrays
 // of 1 to 2 GB holding random values and three row lengths (best throughput at roughly 24 to 36 four-byte row
 // loads in flight per SIMD; a two-byte load counts half).  The best caps, TB/s at the best and one wave more:
 // K = 4 6.71 (8), 6 6.66/6.57, 8 6.57/6.46, 12 6.41/6.28, 22 6.16/5.95; with the fp32 SGD step
@@ -527,17 +527,25 @@ constexpr int grawa_waves_for(int k, bool sgd, bool bf16)
 
 #define GRAWA_CP_ARGS                                                                                                 \
     const grawa_plan *p, float *x, int64_t ldx, const void *g, int64_t ldg, float lr, const float *beta, int per_layer, \
-        float lambda, float *center_out, float rho, int moving, const TileWeights &tw, hipStream_t s, hipEvent_t e0,     \
-        hipEvent_t e1
-#define GRAWA_CP_PASS p, x, ldx, g, ldg, lr, beta, per_layer, lambda, center_out, rho, moving, tw, s, e0, e1
+        float lambda, float *center_out, float rho, int moving, const TileWeights &tw, bool capped, hipStream_t s,       \
+        hipEvent_t e0, hipEvent_t e1
+#define GRAWA_CP_PASS p, x, ldx, g, ldg, lr, beta, per_layer, lambda, center_out, rho, moving, tw, capped, s, e0, e1
 #define GRAWA_CP_STRIDE per_layer ? (int64_t)p->L : (int64_t)1
 #define GRAWA_CP_CELLS per_layer ? (const int32_t *)p->d_cell_layer : (const int32_t *)nullptr
 
 template <int K, bool SGD, typename GT, bool NT, bool TILES> static void launch_plain(GRAWA_CP_ARGS)
 {
-    hipExtLaunchKernelGGL((k_center_pull<K, SGD, GT, NT, grawa_waves_for(K, SGD, sizeof(GT) == 2), TILES>), dim3((unsigned)p->n_cells),
-                          dim3(GRAWA_CELL), 0, s, e0, e1, 0, x, ldx, (const GT *)g, ldg, lr, beta, GRAWA_CP_STRIDE,
-                          GRAWA_CP_CELLS, (const int64_t *)p->d_off, p->L, p->P, lambda, center_out, rho, moving, tw);
+    constexpr int CAP = grawa_waves_for(K, SGD, sizeof(GT) == 2), WPE = NT ? CAP : 8;
+    // Cached accesses: the cap, where it is wanted, is set by the LDS a block asks for, of the CU's 160 KB.  Up to 128 MB the
+    // caches answer, and what counts is that all blocks of a small array run at once (1054 blocks of 8 workers are one more
+    // round than 4 per CU hold).  LGRAWA with the fp32 SGD step, us, capped / not: 8 workers, 270 k columns 13.9 / 12.0,
+    // 317 k 14.9 / 13.1, 10 workers 256 k 15.6 / 13.7, 15 workers 174 k 17.3 / 15.4; MGRAWA 8 workers, 1.6 M 35.0 / 31.4, 3.1 M
+    // 58.8 / 54.7, 20 workers 312 k 23.3 / 21.9.  Rows off the grid from 64 MB on: 15 workers, 90 MB 55.5 / 57.4, 6 workers with
+    // the fp32 step 72.6 / 74.6.
+    const size_t lds = WPE > CAP && capped ? ((size_t)160 << 10) / (CAP + 1) + 1024 : 0;
+    hipExtLaunchKernelGGL((k_center_pull<K, SGD, GT, NT, WPE, TILES>), dim3((unsigned)p->n_cells), dim3(GRAWA_CELL), lds, s, e0,
+                          e1, 0, x, ldx, (const GT *)g, ldg, lr, beta, GRAWA_CP_STRIDE, GRAWA_CP_CELLS,
+                          (const int64_t *)p->d_off, p->L, p->P, lambda, center_out, rho, moving, tw);
 }
 
 // The wide form's cap (best of 2, 3, 4 and 8 waves; one too many costs 3 to 5 %, and more than it gains over the plain form).
@@ -558,6 +566,7 @@ constexpr bool grawa_wide_merges(int k, bool sgd /* fp32 gradients */) { return 
 template <int K, bool SGD, typename GT, bool LNT, int ST> static void launch_wide(GRAWA_CP_ARGS)
 {
     (void)tw;
+    (void)capped;
     hipExtLaunchKernelGGL((k_center_pull_wide<K, SGD, GT, LNT, ST, grawa_waves_wide(K, SGD && sizeof(GT) == 4)>), dim3((unsigned)((p->n_cells + 3) / 4)),
                           dim3(GRAWA_BLOCK), 0, s, e0, e1, 0, x, ldx, (const GT *)g, ldg, lr, beta, GRAWA_CP_STRIDE,
                           GRAWA_CP_CELLS, (const int64_t *)p->d_off, p->L, p->P, lambda, center_out, rho, moving);
@@ -698,10 +707,17 @@ hipError_t grawa_launch_center_pull(const grawa_plan *p, float *x, int64_t ldx, 
         while (group * p->K > GRAWA_WAVE) group >>= 1;
         tw = TileWeights{p->d_partials, p->n_tiles, p->d_layer_tile0, p->d_layer_tile1, weights_out, p->d_flags, group};
     }
-    // Streaming accesses pay off only when the arrays do not fit the last-level cache anyway.
-    const bool large = beta && (int64_t)p->K * p->P * 4 > GRAWA_STREAMING_MIN_BYTES;
-    bool nt = large && rows_line_aligned(x, ldx, 4) && (!center_out || rows_line_aligned(center_out, 0, 4));
+    // Streaming accesses pay off only when the arrays do not fit the last-level cache anyway: x, and g where the step is fused.
+    // (By x alone, fused LGRAWA updates, three sets in turn, us, line-aligned rows / rows off the grid: 70 MB fp32 2 workers 57.3 ->
+    // 53.8 / 58.4 -> 52.4, 6 55.2 -> 51.8 / 57.3 -> 56.7, 48 64.4 -> 60.9 / 67.1 -> 60.8; 95 MB bf16 2 68.4 -> 56.6 / 70.2 -> 57.4, 12
+    // 64.7 -> 58.6 / 67.4 -> 64.6, 32 68.7 -> 62.6 / 71.4 -> 68.6; 125 MB fp32 6 91.8 -> 84.4 / 94.7 -> 92.0.)
+    const int64_t bytes = (int64_t)p->K * p->P * (4 + (fuse_sgd ? (dt == GRAWA_BF16 ? 2 : 4) : 0));
+    const bool large = beta && bytes > GRAWA_STREAMING_MIN_BYTES;
+    bool nt = rows_line_aligned(x, ldx, 4) && (!center_out || rows_line_aligned(center_out, 0, 4));
     if (fuse_sgd) nt = nt && rows_line_aligned(g_sgd, ldg_sgd, dt == GRAWA_BF16 ? 2 : 4);
+    // Cached accesses of small arrays want no cap, unless rows off the grid make many requests of them (launch_plain).
+    const bool capped = large || (!nt && bytes > GRAWA_STREAMING_MIN_BYTES / 2);
+    nt = nt && large;
     const bool wide = large && !nt && grawa_wide_has_kernel(p->K);
     const bool burst = large && !nt && grawa_burst_form(p->K, fuse_sgd && dt != GRAWA_BF16);
     const void *g = g_sgd;

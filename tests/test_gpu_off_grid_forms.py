@@ -6,7 +6,7 @@ bits of a value no larger than the sum of the magnitudes that enter: 4 * 2^-24 o
 import pytest
 import torch
 
-from paper_2403_04206_amd import grawa
+from paper_2403_04206_amd import grawa, workloads as W
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -112,3 +112,33 @@ def test_pull_of_rows_off_the_grid(K, kind):
         v = moved(k)
         assert float(((x[k, :P].double() - (v + lam * (c - v))).abs() / size.clamp_min(1e-30)).max()) <= 2 * tol
     assert (x[:, P:] == 777.0).all() and (cen[P:] == 777.0).all()
+
+
+# A fused pull streams by the size of x and g together (128 MB), with the plain form's cap on cached accesses from 64 MB on
+# where rows are off the grid: either side of both lines, for a cap of 2 (17 workers) and of 5 or 4 waves.
+@pytest.mark.parametrize("K", [4, 6, 17, 24])
+@pytest.mark.parametrize("dtype,mb", [("f32", 60), ("f32", 68), ("bf16", 40), ("bf16", 80), ("bf16", 90)])
+@pytest.mark.parametrize("pad", [0, 8])
+def test_fused_pull_either_side_of_the_lines(K, dtype, mb, pad):
+    P = mb * MB // 4 // K // 1024 * 1024 + 5
+    w = W.Workload("fused_K%d" % K, K, [P // 3, 1, 700, P - P // 3 - 701], grad_dtype=dtype, lam=0.25, lr=0.1, seed=(9, K + mb))
+    x, g = W.make_inputs(w, device=DEV, ld_pad=pad)
+    x0 = x.clone()
+    cen = torch.empty(W.round_up(P, 4), device=DEV)
+    beta = torch.zeros((K, w.L), device=DEV)
+    with grawa.Plan(K, P, w.offsets) as plan:
+        plan.lgrawa_update_sgd(x[:, :P], g[:, :P], 0.25, g[:, :P], 0.1, center_out=cen, weights_out=beta)
+        torch.cuda.synchronize()
+    layer = torch.repeat_interleave(torch.arange(w.L, device=DEV), torch.tensor(w.offsets, device=DEV).diff())
+    lr = float(torch.tensor(0.1))
+    c, size = torch.zeros(P, dtype=torch.float64, device=DEV), torch.zeros(P, dtype=torch.float64, device=DEV)
+    for k in range(K):
+        b = beta[k].double()[layer]
+        c += b * (x0[k, :P].double() - lr * g[k, :P].double())
+        size = torch.maximum(size, (x0[k, :P].double().abs() + lr * g[k, :P].double().abs()) * (b * K).clamp_min(1.0))
+    tol = (K + 5) * 2.0 ** -24                           # as in the test above
+    assert float(((cen[:P].double() - c).abs() / size.clamp_min(1e-30)).max()) <= tol
+    for k in range(K):
+        v = x0[k, :P].double() - lr * g[k, :P].double()
+        assert float(((x[k, :P].double() - (v + 0.25 * (c - v))).abs() / size.clamp_min(1e-30)).max()) <= 2 * tol
+    assert torch.equal(x[:, P:], x0[:, P:])
