@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "grawa_internal.h"
+#include "grawa_route.h"
 
 namespace {
 
@@ -78,7 +79,9 @@ grawa_status_t run_update(grawa_plan *p, float *x, int64_t ldx, const void *g, i
     const bool prof = prof_active(p);
     hipEvent_t *ev = prof ? p->ev + 4 * (size_t)p->profile_n : nullptr;
 
-    GRAWA_TRY_HIP(grawa_launch_sumsq(p, g, ldg, dt, s, prof ? ev[0] : nullptr, prof ? ev[1] : nullptr));
+    grawa_plan for_norms = *p;
+    if (fuse_sgd && g_sgd == g && ldg_sgd == ldg) for_norms.cached_cols = grawa_cached_grad_cols(p->K, p->P, dt == GRAWA_BF16 ? 2 : 4);
+    GRAWA_TRY_HIP(grawa_launch_sumsq(&for_norms, g, ldg, dt, s, prof ? ev[0] : nullptr, prof ? ev[1] : nullptr));
 
     const bool from_tiles = per_layer && grawa_pull_from_tiles(p);
     const int goal = per_layer ? GRAWA_GOAL_LAYER_WEIGHTS

@@ -133,13 +133,14 @@ template <> struct Grad<float> {
     {
         return ld_lane<NT, float>(base, off);
     }
-    // 8 bytes (2 floats) at p, 8-byte aligned, streaming load; and their squares added to acc.
+    // 8 bytes (2 floats) at p, 8-byte aligned; and their squares added to acc.
     // The square of a widened fp32 (or bf16) value is exact in fp64, so no gradient magnitude
     // that the input type can hold underflows or overflows here.
     typedef v2f Vec8;
-    static __device__ __forceinline__ Vec8 load8(const float *p)
+    template <bool NT> static __device__ __forceinline__ Vec8 load8(const float *p)
     {
-        return __builtin_nontemporal_load(reinterpret_cast<const v2f *>(p));
+        const v2f *q = reinterpret_cast<const v2f *>(p);
+        return NT ? __builtin_nontemporal_load(q) : *q;
     }
     static __device__ __forceinline__ double sumsq8(Vec8 q, double acc)
     {
@@ -156,11 +157,12 @@ template <> struct Grad<uint16_t> { // bfloat16 bit patterns
     {
         return bf16_one(ld_lane<NT, uint16_t>(base, off));
     }
-    // 8 bytes (4 bf16) at p, 8-byte aligned, streaming load; and their squares added to acc
+    // 8 bytes (4 bf16) at p, 8-byte aligned; and their squares added to acc
     typedef v2u Vec8;
-    static __device__ __forceinline__ Vec8 load8(const uint16_t *p)
+    template <bool NT> static __device__ __forceinline__ Vec8 load8(const uint16_t *p)
     {
-        return __builtin_nontemporal_load(reinterpret_cast<const v2u *>(p));
+        const v2u *q = reinterpret_cast<const v2u *>(p);
+        return NT ? __builtin_nontemporal_load(q) : *q;
     }
     static __device__ __forceinline__ double sumsq8(Vec8 q, double acc)
     {

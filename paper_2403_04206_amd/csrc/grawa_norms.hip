@@ -8,7 +8,7 @@
 //   k_leader_weights   LSGD (leader) weights                               [App. F]
 //
 // The norm pass is a read-only stream: it runs fastest with several non-temporal loads per
-// lane in flight and a capped occupancy.  Squares and sums are fp64 throughout, added in a
+// lane in flight and a capped occupancy; what a fused pull reads again is read through the caches (grawa_cached_grad_cols).  Squares and sums are fp64 throughout, added in a
 // fixed order (no sum is formed by atomics; how norms pass between the blocks of a launch: grawa_scores.h),
 // so results are bit-reproducible.
 #include "grawa_route.h"
@@ -19,7 +19,7 @@
 // ---------------------------------------------------------------------------------
 
 // grid (n_tiles, K), block 256.  partials[k][tile] = sum over the tile of g[k][i]^2.  Also clears the arrival counter
-// of the launch that follows (null where none arrives).
+// of the launch that follows (null where none arrives).  Tiles that start before cached_cols are read with cached loads.
 // Each lane issues 8 independent 8-byte streaming loads per trip and keeps one accumulator
 // per load; with the occupancy capped at 4 waves per SIMD this shape measured fastest for a
 // read-only stream on this part (7.3-7.4 TB/s; 16-byte loads at full occupancy 6.9-7.0).
@@ -31,7 +31,7 @@
 
 // The last, partial trip of up to N loads per lane: a lane past the end loads a clamped (valid) address and
 // discards the value.
-template <typename GT, int N>
+template <typename GT, bool NT, int N>
 __device__ __forceinline__ void sumsq_rest(const GT *body, int j0, int nvec, double (&acc)[GRAWA_SUMSQ_U])
 {
     if (j0 >= nvec) return;
@@ -39,7 +39,7 @@ __device__ __forceinline__ void sumsq_rest(const GT *body, int j0, int nvec, dou
 #pragma unroll
     for (int u = 0; u < N; ++u) {
         const int j = j0 + u * GRAWA_BLOCK;
-        q[u] = Grad<GT>::load8(body + (int64_t)(j < nvec ? j : j0) * Grad<GT>::VEC8);
+        q[u] = Grad<GT>::template load8<NT>(body + (int64_t)(j < nvec ? j : j0) * Grad<GT>::VEC8);
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -49,10 +49,37 @@ __device__ __forceinline__ void sumsq_rest(const GT *body, int j0, int nvec, dou
     }
 }
 
+// The 8-byte vectors 0 .. nvec - 1 of a tile.
+template <typename GT, bool NT>
+__device__ __forceinline__ void sumsq_body(const GT *body, int nvec, double (&acc)[GRAWA_SUMSQ_U])
+{
+    constexpr int V = Grad<GT>::VEC8;
+    const int tid = threadIdx.x;
+    // All loads of a trip are issued before any is used.  Full trips need no bounds checks.
+    typename Grad<GT>::Vec8 q[GRAWA_SUMSQ_U];
+    int j0 = tid;
+    for (; j0 + (GRAWA_SUMSQ_U - 1) * GRAWA_BLOCK < nvec; j0 += GRAWA_SUMSQ_U * GRAWA_BLOCK) {
+#pragma unroll
+        for (int u = 0; u < GRAWA_SUMSQ_U; ++u)
+            q[u] = Grad<GT>::template load8<NT>(body + (int64_t)(j0 + u * GRAWA_BLOCK) * V);
+        __builtin_amdgcn_sched_barrier(0); // keep the arithmetic from being hoisted between the loads
+#pragma unroll
+        for (int u = 0; u < GRAWA_SUMSQ_U; ++u) acc[u] = Grad<GT>::sumsq8(q[u], acc[u]);
+    }
+    // What is left is less than a trip: a trip of as few loads as hold it, so that a short tile does not load, convert and
+    // discard values.  (All lanes of a block take the same one, except that with more than 7 loads left the lanes that
+    // have all 8 took them as a full trip above and have nothing left.)
+    const int left = nvec - (j0 - tid);
+    if (left > 4 * GRAWA_BLOCK) sumsq_rest<GT, NT, 8>(body, j0, nvec, acc);
+    else if (left > 2 * GRAWA_BLOCK) sumsq_rest<GT, NT, 4>(body, j0, nvec, acc);
+    else if (left > GRAWA_BLOCK) sumsq_rest<GT, NT, 2>(body, j0, nvec, acc);
+    else sumsq_rest<GT, NT, 1>(body, j0, nvec, acc);
+}
+
 template <typename GT>
 __global__ __launch_bounds__(GRAWA_BLOCK) __attribute__((amdgpu_waves_per_eu(1, 4))) void k_sumsq(
     const GT *__restrict__ g, int64_t ldg, const GrawaTile *__restrict__ tiles, int64_t n_tiles,
-    double *__restrict__ partials, unsigned *__restrict__ cnt_all)
+    double *__restrict__ partials, unsigned *__restrict__ cnt_all, int64_t cached_cols)
 {
     constexpr int V = Grad<GT>::VEC8;
     const GrawaTile t = tiles[blockIdx.x];
@@ -78,26 +105,9 @@ __global__ __launch_bounds__(GRAWA_BLOCK) __attribute__((amdgpu_waves_per_eu(1, 
         acc[1] = sq_add(Grad<GT>::one(row + b_al + (tid - GRAWA_WAVE)), 0.0);
     }
 
-    // Body: all loads of a trip are issued before any is used.  Full trips need no bounds checks.
     const int nvec = (int)((b_al - a_al) / V);
-    const GT *body = row + a_al;
-    typename Grad<GT>::Vec8 q[GRAWA_SUMSQ_U];
-    int j0 = tid;
-    for (; j0 + (GRAWA_SUMSQ_U - 1) * GRAWA_BLOCK < nvec; j0 += GRAWA_SUMSQ_U * GRAWA_BLOCK) {
-#pragma unroll
-        for (int u = 0; u < GRAWA_SUMSQ_U; ++u) q[u] = Grad<GT>::load8(body + (int64_t)(j0 + u * GRAWA_BLOCK) * V);
-        __builtin_amdgcn_sched_barrier(0); // keep the arithmetic from being hoisted between the loads
-#pragma unroll
-        for (int u = 0; u < GRAWA_SUMSQ_U; ++u) acc[u] = Grad<GT>::sumsq8(q[u], acc[u]);
-    }
-    // What is left is less than a trip: a trip of as few loads as hold it, so that a short tile does not load, convert and
-    // discard values.  (All lanes of a block take the same one, except that with more than 7 loads left the lanes that
-    // have all 8 took them as a full trip above and have nothing left.)
-    const int left = nvec - (j0 - tid);
-    if (left > 4 * GRAWA_BLOCK) sumsq_rest<GT, 8>(body, j0, nvec, acc);
-    else if (left > 2 * GRAWA_BLOCK) sumsq_rest<GT, 4>(body, j0, nvec, acc);
-    else if (left > GRAWA_BLOCK) sumsq_rest<GT, 2>(body, j0, nvec, acc);
-    else sumsq_rest<GT, 1>(body, j0, nvec, acc);
+    if (a < cached_cols) sumsq_body<GT, false>(row + a_al, nvec, acc);
+    else sumsq_body<GT, true>(row + a_al, nvec, acc);
 
     __shared__ double sm[GRAWA_BLOCK / GRAWA_WAVE];
     double lane = 0.0;
@@ -431,10 +441,10 @@ hipError_t grawa_launch_sumsq(const grawa_plan *p, const void *g, int64_t ldg, g
     const dim3 grid((unsigned)p->n_tiles, (unsigned)p->K), block(GRAWA_BLOCK);
     if (dt == GRAWA_BF16)
         hipExtLaunchKernelGGL(k_sumsq<uint16_t>, grid, block, 0, s, e0, e1, 0, (const uint16_t *)g, ldg,
-                              (const GrawaTile *)p->d_tiles, p->n_tiles, p->d_partials, p->d_cnt_all);
+                              (const GrawaTile *)p->d_tiles, p->n_tiles, p->d_partials, p->d_cnt_all, p->cached_cols);
     else
         hipExtLaunchKernelGGL(k_sumsq<float>, grid, block, 0, s, e0, e1, 0, (const float *)g, ldg,
-                              (const GrawaTile *)p->d_tiles, p->n_tiles, p->d_partials, p->d_cnt_all);
+                              (const GrawaTile *)p->d_tiles, p->n_tiles, p->d_partials, p->d_cnt_all, p->cached_cols);
     return hipGetLastError();
 }
 
