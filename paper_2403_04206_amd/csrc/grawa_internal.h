@@ -19,8 +19,6 @@ struct grawa_plan {
     int64_t P;
     int tile_elems;
     int64_t n_tiles;
-    int64_t cached_cols; // norm pass: tiles that start before this column are read with cached loads (0 in a plan; a call that
-                         // wants some passes a copy of the plan on)
     int64_t n_cells; // ceil(P / 256): blocks of the center+pull pass
     int device;
     // one device allocation, carved up:
@@ -52,6 +50,8 @@ struct grawa_plan {
     int profile_n;
     hipEvent_t *ev;          // 4 per slot: norm begin/end, pull begin/end
     unsigned char *ev_norm;  // per slot: 1 if the call recorded norm-kernel events
+    int64_t cached_cols; // norm pass: tiles that start before this column are read with cached loads (0 in a plan; a call that
+                         // wants some passes a copy of the plan on)
 };
 
 enum { // what the layer scores are wanted for
