@@ -14,7 +14,7 @@ BUILD = os.path.join(PKG, "_build")
 SOURCES = [os.path.join(CSRC, n) for n in ("grawa_api.cpp", "grawa_maps.cpp", "grawa_norms.hip", "grawa_pull.hip",
                                             "grawa_local.hip", "grawa_static.hip")]
 HEADERS = [os.path.join(CSRC, "grawa_internal.h"), os.path.join(CSRC, "grawa_device.h"), os.path.join(CSRC, "grawa_scores.h"),
-           os.path.join(CSRC, "grawa_maps.h"), os.path.join(CSRC, "grawa_route.h"),
+           os.path.join(CSRC, "grawa_maps.h"), os.path.join(CSRC, "grawa_route.h"), os.path.join(CSRC, "grawa_offsets.h"),
            os.path.join(ROOT, "include", "grawa.h")]
 
 # Packed fp32 instructions are switched off for all device code (a hipcc flag, not a host one;

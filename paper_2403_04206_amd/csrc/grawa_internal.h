@@ -52,6 +52,7 @@ struct grawa_plan {
     unsigned char *ev_norm;  // per slot: 1 if the call recorded norm-kernel events
     int64_t cached_cols; // norm pass: tiles that start before this column are read with cached loads (0 in a plan; a call that
                          // wants some passes a copy of the plan on)
+    int tile_shift;      // 0: the maps below are filled; else tiles and cells are found in d_off, tiles of 2^tile_shift columns
 };
 
 enum { // what the layer scores are wanted for

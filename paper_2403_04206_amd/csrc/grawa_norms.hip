@@ -11,6 +11,7 @@
 // lane in flight and a capped occupancy; what a fused pull reads again is read through the caches (grawa_cached_grad_cols).  Squares and sums are fp64 throughout, added in a
 // fixed order (no sum is formed by atomics; how norms pass between the blocks of a launch: grawa_scores.h),
 // so results are bit-reproducible.
+#include "grawa_offsets.h"
 #include "grawa_route.h"
 #include "grawa_scores.h"
 
@@ -76,13 +77,12 @@ __device__ __forceinline__ void sumsq_body(const GT *body, int nvec, double (&ac
     else sumsq_rest<GT, NT, 1>(body, j0, nvec, acc);
 }
 
-template <typename GT>
-__global__ __launch_bounds__(GRAWA_BLOCK) __attribute__((amdgpu_waves_per_eu(1, 4))) void k_sumsq(
-    const GT *__restrict__ g, int64_t ldg, const GrawaTile *__restrict__ tiles, int64_t n_tiles,
-    double *__restrict__ partials, unsigned *__restrict__ cnt_all, int64_t cached_cols)
+// MIX: cached_cols may be above 0.
+template <typename GT, bool MIX>
+__device__ __forceinline__ void sumsq_tile(const GrawaTile t, const GT *__restrict__ g, int64_t ldg, int64_t n_tiles,
+                                           double *__restrict__ partials, unsigned *__restrict__ cnt_all, int64_t cached_cols)
 {
     constexpr int V = Grad<GT>::VEC8;
-    const GrawaTile t = tiles[blockIdx.x];
     const int k = blockIdx.y;
     const GT *row = g + (int64_t)k * ldg;
     const int tid = threadIdx.x;
@@ -106,7 +106,7 @@ __global__ __launch_bounds__(GRAWA_BLOCK) __attribute__((amdgpu_waves_per_eu(1, 
     }
 
     const int nvec = (int)((b_al - a_al) / V);
-    if (a < cached_cols) sumsq_body<GT, false>(row + a_al, nvec, acc);
+    if (MIX && a < cached_cols) sumsq_body<GT, false>(row + a_al, nvec, acc);
     else sumsq_body<GT, true>(row + a_al, nvec, acc);
 
     __shared__ double sm[GRAWA_BLOCK / GRAWA_WAVE];
@@ -116,6 +116,25 @@ __global__ __launch_bounds__(GRAWA_BLOCK) __attribute__((amdgpu_waves_per_eu(1, 
     const double total = block_sum<GRAWA_BLOCK>(lane, sm);
     if (tid == 0) partials[(int64_t)k * n_tiles + blockIdx.x] = total;
     if (cnt_all && tid == 0 && k == 0 && blockIdx.x == 0) *cnt_all = 0u;
+}
+
+template <typename GT, bool MIX>
+__global__ __launch_bounds__(GRAWA_BLOCK) __attribute__((amdgpu_waves_per_eu(1, 4))) void k_sumsq(
+    const GT *__restrict__ g, int64_t ldg, const GrawaTile *__restrict__ tiles, int64_t n_tiles,
+    double *__restrict__ partials, unsigned *__restrict__ cnt_all, int64_t cached_cols)
+{
+    sumsq_tile<GT, MIX>(tiles[blockIdx.x], g, ldg, n_tiles, partials, cnt_all, cached_cols);
+}
+
+// The same without a map: every block finds its tile in the layer offsets.
+template <typename GT>
+__global__ __launch_bounds__(GRAWA_BLOCK) __attribute__((amdgpu_waves_per_eu(1, 4))) void k_sumsq_slots(
+    const GT *__restrict__ g, int64_t ldg, const int64_t *__restrict__ off, int L, int64_t P, int shift, int64_t n_tiles,
+    double *__restrict__ partials)
+{
+    const int64_t i = blockIdx.x;
+    const int layer = wave_last_layer(off, L, [&](int l, int64_t o) { return first_slot(o, l, P, shift) <= i; });
+    sumsq_tile<GT, false>(slot_tile(i, layer, off[layer], off[layer + 1], P, shift), g, ldg, n_tiles, partials, nullptr, 0);
 }
 
 // ---------------------------------------------------------------------------------
@@ -439,12 +458,26 @@ hipError_t grawa_launch_sumsq(const grawa_plan *p, const void *g, int64_t ldg, g
                               hipStream_t s, hipEvent_t e0, hipEvent_t e1)
 {
     const dim3 grid((unsigned)p->n_tiles, (unsigned)p->K), block(GRAWA_BLOCK);
-    if (dt == GRAWA_BF16)
-        hipExtLaunchKernelGGL(k_sumsq<uint16_t>, grid, block, 0, s, e0, e1, 0, (const uint16_t *)g, ldg,
-                              (const GrawaTile *)p->d_tiles, p->n_tiles, p->d_partials, p->d_cnt_all, p->cached_cols);
-    else
-        hipExtLaunchKernelGGL(k_sumsq<float>, grid, block, 0, s, e0, e1, 0, (const float *)g, ldg,
-                              (const GrawaTile *)p->d_tiles, p->n_tiles, p->d_partials, p->d_cnt_all, p->cached_cols);
+    if (p->tile_shift) {
+        if (dt == GRAWA_BF16)
+            k_sumsq_slots<uint16_t><<<grid, block, 0, s>>>((const uint16_t *)g, ldg, p->d_off, p->L, p->P, p->tile_shift, p->n_tiles,
+                                                           p->d_partials);
+        else
+            k_sumsq_slots<float><<<grid, block, 0, s>>>((const float *)g, ldg, p->d_off, p->L, p->P, p->tile_shift, p->n_tiles,
+                                                        p->d_partials);
+        return hipGetLastError();
+    }
+#define GRAWA_SUMSQ_GO(GT, MIX)                                                                              \
+    hipExtLaunchKernelGGL((k_sumsq<GT, MIX>), grid, block, 0, s, e0, e1, 0, (const GT *)g, ldg,              \
+                          (const GrawaTile *)p->d_tiles, p->n_tiles, p->d_partials, p->d_cnt_all, p->cached_cols)
+    if (dt == GRAWA_BF16) {
+        if (p->cached_cols) GRAWA_SUMSQ_GO(uint16_t, true);
+        else GRAWA_SUMSQ_GO(uint16_t, false);
+    } else {
+        if (p->cached_cols) GRAWA_SUMSQ_GO(float, true);
+        else GRAWA_SUMSQ_GO(float, false);
+    }
+#undef GRAWA_SUMSQ_GO
     return hipGetLastError();
 }
 

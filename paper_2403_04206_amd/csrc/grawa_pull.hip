@@ -7,6 +7,7 @@
 // 256-byte piece of every row (one 32-bit element per lane per row), blocks are small and many,
 // and accesses are non-temporal -- provided every row starts on a 128-byte boundary, so that no
 // cache line is written in two parts.  There is no dense contraction, hence no matrix-core code.
+#include "grawa_offsets.h"
 #include "grawa_route.h"
 #include "grawa_scores.h"
 
@@ -101,6 +102,7 @@ struct TileWeights {
     float *weights_out;                   // [K][L] or null
     unsigned *flags;
     int group;                            // lanes per worker: the largest power of two not above 64 / K
+    int shift;                            // without the maps: tiles of 2^shift columns, found in the offsets
 };
 
 template <int K> struct CellWeights {
@@ -115,7 +117,7 @@ template <int K> struct CellWeights {
 // takes two rounds at most, for 3 layers as for 256 (a wave per layer in turn took 16 rounds, and lanes that walked
 // all tiles of their layer more: 4 workers, 600 k columns, of which the first 60 or 100 are layers of their own, update on the
 // device 24.6 and 174 us; with the weights as a launch 17.3 and 21.8; now 11.4 and 11.7).
-template <int K>
+template <int K, bool SLOTS>
 __device__ __forceinline__ int cell_weights(const TileWeights &w, const int64_t *__restrict__ off, int L, int64_t P,
                                             int64_t cell0, int l0, bool boundary, CellWeights<K> &sh)
 {
@@ -134,12 +136,18 @@ __device__ __forceinline__ int cell_weights(const TileWeights &w, const int64_t 
     }
     if (wave == 0 || (wave == 1 && nl > 1)) {
         const int i = wave == 0 ? 0 : nl - 1, l = l0 + i;
-        wave_layer_weights(w.partials, w.pitch, w.tile_begin[l], w.tile_end[l], K, w.group, sh.beta + i * K,
+        int t0, t1;
+        if constexpr (SLOTS) layer_slots(off, l, P, w.shift, t0, t1);
+        else t0 = w.tile_begin[l], t1 = w.tile_end[l];
+        wave_layer_weights(w.partials, w.pitch, t0, t1, K, w.group, sh.beta + i * K,
                            off[l] >= cell0, w.weights_out ? w.weights_out + l : nullptr, L, w.flags);
     } else if (wave >= 2) {
         for (int i = 1 + (int)threadIdx.x - 2 * GRAWA_WAVE; i < nl - 1; i += GRAWA_CELL - 2 * GRAWA_WAVE) {
             const int l = l0 + i;
-            lane_layer_weights<K>(w.partials, w.pitch, w.tile_begin[l], w.tile_end[l], sh.beta + i * K,
+            int t0, t1;
+            if constexpr (SLOTS) layer_slots(off, l, P, w.shift, t0, t1);
+            else t0 = w.tile_begin[l], t1 = w.tile_end[l];
+            lane_layer_weights<K>(w.partials, w.pitch, t0, t1, sh.beta + i * K,
                                   w.weights_out ? w.weights_out + l : nullptr, L, w.flags);
         }
     }
@@ -170,7 +178,9 @@ template <int K> __device__ __forceinline__ int cell_layer_of(const CellWeights<
 // center used and stored is c0 + rho (c - c0).
 // WPE caps the waves per SIMD (grawa_waves_for): more only queues requests to K far-apart rows and costs DRAM
 // efficiency (measured: K = 16 at 3 waves 6.1 TB/s, at 8 waves 5.7; K = 8 at 4 waves 6.5, at 8 waves 6.2).
-template <int K, bool SGD, typename GT, bool NT, int WPE, bool TILES>
+// TILES: weights from the tile sums, by the maps of a plan or found in the offsets (GRAWA_TILES_SLOTS).
+enum { GRAWA_TILES_NONE = 0, GRAWA_TILES_MAPS = 1, GRAWA_TILES_SLOTS = 2 };
+template <int K, bool SGD, typename GT, bool NT, int WPE, int TILES>
 __global__ __launch_bounds__(GRAWA_CELL) __attribute__((amdgpu_waves_per_eu(1, WPE))) void k_center_pull(
     float *__restrict__ x, int64_t ldx, const GT *__restrict__ g, int64_t ldg, float lr,
     const float *__restrict__ beta, int64_t beta_stride, const int32_t *__restrict__ cell_layer,
@@ -199,11 +209,17 @@ __global__ __launch_bounds__(GRAWA_CELL) __attribute__((amdgpu_waves_per_eu(1, W
     float cprev = 0.f;
     if (moving && ok) cprev = ld_lane<NT, float>(uniform_base(center_out + cell0), xoff);
 
-    const int info = cell_layer ? cell_layer[blockIdx.x] : 0;
+    int info = 0;
+    if constexpr (TILES == GRAWA_TILES_SLOTS) {
+        const int l = wave_last_layer(off, L, [&](int, int64_t o) { return o <= cell0; });
+        info = off[l + 1] >= (cell0 + GRAWA_CELL < P ? cell0 + GRAWA_CELL : P) ? l : ~l;
+    } else {
+        info = cell_layer ? cell_layer[blockIdx.x] : 0;
+    }
     float c = 0.f;
     if constexpr (TILES) {
         __shared__ CellWeights<K> cw;
-        const int nl = cell_weights<K>(tw, off, L, P, cell0, info >= 0 ? info : ~info, info < 0, cw);
+        const int nl = cell_weights<K, TILES == GRAWA_TILES_SLOTS>(tw, off, L, P, cell0, info >= 0 ? info : ~info, info < 0, cw);
         const float *b = cw.beta + cell_layer_of<K>(cw, nl, (int)col) * K;
 #pragma unroll
         for (int k = 0; k < K; ++k) c = fmaf(b[k], v[k], c);
@@ -533,9 +549,10 @@ constexpr int grawa_waves_for(int k, bool sgd, bool bf16)
 #define GRAWA_CP_STRIDE per_layer ? (int64_t)p->L : (int64_t)1
 #define GRAWA_CP_CELLS per_layer ? (const int32_t *)p->d_cell_layer : (const int32_t *)nullptr
 
-template <int K, bool SGD, typename GT, bool NT, bool TILES> static void launch_plain(GRAWA_CP_ARGS)
+template <int K, bool SGD, typename GT, bool NT, int TILES> static void launch_plain(GRAWA_CP_ARGS)
 {
-    constexpr int CAP = grawa_waves_for(K, SGD, sizeof(GT) == 2), WPE = NT ? CAP : 8;
+    // (The weights in the pull, 12 and more workers, without the step: the capped kernel, 15 workers, 200 layers 15.8 / 16.0 us.)
+    constexpr int CAP = grawa_waves_for(K, SGD, sizeof(GT) == 2), WPE = NT || (TILES && K >= 12 && !SGD) ? CAP : 8;
     // Cached accesses: the cap, where it is wanted, is set by the LDS a block asks for, of the CU's 160 KB.  Up to 128 MB the
     // caches answer, and what counts is that all blocks of a small array run at once (1054 blocks of 8 workers are one more
     // round than 4 per CU hold).  LGRAWA with the fp32 SGD step, us, capped / not: 8 workers, 270 k columns 13.9 / 12.0,
@@ -606,7 +623,7 @@ template <bool SGD, typename GT, bool NT> static hipError_t dispatch_cp(GRAWA_CP
 #define GRAWA_CP_PLAIN(N)                                                                       \
     case N:                                                                                     \
         if constexpr (N <= WIDE_TO) launch_wide<N, SGD, GT, true, GRAWA_ST_STREAM>(GRAWA_CP_PASS);               \
-        else launch_plain<N, SGD, GT, NT, false>(GRAWA_CP_PASS);                                \
+        else launch_plain<N, SGD, GT, NT, GRAWA_TILES_NONE>(GRAWA_CP_PASS);                                \
         return hipGetLastError();
 #define GRAWA_CP_SPLIT(N)                                                     \
     case N:                                                                   \
@@ -619,7 +636,7 @@ template <bool SGD, typename GT, bool NT> static hipError_t dispatch_cp(GRAWA_CP
         GRAWA_CP_PLAIN(13) GRAWA_CP_PLAIN(14) GRAWA_CP_PLAIN(15) GRAWA_CP_PLAIN(17) GRAWA_CP_PLAIN(18)
         GRAWA_CP_PLAIN(19) GRAWA_CP_PLAIN(20) GRAWA_CP_PLAIN(21) GRAWA_CP_PLAIN(22) GRAWA_CP_PLAIN(23)
     case 16:
-        if constexpr (SGD) launch_plain<16, SGD, GT, NT, false>(GRAWA_CP_PASS);
+        if constexpr (SGD) launch_plain<16, SGD, GT, NT, GRAWA_TILES_NONE>(GRAWA_CP_PASS);
         else launch_split<4, false, 4, 1, 1, 8, SGD, GT, NT, NT ? GRAWA_ST_STREAM : GRAWA_ST_CACHED>(GRAWA_CP_PASS);
         return hipGetLastError();
     }
@@ -685,8 +702,15 @@ template <bool SGD, typename GT> static hipError_t dispatch_cp_burst(GRAWA_CP_AR
 // Weights straight from the tile sums (GRAWA_TILES_COUNTS), cached accesses.
 template <bool SGD, typename GT> static hipError_t dispatch_cp_tiles(GRAWA_CP_ARGS)
 {
-#define GRAWA_CP_TILES(N) \
-    case N: launch_plain<N, SGD, GT, false, true>(GRAWA_CP_PASS); return hipGetLastError();
+#define GRAWA_CP_TILES(N)                                                                                      \
+    case N:                                                                                                    \
+        if constexpr (!SGD) /* the call without maps has no fused step */                                      \
+            if (p->tile_shift) {                                                                               \
+                launch_plain<N, SGD, GT, false, GRAWA_TILES_SLOTS>(GRAWA_CP_PASS);                             \
+                return hipGetLastError();                                                                      \
+            }                                                                                                  \
+        launch_plain<N, SGD, GT, false, GRAWA_TILES_MAPS>(GRAWA_CP_PASS);                                      \
+        return hipGetLastError();
     switch (p->K) {
         GRAWA_TILES_COUNTS(GRAWA_CP_TILES)
     }
@@ -705,7 +729,7 @@ hipError_t grawa_launch_center_pull(const grawa_plan *p, float *x, int64_t ldx, 
     if (!beta) {
         int group = GRAWA_WAVE;
         while (group * p->K > GRAWA_WAVE) group >>= 1;
-        tw = TileWeights{p->d_partials, p->n_tiles, p->d_layer_tile0, p->d_layer_tile1, weights_out, p->d_flags, group};
+        tw = TileWeights{p->d_partials, p->n_tiles, p->d_layer_tile0, p->d_layer_tile1, weights_out, p->d_flags, group, p->tile_shift};
     }
     // Streaming accesses pay off only when the arrays do not fit the last-level cache anyway: x, and g where the step is fused.
     // (By x alone, fused LGRAWA updates, three sets in turn, us, line-aligned rows / rows off the grid: 70 MB fp32 2 workers 57.3 ->

@@ -2,13 +2,14 @@
 // tight serving loops, harnesses that forbid hipMalloc): the same kernels as grawa_lgrawa_update,
 // with the plan's workspace replaced by a fixed array that lives in the library's device image.
 // The index maps a plan builds on the host are built here by one small kernel from layer
-// offsets that already sit in device memory, so the call enqueues kernels and nothing else.
+// offsets that already sit in device memory, or, for small problems, not at all: so the call enqueues kernels and nothing else.
 #include <cstring>
 #include <mutex>
 
-#include "grawa_device.h"
+#include "grawa_offsets.h"
 
 #define GRAWA_STATIC_SCRATCH_BYTES ((size_t)32 << 20)
+#define GRAWA_STATIC_NO_MAPS 2560 // workers times layers
 
 // One copy per GPU the library runs on, held until the process ends.  In host code this name
 // is only a handle for the symbol lookup below; the device address comes from that lookup.
@@ -43,21 +44,6 @@ inline size_t round256(size_t n) { return (n + 255) & ~size_t(255); }
 
 } // namespace
 
-// Offsets are read from device memory the host never sees, so they cannot be validated before
-// the launch; they are clamped to [0, P] (and made monotone) wherever an address is formed from
-// them, which keeps every access in range whatever they hold.
-__device__ __forceinline__ int64_t clamp_off(int64_t v, int64_t lo, int64_t hi) { return v < lo ? lo : (v > hi ? hi : v); }
-
-// Tile slots.  Every layer is cut at the multiples of T = 2^shift (the same cut the host-side plan makes).
-// The piece of layer l in the aligned stretch j of T columns gets slot j + l: going along the row, every new piece
-// starts a new stretch, a new layer or both, so slots never repeat and those of a layer are consecutive, and a
-// slot is found without a count of the pieces before it.  Slots skipped where a layer starts on a multiple of T
-// become tiles of length 0, whose blocks add nothing.  No slot exceeds P / T + L - 1.
-__device__ __forceinline__ int64_t first_slot(const int64_t *off, int l, int64_t P, int shift)
-{
-    return (clamp_off(off[l], 0, P) >> shift) + l;
-}
-
 // One entry of each of the maps per thread; `off` may be LDS or global memory.
 __device__ __forceinline__ void static_maps_entry(const int64_t *off, int64_t i, int64_t n, int L, int64_t P, int shift,
                                                   int64_t bound, GrawaTile *__restrict__ tiles, int64_t n_cells,
@@ -68,20 +54,10 @@ __device__ __forceinline__ void static_maps_entry(const int64_t *off, int64_t i,
         int lo = 0, hi = L - 1; // the last layer whose first slot is not above i
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
-            if (first_slot(off, mid, P, shift) <= i) lo = mid;
+            if (first_slot(off[mid], mid, P, shift) <= i) lo = mid;
             else hi = mid - 1;
         }
-        const int64_t a = clamp_off(off[lo], 0, P), b = clamp_off(off[lo + 1], a, P);
-        const int64_t j = i - lo;
-        int64_t start = j << shift, stop = (j + 1) << shift;
-        if (start < a) start = a;
-        if (stop > b) stop = b;
-        if (stop < start) stop = start;
-        GrawaTile t;
-        t.start = start;
-        t.len = (int32_t)(stop - start);
-        t.layer = lo;
-        tiles[i] = t;
+        tiles[i] = slot_tile(i, lo, off[lo], off[lo + 1], P, shift);
     }
     if (i < n_cells) {
         const int64_t first = i * GRAWA_CELL;
@@ -94,11 +70,7 @@ __device__ __forceinline__ void static_maps_entry(const int64_t *off, int64_t i,
         }
         cell_layer[i] = off[lo + 1] > last ? (int32_t)lo : ~(int32_t)lo;
     }
-    for (int64_t l = i; l < L; l += n) {
-        const int64_t a = clamp_off(off[l], 0, P), b = clamp_off(off[l + 1], a, P);
-        tile_begin[l] = (int32_t)((a >> shift) + l);
-        tile_end[l] = b > a ? (int32_t)(((b - 1) >> shift) + l + 1) : (int32_t)((a >> shift) + l);
-    }
+    for (int64_t l = i; l < L; l += n) layer_slots(off, (int)l, P, shift, tile_begin[l], tile_end[l]);
 }
 
 // grid ceil(max(bound, n_cells)/256), block 256.  Tile i of the norm pass, the layer of 256-column cell i of
@@ -176,16 +148,25 @@ extern "C" grawa_status_t grawa_lgrawa_update_static(int K, int64_t P, int L, co
     p.d_layer_tile1 = reinterpret_cast<int32_t *>(w); w += b_S; // 4 L of the 8 K L bytes that the limit counts for S
     p.d_beta_layer = reinterpret_cast<float *>(w);
 
+    // With the weights worked out in the pull, both kernels find their tile or cell in the offsets themselves, which saves the
+    // launch that writes the maps (2.5 us and its boundary); what they repeat for it grows with the workers and the layers of a
+    // cell.  Whole call, us, with maps / without, 3 layers, 59 and 200: 4 workers, 640 k columns 16.2 / 13.6, 16.5 / 13.9, 17.5 /
+    // 16.0; 8 workers, 320 k 15.5 / 12.0, 16.7 / 13.5, 18.5 / 16.5; 12 workers, 213 k 15.6 / 11.9, 16.3 / 14.0, 20.3 / 18.5; 15
+    // workers, 170 k 15.5 / 11.8, 16.8 / 15.1, 20.2 / 20.7.
+    p.tile_shift = grawa_pull_from_tiles(&p) && (int64_t)K * L <= GRAWA_STATIC_NO_MAPS ? __builtin_ctz((unsigned)T) : 0;
+
     // Nothing in the scratch has to start at zero: the maps, every partial that is read and the weights
     // are written in full before they are read.
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const int64_t n_map = bound > nc ? bound : nc;
-    k_static_maps<<<dim3((unsigned)((n_map + GRAWA_BLOCK - 1) / GRAWA_BLOCK)), dim3(GRAWA_BLOCK), 0, s>>>(
-        layer_offsets_dev, L, P, __builtin_ctz((unsigned)T), bound, p.d_tiles, nc, p.d_cell_layer, p.d_layer_tile0,
-        p.d_layer_tile1);
-    if (hipGetLastError() != hipSuccess) return GRAWA_ERR_HIP;
-    if (grawa_launch_sumsq(&p, g, ldg, dt, s, nullptr, nullptr) != hipSuccess) return GRAWA_ERR_HIP;
     const bool from_tiles = grawa_pull_from_tiles(&p);
+    if (!p.tile_shift) {
+        const int64_t n_map = bound > nc ? bound : nc;
+        k_static_maps<<<dim3((unsigned)((n_map + GRAWA_BLOCK - 1) / GRAWA_BLOCK)), dim3(GRAWA_BLOCK), 0, s>>>(
+            layer_offsets_dev, L, P, __builtin_ctz((unsigned)T), bound, p.d_tiles, nc, p.d_cell_layer, p.d_layer_tile0,
+            p.d_layer_tile1);
+        if (hipGetLastError() != hipSuccess) return GRAWA_ERR_HIP;
+    }
+    if (grawa_launch_sumsq(&p, g, ldg, dt, s, nullptr, nullptr) != hipSuccess) return GRAWA_ERR_HIP;
     if (!from_tiles && grawa_launch_finalize_layers(&p, GRAWA_GOAL_LAYER_WEIGHTS, nullptr, weights_out, s) != hipSuccess)
         return GRAWA_ERR_HIP;
     if (grawa_launch_center_pull(&p, x, ldx, from_tiles ? nullptr : p.d_beta_layer, 1, lambda, nullptr, 0, GRAWA_F32,
