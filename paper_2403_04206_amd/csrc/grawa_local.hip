@@ -3,11 +3,13 @@
 //                  (+ proximity step toward the stored center)                    [Alg. 1, 2, "Prox."]
 //                  (+ per-tile sums of squares of the gradient, for the running
 //                     norm estimate of Local-GRAWA)                               [App. G]
+//   k_layer_step   the scored step of a small model, estimate included           [App. G]
 //   k_nesterov     SGD with Nesterov momentum and weight decay                   [App. B.2.2]
 //   k_stream_copy  plain copy (measurement aid)
 // All are read-modify-write streams with no reuse: global loads and stores kept in flight, one
 // row (worker) per block, which is the access shape that streams fastest on this part.
 #include "grawa_device.h"
+#include "grawa_route.h"
 
 // ---------------------------------------------------------------------------------
 // local step, row by row
@@ -127,6 +129,78 @@ __global__ __launch_bounds__(GRAWA_CELL) __attribute__((amdgpu_waves_per_eu(1, P
                 if (threadIdx.x == 0) out[t] = tot;
             }
         }
+    }
+}
+
+// Scored step of a small model in one launch: a block owns a whole layer of one worker, so that the norm of its gradient, and
+// with it the running estimate, need no second launch and no exchange between blocks.  grid (L, K), block T; a lane handles
+// vectors of 4 adjacent columns (rows are aligned to 16 bytes), U of them in flight at a time; a vector that the layer shares
+// with a neighbour is handled element by element.  Short chains bound it: what counts is the longest layer (grawa_step_by_layers).
+#define GRAWA_LAYER_U 5
+template <typename GT, bool PROX, int T>
+__global__ __launch_bounds__(T) void k_layer_step(
+    float *__restrict__ x, int64_t ldx, const GT *__restrict__ g, int64_t ldg, float lr, const float *__restrict__ center, float w,
+    const int64_t *__restrict__ off, int L, double *__restrict__ mvg, double gamma, int64_t *__restrict__ local_t,
+    unsigned *__restrict__ flags)
+{
+    constexpr int V = 4, U = GRAWA_LAYER_U;
+    typedef typename FloatVec<V>::T XV;
+    const int l = blockIdx.x, k = blockIdx.y;
+    const int64_t a = off[l], b = off[l + 1];
+    const int64_t va = (a + V - 1) / V, vb = b / V; // whole vectors [va, vb), none where vb <= va
+    float *xr = x + (int64_t)k * ldx;
+    const GT *gr = g + (int64_t)k * ldg;
+    const double before = threadIdx.x == 0 ? mvg[(int64_t)k * L + l] : 0.0;
+    double acc = 0.0;
+    const auto one = [&](int64_t c) {
+        const float gv = Grad<GT>::one(gr + c);
+        float v = fmaf(-lr, gv, xr[c]);
+        if (PROX) v = fmaf(w, center[c] - v, v);
+        xr[c] = v;
+        acc = sq_add(gv, acc);
+    };
+    // The columns outside whole vectors: up to 3 at either end (a layer inside one vector: up to 3 in all).
+    const int64_t head = vb > va ? va * V : b < va * V ? b : va * V, tail = vb > va ? vb * V : head;
+    if (threadIdx.x < GRAWA_WAVE) {
+        if (a + (int64_t)threadIdx.x < head) one(a + threadIdx.x);
+        else if (threadIdx.x >= GRAWA_WAVE / 2 && tail + (int64_t)threadIdx.x - GRAWA_WAVE / 2 < b) one(tail + threadIdx.x - GRAWA_WAVE / 2);
+    }
+    for (int64_t v0 = va + threadIdx.x; v0 - (int64_t)threadIdx.x < vb; v0 += U * T) {
+        XV xv[U], cv[U];
+        float gf[U][V];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t v = v0 + u * T;
+            if (v < vb) {
+                xv[u] = *reinterpret_cast<const XV *>(xr + v * V);
+                GradVec<GT, V, false>::load(gr + v * V, gf[u]);
+                if (PROX) cv[u] = *reinterpret_cast<const XV *>(center + v * V);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t v = v0 + u * T;
+            if (v < vb) {
+                XV o = xv[u];
+#pragma unroll
+                for (int e = 0; e < V; ++e) {
+                    float t = fmaf(-lr, gf[u][e], vec_get<V>(xv[u], e));
+                    if (PROX) t = fmaf(w, vec_get<V>(cv[u], e) - t, t);
+                    vec_set<V>(o, e, t);
+                    acc = sq_add(gf[u][e], acc);
+                }
+                *reinterpret_cast<XV *>(xr + v * V) = o;
+            }
+        }
+    }
+    __shared__ double sm[T / GRAWA_WAVE];
+    const double tot = block_sum<T>(acc, sm);
+    if (threadIdx.x == 0) {
+        const double norm = sqrt(tot);
+        mvg[(int64_t)k * L + l] = gamma * before + (1.0 - gamma) * norm;
+        if (flags && !isfinite(norm)) atomicOr(flags, GRAWA_NONFINITE_LAYER_SCORE);
+        if (k == 0) local_t[l] += 1;
     }
 }
 
@@ -251,6 +325,28 @@ static hipError_t launch_row_step(const grawa_plan *p, float *x, int64_t ldx, co
 {
     const int64_t nb = (P + GRAWA_ROW_BLOCK - 1) / GRAWA_ROW_BLOCK;
     const bool prox = center != nullptr;
+    const int layer_threads = p ? grawa_step_by_layers(K, p->L, P, p->max_rtiles) : 0;
+    if (layer_threads) {
+#define GRAWA_LS_GO(GT, PROX)                                                                                              \
+    do {                                                                                                                   \
+        const dim3 layers((unsigned)p->L, (unsigned)K);                                                                    \
+        if (layer_threads == 256)                                                                                          \
+            k_layer_step<GT, PROX, 256><<<layers, dim3(256), 0, s>>>(x, ldx, (const GT *)g, ldg, lr, center, w, p->d_off,  \
+                                                                     p->L, p->d_mvg, gamma, p->d_local_t, p->d_flags);     \
+        else                                                                                                               \
+            k_layer_step<GT, PROX, 1024><<<layers, dim3(1024), 0, s>>>(x, ldx, (const GT *)g, ldg, lr, center, w, p->d_off, \
+                                                                       p->L, p->d_mvg, gamma, p->d_local_t, p->d_flags);   \
+    } while (0)
+        if (dt == GRAWA_BF16) {
+            if (prox) GRAWA_LS_GO(uint16_t, true);
+            else GRAWA_LS_GO(uint16_t, false);
+        } else {
+            if (prox) GRAWA_LS_GO(float, true);
+            else GRAWA_LS_GO(float, false);
+        }
+#undef GRAWA_LS_GO
+        return hipGetLastError();
+    }
     // Nothing is shared between the rows without a center: one group, i.e. row after row (3 % faster).
     const int64_t group = (prox && nb > GRAWA_ROW_GROUP) ? GRAWA_ROW_GROUP : nb;
     const int64_t n_groups = (nb + group - 1) / group;
