@@ -11,6 +11,8 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libgrawa.so")
 BUILD = os.path.join(PKG, "_build")
+ROWS = os.path.join(PKG, "_rows.so")
+ROWS_SOURCE = os.path.join(CSRC, "grawa_rows.cpp")
 SOURCES = [os.path.join(CSRC, n) for n in ("grawa_api.cpp", "grawa_maps.cpp", "grawa_norms.hip", "grawa_pull.hip",
                                             "grawa_local.hip", "grawa_static.hip")]
 HEADERS = [os.path.join(CSRC, "grawa_internal.h"), os.path.join(CSRC, "grawa_device.h"), os.path.join(CSRC, "grawa_scores.h"),
@@ -81,6 +83,27 @@ def build(force: bool = True, verbose: bool = False) -> str:
     return LIB
 
 
+def build_rows() -> str:
+    """Compile the binding's native argument checks (an extension module that sees torch's tensors) with g++."""
+    import sysconfig
+    import torch
+    from torch.utils.cpp_extension import include_paths, library_paths
+    tmp = ROWS + ".tmp.%d" % os.getpid()
+    cmd = ["g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-I", sysconfig.get_paths()["include"]]
+    cmd += [a for p in include_paths() for a in ("-isystem", p)] + [ROWS_SOURCE, "-o", tmp]
+    cmd += ["-L" + p for p in library_paths()] + ["-lc10", "-ltorch_cpu", "-ltorch_python"]
+    try:
+        res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        if res.returncode != 0:
+            raise RuntimeError("g++ failed:\n" + res.stdout)
+        os.replace(tmp, ROWS)
+    finally:
+        if os.path.exists(tmp):
+            os.remove(tmp)
+    return ROWS
+
+
 def build_c_client(src: str, out: str) -> str:
     """Compile a plain C99 program that calls the library through include/grawa.h (gcc, linked against
     libgrawa.so and the HIP runtime; the library is found relative to the program's own location)."""
@@ -98,3 +121,4 @@ def build_c_client(src: str, out: str) -> str:
 
 if __name__ == "__main__":
     print(build(force=True, verbose=True))
+    print(build_rows())

@@ -107,6 +107,15 @@ def _stream_no_tensors(stream=None):
     return _stream(torch.cuda.current_stream() if stream is None else stream)
 
 
+# The checks of _params and _grads on a CUDA tensor by native code (csrc/grawa_rows.cpp): (pointer, row stride, dtype code), or
+# None for whatever is not plainly in order; the Python checks below look again then, and raise.
+try:
+    from ._rows import rows as _native_rows
+except ImportError:                      # not built: the Python checks alone
+    def _native_rows(t, K, P, grads):
+        return None
+
+
 _NULL = C.c_void_p(0)
 
 
@@ -148,6 +157,10 @@ def _rows(t, rows, cols, K, P, ld, what: str):
 
 def _params(x: torch.Tensor, K=None, P=None, what="x"):
     """float32 [K, >= P], unit column stride, rows not overlapping; returns (pointer, row stride)."""
+    if K is not None and P is not None:
+        r = _native_rows(x, K, P, False)
+        if r is not None:
+            return r[0], r[1]
     if x.dtype is torch.float32 and x.ndim == 2 and (x.is_cuda or not _REQUIRE_DEVICE):
         ld, unit = x.stride()
         if unit == 1:
@@ -159,6 +172,10 @@ def _params(x: torch.Tensor, K=None, P=None, what="x"):
 
 def _grads(g: torch.Tensor, K=None, P=None, what="g"):
     """float32 or bfloat16 [K, >= P]; returns (pointer, row stride, dtype code)."""
+    if K is not None and P is not None:
+        r = _native_rows(g, K, P, True)
+        if r is not None:
+            return r
     if g.ndim == 2 and (g.is_cuda or not _REQUIRE_DEVICE):
         ld, unit = g.stride()
         if unit == 1:
@@ -247,6 +264,9 @@ class Plan:
     # Every tensor's dtype, shape and extent is checked against the plan's (K, P, L) here: the C side
     # sees only pointers and strides, and a short buffer would be a device memory fault.
     def _xg(self, x, g):
+        a, b = _native_rows(x, self.K, self.P, False), _native_rows(g, self.K, self.P, True)
+        if a is not None and b is not None:
+            return a[0], a[1], b[0], b[1], b[2]
         xp, ldx = _params(x, self.K, self.P)
         gp, ldg, dt = _grads(g, self.K, self.P)
         return xp, ldx, gp, ldg, dt
