@@ -135,8 +135,10 @@ __global__ __launch_bounds__(GRAWA_CELL) __attribute__((amdgpu_waves_per_eu(1, P
 // Scored step of a small model in one launch: a block owns a whole layer of one worker, so that the norm of its gradient, and
 // with it the running estimate, need no second launch and no exchange between blocks.  grid (L, K), block T; a lane handles
 // vectors of 4 adjacent columns (rows are aligned to 16 bytes), U of them in flight at a time; a vector that the layer shares
-// with a neighbour is handled element by element.  Short chains bound it: what counts is the longest layer (grawa_step_by_layers).
-#define GRAWA_LAYER_U 5
+// with a neighbour is handled element by element.  What bounds it is the longest layer, at the rate of one CU
+// (grawa_step_by_layers): 37 k columns 8.8 us.  More vectors in flight cost registers and gain nothing: round of four steps and the
+// communication, 4 workers, 270 k columns, U = 2 42.9 us, 3 43.5, 5 43.7, 10 56.
+#define GRAWA_LAYER_U 2
 template <typename GT, bool PROX, int T>
 __global__ __launch_bounds__(T) void k_layer_step(
     float *__restrict__ x, int64_t ldx, const GT *__restrict__ g, int64_t ldg, float lr, const float *__restrict__ center, float w,

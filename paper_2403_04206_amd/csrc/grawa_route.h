@@ -134,7 +134,7 @@ static inline int64_t grawa_cached_grad_cols(int K, int64_t P, int elem_bytes)
 
 // Scored step: threads of a block that owns a layer of one worker, or 0: blocks of 1024 columns, the estimate as a launch of its
 // own.  One launch saves the other and its boundary (4 us a step) as long as all blocks run at once and the longest layer takes
-// a block few trips: 5120 columns a trip of 256 threads, 20 480 of 1024.  max_tiles: the most 1024-column tiles of a layer.  Round of
+// a block not too long (the rate of one CU bounds it).  max_tiles: the most 1024-column tiles of a layer.  Round of
 // four steps and the communication, fp32, us, two launches / one: 2 workers, 200 k columns, 300 layers 47.3 / 39.0; 4 workers, 270 k,
 // 59 layers (37 k the longest) 48.5 / 43.5, 420 k, 60 layers 52.0 / 43.1; 8 workers, 200 k, 20 layers 52.5 / 43.8, 300 layers 55.2 / 40.4;
 // 16 workers, 200 k, 150 layers 61.5 / 53.0; 20 workers, 200 k, 120 layers 69.7 / 63.6.  Beyond the lines: longest layer 48 k 52.2 /
