@@ -263,7 +263,7 @@ template <int V> __device__ __forceinline__ void vec_set(typename FloatVec<V>::T
 //   Nesterov step   8 workers, x 80 MB: 1.13 x faster (0.9), 120 MB 1.13 (1.06), 160 MB 1.15 (1.15)
 //   step with center or scores: 80 MB 1.04 to 1.21 (0.98 to 1.12), 160 MB 1.22 (1.12); 40 MB 0.96.  Scored, aligned rows, 4
 //   and 52 workers: 90 MB 56.3/49.6 and 55.0/49.1 (45.7/49.2 and 44.7/48.7), after a pass over x, g and 256 MB of other memory
-//   67.6/52.0 and 67.3/50.8.  With the center, off the line grid: 90 MB 58.2/53.7 and 49.9/44.9 (49.6/49.9 and 41.1/42.8),
+//   67.6/52.0 and 67.3/50.8.  With the center, off the line grid (cached loads, stores written through; fp32 streams its loads now): 90 MB 58.2/53.7 and 49.9/44.9 (49.6/49.9 and 41.1/42.8),
 //   after such a pass 72.1/71.8 and 62.0/61.1.  What the line costs: a step that finds its arrays in the cache, two scored steps
 //   and the communication, 8 workers, 95 MB 131/140; one scored step after a pass that leaves them there, 70 MB 34.9/38.3.
 //   plain SGD step: 187 MB 100.5/90.2 alone, but the pull that follows finds x in the cache after a cached one: step

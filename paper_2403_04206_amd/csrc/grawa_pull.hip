@@ -176,7 +176,7 @@ template <int K> __device__ __forceinline__ int cell_layer_of(const CellWeights<
 // The pull is x + lambda (c - x), one fma, which leaves a single worker exactly unchanged.
 // moving != 0 (EASGD, Appendix F): center_out holds the previous center c0 on entry and the
 // center used and stored is c0 + rho (c - c0).
-// WPE caps the waves per SIMD (grawa_waves_for): more only queues requests to K far-apart rows and costs DRAM
+// WPE caps the waves per SIMD (grawa_waves_for; cached accesses: launch_plain): more only queues requests to K far-apart rows and costs DRAM
 // efficiency (measured: K = 16 at 3 waves 6.1 TB/s, at 8 waves 5.7; K = 8 at 4 waves 6.5, at 8 waves 6.2).
 // TILES: weights from the tile sums, by the maps of a plan or found in the offsets (GRAWA_TILES_SLOTS).
 enum { GRAWA_TILES_NONE = 0, GRAWA_TILES_MAPS = 1, GRAWA_TILES_SLOTS = 2 };
