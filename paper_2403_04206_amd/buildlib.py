@@ -42,11 +42,22 @@ def needs_build() -> bool:
     return any(os.path.getmtime(f) > t for f in SOURCES + HEADERS)
 
 
+def rows_need_build() -> bool:
+    return not os.path.exists(ROWS) or os.path.getmtime(ROWS) < os.path.getmtime(ROWS_SOURCE)
+
+
 def build(force: bool = True, verbose: bool = False) -> str:
-    """Compile the library (one object per source, in parallel, then one link); returns its path.
-    force=False skips an up-to-date build."""
-    if not force and not needs_build():
-        return LIB
+    """Compile the library and the binding's native argument checks; returns the library's path.
+    force=False skips what is up to date."""
+    if force or needs_build():
+        build_library(verbose)
+    if force or rows_need_build():
+        build_rows()
+    return LIB
+
+
+def build_library(verbose: bool = False) -> str:
+    """Compile the library: one object per source, in parallel, then one link."""
     os.makedirs(BUILD, exist_ok=True)
     tag = ".tmp.%d" % os.getpid()
     inc = ["-I", os.path.join(ROOT, "include"), "-I", CSRC]
@@ -83,14 +94,22 @@ def build(force: bool = True, verbose: bool = False) -> str:
     return LIB
 
 
+def rows_built_for() -> str:
+    """The torch and the Python whose object layouts the native argument checks are compiled against."""
+    import sys
+    import torch
+    return "torch %s %s, %s" % (torch.__version__, torch.version.git_version, sys.implementation.cache_tag)
+
+
 def build_rows() -> str:
     """Compile the binding's native argument checks (an extension module that sees torch's tensors) with g++."""
     import sysconfig
     import torch
     from torch.utils.cpp_extension import include_paths, library_paths
     tmp = ROWS + ".tmp.%d" % os.getpid()
-    cmd = ["g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__",
-           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-I", sysconfig.get_paths()["include"]]
+    cmd = ["g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall", "-Wextra", "-D__HIP_PLATFORM_AMD__",
+           "-DGRAWA_ROWS_BUILT_FOR=\"%s\"" % rows_built_for(),
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-isystem", sysconfig.get_paths()["include"]]
     cmd += [a for p in include_paths() for a in ("-isystem", p)] + [ROWS_SOURCE, "-o", tmp]
     cmd += ["-L" + p for p in library_paths()] + ["-lc10", "-ltorch_cpu", "-ltorch_python"]
     try:
@@ -121,4 +140,3 @@ def build_c_client(src: str, out: str) -> str:
 
 if __name__ == "__main__":
     print(build(force=True, verbose=True))
-    print(build_rows())

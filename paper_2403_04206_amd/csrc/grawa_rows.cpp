@@ -40,4 +40,14 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_rows", nullptr, -1, methods, null
 
 } // namespace
 
-PyMODINIT_FUNC PyInit__rows() { return PyModule_Create(&module); }
+// The functions above read torch's objects through the headers this file was compiled with, so the module names the torch
+// and the Python that it is for, and grawa.py uses it with no other.
+PyMODINIT_FUNC PyInit__rows()
+{
+    PyObject *m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "built_for", GRAWA_ROWS_BUILT_FOR) != 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}

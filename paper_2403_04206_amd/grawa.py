@@ -13,6 +13,8 @@ import os
 import numpy as np
 import torch
 
+from . import buildlib
+
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libgrawa.so")
 
@@ -108,10 +110,13 @@ def _stream_no_tensors(stream=None):
 
 
 # The checks of _params and _grads on a CUDA tensor by native code (csrc/grawa_rows.cpp): (pointer, row stride, dtype code), or
-# None for whatever is not plainly in order; the Python checks below look again then, and raise.
+# None for whatever is not plainly in order; the Python checks below look again then, and raise.  The module reads torch's
+# objects by the layout it was compiled for: one of another torch or Python may load all the same and is not used.
 try:
-    from ._rows import rows as _native_rows
-except ImportError:                      # not built: the Python checks alone
+    from ._rows import built_for, rows as _native_rows
+    if built_for != buildlib.rows_built_for():
+        raise ImportError("_rows.so is for %s" % built_for)
+except Exception:                        # not built, or not for this torch: the Python checks alone
     def _native_rows(t, K, P, grads):
         return None
 

@@ -1,11 +1,15 @@
 """The native argument checks of the binding against the Python ones, over tensors that are in order and tensors that are
 not: where the native code gives an answer it is the Python checks' answer, and what they refuse it leaves to them."""
+import importlib.util
 import itertools
+import os
+import sys
+import types
 
 import pytest
 import torch
 
-from paper_2403_04206_amd import grawa
+from paper_2403_04206_amd import buildlib, grawa
 
 
 def forms(dev):
@@ -55,6 +59,37 @@ def test_host_tensors_are_left_to_the_python_checks(monkeypatch):
     if grawa._native_rows.__module__ == grawa.__name__:
         pytest.skip("the native checks are not built here")
     assert compare("cpu", monkeypatch) == {False}
+
+
+@pytest.mark.parametrize("built_for", [None, "torch 1.0 abc, cpython-310", buildlib.rows_built_for() + "0"])
+def test_module_of_another_torch_is_not_used(built_for, monkeypatch):
+    # the checks read torch's objects by a layout compiled in: a module of another torch could give wrong pointers
+    other = types.ModuleType("paper_2403_04206_amd._rows")
+    other.rows = lambda t, K, P, grads: (1, 2, 0)
+    if built_for is not None:
+        other.built_for = built_for
+    monkeypatch.setitem(sys.modules, other.__name__, other)
+    spec = importlib.util.spec_from_file_location("paper_2403_04206_amd.grawa_again", grawa.__file__)
+    again = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(again)
+    assert again._native_rows is not other.rows and again._native_rows(torch.zeros(2, 4), 2, 4, False) is None
+
+
+def test_native_checks_are_rebuilt_when_their_source_is_newer(tmp_path, monkeypatch):
+    source, module, built = tmp_path / "rows.cpp", tmp_path / "rows.so", []
+    source.write_text("")
+    monkeypatch.setattr(buildlib, "ROWS_SOURCE", str(source))
+    monkeypatch.setattr(buildlib, "ROWS", str(module))
+    monkeypatch.setattr(buildlib, "needs_build", lambda: False)
+    monkeypatch.setattr(buildlib, "build_rows", lambda: built.append(module.write_text("")))
+    buildlib.build(force=False)
+    assert len(built) == 1                               # not there
+    os.utime(source, (1, 1))
+    buildlib.build(force=False)
+    assert len(built) == 1                               # up to date
+    os.utime(module, (0, 0))
+    buildlib.build(force=False)
+    assert len(built) == 2                               # older than its source
 
 
 @pytest.mark.gpu
