@@ -4,6 +4,7 @@ from __future__ import annotations
 import os
 import shutil
 import subprocess
+import sys
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -48,11 +49,17 @@ def rows_need_build() -> bool:
 
 def build(force: bool = True, verbose: bool = False) -> str:
     """Compile the library and the binding's native argument checks; returns the library's path.
-    force=False skips what is up to date."""
+    force=False skips what is up to date.  The binding works without the native checks (a machine may lack g++ or the
+    headers of Python or torch): if they fail to compile, that is reported and no older module is left in their place."""
     if force or needs_build():
         build_library(verbose)
     if force or rows_need_build():
-        build_rows()
+        try:
+            build_rows()
+        except Exception as e:
+            if os.path.exists(ROWS):
+                os.remove(ROWS)
+            print("the binding's native argument checks are not built, the Python checks serve: %s" % e, file=sys.stderr, flush=True)
     return LIB
 
 
@@ -96,7 +103,6 @@ def build_library(verbose: bool = False) -> str:
 
 def rows_built_for() -> str:
     """The torch and the Python whose object layouts the native argument checks are compiled against."""
-    import sys
     import torch
     return "torch %s %s, %s" % (torch.__version__, torch.version.git_version, sys.implementation.cache_tag)
 

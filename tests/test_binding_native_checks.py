@@ -92,6 +92,17 @@ def test_native_checks_are_rebuilt_when_their_source_is_newer(tmp_path, monkeypa
     assert len(built) == 2                               # older than its source
 
 
+def test_a_build_without_the_native_checks(tmp_path, monkeypatch, capfd):
+    # no compiler for them: the library is built all the same, and a module of an older source is not left to be loaded
+    module = tmp_path / "rows.so"
+    module.write_text("")
+    monkeypatch.setattr(buildlib, "ROWS", str(module))
+    monkeypatch.setattr(buildlib, "build_library", lambda verbose=False: None)
+    monkeypatch.setenv("PATH", str(tmp_path))
+    assert buildlib.build(force=True) == buildlib.LIB
+    assert not module.exists() and "not built" in capfd.readouterr().err
+
+
 @pytest.mark.gpu
 def test_native_checks_agree(monkeypatch):
     assert grawa._native_rows.__module__ != grawa.__name__, "the native checks are not built"
