@@ -592,6 +592,7 @@ template <int K, bool SGD, typename GT, bool LNT, int ST> static void launch_wid
 // W cells a block; WPE caps the waves per SIMD.
 template <int Q, bool REM, int S, int V, int W, int WPE, bool SGD, typename GT, bool NT, int ST> static void launch_split(GRAWA_CP_ARGS)
 {
+    static_assert(GRAWA_SPLIT_LAUNCH_CELLS % W == 0, "a launch begins with the first cell of a block");
     for (int64_t at = 0; at < p->n_cells;) { // one launch but for the longest rows
         const int64_t n = grawa_split_blocks(p->n_cells, at);
         hipExtLaunchKernelGGL((k_center_pull_split<Q, REM, S, V, W, WPE, SGD, GT, NT, ST>), dim3((unsigned)((n + W - 1) / W)),

@@ -49,11 +49,12 @@ def test_row_split_streaming(K, dtype, fused):
     torch.cuda.empty_cache()
 
 
-@pytest.mark.parametrize("K", [16, 24])
-def test_row_split_second_launch(K):
+# Rows on the line grid: one cell a block; 8 elements off it: 8 cells a block (6 workers), 4 (10 and 16) and 2 (24 and 25).
+@pytest.mark.parametrize("K,pad", [(16, 0), (24, 0), (6, 8), (10, 8), (16, 8), (24, 8), (25, 8)])
+def test_row_split_second_launch(K, pad):
     # 2^18 cells are one launch; one column more starts a second.  The caller's weights, so that x is the only large array.
     for P in ((1 << 26) + 1, (1 << 26) + 256 + 1):
-        x = torch.empty((K, W.round_up(P, 256)), device=DEV).normal_(0.0, 0.05, generator=torch.Generator(device=DEV).manual_seed(K))
+        x = torch.empty((K, W.round_up(P, 256) + pad), device=DEV).normal_(0.0, 0.05, generator=torch.Generator(device=DEV).manual_seed(K))
         x0 = x.clone()
         off = [0, P // 2 + 3, P]
         beta = torch.rand((K, 2), device=DEV, generator=torch.Generator(device=DEV).manual_seed(P))
