@@ -574,12 +574,6 @@ constexpr int grawa_waves_wide(int k, bool sgd /* fp32 gradients */)
     return k <= 5 ? 2 : 1;
 }
 
-// The wide form off the line grid: with the fp32 SGD step streaming loads and stores that the L2 merges, else cached loads and
-// stores written through.  LGRAWA with the step, us, cached loads / streaming: 2 workers 140 MB 98.2 / 94.1, 1.2 GB 783 / 775, 4
-// 99.3 / 98.1 and 789 / 787, 5 100.4 / 98.9 and 820 / 798, but 3 1.2 GB 798 / 810; MGRAWA without it 2 477 / 481, 3 482 / 489,
-// 4 491 / 507, 5 489 / 498; with bf16 gradients 140 MB 4 workers 80.3 / 83.2, 5 80.1 / 82.5.
-constexpr bool grawa_wide_merges(int k, bool sgd /* fp32 gradients */) { return sgd && k <= 5 && k != 3; }
-
 template <int K, bool SGD, typename GT, bool LNT, int ST> static void launch_wide(GRAWA_CP_ARGS)
 {
     (void)tw;
@@ -657,47 +651,35 @@ template <bool SGD, typename GT, bool NT> static hipError_t dispatch_cp(GRAWA_CP
 #undef GRAWA_CP_SPLIT
 }
 
-// Rows off the line grid, 16-byte lanes: up to 5 workers, and with the fp32 SGD step, the wide form, else row-split bursts.  A
-// worker count without a kernel is an error, never a call that does nothing.
-template <bool SGD, typename GT> static hipError_t dispatch_cp_wide(GRAWA_CP_ARGS)
+// Large rows off the line grid, 16-byte lanes: the forms of grawa_off_grid, whose plain ones do not come here.  A worker count
+// without a kernel is an error, never a call that does nothing.
+template <bool SGD, typename GT> static hipError_t dispatch_cp_off_grid(GRAWA_CP_ARGS)
 {
     constexpr bool F32_SGD = SGD && sizeof(GT) == 4;
-#define GRAWA_CP_WIDE(N)                                                                                                    \
-    case N:                                                                                                                 \
-        if constexpr (grawa_wide_merges(N, F32_SGD)) launch_wide<N, SGD, GT, true, GRAWA_ST_MERGE>(GRAWA_CP_PASS);          \
-        else if constexpr (N <= 5 || F32_SGD) launch_wide<N, SGD, GT, false, GRAWA_ST_STREAM>(GRAWA_CP_PASS);               \
-        else if constexpr (N < 16) launch_burst<N / 4, (N % 4 != 0), 4, SGD, GT, true, GRAWA_ST_MERGE>(GRAWA_CP_PASS);      \
-        else launch_burst<N / 4, (N % 4 != 0), 4, SGD, GT, false, GRAWA_ST_STREAM>(GRAWA_CP_PASS);                          \
-        return hipGetLastError();
-    switch (p->K) {
-        GRAWA_WIDE_COUNTS(GRAWA_CP_WIDE)
+#define GRAWA_CP_EACH(N)                                                                                                     \
+    case N: {                                                                                                                \
+        constexpr GrawaOffGrid F = grawa_off_grid(N, F32_SGD);                                                               \
+        constexpr int ST = F.merge ? GRAWA_ST_MERGE : GRAWA_ST_STREAM;                                                       \
+        if constexpr (F.form == GRAWA_OFF_GRID_WIDE) launch_wide<N, SGD, GT, F.merge, ST>(GRAWA_CP_PASS);                    \
+        else if constexpr (F.form == GRAWA_OFF_GRID_BURST)                                                                   \
+            launch_burst<N / F.groups, (N % F.groups != 0), F.groups, SGD, GT, F.merge, ST>(GRAWA_CP_PASS);                  \
+        else return hipErrorInvalidValue;                                                                                    \
+        return hipGetLastError();                                                                                            \
     }
-    return hipErrorInvalidValue;
-#undef GRAWA_CP_WIDE
-}
-
-// Row-split bursts for the worker counts between and beyond those (grawa_burst_form).
-template <bool SGD, typename GT> static hipError_t dispatch_cp_burst(GRAWA_CP_ARGS)
-{
-#define GRAWA_CP_BURST2(N) \
-    case N: launch_burst<N / 2, (N % 2 != 0), 2, SGD, GT, true, GRAWA_ST_MERGE>(GRAWA_CP_PASS); return hipGetLastError();
-#define GRAWA_CP_BURST4(N) \
-    case N: launch_burst<N / 4, (N % 4 != 0), 4, SGD, GT, true, GRAWA_ST_MERGE>(GRAWA_CP_PASS); return hipGetLastError();
-#define GRAWA_CP_BURST8(N)                                                                                     \
-    case N:                                                                                                    \
-        if (p->K % 8 == 0) launch_burst<N, false, 8, SGD, GT, false, GRAWA_ST_STREAM>(GRAWA_CP_PASS);          \
-        else launch_burst<N, true, 8, SGD, GT, false, GRAWA_ST_STREAM>(GRAWA_CP_PASS);                         \
+#define GRAWA_CP_EIGHTH(N)                                                                                 \
+    case N:                                                                                                \
+        if (p->K % 8 == 0) launch_burst<N, false, 8, SGD, GT, false, GRAWA_ST_STREAM>(GRAWA_CP_PASS);      \
+        else launch_burst<N, true, 8, SGD, GT, false, GRAWA_ST_STREAM>(GRAWA_CP_PASS);                     \
         return hipGetLastError();
     switch (p->K) {
-        GRAWA_CP_BURST2(6) GRAWA_CP_BURST2(7) GRAWA_CP_BURST2(8) GRAWA_CP_BURST2(9) GRAWA_CP_BURST4(10) GRAWA_CP_BURST4(11)
+        GRAWA_OFF_GRID_EACH(GRAWA_CP_EACH)
     }
     switch (p->K / 8) {
-        GRAWA_CP_BURST8(3) GRAWA_CP_BURST8(4) GRAWA_CP_BURST8(5) GRAWA_CP_BURST8(6) GRAWA_CP_BURST8(7) GRAWA_CP_BURST8(8)
+        GRAWA_OFF_GRID_EIGHTHS(GRAWA_CP_EIGHTH)
     }
     return hipErrorInvalidValue;
-#undef GRAWA_CP_BURST2
-#undef GRAWA_CP_BURST4
-#undef GRAWA_CP_BURST8
+#undef GRAWA_CP_EACH
+#undef GRAWA_CP_EIGHTH
 }
 
 // Weights straight from the tile sums (GRAWA_TILES_COUNTS), cached accesses.
@@ -743,15 +725,13 @@ hipError_t grawa_launch_center_pull(const grawa_plan *p, float *x, int64_t ldx, 
     // Cached accesses of small arrays want no cap, unless rows off the grid make many requests of them (launch_plain).
     const bool capped = large || (!nt && bytes > GRAWA_STREAMING_MIN_BYTES / 2);
     nt = nt && large;
-    const bool wide = large && !nt && grawa_wide_has_kernel(p->K);
-    const bool burst = large && !nt && grawa_burst_form(p->K, fuse_sgd && dt != GRAWA_BF16);
+    const bool off_grid = large && !nt && grawa_off_grid(p->K, fuse_sgd && dt != GRAWA_BF16).form != GRAWA_OFF_GRID_PLAIN;
     const void *g = g_sgd;
     const int64_t ldg = ldg_sgd;
 #define GRAWA_CP_GO(SGD, GT)                                                      \
     (!beta  ? dispatch_cp_tiles<SGD, GT>(GRAWA_CP_PASS)                           \
      : nt   ? dispatch_cp<SGD, GT, true>(GRAWA_CP_PASS)                           \
-     : wide ? dispatch_cp_wide<SGD, GT>(GRAWA_CP_PASS)                            \
-     : burst ? dispatch_cp_burst<SGD, GT>(GRAWA_CP_PASS)                          \
+     : off_grid ? dispatch_cp_off_grid<SGD, GT>(GRAWA_CP_PASS)                    \
             : dispatch_cp<SGD, GT, false>(GRAWA_CP_PASS))
     if (!fuse_sgd) return GRAWA_CP_GO(false, float);
     return dt == GRAWA_BF16 ? GRAWA_CP_GO(true, uint16_t) : GRAWA_CP_GO(true, float);

@@ -17,28 +17,47 @@ static inline int64_t grawa_split_blocks(int64_t n_cells, int64_t at)
     return n_cells - at < GRAWA_SPLIT_LAUNCH_CELLS ? n_cells - at : GRAWA_SPLIT_LAUNCH_CELLS;
 }
 
-// The worker counts that have a kernel of their own for large rows off the line grid (up to 5 the wide form, from 12 on
-// row-split bursts), and of the form with the weights from the tile sums.  The rules below and the dispatch (grawa_pull.hip)
-// are made from the same lists.
-#define GRAWA_WIDE_COUNTS(X) \
-    X(1) X(2) X(3) X(4) X(5) X(12) X(13) X(14) X(15) X(16) X(17) X(18) X(19) X(20) X(21) X(22) X(23)
+// Form of the pull of large rows off the line grid (16-byte lanes, grawa_pull.hip): the wide form, or row-split bursts with
+// `groups` groups of waves; plain: the forms of the other rows.  merge: streaming loads and stores that the L2 merges, else cached loads and
+// stores written through.  The dispatch is made from this rule; why the lines lie here stands at the kernels.
+enum { GRAWA_OFF_GRID_PLAIN = 0, GRAWA_OFF_GRID_WIDE = 1, GRAWA_OFF_GRID_BURST = 2 };
+struct GrawaOffGrid {
+    int form, groups;
+    bool merge;
+};
+static constexpr GrawaOffGrid grawa_off_grid(int K, bool f32_sgd)
+{
+    // Wide, up to 5 workers, the step with fp32 gradients.  LGRAWA with the step, us, cached loads / streaming: 2 workers 140 MB
+    // 98.2 / 94.1, 1.2 GB 783 / 775, 4 99.3 / 98.1 and 789 / 787, 5 100.4 / 98.9 and 820 / 798, but 3 1.2 GB 798 / 810; MGRAWA
+    // without it 2 477 / 481, 3 482 / 489, 4 491 / 507, 5 489 / 498; with bf16 gradients 140 MB 4 workers 80.3 / 83.2, 5 80.1 / 82.5.
+    if (K <= 5) return {GRAWA_OFF_GRID_WIDE, 1, f32_sgd && K != 3};
+    if (f32_sgd && K >= 12 && K <= 23) return {GRAWA_OFF_GRID_WIDE, 1, false};
+    // Nine workers with the fp32 SGD step (10 loads of a lane in two groups of waves, 6 in four): 1.2 GB 866 us plain, 884 and 890 for 918
+    // (200 MB 150.5 / 146.6).
+    if (K > 71 || (K == 9 && f32_sgd)) return {GRAWA_OFF_GRID_PLAIN, 1, false};
+    return {GRAWA_OFF_GRID_BURST, K <= 9 ? 2 : K <= 23 ? 4 : 8, K <= 15};
+}
+// The counts that have a kernel each; the others share one by K / 8.
+#define GRAWA_OFF_GRID_EACH(X) \
+    X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16) X(17) X(18) X(19) X(20) X(21) X(22) X(23)
+#define GRAWA_OFF_GRID_EIGHTHS(X) X(3) X(4) X(5) X(6) X(7) X(8)
+static constexpr bool grawa_off_grid_has_kernel(int K, bool f32_sgd)
+{
+    const GrawaOffGrid f = grawa_off_grid(K, f32_sgd);
+    if (f.form == GRAWA_OFF_GRID_PLAIN) return true; // any count
+#define GRAWA_COUNT_IS(N) || K == N
+#define GRAWA_EIGHTH_IS(N) || K / 8 == N
+    if (false GRAWA_OFF_GRID_EACH(GRAWA_COUNT_IS)) return f.form == GRAWA_OFF_GRID_WIDE || K >= f.groups;
+    return f.form == GRAWA_OFF_GRID_BURST && f.groups == 8 && !f.merge && (false GRAWA_OFF_GRID_EIGHTHS(GRAWA_EIGHTH_IS));
+#undef GRAWA_COUNT_IS
+#undef GRAWA_EIGHTH_IS
+}
+
+// The worker counts that have a kernel of the form with the weights from the tile sums.  The rule below and the dispatch
+// (grawa_pull.hip) are made from the same list.
 #define GRAWA_TILES_COUNTS(X) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15)
 #define GRAWA_COUNT_TRUE(N) \
     case N: return true;
-static inline bool grawa_wide_has_kernel(int K)
-{
-    switch (K) {
-        GRAWA_WIDE_COUNTS(GRAWA_COUNT_TRUE)
-    }
-    return false;
-}
-// Row-split bursts by K / 2, K / 4 and K / 8 serve the counts between and beyond those.
-// Nine workers with the fp32 SGD step (10 loads of a lane in two groups of waves, 6 in four) keep the plain form: 1.2 GB 866 us
-// for 884 and 890 for 918 (200 MB 150.5 / 146.6).
-static inline bool grawa_burst_form(int K, bool f32_sgd)
-{
-    return K >= 6 && K <= 71 && !grawa_wide_has_kernel(K) && !(K == 9 && f32_sgd);
-}
 static inline bool grawa_tiles_has_kernel(int K)
 {
     switch (K) {

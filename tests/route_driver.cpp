@@ -1,7 +1,8 @@
 // Prints the launch shapes that the host-side rules of paper_2403_04206_amd/csrc/grawa_route.h give (no GPU toolchain).
 //   split <n_cells>...   -> per launch: n_cells, first cell, blocks, threads
 //   model <L>...         -> per line: L, 1 if the last block of the norms' launch forms the model-level weights
-//   counts <K>...        -> per line: K, 1 if the wide form has a kernel for it, 1 if the weights-in-the-pull form has
+//   counts <K>...        -> per line: K, 1 if the weights-in-the-pull form has a kernel for it
+//   offgrid <K>...       -> per line, without and with the fp32 SGD step: K, 0 or 1, form, groups, merge, 1 if that has a kernel
 //   plain <K> <n_cells>... -> per pair: the pair, 1 if the one-column-per-lane form serves it
 //   tiles <K> <n_cells>... -> per pair: the pair, 1 if the pull forms the per-layer weights
 //   estimate <K> <L> <max_tiles> ... -> per triple: the triple, rows, threads
@@ -27,8 +28,16 @@ int main(int argc, char **argv)
         return 0;
     }
     if (!std::strcmp(argv[1], "counts")) {
+        for (int i = 2; i < argc; ++i) std::printf("%s %d\n", argv[i], grawa_tiles_has_kernel(std::atoi(argv[i])));
+        return 0;
+    }
+    if (!std::strcmp(argv[1], "offgrid")) {
         for (int i = 2; i < argc; ++i)
-            std::printf("%s %d %d\n", argv[i], grawa_wide_has_kernel(std::atoi(argv[i])), grawa_tiles_has_kernel(std::atoi(argv[i])));
+            for (int f32_sgd = 0; f32_sgd < 2; ++f32_sgd) {
+                const GrawaOffGrid f = grawa_off_grid(std::atoi(argv[i]), f32_sgd);
+                std::printf("%s %d %d %d %d %d\n", argv[i], f32_sgd, f.form, f.groups, f.merge,
+                            grawa_off_grid_has_kernel(std::atoi(argv[i]), f32_sgd));
+            }
         return 0;
     }
     if (!std::strcmp(argv[1], "plain")) {

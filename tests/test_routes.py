@@ -60,11 +60,23 @@ def test_weights_in_the_pull(driver):
 
 
 def test_no_route_without_a_kernel(driver):
-    # the rules that send a call to the wide or the weights-in-the-pull form know no other counts than their dispatch
-    have = {k: (wide, tiles) for k, wide, tiles in driver("counts", *range(1, 1025))}
-    assert [k for k in have if have[k][0]] == [1, 2, 3, 4, 5] + list(range(12, 24))
-    assert [k for k in have if have[k][1]] == list(range(1, 16))
-    assert all(r[2] == have[r[0]][1] for r in driver("tiles", *[v for k in range(1, 1025) for v in (k, 1)]))
+    # the rule that sends a call to the weights-in-the-pull form knows no other counts than its dispatch
+    have = dict(driver("counts", *range(1, 1025)))
+    assert [k for k in have if have[k]] == list(range(1, 16))
+    assert all(r[2] == have[r[0]] for r in driver("tiles", *[v for k in range(1, 1025) for v in (k, 1)]))
+
+
+def test_forms_of_rows_off_the_grid(driver):
+    plain, wide, burst = range(3)
+    rows = {(k, sgd): tuple(rest) for k, sgd, *rest in driver("offgrid", *range(1, 1025))}
+    assert all(has for _, _, _, has in rows.values())     # every count has a kernel of the form that the rule names
+    for (k, sgd), (form, groups, merge, _) in rows.items():
+        if k > 71 or (k == 9 and sgd):
+            assert form == plain
+        elif k <= 5 or (sgd and 12 <= k <= 23):
+            assert form == wide
+        else:
+            assert form == burst and (groups, merge) == ((2, 1) if k <= 9 else (4, 1) if k <= 15 else (4, 0) if k <= 23 else (8, 0))
 
 
 def test_plain_form_counts(driver):
@@ -75,7 +87,8 @@ def test_plain_form_counts(driver):
 
 def test_a_missing_kernel_is_an_error():
     src = open(os.path.join(ROOT, "paper_2403_04206_amd", "csrc", "grawa_pull.hip")).read()
-    for name, counts in (("dispatch_cp_wide", "GRAWA_WIDE_COUNTS"), ("dispatch_cp_tiles", "GRAWA_TILES_COUNTS")):
+    for name, counts in (("dispatch_cp_off_grid", "GRAWA_OFF_GRID_EACH"), ("dispatch_cp_off_grid", "GRAWA_OFF_GRID_EIGHTHS"),
+                         ("dispatch_cp_tiles", "GRAWA_TILES_COUNTS")):
         body = src[src.index("static hipError_t %s(" % name):]
         body = body[:body.index("\n}\n")]
         assert counts in body and "return hipErrorInvalidValue;" in body
