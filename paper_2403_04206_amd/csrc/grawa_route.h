@@ -28,13 +28,12 @@ struct GrawaOffGrid {
 static constexpr GrawaOffGrid grawa_off_grid(int K, bool f32_sgd)
 {
     // Wide, up to 5 workers, the step with fp32 gradients.  LGRAWA with the step, us, cached loads / streaming: 2 workers 140 MB
-    // 98.2 / 94.1, 1.2 GB 783 / 775, 4 99.3 / 98.1 and 789 / 787, 5 100.4 / 98.9 and 820 / 798, but 3 1.2 GB 798 / 810; MGRAWA
-    // without it 2 477 / 481, 3 482 / 489, 4 491 / 507, 5 489 / 498; with bf16 gradients 140 MB 4 workers 80.3 / 83.2, 5 80.1 / 82.5.
-    if (K <= 5) return {GRAWA_OFF_GRID_WIDE, 1, f32_sgd && K != 3};
+    // 98.2 / 94.1, 1.2 GB 783 / 775, 3 200 MB 137.6 / 133.7, 1.2 GB 808 / 800, 4 99.3 / 98.1 and 789 / 787, 5 100.4 / 98.9 and 820 /
+    // 798; MGRAWA without it 2 477 / 481, 3 482 / 489, 4 491 / 507, 5 489 / 498; with bf16 gradients 140 MB 4 workers 80.3 / 83.2, 5
+    // 80.1 / 82.5.
+    if (K <= 5) return {GRAWA_OFF_GRID_WIDE, 1, f32_sgd};
     if (f32_sgd && K >= 12 && K <= 23) return {GRAWA_OFF_GRID_WIDE, 1, false};
-    // Nine workers with the fp32 SGD step (10 loads of a lane in two groups of waves, 6 in four): 1.2 GB 866 us plain, 884 and 890 for 918
-    // (200 MB 150.5 / 146.6).
-    if (K > 71 || (K == 9 && f32_sgd)) return {GRAWA_OFF_GRID_PLAIN, 1, false};
+    if (K > 71) return {GRAWA_OFF_GRID_PLAIN, 1, false};
     return {GRAWA_OFF_GRID_BURST, K <= 9 ? 2 : K <= 23 ? 4 : 8, K <= 15};
 }
 // The counts that have a kernel each; the others share one by K / 8.

@@ -68,7 +68,7 @@ def test_local_steps_either_side_of_a_line(step, dtype, mb):
 
 # Each number of wave groups (2, 4, 8) with and without the guarded row, the first and last worker count of each, and the
 # neighbours of the dispatch's lines (5/6, 9/10, 11/12, 15/16, 23/24, 71/72).
-@pytest.mark.parametrize("K", [5, 6, 9, 10, 11, 12, 15, 16, 19, 23, 24, 25, 40, 63, 71, 72])
+@pytest.mark.parametrize("K", [3, 5, 6, 9, 10, 11, 12, 15, 16, 19, 23, 24, 25, 40, 63, 71, 72])
 @pytest.mark.parametrize("kind", ["pull", "easgd", "f32", "bf16"])
 def test_pull_of_rows_off_the_grid(K, kind):
     # cells of one layer, of 2 to 8 and of 256, a boundary on a cell's edge; the row ends inside a lane, a cell and a block

@@ -71,10 +71,10 @@ def test_forms_of_rows_off_the_grid(driver):
     rows = {(k, sgd): tuple(rest) for k, sgd, *rest in driver("offgrid", *range(1, 1025))}
     assert all(has for _, _, _, has in rows.values())     # every count has a kernel of the form that the rule names
     for (k, sgd), (form, groups, merge, _) in rows.items():
-        if k > 71 or (k == 9 and sgd):
+        if k > 71:
             assert form == plain
         elif k <= 5 or (sgd and 12 <= k <= 23):
-            assert form == wide
+            assert form == wide and merge == (sgd and k <= 5)
         else:
             assert form == burst and (groups, merge) == ((2, 1) if k <= 9 else (4, 1) if k <= 15 else (4, 0) if k <= 23 else (8, 0))
 
