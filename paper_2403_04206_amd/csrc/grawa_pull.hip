@@ -725,7 +725,8 @@ hipError_t grawa_launch_center_pull(const grawa_plan *p, float *x, int64_t ldx, 
     // Cached accesses of small arrays want no cap, unless rows off the grid make many requests of them (launch_plain).
     const bool capped = large || (!nt && bytes > GRAWA_STREAMING_MIN_BYTES / 2);
     nt = nt && large;
-    const bool off_grid = large && !nt && grawa_off_grid(p->K, fuse_sgd && dt != GRAWA_BF16).form != GRAWA_OFF_GRID_PLAIN;
+    const bool off_grid = large && !nt && grawa_off_grid_large(p->K, fuse_sgd, bytes, GRAWA_STREAMING_MIN_BYTES) &&
+                          grawa_off_grid(p->K, fuse_sgd && dt != GRAWA_BF16).form != GRAWA_OFF_GRID_PLAIN;
     const void *g = g_sgd;
     const int64_t ldg = ldg_sgd;
 #define GRAWA_CP_GO(SGD, GT)                                                      \

@@ -25,6 +25,15 @@ struct GrawaOffGrid {
     int form, groups;
     bool merge;
 };
+// Bursts of a pull without the SGD step, of the counts whose other form leaves x in the last-level cache, from 320 MB of x on.  MGRAWA, us,
+// that form / bursts, one set again and again and three sets in turn: 8 workers 134 MB 73 / 78 and 81 / 79, 200 MB 103 / 113 and 118 / 113, 260 MB
+// 139 / 145 and 144 / 147, 400 MB 223 / 214 and 227 / 213; 32 workers 134 MB 78 / 88 and 89 / 89, 200 MB 109 / 123 and 128 / 124, 260 MB
+// 150 / 156 and 164 / 157, 400 MB 245 / 244 and 250 / 240; 64 workers 200 MB 116 / 136 and 141 / 137, 400 MB 259 / 252 and 264 / 251.
+#define GRAWA_BURST_MIN_BYTES ((int64_t)320 << 20)
+static constexpr bool grawa_off_grid_large(int K, bool sgd, int64_t bytes, int64_t large)
+{
+    return bytes > (!sgd && ((K >= 6 && K <= 11) || K >= 24) ? GRAWA_BURST_MIN_BYTES : large);
+}
 static constexpr GrawaOffGrid grawa_off_grid(int K, bool f32_sgd)
 {
     // Wide, up to 5 workers, the step with fp32 gradients.  LGRAWA with the step, us, cached loads / streaming: 2 workers 140 MB

@@ -3,6 +3,7 @@
 //   model <L>...         -> per line: L, 1 if the last block of the norms' launch forms the model-level weights
 //   counts <K>...        -> per line: K, 1 if the weights-in-the-pull form has a kernel for it
 //   offgrid <K>...       -> per line, without and with the fp32 SGD step: K, 0 or 1, form, groups, merge, 1 if that has a kernel
+//   offgrid_large <K> <sgd> <MB>... -> per triple: the triple, 1 if a pull of so many bytes takes that form (others from 128 MB on)
 //   plain <K> <n_cells>... -> per pair: the pair, 1 if the one-column-per-lane form serves it
 //   tiles <K> <n_cells>... -> per pair: the pair, 1 if the pull forms the per-layer weights
 //   estimate <K> <L> <max_tiles> ... -> per triple: the triple, rows, threads
@@ -38,6 +39,12 @@ int main(int argc, char **argv)
                 std::printf("%s %d %d %d %d %d\n", argv[i], f32_sgd, f.form, f.groups, f.merge,
                             grawa_off_grid_has_kernel(std::atoi(argv[i]), f32_sgd));
             }
+        return 0;
+    }
+    if (!std::strcmp(argv[1], "offgrid_large")) {
+        for (int i = 2; i + 2 < argc; i += 3)
+            std::printf("%s %s %s %d\n", argv[i], argv[i + 1], argv[i + 2],
+                        grawa_off_grid_large(std::atoi(argv[i]), std::atoi(argv[i + 1]), (int64_t)std::atoll(argv[i + 2]) << 20, (int64_t)128 << 20));
         return 0;
     }
     if (!std::strcmp(argv[1], "plain")) {

@@ -69,10 +69,11 @@ def test_local_steps_either_side_of_a_line(step, dtype, mb):
 # Each number of wave groups (2, 4, 8) with and without the guarded row, the first and last worker count of each, and the
 # neighbours of the dispatch's lines (5/6, 9/10, 11/12, 15/16, 23/24, 71/72).
 @pytest.mark.parametrize("K", [3, 5, 6, 9, 10, 11, 12, 15, 16, 19, 23, 24, 25, 40, 63, 71, 72])
-@pytest.mark.parametrize("kind", ["pull", "easgd", "f32", "bf16"])
-def test_pull_of_rows_off_the_grid(K, kind):
-    # cells of one layer, of 2 to 8 and of 256, a boundary on a cell's edge; the row ends inside a lane, a cell and a block
-    P = (130 * MB) // (4 * K) // 2048 * 2048 + 2048 + 256 * (K % 5) + 1 + K % 3
+@pytest.mark.parametrize("kind,mb", [("pull", 130), ("pull", 322), ("easgd", 130), ("easgd", 322), ("f32", 130), ("bf16", 130)])
+def test_pull_of_rows_off_the_grid(K, kind, mb):
+    # cells of one layer, of 2 to 8 and of 256, a boundary on a cell's edge; the row ends inside a lane, a cell and a block.
+    # 130 MB and 322 MB: either side of the line from which the counts of bursts alone take them without the step
+    P = (mb * MB) // (4 * K) // 2048 * 2048 + 2048 + 256 * (K % 5) + 1 + K % 3
     sizes = [256, 100, 412] + [32] * 8 + [1] * 256 + [300] * 200
     sizes += [P - sum(sizes) - 130, 120, 10]
     L, gen = len(sizes), torch.Generator(device=DEV).manual_seed(K)

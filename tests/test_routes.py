@@ -79,6 +79,12 @@ def test_forms_of_rows_off_the_grid(driver):
             assert form == burst and (groups, merge) == ((2, 1) if k <= 9 else (4, 1) if k <= 15 else (4, 0) if k <= 23 else (8, 0))
 
 
+def test_bursts_without_the_step_begin_where_no_cache_holds_the_array(driver):
+    rows = driver("offgrid_large", *[v for k in range(1, 72) for sgd in (0, 1) for mb in (128, 129, 320, 321) for v in (k, sgd, mb)])
+    for k, sgd, mb, yes in rows:
+        assert yes == (mb > (320 if not sgd and (6 <= k <= 11 or k >= 24) else 128))
+
+
 def test_plain_form_counts(driver):
     # each count the rule names has a kernel: 1..15 and 17..32 (16 has its own form), and 32 only on few cells
     rows = driver("plain", *[v for k in (1, 23, 24, 32, 33, 64) for n in (1, 800, 801, 1 << 24) for v in (k, n)])
