@@ -311,13 +311,11 @@ __global__ __launch_bounds__(GRAWA_COPY_BLOCK) void k_stream_copy(v4u *__restric
 // V = 4, U = 1 with the proximity step or the scores; bf16 V = 2, U = 2 for the plain step, else
 // V = 4, U = 1 (each the fastest measured for its case on arrays of random values; the spread
 // between shapes is 3-10 %).
-// Large rows off the cache-line grid (wide): 16-byte lanes, streaming loads, and stores that the L2 merges (GRAWA_ST_MERGE).
-// Against cached loads with stores written through (the form before), three sets of arrays in turn, us, 3 and 16 workers,
-// rows 4 or 12 bytes off a line: with the center fp32 100 MB 58.7 -> 51.8, 200 MB 120 -> 103, 1.5 GB 879 -> 815; bf16 200 MB
+// Large rows off the cache-line grid (wide): 16-byte lanes, streaming loads, and stores that the L2 merges (GRAWA_ST_MERGE), up to some
+// sizes cached loads and stores written through (grawa_row_step_merges_from).  Three sets of arrays in turn, us, these / those, rows 4 or
+// 12 bytes off a line: with the center fp32 100 MB 58.7 -> 51.8, 200 MB 120 -> 103, 1.5 GB 879 -> 815; bf16, 3 and 16 workers, 200 MB
 // 97.4 -> 89.8 and 99.4 -> 87.1, 1.5 GB 729 -> 705; scored step with the center and the communication fp32 70 MB 79.9 -> 72.8,
-// 400 MB 378 -> 357, bf16 100 MB 97.7 -> 94.2 and 100.0 -> 93.1.  With the center and bf16 gradients the old form stays up to
-// 128 MB, where its loads find part of the arrays in the cache: 3 workers 70 MB 32.2 / 33.8, 100 MB 44.0 / 45.8, 16 workers
-// 70 MB 35.9 / 36.5 (100 MB 49.8 / 45.5).
+// 400 MB 378 -> 357, bf16 100 MB 97.7 -> 94.2 and 100.0 -> 93.1.
 // The plain step only from 512 MB on: below, the pull that follows would lose the part of x a cached step leaves in the
 // cache (step and LSGD phase, bf16, 3 and 16 workers: 300 MB 210 / 222 and 216 / 229, 520 MB 364 / 376 and 388 / 402, 800 MB
 // 609 / 596 and 638 / 626).
@@ -367,15 +365,17 @@ static hipError_t launch_row_step(const grawa_plan *p, float *x, int64_t ldx, co
     k_row_step<GT, V, U, LNT, ST, PROX, SCORE><<<grid, block, 0, s>>>(x, ldx, (const GT *)g, ldg, lr, center, w, P, \
                                                                        (unsigned)nb, tiles, block_tile0, n_tiles,  \
                                                                        partials)
-#define GRAWA_RS_NT(GT, V, U, PROX, SCORE)                          \
-    do {                                                            \
-        if (nt) GRAWA_RS_GO(GT, V, U, true, GRAWA_ST_STREAM, PROX, SCORE);       \
-        else if (wide) GRAWA_RS_GO(GT, 4, 1, true, GRAWA_ST_MERGE, PROX, SCORE); \
-        else GRAWA_RS_GO(GT, V, U, false, GRAWA_ST_CACHED, PROX, SCORE);         \
+#define GRAWA_RS_NT(GT, V, U, PROX, SCORE)                                                                            \
+    do {                                                                                                              \
+        constexpr int64_t FROM = grawa_row_step_merges_from(sizeof(GT) == 2, PROX, SCORE);                            \
+        constexpr bool NEVER = FROM == GRAWA_ROW_STEP_NEVER, ALWAYS = FROM == 0;                                      \
+        if (nt) GRAWA_RS_GO(GT, V, U, true, GRAWA_ST_STREAM, PROX, SCORE);                                            \
+        else if (!wide) GRAWA_RS_GO(GT, V, U, false, GRAWA_ST_CACHED, PROX, SCORE);                                   \
+        else if (bytes > FROM) GRAWA_RS_GO(GT, 4, 1, !NEVER, (NEVER ? GRAWA_ST_STREAM : GRAWA_ST_MERGE), PROX, SCORE); \
+        else GRAWA_RS_GO(GT, 4, 1, ALWAYS, (ALWAYS ? GRAWA_ST_MERGE : GRAWA_ST_STREAM), PROX, SCORE);                 \
     } while (0)
     if (dt == GRAWA_BF16) {
         if (prox && p) GRAWA_RS_NT(uint16_t, 4, 1, true, true);
-        else if (prox && wide && bytes <= GRAWA_STREAMING_MIN_BYTES) GRAWA_RS_GO(uint16_t, 4, 1, false, GRAWA_ST_STREAM, true, false);
         else if (prox) GRAWA_RS_NT(uint16_t, 4, 1, true, false);
         else if (p) GRAWA_RS_NT(uint16_t, 4, 1, false, true);
         else GRAWA_RS_NT(uint16_t, 2, 2, false, false);

@@ -159,6 +159,24 @@ static inline int64_t grawa_cached_grad_cols(int K, int64_t P, int elem_bytes)
     return cols < P ? cols : P;
 }
 
+// Local steps (k_row_step) over large rows off the line grid: the bytes of x beyond which loads stream and the L2 merges the stores.  Up to
+// there loads are cached and stores written through, which leaves part of the arrays to the next pass.  0: at any size.  Three sets in
+// turn, us, up to the line / beyond it, 3 to 5 workers (in brackets one set again and again):
+//   scored, a round of four steps and the communication: fp32 100 MB 258 / 259 (250 / 261), 180 MB 435 / 443 (424 / 450), 260 MB 624 / 635
+//   (582 / 618), 300 MB 736 / 725 (700 / 721), 350 MB 875 / 845 (868 / 835), 1.5 GB 3695 / 3535; of one step and it: 100 MB 104 / 94
+//   (90 / 92), 260 MB 235 / 226 (216 / 225), 350 MB 311 / 303.  bf16 four steps 100 MB 227 / 231 (218 / 229), 260 MB 535 / 547 (526 / 548),
+//   400 MB 789 / 819 (776 / 821), 700 MB 1425 / 1421, 1.5 GB 3097 / 3068, 2.5 GB 4945 / 4995; one step 100 MB 94 / 88 (84 / 87), 260 MB
+//   210 / 208 (202 / 208)
+//   scored with the center, four steps: fp32 260 MB 729 / 665 (718 / 658); bf16 260 MB 599 / 596 (581 / 596), 500 MB 1205 / 1137; one step
+//   231 / 222 (216 / 220) and 433 / 421
+//   with the center alone: fp32 100 MB 58.7 / 51.8, bf16 70 MB 32.2 / 33.8, 100 MB 44.0 / 45.8, 180 MB 91.7 / 84.9 (82.7 / 84.1)
+#define GRAWA_ROW_STEP_NEVER INT64_MAX
+static constexpr int64_t grawa_row_step_merges_from(bool bf16, bool center, bool scored)
+{
+    if (scored && !center) return bf16 ? GRAWA_ROW_STEP_NEVER : (int64_t)320 << 20;
+    return bf16 && center && !scored ? (int64_t)128 << 20 : 0;
+}
+
 // Scored step: threads of a block that owns a layer of one worker, or 0: blocks of 1024 columns, the estimate as a launch of its
 // own.  One launch saves the other and its boundary (4 us a step) as long as all blocks run at once and the longest layer takes
 // a block not too long (the rate of one CU bounds it).  max_tiles: the most 1024-column tiles of a layer.  Round of

@@ -4,6 +4,7 @@
 //   counts <K>...        -> per line: K, 1 if the weights-in-the-pull form has a kernel for it
 //   offgrid <K>...       -> per line, without and with the fp32 SGD step: K, 0 or 1, form, groups, merge, 1 if that has a kernel
 //   offgrid_large <K> <sgd> <MB>... -> per triple: the triple, 1 if a pull of so many bytes takes that form (others from 128 MB on)
+//   rowstep              -> bf16, center, scored, MB beyond which loads stream and the L2 merges (-1: at no size)
 //   plain <K> <n_cells>... -> per pair: the pair, 1 if the one-column-per-lane form serves it
 //   tiles <K> <n_cells>... -> per pair: the pair, 1 if the pull forms the per-layer weights
 //   estimate <K> <L> <max_tiles> ... -> per triple: the triple, rows, threads
@@ -45,6 +46,13 @@ int main(int argc, char **argv)
         for (int i = 2; i + 2 < argc; i += 3)
             std::printf("%s %s %s %d\n", argv[i], argv[i + 1], argv[i + 2],
                         grawa_off_grid_large(std::atoi(argv[i]), std::atoi(argv[i + 1]), (int64_t)std::atoll(argv[i + 2]) << 20, (int64_t)128 << 20));
+        return 0;
+    }
+    if (!std::strcmp(argv[1], "rowstep")) {
+        for (int i = 0; i < 8; ++i) {
+            const int64_t from = grawa_row_step_merges_from(i & 4, i & 2, i & 1);
+            std::printf("%d %d %d %lld\n", i >> 2, i >> 1 & 1, i & 1, from == GRAWA_ROW_STEP_NEVER ? -1LL : (long long)(from >> 20));
+        }
         return 0;
     }
     if (!std::strcmp(argv[1], "plain")) {

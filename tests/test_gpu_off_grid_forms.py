@@ -32,6 +32,7 @@ def close(got, ref, size):
 
 @pytest.mark.parametrize("step,dtype,mb", [
     ("prox", torch.bfloat16, 120), ("prox", torch.bfloat16, 136), ("prox", torch.float32, 72),
+    ("scored", torch.float32, 72), ("scored", torch.float32, 322), ("scored", torch.bfloat16, 72),
     ("nesterov", torch.bfloat16, 130), ("nesterov", torch.bfloat16, 200), ("nesterov", torch.float32, 130)])
 def test_local_steps_either_side_of_a_line(step, dtype, mb):
     K = 3
@@ -44,6 +45,15 @@ def test_local_steps_either_side_of_a_line(step, dtype, mb):
         cen = torch.empty((P + 3) // 4 * 4, device=DEV).normal_(0.0, 0.05, generator=gen)
         grawa.local_sgd_prox(xs, gs, lr, cen[:P], 0.05, 4.0)
         w = float(torch.tensor(0.05) / torch.tensor(4.0))
+    elif step == "scored":
+        est = torch.empty((K, 2), device=DEV)
+        with grawa.Plan(K, P, [0, P // 3, P]) as plan:
+            plan.local_step_scored(xs, gs, lr, 0.9)
+            plan.local_lgrawa_update(xs, 0.0, est_out=est)               # lambda = 0: x keeps the step's result
+            torch.cuda.synchronize()
+        norms = torch.stack([gs[:, a:b].double().norm(dim=1) for a, b in ((0, P // 3), (P // 3, P))], 1)
+        # after one step the estimate is gamma times the norm; gamma and the result are rounded to 24 bits
+        assert float((est.double() / (0.9 * norms) - 1.0).abs().max()) <= 2.0 ** -23
     else:
         buf = rows(K, P, torch.float32, gen, 0.01)
         b0 = buf.clone()
@@ -56,6 +66,8 @@ def test_local_steps_either_side_of_a_line(step, dtype, mb):
             c64 = cen[:P].double()
             v = x64 - lr64 * g64
             close(x[k, :P], v + w * (c64 - v), size + c64.abs())
+        elif step == "scored":
+            close(x[k, :P], x64 - lr64 * g64, size)
         else:
             b64 = b0[k, :P].double()
             d = g64 + wd * x64

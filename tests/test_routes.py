@@ -85,6 +85,13 @@ def test_bursts_without_the_step_begin_where_no_cache_holds_the_array(driver):
         assert yes == (mb > (320 if not sgd and (6 <= k <= 11 or k >= 24) else 128))
 
 
+def test_local_steps_off_the_grid(driver):
+    # steps that follow each other find part of x in the cache: without the center they stream only where it is larger than that
+    from_mb = {(bf16, center, scored): mb for bf16, center, scored, mb in driver("rowstep")}
+    assert from_mb == {(0, 0, 0): 0, (0, 0, 1): 320, (0, 1, 0): 0, (0, 1, 1): 0,
+                       (1, 0, 0): 0, (1, 0, 1): -1, (1, 1, 0): 128, (1, 1, 1): 0}
+
+
 def test_plain_form_counts(driver):
     # each count the rule names has a kernel: 1..15 and 17..32 (16 has its own form), and 32 only on few cells
     rows = driver("plain", *[v for k in (1, 23, 24, 32, 33, 64) for n in (1, 800, 801, 1 << 24) for v in (k, n)])
