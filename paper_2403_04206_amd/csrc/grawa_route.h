@@ -178,21 +178,33 @@ static constexpr int64_t grawa_row_step_merges_from(bool bf16, bool center, bool
 }
 
 // Scored step: threads of a block that owns a layer of one worker, or 0: blocks of 1024 columns, the estimate as a launch of its
-// own.  One launch saves the other and its boundary (4 us a step) as long as all blocks run at once and the longest layer takes
-// a block not too long (the rate of one CU bounds it).  max_tiles: the most 1024-column tiles of a layer.  Round of
-// four steps and the communication, fp32, us, two launches / one: 2 workers, 200 k columns, 300 layers 47.3 / 39.0; 4 workers, 270 k,
-// 59 layers (37 k the longest) 48.5 / 43.5, 420 k, 60 layers 52.0 / 43.1; 8 workers, 200 k, 20 layers 52.5 / 43.8, 300 layers 55.2 / 40.4;
-// 16 workers, 200 k, 150 layers 61.5 / 53.0; 20 workers, 200 k, 120 layers 69.7 / 63.6.  Beyond the lines: longest layer 48 k 52.2 /
-// 54.2, 116 k 47.0 / 54.3; 2 workers, 1 M, 150 layers 49.1 / 50.7; 16 workers, 200 k, 60 layers of up to 17 k 57.9 / 67.6.
+// own.  One launch saves the other and its boundary; what it costs is that the longest layer takes one block, at the rate of one
+// CU.  max_tiles: the most 1024-column tiles of a layer.  (Of the most blocks that are accepted, 2560 of 256 threads or 640 of 1024,
+// a fifth starts in a second round.)
+// The lines lie where calls made one by one gain; there the host's launches bound a round of four steps and the communication.  fp32, us, two
+// launches a step / one: 2 workers, 200 k columns, 300 layers 47.3 / 39.0; 4 workers, 270 k, 59 layers (37 k the longest) 48.5 / 43.5, 420 k,
+// 60 layers 52.0 / 43.1; 8 workers, 200 k, 20 layers 52.5 / 43.8, 300 layers 55.2 / 40.4; 16 workers, 200 k, 150 layers 61.5 / 53.0; 20 workers,
+// 200 k, 120 layers 69.7 / 63.6.  Beyond the lines: longest layer 48 k 52.2 / 54.2, 116 k 47.0 / 54.3; 2 workers, 1 M, 150 layers 49.1 / 50.7;
+// 16 workers, 200 k, 60 layers of up to 17 k 57.9 / 67.6.
+// What they cost: in a captured graph, or behind work that keeps the device busy, the device's time counts, and a long layer among
+// few loses.  The same round replayed as a graph, with the center, 4 workers, one layer of so many thousand columns (in brackets: and 58 more of
+// 2000): 5 23 / 20 (32 / 23), 11 23 / 20 (32 / 23), 14 23 / 22 (32 / 25), 18 23 / 24 (32 / 27), 27 23 / 28 (33 / 32), 39 23 / 35 (33 / 38);
+// without it 18 23 / 22, 27 23 / 25, 39 23 / 30 (32 / 34); 32 workers, with it, 18 29 / 28, 39 33 / 41.
+// Threads: 256 up to 7 tiles (23 / 22), beyond it 1024 as long as the blocks and elements are few enough (9 tiles 22 / 24 with 256, 23 / 20 with
+// 1024, 10 tiles 22 / 26 and 23 / 20); where they are too many, 256 up to 10 tiles (16 workers, 59 layers 47 / 39).
 #define GRAWA_LAYER_MAX_TILES 40
 #define GRAWA_LAYER_MAX_ELEMS ((int64_t)7 << 18)
-#define GRAWA_LAYER_SHORT_TILES 10
+#define GRAWA_LAYER_MAX_BLOCKS 640
+#define GRAWA_LAYER_SHORT_TILES 7
+#define GRAWA_LAYER_SHORT_MAX_TILES 10
 #define GRAWA_LAYER_SHORT_MAX_ELEMS ((int64_t)1 << 22)
+#define GRAWA_LAYER_SHORT_MAX_BLOCKS 2560
 static inline int grawa_step_by_layers(int K, int L, int64_t P, int64_t max_tiles)
 {
     const int64_t blocks = (int64_t)K * L, elems = (int64_t)K * P;
-    if (max_tiles <= GRAWA_LAYER_SHORT_TILES) return elems <= GRAWA_LAYER_SHORT_MAX_ELEMS && blocks <= 2560 ? 256 : 0;
-    return max_tiles <= GRAWA_LAYER_MAX_TILES && elems <= GRAWA_LAYER_MAX_ELEMS && blocks <= 640 ? 1024 : 0;
+    if (max_tiles > GRAWA_LAYER_SHORT_TILES && elems <= GRAWA_LAYER_MAX_ELEMS && blocks <= GRAWA_LAYER_MAX_BLOCKS)
+        return max_tiles <= GRAWA_LAYER_MAX_TILES ? 1024 : 0;
+    return max_tiles <= GRAWA_LAYER_SHORT_MAX_TILES && elems <= GRAWA_LAYER_SHORT_MAX_ELEMS && blocks <= GRAWA_LAYER_SHORT_MAX_BLOCKS ? 256 : 0;
 }
 
 #endif

@@ -5,6 +5,7 @@
 //   offgrid <K>...       -> per line, without and with the fp32 SGD step: K, 0 or 1, form, groups, merge, 1 if that has a kernel
 //   offgrid_large <K> <sgd> <MB>... -> per triple: the triple, 1 if a pull of so many bytes takes that form (others from 128 MB on)
 //   rowstep              -> bf16, center, scored, MB beyond which loads stream and the L2 merges (-1: at no size)
+//   layers <K> <L> <P> <max_tiles>... -> per case: the case, threads of a block that owns a layer in the scored step, or 0
 //   plain <K> <n_cells>... -> per pair: the pair, 1 if the one-column-per-lane form serves it
 //   tiles <K> <n_cells>... -> per pair: the pair, 1 if the pull forms the per-layer weights
 //   estimate <K> <L> <max_tiles> ... -> per triple: the triple, rows, threads
@@ -53,6 +54,12 @@ int main(int argc, char **argv)
             const int64_t from = grawa_row_step_merges_from(i & 4, i & 2, i & 1);
             std::printf("%d %d %d %lld\n", i >> 2, i >> 1 & 1, i & 1, from == GRAWA_ROW_STEP_NEVER ? -1LL : (long long)(from >> 20));
         }
+        return 0;
+    }
+    if (!std::strcmp(argv[1], "layers")) {
+        for (int i = 2; i + 3 < argc; i += 4)
+            std::printf("%s %s %s %s %d\n", argv[i], argv[i + 1], argv[i + 2], argv[i + 3],
+                        grawa_step_by_layers(std::atoi(argv[i]), std::atoi(argv[i + 1]), std::atoll(argv[i + 2]), std::atoll(argv[i + 3])));
         return 0;
     }
     if (!std::strcmp(argv[1], "plain")) {

@@ -92,6 +92,19 @@ def test_local_steps_off_the_grid(driver):
                        (1, 0, 0): 0, (1, 0, 1): -1, (1, 1, 0): 128, (1, 1, 1): 0}
 
 
+def test_scored_step_by_layers(driver):
+    M = 1 << 20
+    ask = lambda *case: driver("layers", *case)[0][4]
+    for tiles, threads in ((1, 256), (7, 256), (8, 1024), (40, 1024), (41, 0)):      # longest layer
+        assert ask(1, 1, 1024 * tiles, tiles) == threads
+    assert [ask(1, 100, p, 9) for p in (7 * M // 4, 7 * M // 4 + 1, 4 * M, 4 * M + 1)] == [1024, 256, 256, 0]        # elements
+    assert [ask(1, 100, p, 11) for p in (7 * M // 4, 7 * M // 4 + 1)] == [1024, 0]
+    assert [ask(k, L, 1000, 9) for k, L in ((1, 640), (64, 10), (1, 641), (1, 2560), (1024, 2), (1, 2561))] == [1024, 1024, 256, 256, 256, 0]
+    assert [ask(k, L, 1000, 11) for k, L in ((1, 640), (1, 641))] == [1024, 0]                                         # blocks
+    # products beyond 32 bits
+    assert ask(1024, 1 << 30, 1 << 31, 1) == 0 and ask(1024, 1, 1 << 31, 1 << 21) == 0
+
+
 def test_plain_form_counts(driver):
     # each count the rule names has a kernel: 1..15 and 17..32 (16 has its own form), and 32 only on few cells
     rows = driver("plain", *[v for k in (1, 23, 24, 32, 33, 64) for n in (1, 800, 801, 1 << 24) for v in (k, n)])
