@@ -6,6 +6,7 @@
 //   offgrid_large <K> <sgd> <MB>... -> per triple: the triple, 1 if a pull of so many bytes takes that form (others from 128 MB on)
 //   rowstep              -> bf16, center, scored, MB beyond which loads stream and the L2 merges (-1: at no size)
 //   layers <K> <L> <P> <max_tiles>... -> per case: the case, threads of a block that owns a layer in the scored step, or 0
+//   cachedg <K> <P> <elem_bytes>... -> per triple: the triple, columns of g that the norm pass of a fused update reads through the caches
 //   plain <K> <n_cells>... -> per pair: the pair, 1 if the one-column-per-lane form serves it
 //   tiles <K> <n_cells>... -> per pair: the pair, 1 if the pull forms the per-layer weights
 //   estimate <K> <L> <max_tiles> ... -> per triple: the triple, rows, threads
@@ -60,6 +61,12 @@ int main(int argc, char **argv)
         for (int i = 2; i + 3 < argc; i += 4)
             std::printf("%s %s %s %s %d\n", argv[i], argv[i + 1], argv[i + 2], argv[i + 3],
                         grawa_step_by_layers(std::atoi(argv[i]), std::atoi(argv[i + 1]), std::atoll(argv[i + 2]), std::atoll(argv[i + 3])));
+        return 0;
+    }
+    if (!std::strcmp(argv[1], "cachedg")) {
+        for (int i = 2; i + 2 < argc; i += 3)
+            std::printf("%s %s %s %lld\n", argv[i], argv[i + 1], argv[i + 2],
+                        (long long)grawa_cached_grad_cols(std::atoi(argv[i]), std::atoll(argv[i + 1]), std::atoi(argv[i + 2])));
         return 0;
     }
     if (!std::strcmp(argv[1], "plain")) {

@@ -105,6 +105,13 @@ def test_scored_step_by_layers(driver):
     assert ask(1024, 1 << 30, 1 << 31, 1) == 0 and ask(1024, 1, 1 << 31, 1 << 21) == 0
 
 
+def test_columns_of_g_read_through_the_caches(driver):
+    cases = [(k, p, e) for k in (1, 2, 3, 7, 64, 1000, 1024) for p in (1, 255, 60000, 1 << 20, (1 << 32) - 1) for e in (2, 4)]
+    for k, p, e, cols in driver("cachedg", *[v for c in cases for v in c]):
+        assert 1 <= cols <= p and cols * k * e <= 224 << 20
+        assert cols == p or (cols + 1) * k * e > 224 << 20
+
+
 def test_plain_form_counts(driver):
     # each count the rule names has a kernel: 1..15 and 17..32 (16 has its own form), and 32 only on few cells
     rows = driver("plain", *[v for k in (1, 23, 24, 32, 33, 64) for n in (1, 800, 801, 1 << 24) for v in (k, n)])
