@@ -79,9 +79,9 @@ grawa_status_t run_update(grawa_plan *p, float *x, int64_t ldx, const void *g, i
     const bool prof = prof_active(p);
     hipEvent_t *ev = prof ? p->ev + 4 * (size_t)p->profile_n : nullptr;
 
-    grawa_plan for_norms = *p;
-    if (fuse_sgd && g_sgd == g && ldg_sgd == ldg) for_norms.cached_cols = grawa_cached_grad_cols(p->K, p->P, dt == GRAWA_BF16 ? 2 : 4);
-    GRAWA_TRY_HIP(grawa_launch_sumsq(&for_norms, g, ldg, dt, s, prof ? ev[0] : nullptr, prof ? ev[1] : nullptr));
+    const bool read_twice = fuse_sgd && g_sgd == g && ldg_sgd == ldg; // the pull reads g again
+    const int64_t cached_cols = read_twice ? grawa_cached_grad_cols(p->K, p->P, dt == GRAWA_BF16 ? 2 : 4) : 0;
+    GRAWA_TRY_HIP(grawa_launch_sumsq(p, g, ldg, dt, cached_cols, s, prof ? ev[0] : nullptr, prof ? ev[1] : nullptr));
 
     const bool from_tiles = per_layer && grawa_pull_from_tiles(p);
     const int goal = per_layer ? GRAWA_GOAL_LAYER_WEIGHTS
@@ -268,7 +268,7 @@ grawa_status_t grawa_grad_norms(grawa_plan_t *p, const void *g, int64_t ldg, gra
     DeviceGuard guard(p->device);
     if (!guard.ok) return GRAWA_ERR_HIP;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    GRAWA_TRY_HIP(grawa_launch_sumsq(p, g, ldg, dt, s, nullptr, nullptr));
+    GRAWA_TRY_HIP(grawa_launch_sumsq(p, g, ldg, dt, 0, s, nullptr, nullptr));
     GRAWA_TRY_HIP(grawa_launch_finalize_layers(p, GRAWA_GOAL_SCORES, norms_out, nullptr, s));
     return GRAWA_OK;
 }

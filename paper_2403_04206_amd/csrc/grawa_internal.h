@@ -50,8 +50,6 @@ struct grawa_plan {
     int profile_n;
     hipEvent_t *ev;          // 4 per slot: norm begin/end, pull begin/end
     unsigned char *ev_norm;  // per slot: 1 if the call recorded norm-kernel events
-    int64_t cached_cols; // norm pass: tiles that start before this column are read with cached loads (0 in a plan; a call that
-                         // wants some passes a copy of the plan on)
     int tile_shift;      // 0: the maps below are filled; else tiles and cells are found in d_off, tiles of 2^tile_shift columns
 };
 
@@ -96,7 +94,8 @@ static inline grawa_status_t grawa_check_center(const float *c)
 
 // Launchers (defined next to their kernels).  All return the hipError_t of the launch.
 // e0/e1: optional start/stop events of the launch itself (null when not profiling).
-hipError_t grawa_launch_sumsq(const grawa_plan *p, const void *g, int64_t ldg, grawa_dtype_t dt,
+// cached_cols: tiles that start before this column are read with cached loads (0 where the tiles are found in the offsets).
+hipError_t grawa_launch_sumsq(const grawa_plan *p, const void *g, int64_t ldg, grawa_dtype_t dt, int64_t cached_cols,
                               hipStream_t s, hipEvent_t e0, hipEvent_t e1);
 hipError_t grawa_launch_finalize_layers(const grawa_plan *p, int goal, float *norms_user, float *beta_user,
                                         hipStream_t s);

@@ -459,7 +459,7 @@ __global__ __launch_bounds__(GRAWA_WAVE) void k_leader_weights(const float *__re
 
 // Kernels that are timed carry their own start/stop events (taken from the dispatch itself,
 // so nothing extra is queued on the stream); both may be null.
-hipError_t grawa_launch_sumsq(const grawa_plan *p, const void *g, int64_t ldg, grawa_dtype_t dt,
+hipError_t grawa_launch_sumsq(const grawa_plan *p, const void *g, int64_t ldg, grawa_dtype_t dt, int64_t cached_cols,
                               hipStream_t s, hipEvent_t e0, hipEvent_t e1)
 {
     const dim3 grid((unsigned)p->n_tiles, (unsigned)p->K), block(GRAWA_BLOCK);
@@ -474,12 +474,12 @@ hipError_t grawa_launch_sumsq(const grawa_plan *p, const void *g, int64_t ldg, g
     }
 #define GRAWA_SUMSQ_GO(GT, MIX)                                                                              \
     hipExtLaunchKernelGGL((k_sumsq<GT, MIX>), grid, block, 0, s, e0, e1, 0, (const GT *)g, ldg,              \
-                          (const GrawaTile *)p->d_tiles, p->n_tiles, p->d_partials, p->d_cnt_all, p->cached_cols)
+                          (const GrawaTile *)p->d_tiles, p->n_tiles, p->d_partials, p->d_cnt_all, cached_cols)
     if (dt == GRAWA_BF16) {
-        if (p->cached_cols) GRAWA_SUMSQ_GO(uint16_t, true);
+        if (cached_cols) GRAWA_SUMSQ_GO(uint16_t, true);
         else GRAWA_SUMSQ_GO(uint16_t, false);
     } else {
-        if (p->cached_cols) GRAWA_SUMSQ_GO(float, true);
+        if (cached_cols) GRAWA_SUMSQ_GO(float, true);
         else GRAWA_SUMSQ_GO(float, false);
     }
 #undef GRAWA_SUMSQ_GO

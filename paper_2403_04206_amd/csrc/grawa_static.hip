@@ -166,7 +166,7 @@ extern "C" grawa_status_t grawa_lgrawa_update_static(int K, int64_t P, int L, co
             p.d_layer_tile1);
         if (hipGetLastError() != hipSuccess) return GRAWA_ERR_HIP;
     }
-    if (grawa_launch_sumsq(&p, g, ldg, dt, s, nullptr, nullptr) != hipSuccess) return GRAWA_ERR_HIP;
+    if (grawa_launch_sumsq(&p, g, ldg, dt, 0, s, nullptr, nullptr) != hipSuccess) return GRAWA_ERR_HIP;
     if (!from_tiles && grawa_launch_finalize_layers(&p, GRAWA_GOAL_LAYER_WEIGHTS, nullptr, weights_out, s) != hipSuccess)
         return GRAWA_ERR_HIP;
     if (grawa_launch_center_pull(&p, x, ldx, from_tiles ? nullptr : p.d_beta_layer, 1, lambda, nullptr, 0, GRAWA_F32,

@@ -23,7 +23,7 @@ hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { *ms = 0.f; r
 }
 
 bool grawa_pull_from_tiles(const grawa_plan *) { return false; }
-hipError_t grawa_launch_sumsq(const grawa_plan *, const void *, int64_t, grawa_dtype_t, hipStream_t, hipEvent_t, hipEvent_t) { return hipSuccess; }
+hipError_t grawa_launch_sumsq(const grawa_plan *, const void *, int64_t, grawa_dtype_t, int64_t, hipStream_t, hipEvent_t, hipEvent_t) { return hipSuccess; }
 hipError_t grawa_launch_finalize_layers(const grawa_plan *, int, float *, float *, hipStream_t) { return hipSuccess; }
 hipError_t grawa_launch_local_weights(const grawa_plan *, double, int, float *, float *, hipStream_t)
 {
