@@ -543,7 +543,8 @@ constexpr int grawa_waves_for(int k, bool sgd, bool bf16)
 
 #define GRAWA_CP_ARGS                                                                                                 \
     const grawa_plan *p, float *x, int64_t ldx, const void *g, int64_t ldg, float lr, const float *beta, int per_layer, \
-        float lambda, float *center_out, float rho, int moving, const TileWeights &tw, bool capped, hipStream_t s,       \
+        float lambda, float *center_out, float rho, int moving, [[maybe_unused]] const TileWeights &tw,                 \
+        [[maybe_unused]] bool capped, hipStream_t s,                                                                   \
         hipEvent_t e0, hipEvent_t e1
 #define GRAWA_CP_PASS p, x, ldx, g, ldg, lr, beta, per_layer, lambda, center_out, rho, moving, tw, capped, s, e0, e1
 #define GRAWA_CP_STRIDE per_layer ? (int64_t)p->L : (int64_t)1
@@ -576,8 +577,6 @@ constexpr int grawa_waves_wide(int k, bool sgd /* fp32 gradients */)
 
 template <int K, bool SGD, typename GT, bool LNT, int ST> static void launch_wide(GRAWA_CP_ARGS)
 {
-    (void)tw;
-    (void)capped;
     hipExtLaunchKernelGGL((k_center_pull_wide<K, SGD, GT, LNT, ST, grawa_waves_wide(K, SGD && sizeof(GT) == 4)>), dim3((unsigned)((p->n_cells + 3) / 4)),
                           dim3(GRAWA_BLOCK), 0, s, e0, e1, 0, x, ldx, (const GT *)g, ldg, lr, beta, GRAWA_CP_STRIDE,
                           GRAWA_CP_CELLS, (const int64_t *)p->d_off, p->L, p->P, lambda, center_out, rho, moving);
