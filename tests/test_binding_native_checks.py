@@ -115,4 +115,4 @@ def test_tensors_of_transforms_are_left_alone():
     t = torch.zeros((3, 6, 40), device="cuda:0")
     torch.func.vmap(lambda v: (seen.append(rows(v, 6, 40, False)), v)[1])(t)
     torch.func.grad(lambda v: (seen.append(rows(v, 6, 40, False)), v.sum())[1])(t[0])
-    assert all(s is None or len(s) == 3 for s in seen) and seen[0] is None
+    assert seen == [None, None]                          # no storage of their own: the Python checks refuse them too
