@@ -341,12 +341,7 @@ __global__ __launch_bounds__(GRAWA_LW_BLOCK_MODEL) void k_local_weights(double *
     const int wave = threadIdx.x / GRAWA_WAVE, waves = (int)blockDim.x / GRAWA_WAVE;
     const int l0 = per_layer ? (int)blockIdx.x : 0;
     const int64_t t = local_t[l0];
-    double power = 1.0, factor = gamma; // gamma^t by squaring: a round or two where pow() is a chain of a microsecond
-    for (int64_t e = t; e > 0; e >>= 1) {
-        if (e & 1) power *= factor;
-        factor *= factor;
-    }
-    const double scale = t > 0 ? gamma / (1.0 - power) : 0.0;
+    const double scale = t > 0 ? gamma / grawa_one_minus_power(gamma, t) : 0.0;
     if (per_layer) {
         for (int k = threadIdx.x; k < K; k += blockDim.x) {
             const int64_t at = (int64_t)k * L + l0;

@@ -207,4 +207,23 @@ static inline int grawa_step_by_layers(int K, int L, int64_t P, int64_t max_tile
     return max_tiles <= GRAWA_LAYER_SHORT_MAX_TILES && elems <= GRAWA_LAYER_SHORT_MAX_ELEMS && blocks <= GRAWA_LAYER_SHORT_MAX_BLOCKS ? 256 : 0;
 }
 
+// 1 - gamma^t for 0 < gamma < 1, by squaring, since pow() is a chain of a microsecond in k_local_weights.  Every product keeps what its
+// rounding drops, so that the error stays at the last place however near to 1 gamma is (plain squaring loses t units of it, pow() one, and the
+// difference divides both by 1 - gamma^t).  Used on the device too (constexpr).
+static constexpr double grawa_one_minus_power(double gamma, int64_t t)
+{
+    double power = 1.0, power_rest = 0.0, factor = gamma, factor_rest = 0.0; // value and what its rounding dropped
+    for (int64_t e = t; e > 0; e >>= 1) {
+        if (e & 1) {
+            const double p = power * factor;
+            power_rest = __builtin_fma(power, factor, -p) + (power * factor_rest + power_rest * factor);
+            power = p;
+        }
+        const double f = factor * factor;
+        factor_rest = __builtin_fma(factor, factor, -f) + 2.0 * factor * factor_rest;
+        factor = f;
+    }
+    return (1.0 - power) - power_rest;
+}
+
 #endif

@@ -7,6 +7,7 @@
 //   rowstep              -> bf16, center, scored, MB beyond which loads stream and the L2 merges (-1: at no size)
 //   layers <K> <L> <P> <max_tiles>... -> per case: the case, threads of a block that owns a layer in the scored step, or 0
 //   cachedg <K> <P> <elem_bytes>... -> per triple: the triple, columns of g that the norm pass of a fused update reads through the caches
+//   power <gamma> <t>... -> per pair, exactly (%a): gamma, 1 - gamma^t
 //   plain <K> <n_cells>... -> per pair: the pair, 1 if the one-column-per-lane form serves it
 //   tiles <K> <n_cells>... -> per pair: the pair, 1 if the pull forms the per-layer weights
 //   estimate <K> <L> <max_tiles> ... -> per triple: the triple, rows, threads
@@ -67,6 +68,11 @@ int main(int argc, char **argv)
         for (int i = 2; i + 2 < argc; i += 3)
             std::printf("%s %s %s %lld\n", argv[i], argv[i + 1], argv[i + 2],
                         (long long)grawa_cached_grad_cols(std::atoi(argv[i]), std::atoll(argv[i + 1]), std::atoi(argv[i + 2])));
+        return 0;
+    }
+    if (!std::strcmp(argv[1], "power")) {
+        for (int i = 2; i + 1 < argc; i += 2)
+            std::printf("%a %a\n", std::atof(argv[i]), grawa_one_minus_power(std::atof(argv[i]), std::atoll(argv[i + 1])));
         return 0;
     }
     if (!std::strcmp(argv[1], "plain")) {

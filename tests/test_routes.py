@@ -3,7 +3,9 @@ allocate: a small program prints what the rules give."""
 import os
 import shutil
 import subprocess
+from decimal import Decimal, getcontext
 
+import numpy as np
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -17,7 +19,7 @@ def driver(tmp_path_factory):
                           os.path.join(ROOT, "paper_2403_04206_amd", "csrc"), os.path.join(ROOT, "tests", "route_driver.cpp"),
                           "-o", out], capture_output=True, text=True)
     assert res.returncode == 0, res.stderr
-    return lambda *args: [[int(v) for v in line.split()] for line in
+    return lambda *args, read=int: [[read(v) for v in line.split()] for line in
                           subprocess.run([out] + [str(a) for a in args], capture_output=True, text=True,
                                          check=True).stdout.splitlines()]
 
@@ -110,6 +112,18 @@ def test_columns_of_g_read_through_the_caches(driver):
     for k, p, e, cols in driver("cachedg", *[v for c in cases for v in c]):
         assert 1 <= cols <= p and cols * k * e <= 224 << 20
         assert cols == p or (cols + 1) * k * e > 224 << 20
+
+
+def test_power_of_gamma(driver):
+    # 1 - gamma^t of the running estimate, gamma a float32 up to the last one below 1: at most four units of the last place
+    getcontext().prec = 60
+    cases = [(float(np.float32(g)), t) for g in (1e-30, 0.1, 0.5, 0.9, 0.99, 0.999, 1 - 2.0 ** -20, 1 - 2.0 ** -24)
+             for t in (1, 2, 3, 4, 5, 7, 10, 16, 31, 100, 1000, 4097)]
+    got = driver("power", *[v for g, t in cases for v in (repr(g), t)], read=float.fromhex)
+    for (g, t), (read, value) in zip(cases, got):
+        assert read == g
+        exact = 1 - Decimal(g) ** t
+        assert abs(Decimal(value) / exact - 1) <= Decimal(4 * 2.0 ** -53), (g, t)
 
 
 def test_plain_form_counts(driver):
