@@ -552,13 +552,13 @@ constexpr int grawa_waves_for(int k, bool sgd, bool bf16)
 
 template <int K, bool SGD, typename GT, bool NT, int TILES> static void launch_plain(GRAWA_CP_ARGS)
 {
-    // (The weights in the pull, 12 and more workers, without the step: the capped kernel, 15 workers, 200 layers 15.8 / 16.0 us.)
-    constexpr int CAP = grawa_waves_for(K, SGD, sizeof(GT) == 2), WPE = NT || (TILES && K >= 12 && !SGD) ? CAP : 8;
+    constexpr int CAP = grawa_waves_for(K, SGD, sizeof(GT) == 2), WPE = NT ? CAP : 8;
     // Cached accesses: the cap, where it is wanted, is set by the LDS a block asks for, of the CU's 160 KB.  Up to 128 MB the
     // caches answer, and what counts is that all blocks of a small array run at once (1054 blocks of 8 workers are one more
     // round than 4 per CU hold).  LGRAWA with the fp32 SGD step, us, capped / not: 8 workers, 270 k columns 13.9 / 12.0,
     // 317 k 14.9 / 13.1, 10 workers 256 k 15.6 / 13.7, 15 workers 174 k 17.3 / 15.4; MGRAWA 8 workers, 1.6 M 35.0 / 31.4, 3.1 M
-    // 58.8 / 54.7, 20 workers 312 k 23.3 / 21.9.  Rows off the grid from 64 MB on: 15 workers, 90 MB 55.5 / 57.4, 6 workers with
+    // 58.8 / 54.7, 20 workers 312 k 23.3 / 21.9; LGRAWA with the weights in the pull 12 workers, 218 k, 20 layers 10.8 / 9.4, 200 layers 14.4 /
+    // 13.2, 13 workers, 201 k 10.9 / 9.6 and 15.4 / 14.2 (fewer columns, and 14 and 15 workers, 0 to 0.2 us slower).  Rows off the grid from 64 MB on: 15 workers, 90 MB 55.5 / 57.4, 6 workers with
     // the fp32 step 72.6 / 74.6.
     const size_t lds = WPE > CAP && capped ? ((size_t)160 << 10) / (CAP + 1) + 1024 : 0;
     hipExtLaunchKernelGGL((k_center_pull<K, SGD, GT, NT, WPE, TILES>), dim3((unsigned)p->n_cells), dim3(GRAWA_CELL), lds, s, e0,
