@@ -280,8 +280,9 @@ grawa_status_t grawa_lsgd_update(grawa_plan_t *plan, float *x, int64_t ldx, cons
  * forbid allocation.  It needs no plan.  The workspace a plan would own (tile
  * map, cell map, per-tile partial sums, the K x L tables) lives in a fixed
  * 32 MiB array inside the library's device image, one copy per GPU, held until
- * the process ends; the maps are built by a small kernel from layer offsets
- * that are already in DEVICE memory.  The call enqueues kernels on `stream` and
+ * the process ends; what the maps hold is worked out from layer offsets that
+ * are already in DEVICE memory, by a small kernel or, for small problems, by the
+ * kernels that need it.  The call enqueues kernels on `stream` and
  * nothing else (no hipMalloc / hipFree / memset / copy, no synchronisation), and
  * gives bit for bit what grawa_lgrawa_update gives for the same inputs.
  *   layer_offsets_dev   device int64 [L+1], 8-byte aligned: [0] = 0, strictly
