@@ -1,6 +1,6 @@
-"""GPU parity of the wide center+pull form on arrays beyond the last-level cache: rows that do not start on cache-line
-boundaries (a plain [K, P] tensor) at the first and last worker counts of its range, beside the forms on either
-side of it, and line-aligned rows of one and two workers."""
+"""GPU parity of the center+pull forms with 16-byte lanes on arrays beyond the last-level cache: rows that do not start on cache-line
+boundaries (a plain [K, P] tensor) as the wide form (up to 5 workers, with the fp32 step also 12 and 23) and as row-split bursts
+(6, 16 and 24 workers, 23 without the step), and line-aligned rows of one and two workers (the wide form)."""
 import pytest
 import torch
 
@@ -13,8 +13,8 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-@pytest.mark.parametrize("K,pad", [(1, 0), (2, 8), (4, 8), (16, 8)])
-def test_wide_form_with_layers_in_every_cell(K, pad):
+@pytest.mark.parametrize("K,pad", [(1, 0), (2, 8), (4, 8), (5, 8), (16, 8)])
+def test_16_byte_lanes_with_layers_in_every_cell(K, pad):
     # cells of 2, 8, 9 and 256 layers and one that ends with the row: weights by scalar loads, and by column
     P = (140 << 20) // (4 * K) // 256 * 256 + 129
     sizes = [100, 412] + [32] * 8 + [29] * 8 + [24] + [1] * 256 + [7] * 500 + [300] * 2000
@@ -47,7 +47,7 @@ def test_wide_form_with_layers_in_every_cell(K, pad):
                                                     (6, "f32", False, 2, 8), (12, "f32", True, 0, 8), (23, "bf16", False, 2, 8),
                                                     (23, "f32", True, 1, 8), (24, "f32", False, 1, 8), (1, "bf16", True, 1, 0),
                                                     (1, "f32", True, 2, 0), (2, "f32", False, 3, 0), (2, "bf16", True, 1, 0)])
-def test_wide_form(K, dtype, fused, tail, pad):
+def test_16_byte_lanes(K, dtype, fused, tail, pad):
     P = (530 << 20) // (4 * K) // 1024 * 1024 + 1024 - 300 + tail       # the last block is partly empty, its last lane too
     w = W.Workload("tight_K%d" % K, K, [P // 3, 1, 5, P - P // 3 - 6], grad_dtype=dtype, lam=0.1, lr=0.1, seed=(5, K))
     x, g = W.make_inputs(w, device=DEV, ld_pad=pad)
