@@ -364,7 +364,7 @@ __global__ __launch_bounds__(GRAWA_BLOCK) __attribute__((amdgpu_waves_per_eu(1, 
 //   memory's handling of the parts of lines and of the many rows.  MGRAWA update, arrays of 1.2 GB, us, the forms before / this one:
 //   7 workers 513 / 499, 8 538 / 520, 10 535 / 522, 11 525 / 513, 12 533 / 512, 16 542 / 544, 23 534 / 520, 24 582 / 561, 27 630 / 564,
 //   32 607 / 554, 48 617 / 558, 64 644 / 550; with the fp32 SGD step 9 861 / 837, 10 887 / 833, 32 963 / 877, 48 1013 / 891, 64 1015 / 892;
-//   200 MB 8 to 11 workers 3 to 8 % faster, 30 to 64 2 to 10 %.  Two blocks per CU are slower than the forms before.  Up to 15
+//   fused, fp32, 200 MB 8 151 / 135, 9 152 / 133, 32 170 / 148 (without the step: GRAWA_BURST_MIN_BYTES).  Two blocks per CU are slower than the forms before.  Up to 15
 //   workers streaming loads and stores that the L2 merges; beyond, cached loads and stores written through (12 workers 5.81 / 5.99
 //   TB/s against these, 20 workers 5.85 / 5.33).  S: 2 up to 9 workers, 4 up to 23, 8 beyond (10 workers with 2: 540 us, 9 with
 //   4 and the SGD step: 918 for 894).  With the fp32 SGD step the wide form stays for 12 to 23 workers (12, 1.2 GB: 861 / 882, 855 /
