@@ -151,7 +151,9 @@ static inline void grawa_estimate_shape(int K, int L, int64_t max_tiles, int *ro
 // gradient type, none / 64 / 128 / 192 / 224 / 256 MB cached: 4 workers 20 MB fp32 21.5 / 20.5 / 20.5 / 20.6 / 20.3 / 20.6, 200 MB
 // bf16 100.3 / 97.1 / 95.9 / 95.9 / 95.8 / 95.9, 400 MB fp32 246 / 244 / 243 / 243 / 243 / 250; 12 workers 200 MB fp32 147 / 141 / 136
 // / 135 / 135 / 134, 400 MB bf16 206 / 197 / 189 / 185 / 185 / 183; 32 workers 150 MB fp32 126 / 118 / 106 / 104 / 104 / 105, 260 MB
-// 179 / 175 / 169 / 163 / 162 / 161, 800 MB 536 / 528 / 522 / 517 / 512 / 509, 3.2 GB 2166 / 2157 / 2155 / 2154 / 2143 / 2146.
+// 179 / 175 / 169 / 163 / 162 / 161, 800 MB 536 / 528 / 522 / 517 / 512 / 509, 3.2 GB 2166 / 2157 / 2155 / 2154 / 2143 / 2146, no more than runs
+// differ by.  Norm pass and pull apart, 32 workers, none / 224 MB: 150 MB 26.9 / 27.6 and 84.6 / 71.1, 260 MB 43.8 / 45.7 and 138.7 / 119.5, 3.1 GB
+// 464 / 471 and 1714 / 1715.  (The L2's traffic counters do not tell: they count what it asks for, whoever answers.)
 #define GRAWA_CACHED_GRAD_BYTES ((int64_t)224 << 20)
 static inline int64_t grawa_cached_grad_cols(int K, int64_t P, int elem_bytes)
 {
