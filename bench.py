@@ -328,8 +328,8 @@ def kernel_source_hash():
 
 
 def measured_traffic(workload, variant):
-    """(bytes, source): HBM bytes per launch of the center+pull kernel from the committed rocprofv3
-    counter runs (profiles/traffic.json: FETCH_SIZE and WRITE_SIZE, each scaled by what it reads for the
+    """(bytes, source): bytes per launch of the center+pull kernel between the L2 and the memory side (HBM, or the
+    last-level cache before it: the counters do not tell them apart) from the committed rocprofv3 counter runs (profiles/traffic.json: FETCH_SIZE and WRITE_SIZE, each scaled by what it reads for the
     plain copy kernel in the same run).  bytes is None when there is no entry for this workload or the
     library sources have changed since the counters were taken."""
     try:
