@@ -217,7 +217,8 @@ __global__ __launch_bounds__(T) void k_layer_step(
 // up to 192 MB cached loads and stores written through, which find part of the arrays in the cache.  Three sets in turn, us:
 // fp32 against cached accesses with V = 1, 140 MB 126 -> 119, 400 MB 361 -> 348, 1.5 GB 1367 -> 1335; bf16, the form up to 192 MB
 // against the one beyond, 3 and 16 workers: 140 MB 100 / 106 and 93 / 103, 180 MB 136 / 137 and 130 / 134, 260 MB 208 / 200 and
-// 201 / 194, 1.5 GB 1216 / 1163.
+// 201 / 194, 1.5 GB 1216 / 1163.  One set again and again, 3 and 16 workers: bf16 260 MB 191 / 200 and 189 / 197, fp32, against cached accesses,
+// 500 MB 462 / 468 and 462 / 482 (three sets 468 / 468 and 464 / 463).
 #define GRAWA_NAG_CACHED_LOADS_BYTES ((int64_t)192 << 20)
 #define GRAWA_SGD_V_F32 1
 #define GRAWA_SGD_U_F32 4

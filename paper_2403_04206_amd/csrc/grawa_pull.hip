@@ -718,8 +718,10 @@ hipError_t grawa_launch_center_pull(const grawa_plan *p, float *x, int64_t ldx, 
     // 53.8 / 58.4 -> 52.4, 6 55.2 -> 51.8 / 57.3 -> 56.7, 48 64.4 -> 60.9 / 67.1 -> 60.8; 95 MB bf16 2 68.4 -> 56.6 / 70.2 -> 57.4, 12
     // 64.7 -> 58.6 / 67.4 -> 64.6, 32 68.7 -> 62.6 / 71.4 -> 68.6; 125 MB fp32 6 91.8 -> 84.4 / 94.7 -> 92.0.  What it costs where nothing
     // else is touched between the calls and the last-level cache still holds part of x and g, one set again and again, line-aligned rows, fp32: 2
-    // and 4 workers 1 % at most, 8 84 MB 60.8 -> 62.0, 12 70 MB 53.6 -> 56.3, 32 84 MB 61.6 -> 64.6, 124 MB 85.0 -> 87.1, three sets in turn
-    // 69.8 -> 61.8, 61.1 -> 56.9, 76.1 -> 65.5 and 106.6 -> 88.8; rows off the grid, bf16, 32 workers 150 MB 89.7 -> 95.5 and 106.8 -> 96.5.)
+    // and 4 workers 1 % at most, 8 84 MB 60.8 -> 62.0, 12 70 MB 53.6 -> 56.3, 16 66 MB 51.5 -> 55.6, 32 84 MB 61.6 -> 64.6, 124 MB 85.0 -> 87.1,
+    // three sets in turn 69.8 -> 61.8, 61.1 -> 56.9, 58.2 -> 55.3, 76.1 -> 65.5 and 106.6 -> 88.8; rows off the grid 16 66 MB 55.2 -> 61.6 and
+    // 60.5 -> 60.4, and, as bursts, 24 130 MB 94.8 -> 102.9 and 112.5 -> 106.0, bf16 24 and 48 130 MB 79.6 -> 87.9 and 79.5 -> 94.8 against
+    // 94.8 -> 88.7 and 99.8 -> 93.3, 200 MB 113.1 -> 117.3 and 115.3 -> 118.9 against 132.5 -> 121.5 and 141.5 -> 124.7.)
     const int64_t bytes = (int64_t)p->K * p->P * (4 + (fuse_sgd ? (dt == GRAWA_BF16 ? 2 : 4) : 0));
     const bool large = beta && bytes > GRAWA_STREAMING_MIN_BYTES;
     bool nt = rows_line_aligned(x, ldx, 4) && (!center_out || rows_line_aligned(center_out, 0, 4));

@@ -170,7 +170,7 @@ static inline int64_t grawa_cached_grad_cols(int K, int64_t P, int elem_bytes)
 //   400 MB 789 / 819 (776 / 821), 700 MB 1425 / 1421, 1.5 GB 3097 / 3068, 2.5 GB 4945 / 4995; one step 100 MB 94 / 88 (84 / 87), 260 MB
 //   210 / 208 (202 / 208)
 //   scored with the center, four steps: fp32 260 MB 729 / 665 (718 / 658); bf16 260 MB 599 / 596 (581 / 596), 500 MB 1205 / 1137; one step
-//   231 / 222 (216 / 220) and 433 / 421
+//   231 / 222 (216 / 220) and 433 / 421; 40 workers, four steps, 220 MB 564 / 578, 400 MB 1001 / 1017
 //   with the center alone: fp32 100 MB 58.7 / 51.8, bf16 70 MB 32.2 / 33.8, 100 MB 44.0 / 45.8, 180 MB 91.7 / 84.9 (82.7 / 84.1)
 #define GRAWA_ROW_STEP_NEVER INT64_MAX
 static constexpr int64_t grawa_row_step_merges_from(bool bf16, bool center, bool scored)
