@@ -16,7 +16,7 @@ ROWS = os.path.join(PKG, "_rows.so")
 ROWS_SOURCE = os.path.join(CSRC, "grawa_rows.cpp")
 SOURCES = [os.path.join(CSRC, n) for n in ("grawa_api.cpp", "grawa_maps.cpp", "grawa_norms.hip", "grawa_pull.hip",
                                             "grawa_local.hip", "grawa_static.hip")]
-HEADERS = [os.path.join(CSRC, "grawa_internal.h"), os.path.join(CSRC, "grawa_device.h"), os.path.join(CSRC, "grawa_scores.h"),
+HEADERS = [os.path.join(CSRC, "grawa_internal.h"), os.path.join(CSRC, "grawa_device.h"), os.path.join(CSRC, "grawa_scores.h"), os.path.join(CSRC, "grawa_fold.h"),
            os.path.join(CSRC, "grawa_maps.h"), os.path.join(CSRC, "grawa_route.h"), os.path.join(CSRC, "grawa_offsets.h"),
            os.path.join(ROOT, "include", "grawa.h")]
 

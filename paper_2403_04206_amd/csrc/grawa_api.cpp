@@ -160,8 +160,17 @@ static grawa_status_t plan_create_impl(grawa_plan_t **out, int K, int64_t P, int
     const size_t b_bm = round256(sizeof(float) * (size_t)K);
     const size_t b_mvg = b_S;
     const size_t b_t = round256(sizeof(int64_t) * (size_t)L);
+    int64_t max_rtiles = 0;
+    for (int l = 0; l < L; ++l) {
+        const int64_t n = m.layer_rtile0[(size_t)l + 1] - m.layer_rtile0[(size_t)l];
+        if (n > max_rtiles) max_rtiles = n;
+    }
+    const bool later = grawa_fold_later(K, L, P, max_rtiles);
+    const size_t b_sums = later ? round256(sizeof(double) * GRAWA_SUM_BUFFERS * (size_t)K * (size_t)nrt) : 0;
+    const size_t b_est = later ? round256(sizeof(GrawaEstimate) * (size_t)K * (size_t)L) : 0;
+    const size_t b_used = later ? round256(sizeof(unsigned) * (size_t)L) : 0;
     const size_t b_words = 256; // flag word, arrival counter
-    const size_t b_zeroed = b_part + b_S + b_bl + b_bm + b_mvg + b_t + b_words;
+    const size_t b_zeroed = b_part + b_S + b_bl + b_bm + b_mvg + b_t + b_sums + b_est + b_used + b_words;
     const size_t b_host = b_off + b_cells + b_tiles + b_lt0 + b_rtiles + b_lt0 + b_brt0 + b_bm;
     // These may throw: before anything that would have to be freed.
     const std::vector<float> uniform((size_t)K, 1.f / (float)K);
@@ -177,10 +186,8 @@ static grawa_status_t plan_create_impl(grawa_plan_t **out, int K, int64_t P, int
     p->n_tiles = nt;
     p->n_rtiles = nrt;
     p->n_cells = nc;
-    for (int l = 0; l < L; ++l) {
-        const int64_t n = m.layer_rtile0[(size_t)l + 1] - m.layer_rtile0[(size_t)l];
-        if (n > p->max_rtiles) p->max_rtiles = n;
-    }
+    p->max_rtiles = max_rtiles;
+    p->fold_later = later ? 1 : 0;
     if (hipGetDevice(&p->device) != hipSuccess) {
         delete p;
         return GRAWA_ERR_HIP;
@@ -207,6 +214,9 @@ static grawa_status_t plan_create_impl(grawa_plan_t **out, int K, int64_t P, int
     p->d_beta_model = reinterpret_cast<float *>(w); w += b_bm;
     p->d_mvg = reinterpret_cast<double *>(w); w += b_mvg;
     p->d_local_t = reinterpret_cast<int64_t *>(w); w += b_t;
+    p->d_sums = reinterpret_cast<double *>(w); w += b_sums;
+    p->d_est = reinterpret_cast<GrawaEstimate *>(w); w += b_est;
+    p->d_consumed = reinterpret_cast<unsigned *>(w); w += b_used;
     p->d_flags = reinterpret_cast<unsigned *>(w);
     p->d_cnt_all = reinterpret_cast<unsigned *>(w + 128);
 

@@ -10,8 +10,19 @@
 
 #include "grawa.h"
 #include "grawa_maps.h"
+#include "grawa_route.h"
 
 #define GRAWA_PROFILE_SLOTS 4096
+
+// Running estimate of one worker and layer where the sums of a scored step are folded in by the launch that needs them next
+// (grawa_fold.h).  Counts of steps; they wrap.
+struct GrawaEstimate {
+    double mvg;      // moving average up to step `folded`
+    double gamma;    // of step n
+    unsigned n;      // scored steps so far
+    unsigned folded; // n or n - 1
+    unsigned buffer; // of d_sums that holds the sums of step n
+};
 
 struct grawa_plan {
     int K;
@@ -42,6 +53,11 @@ struct grawa_plan {
     unsigned *d_cnt_all;    // [1] arrivals of the layers, cleared by the norm pass of the call
     double *d_mvg;          // [K][L] moving average of the layer norms (running estimate, Appendix G)
     int64_t *d_local_t;     // [L], all equal: local steps since the last communication (what the kernels use)
+    int fold_later;         // the scored step leaves its sums to the next launch (grawa_fold_later); then, instead of d_mvg and d_local_t:
+    double *d_sums;         // [GRAWA_SUM_BUFFERS][K][n_rtiles] tile sums of scored steps
+    mutable GrawaSteps steps;
+    GrawaEstimate *d_est;   // [K][L]
+    unsigned *d_consumed;   // [L], all equal: the step that the last communication took into account
     unsigned *d_flags;      // device: GRAWA_NONFINITE_* bits, sticky until read-and-cleared (may be null)
     int64_t local_t;        // host mirror of the counter as of the last enqueued call (argument checks only)
     double local_gamma;     // momentum of the running estimate used so far (0 = none yet)
@@ -100,6 +116,9 @@ hipError_t grawa_launch_sumsq(const grawa_plan *p, const void *g, int64_t ldg, g
 hipError_t grawa_launch_finalize_layers(const grawa_plan *p, int goal, float *norms_user, float *beta_user,
                                         hipStream_t s);
 hipError_t grawa_launch_estimate(const grawa_plan *p, double gamma, hipStream_t s);
+struct GrawaFold;
+hipError_t grawa_launch_fold(const grawa_plan *p, const GrawaFold *step, hipStream_t s);
+bool grawa_is_recorded(hipStream_t s, unsigned long long *id);
 hipError_t grawa_launch_local_weights(const grawa_plan *p, double gamma, int per_layer, float *beta_user,
                                       float *est_user, hipStream_t s);
 hipError_t grawa_launch_zero_estimate(const grawa_plan *p, hipStream_t s);

@@ -8,7 +8,7 @@
 //   k_stream_copy  plain copy (measurement aid)
 // All are read-modify-write streams with no reuse: global loads and stores kept in flight, one
 // row (worker) per block, which is the access shape that streams fastest on this part.
-#include "grawa_device.h"
+#include "grawa_fold.h"
 #include "grawa_route.h"
 
 // ---------------------------------------------------------------------------------
@@ -32,26 +32,37 @@
 // blocks in flight spread over all K rows (5.8-6.0).
 // SCORE: only after its loads are issued does a block consult the 1024-column tile map (tiles
 // block_tile0[m] .. block_tile0[m+1]-1 lie in aligned block m, each inside one layer).  Nearly
-// every block holds one tile; a block that contains layer boundaries reduces once per tile.  The tile sums go to
-// k_estimate.  (Updating the estimate inside this launch, by the block that brings the last tile of a (worker, layer), was
+// every block holds one tile; in a block that contains layer boundaries every wave adds the tiles of its own columns (the block
+// reducing once per tile, with two barriers each: 4 workers, ResNet-20's 59 tensors 6.1 us, now 5.7).
+// The tile sums go to k_estimate, to k_fold or, GRAWA_SCORE_LATER, to the launch that needs them next (grawa_fold.h): a few blocks at
+// the head of the rows fold in those of the step before, 5 us of a launch that they hide (5.7 us in all on that model; a row
+// of blocks of their own, most of them empty, took large steps 3 us).  (Updating the estimate inside this launch, by the block that brings the last tile of a (worker, layer), was
 // tried: its device-scope traffic costs more than the launch from about 1000 blocks or 30 tiles per layer on, 4 steps and
 // the communication on 8 workers 117 us instead of 45.)  The maps are parameters of their own, each __restrict__: as
 // members of a struct they may alias the stores, and a block with many tiles then reads them by vector loads that wait for
 // its stores (64 workers, 300 k columns, 5000 layers: this kernel 141 us for 114).
 // The last P % V columns of a row are handled element by element.
-template <typename GT, int V, int U, bool LNT, int ST, bool PROX, bool SCORE>
+template <typename GT, int V, int U, bool LNT, int ST, bool PROX, int SCORE>
 __global__ __launch_bounds__(GRAWA_CELL) __attribute__((amdgpu_waves_per_eu(1, PROX && !SCORE ? 7 : 8))) void k_row_step(float *__restrict__ x, int64_t ldx,
                                                          const GT *__restrict__ g, int64_t ldg, float lr,
                                                          const float *__restrict__ center, float w, int64_t P,
                                                          unsigned n_blocks,
                                                          const GrawaTile *__restrict__ tiles,
                                                          const int32_t *__restrict__ block_tile0, int64_t n_tiles,
-                                                         double *__restrict__ partials)
+                                                         double *__restrict__ partials, const GrawaFold fold)
 {
     static_assert(V * U * GRAWA_CELL == GRAWA_ROW_BLOCK, "one trip covers one aligned block of columns");
     typedef typename FloatVec<V>::T XV;
     const unsigned k = blockIdx.y;
-    const unsigned m = blockIdx.z * gridDim.x + blockIdx.x;
+    unsigned m = blockIdx.z * gridDim.x + blockIdx.x;
+    if constexpr (SCORE == GRAWA_SCORE_LATER) {
+        if (blockIdx.x < fold.blocks) { // the first blocks of a row fold in the sums of the step before
+            fold_all<GRAWA_CELL, GRAWA_FOLD_STEP>(fold, partials, n_tiles, (blockIdx.z * gridDim.y + k) * fold.blocks + blockIdx.x,
+                                                  gridDim.z * gridDim.y * fold.blocks);
+            return;
+        }
+        m = blockIdx.z * (gridDim.x - fold.blocks) + blockIdx.x - fold.blocks;
+    }
     if (m >= n_blocks) return; // the last group may be short (whole block leaves, before any barrier)
     const int64_t c0 = (int64_t)m * GRAWA_ROW_BLOCK + (int64_t)threadIdx.x * V;
     float *xr = x + (int64_t)k * ldx;
@@ -104,48 +115,96 @@ __global__ __launch_bounds__(GRAWA_CELL) __attribute__((amdgpu_waves_per_eu(1, P
         }
     }
     if constexpr (SCORE) {
+        static_assert(V == 4 && U == 1, "a wave holds 256 adjacent columns");
         __shared__ double sm[GRAWA_BLOCK / GRAWA_WAVE];
         double *out = partials + (int64_t)k * n_tiles;
+        out += fold.buffer * fold.pitch;
+        const auto put = [&](int t, double tot) {
+            out[t] = tot;
+            if (fold.flags && !isfinite(tot)) atomicOr(fold.flags, GRAWA_NONFINITE_LAYER_SCORE); // null: k_estimate looks
+        };
         if (r1 - r0 == 1) { // the usual case: the whole block lies in one tile
             double acc = 0.0; // squares and sums in fp64: exact squares at any gradient magnitude
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-#pragma unroll
-                for (int e = 0; e < V; ++e) acc = sq_add(gf[u][e], acc);
+            for (int e = 0; e < V; ++e) acc = sq_add(gf[0][e], acc);
             const double tot = block_sum<GRAWA_BLOCK>(acc, sm);
-            if (threadIdx.x == 0) out[r0] = tot;
+            if (threadIdx.x == 0) put(r0, tot);
         } else {
-            for (int t = r0; t < r1; ++t) {
-                const int64_t lo = tiles[t].start, hi = lo + tiles[t].len;
-                double acc = 0.0;
+            // Every wave adds the tiles of its own 256 columns; the sums of a tile that goes on in other waves are added
+            // in wave order.
+            __shared__ double tail[GRAWA_BLOCK / GRAWA_WAVE];
+            __shared__ int head_tile[GRAWA_BLOCK / GRAWA_WAVE], tail_tile[GRAWA_BLOCK / GRAWA_WAVE];
+            const int lane = threadIdx.x & (GRAWA_WAVE - 1);
+            const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / GRAWA_WAVE));
+            const int begin = wave * (GRAWA_WAVE * V), end = begin + GRAWA_WAVE * V, at = threadIdx.x * V; // in the block
+            int head_at = -1, tail_at = -1;
+            for (int t = r0; t < r1; t += GRAWA_WAVE) {
+                int lo = GRAWA_ROW_BLOCK, hi = lo;
+                if (t + lane < r1) {
+                    const GrawaTile tile = tiles[t + lane];
+                    lo = (int)(tile.start - (int64_t)m * GRAWA_ROW_BLOCK);
+                    hi = lo + tile.len;
+                }
+                for (unsigned long long in = __ballot(lo < end && hi > begin); in; in &= in - 1) {
+                    const int i = __builtin_ctzll(in);
+                    const int a = __builtin_amdgcn_readlane(lo, i), b = __builtin_amdgcn_readlane(hi, i);
+                    double acc = 0.0;
 #pragma unroll
-                for (int u = 0; u < U; ++u)
-#pragma unroll
-                    for (int e = 0; e < V; ++e) {
-                        const int64_t c = c0 + (int64_t)u * (GRAWA_CELL * V) + e;
-                        acc = (c >= lo && c < hi) ? sq_add(gf[u][e], acc) : acc;
+                    for (int e = 0; e < V; ++e) acc = (at + e >= a && at + e < b) ? sq_add(gf[0][e], acc) : acc;
+                    const double tot = wave_sum(acc);
+                    if (a < begin) {
+                        head_at = t + i;
+                        if (lane == 0) sm[wave] = tot;
+                    } else if (b > end) {
+                        tail_at = t + i;
+                        if (lane == 0) tail[wave] = tot;
+                    } else if (lane == 0) {
+                        put(t + i, tot);
                     }
-                const double tot = block_sum<GRAWA_BLOCK>(acc, sm);
-                if (threadIdx.x == 0) out[t] = tot;
+                }
+            }
+            if (lane == 0) {
+                head_tile[wave] = head_at;
+                tail_tile[wave] = tail_at;
+            }
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                int t = -1; // the tile that goes on
+                double tot = 0.0;
+#pragma unroll
+                for (int w = 0; w < GRAWA_BLOCK / GRAWA_WAVE; ++w) {
+                    if (t >= 0 && head_tile[w] != t) {
+                        put(t, tot);
+                        t = -1;
+                    }
+                    if (head_tile[w] >= 0) tot += sm[w];
+                    if (tail_tile[w] >= 0) {
+                        if (t >= 0) put(t, tot);
+                        t = tail_tile[w];
+                        tot = tail[w];
+                    }
+                }
+                if (t >= 0) put(t, tot);
             }
         }
     }
 }
 
 // Scored step of a small model in one launch: a block owns a whole layer of one worker, so that the norm of its gradient, and
-// with it the running estimate, need no second launch and no exchange between blocks.  grid (L, K), block T; a lane handles
+// with it the running estimate, need no second launch and no exchange between blocks.  grid (L, K), block 256; a lane handles
 // vectors of 4 adjacent columns (rows are aligned to 16 bytes), U of them in flight at a time; a vector that the layer shares
-// with a neighbour is handled element by element.  What bounds it is the longest layer, at the rate of one CU
-// (grawa_step_by_layers): 37 k columns 8.8 us.  More vectors in flight cost registers and gain nothing: round of four steps and the
+// with a neighbour is handled element by element.  What bounds it is the longest layer, at the rate of one CU: so it serves where all
+// layers are short (grawa_fold_later).  More vectors in flight cost registers and gain nothing: round of four steps and the
 // communication, 4 workers, 270 k columns, U = 2 42.9 us, 3 43.5, 5 43.7, 10 56.
 #define GRAWA_LAYER_U 2
-template <typename GT, bool PROX, int T>
-__global__ __launch_bounds__(T) void k_layer_step(
+#define GRAWA_LAYER_THREADS 256
+template <typename GT, bool PROX>
+__global__ __launch_bounds__(GRAWA_LAYER_THREADS) void k_layer_step(
     float *__restrict__ x, int64_t ldx, const GT *__restrict__ g, int64_t ldg, float lr, const float *__restrict__ center, float w,
     const int64_t *__restrict__ off, int L, double *__restrict__ mvg, double gamma, int64_t *__restrict__ local_t,
     unsigned *__restrict__ flags)
 {
-    constexpr int V = 4, U = GRAWA_LAYER_U;
+    constexpr int V = 4, U = GRAWA_LAYER_U, T = GRAWA_LAYER_THREADS;
     typedef typename FloatVec<V>::T XV;
     const int l = blockIdx.x, k = blockIdx.y;
     const int64_t a = off[l], b = off[l + 1];
@@ -326,18 +385,11 @@ static hipError_t launch_row_step(const grawa_plan *p, float *x, int64_t ldx, co
 {
     const int64_t nb = (P + GRAWA_ROW_BLOCK - 1) / GRAWA_ROW_BLOCK;
     const bool prox = center != nullptr;
-    const int layer_threads = p ? grawa_step_by_layers(K, p->L, P, p->max_rtiles) : 0;
-    if (layer_threads) {
+    const bool later = p && p->fold_later;
+    if (p && !later && grawa_step_by_layers(K, p->L, P, p->max_rtiles) == GRAWA_LAYER_THREADS) {
 #define GRAWA_LS_GO(GT, PROX)                                                                                              \
-    do {                                                                                                                   \
-        const dim3 layers((unsigned)p->L, (unsigned)K);                                                                    \
-        if (layer_threads == 256)                                                                                          \
-            k_layer_step<GT, PROX, 256><<<layers, dim3(256), 0, s>>>(x, ldx, (const GT *)g, ldg, lr, center, w, p->d_off,  \
-                                                                     p->L, p->d_mvg, gamma, p->d_local_t, p->d_flags);     \
-        else                                                                                                               \
-            k_layer_step<GT, PROX, 1024><<<layers, dim3(1024), 0, s>>>(x, ldx, (const GT *)g, ldg, lr, center, w, p->d_off, \
-                                                                       p->L, p->d_mvg, gamma, p->d_local_t, p->d_flags);   \
-    } while (0)
+    k_layer_step<GT, PROX><<<dim3((unsigned)p->L, (unsigned)K), dim3(GRAWA_LAYER_THREADS), 0, s>>>(                        \
+        x, ldx, (const GT *)g, ldg, lr, center, w, p->d_off, p->L, p->d_mvg, gamma, p->d_local_t, p->d_flags)
         if (dt == GRAWA_BF16) {
             if (prox) GRAWA_LS_GO(uint16_t, true);
             else GRAWA_LS_GO(uint16_t, false);
@@ -352,7 +404,21 @@ static hipError_t launch_row_step(const grawa_plan *p, float *x, int64_t ldx, co
     const int64_t group = (prox && nb > GRAWA_ROW_GROUP) ? GRAWA_ROW_GROUP : nb;
     const int64_t n_groups = (nb + group - 1) / group;
     if (K > 65535 || n_groups > 65535 || group >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)group, (unsigned)K, (unsigned)n_groups), block(GRAWA_CELL);
+    // The blocks that fold in the step before stand at the head of the rows.  Eight in a row keep the columns of the center on
+    // the XCD that the other rows read them from.
+    unsigned long long id = 0;
+    const bool recorded = later && grawa_is_recorded(s, &id);
+    bool at_once = false;
+    const unsigned buffer = later ? grawa_step_buffer(p->steps, recorded, id, &at_once) : 0;
+    unsigned fold_blocks = 0;
+    if (later && !at_once) {
+        const int64_t units = (int64_t)K * p->L, blocks = p->max_rtiles <= GRAWA_FOLD_WAVE_TILES ? (units + 3) / 4 : units;
+        fold_blocks = (unsigned)((blocks + K * n_groups - 1) / (K * n_groups));
+        if (group >= 256) fold_blocks = (fold_blocks + 7) / 8 * 8;
+    }
+    GrawaFold fold = {}; // no flags either: k_estimate looks at the norms
+    if (later) fold = grawa_fold_of(p, gamma, buffer, fold_blocks);
+    const dim3 grid((unsigned)group + fold_blocks, (unsigned)K, (unsigned)n_groups), block(GRAWA_CELL);
     const bool aligned = rows_line_aligned(x, ldx, 4) && rows_line_aligned(g, ldg, dt == GRAWA_BF16 ? 2 : 4);
     const int64_t bytes = (int64_t)K * P * 4;
     const bool plain = !prox && !p;
@@ -360,12 +426,12 @@ static hipError_t launch_row_step(const grawa_plan *p, float *x, int64_t ldx, co
     const bool wide = !aligned && bytes > (plain ? 2 * GRAWA_STREAMING_MIN_SGD_BYTES : GRAWA_STREAMING_MIN_ROW_BYTES);
     const GrawaTile *tiles = p ? p->d_rtiles : nullptr;
     const int32_t *block_tile0 = p ? p->d_block_rtile0 : nullptr;
-    double *partials = p ? p->d_partials : nullptr;
+    double *partials = later ? p->d_sums : p ? p->d_partials : nullptr;
     const int64_t n_tiles = p ? p->n_rtiles : 0;
 #define GRAWA_RS_GO(GT, V, U, LNT, ST, PROX, SCORE)                                                                    \
     k_row_step<GT, V, U, LNT, ST, PROX, SCORE><<<grid, block, 0, s>>>(x, ldx, (const GT *)g, ldg, lr, center, w, P, \
                                                                        (unsigned)nb, tiles, block_tile0, n_tiles,  \
-                                                                       partials)
+                                                                       partials, fold)
 #define GRAWA_RS_NT(GT, V, U, PROX, SCORE)                                                                            \
     do {                                                                                                              \
         constexpr int64_t FROM = grawa_row_step_merges_from(sizeof(GT) == 2, PROX, SCORE);                            \
@@ -376,20 +442,28 @@ static hipError_t launch_row_step(const grawa_plan *p, float *x, int64_t ldx, co
         else GRAWA_RS_GO(GT, 4, 1, ALWAYS, (ALWAYS ? GRAWA_ST_MERGE : GRAWA_ST_STREAM), PROX, SCORE);                 \
     } while (0)
     if (dt == GRAWA_BF16) {
-        if (prox && p) GRAWA_RS_NT(uint16_t, 4, 1, true, true);
-        else if (prox) GRAWA_RS_NT(uint16_t, 4, 1, true, false);
-        else if (p) GRAWA_RS_NT(uint16_t, 4, 1, false, true);
-        else GRAWA_RS_NT(uint16_t, 2, 2, false, false);
+        if (prox && later && !at_once) GRAWA_RS_NT(uint16_t, 4, 1, true, GRAWA_SCORE_LATER);
+        else if (later && !at_once) GRAWA_RS_NT(uint16_t, 4, 1, false, GRAWA_SCORE_LATER);
+        else if (prox && p) GRAWA_RS_NT(uint16_t, 4, 1, true, GRAWA_SCORE_SUMS);
+        else if (prox) GRAWA_RS_NT(uint16_t, 4, 1, true, GRAWA_SCORE_NONE);
+        else if (p) GRAWA_RS_NT(uint16_t, 4, 1, false, GRAWA_SCORE_SUMS);
+        else GRAWA_RS_NT(uint16_t, 2, 2, false, GRAWA_SCORE_NONE);
     } else {
-        if (prox && p) GRAWA_RS_NT(float, 4, 1, true, true);
-        else if (prox) GRAWA_RS_NT(float, 4, 1, true, false);
-        else if (p) GRAWA_RS_NT(float, 4, 1, false, true);
-        else GRAWA_RS_NT(float, 1, 4, false, false);
+        if (prox && later && !at_once) GRAWA_RS_NT(float, 4, 1, true, GRAWA_SCORE_LATER);
+        else if (later && !at_once) GRAWA_RS_NT(float, 4, 1, false, GRAWA_SCORE_LATER);
+        else if (prox && p) GRAWA_RS_NT(float, 4, 1, true, GRAWA_SCORE_SUMS);
+        else if (prox) GRAWA_RS_NT(float, 4, 1, true, GRAWA_SCORE_NONE);
+        else if (p) GRAWA_RS_NT(float, 4, 1, false, GRAWA_SCORE_SUMS);
+        else GRAWA_RS_NT(float, 1, 4, false, GRAWA_SCORE_NONE);
     }
 #undef GRAWA_RS_NT
 #undef GRAWA_RS_GO
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || !p) return e;
+    if (later) {
+        grawa_step_sent(p->steps, recorded, id);
+        return at_once ? grawa_launch_fold(p, &fold, s) : e;
+    }
     return grawa_launch_estimate(p, gamma, s);
 }
 

@@ -11,9 +11,9 @@
 // lane in flight and a capped occupancy; what a fused pull reads again is read through the caches (grawa_cached_grad_cols).  Squares and sums are fp64 throughout, added in a
 // fixed order (no sum is formed by atomics; how norms pass between the blocks of a launch: grawa_scores.h),
 // so results are bit-reproducible.
+#include "grawa_fold.h"
 #include "grawa_offsets.h"
 #include "grawa_route.h"
-#include "grawa_scores.h"
 
 // ---------------------------------------------------------------------------------
 // gradient norms: per-tile sums of squares
@@ -143,23 +143,6 @@ __global__ __launch_bounds__(GRAWA_BLOCK) __attribute__((amdgpu_waves_per_eu(1, 
 
 #define GRAWA_FIN_BLOCK 1024
 #define GRAWA_FIN_WAVES (GRAWA_FIN_BLOCK / GRAWA_WAVE)
-
-// Sum of p[t0 + first], p[t0 + first + step], ... below t1 over the lanes of one wave, four
-// independent loads in flight per lane; every lane gets the total.
-__device__ __forceinline__ double wave_strided_sum(const double *__restrict__ p, int t0, int t1, int first,
-                                                   int step)
-{
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-    int t = t0 + first;
-    for (; t + 3 * step < t1; t += 4 * step) {
-        s0 += p[t];
-        s1 += p[t + step];
-        s2 += p[t + 2 * step];
-        s3 += p[t + 3 * step];
-    }
-    for (; t < t1; t += step) s0 += p[t];
-    return wave_sum((s0 + s1) + (s2 + s3));
-}
 
 // Score of every worker (the sum of its layer norms, or the norm of the flattened gradient) from S[k][l], then the K
 // weights, by one block of 1024.
@@ -383,6 +366,89 @@ __global__ __launch_bounds__(GRAWA_LW_BLOCK_MODEL) void k_local_weights(double *
     }
 }
 
+// The same where the last step's sums may not be folded in yet (grawa_fold.h).  per_layer: grid L, and what is pending is folded in on the way:
+// by a thread per worker, a wave per worker in turn, or the block for one worker after the other, as the layers are longer.  Model level:
+// grid 1.  Where layers are long, and for the model level, k_fold goes before; what is still pending then was replayed after calls made one by one.
+__global__ __launch_bounds__(GRAWA_FIN_BLOCK) void k_fold_weights(const GrawaFold f, const double *__restrict__ sums, int64_t n_tiles,
+                                                                   int per_layer, unsigned *__restrict__ consumed,
+                                                                   float *__restrict__ beta, float *__restrict__ beta_user,
+                                                                   float *__restrict__ est_user)
+{
+    __shared__ double sA[GRAWA_MAX_WORKERS];
+    __shared__ double part[GRAWA_FOLD_LANES / GRAWA_WAVE];
+    const int lane = threadIdx.x & (GRAWA_WAVE - 1);
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / GRAWA_WAVE)), waves = (int)blockDim.x / GRAWA_WAVE;
+    const int l0 = per_layer ? (int)blockIdx.x : 0;
+    const int K = f.K, L = f.L;
+    const GrawaEstimate e0 = f.est[l0]; // counts and buffer: the same for all workers and layers
+    const unsigned n = e0.n, used = consumed[l0];
+    const bool pending = estimate_pending(e0, used);
+    if (per_layer) {
+        const int t0 = f.layer_tile0[l0], t1 = f.layer_tile0[l0 + 1], tiles = t1 - t0;
+        const double *p = sums + e0.buffer * f.pitch;
+        if (pending && tiles > 16 && f.by_wave) {
+            for (int k = wave; k < K; k += waves) {
+                const double s = wave_strided_sum(p + (int64_t)k * n_tiles, t0, t1, lane, GRAWA_WAVE);
+                if (lane == 0) sA[k] = s;
+            }
+        } else if (pending && tiles > 16) {
+            for (int k = 0; k < K; ++k) { // GRAWA_FOLD_LANES threads
+                const double s = block_tile_sum<GRAWA_FOLD_LANES>(p + (int64_t)k * n_tiles, t0, t1, part);
+                if (threadIdx.x == 0) sA[k] = s;
+            }
+        }
+        const double scale = n != used ? f.gamma / grawa_one_minus_power(f.gamma, (int64_t)(n - used)) : 0.0;
+        __syncthreads(); // also: every thread has read `used`
+        if (threadIdx.x == 0) consumed[l0] = n;
+        for (int k = (int)threadIdx.x; k < K; k += (int)blockDim.x) {
+            double s = 0.0;
+            if (pending) s = tiles <= 4    ? few_tiles_sum<4>(p + (int64_t)k * n_tiles, t0, t1)
+                             : tiles <= 16 ? few_tiles_sum<16>(p + (int64_t)k * n_tiles, t0, t1)
+                                           : sA[k];
+            const double v = scale * estimate_value(f.est[(int64_t)k * L + l0], used, s);
+            sA[k] = v;
+            if (est_user) est_user[(int64_t)k * L + l0] = (float)v;
+        }
+        __syncthreads();
+        if (wave == 0)
+            group_weights(sA, K, beta + l0, L, beta_user ? beta_user + l0 : nullptr, f.flags, GRAWA_NONFINITE_LAYER_SCORE);
+    } else {
+        const double scale = n != used ? f.gamma / grawa_one_minus_power(f.gamma, (int64_t)(n - used)) : 0.0;
+        if (pending) {
+            __syncthreads(); // every thread has read e0
+            fold_all<GRAWA_LW_BLOCK_MODEL, GRAWA_FOLD_ONLY>(f, sums, n_tiles, 0, 1);
+            __syncthreads();
+        }
+        for (int k = wave; k < K; k += waves) {
+            double s = 0.0;
+            for (int l = lane; l < L; l += GRAWA_WAVE) {
+                const double v = scale * estimate_value(f.est[(int64_t)k * L + l], used, 0.0);
+                s += v;
+                if (est_user) est_user[(int64_t)k * L + l] = (float)v;
+            }
+            s = wave_sum(s);
+            if (lane == 0) sA[k] = s;
+        }
+        __syncthreads(); // also: every thread has read `used`
+        for (int l = threadIdx.x; l < L; l += blockDim.x) consumed[l] = n;
+        if (wave == 0) group_weights(sA, K, beta, 1, beta_user, f.flags, GRAWA_NONFINITE_MODEL_SCORE);
+    }
+}
+
+// The estimates up to the last step, in a launch of its own; FOLD_SUMS: of a recorded step.
+template <int THREADS, int MODE>
+__global__ __launch_bounds__(THREADS) void k_fold(const GrawaFold f, const double *__restrict__ sums, int64_t n_tiles)
+{
+    fold_all<THREADS, MODE>(f, sums, n_tiles, blockIdx.x, gridDim.x);
+}
+
+// An explicit reset: everything so far is used up.
+__global__ __launch_bounds__(GRAWA_BLOCK) void k_fold_reset(const GrawaEstimate *__restrict__ est, int L, unsigned *__restrict__ consumed)
+{
+    const int l = blockIdx.x * GRAWA_BLOCK + threadIdx.x;
+    if (l < L) consumed[l] = est[l].n;
+}
+
 // g_mvg <- 0 and t <- 0 (an explicit reset).
 __global__ __launch_bounds__(GRAWA_BLOCK) void k_zero_estimate(double *__restrict__ p, int64_t n,
                                                                int64_t *__restrict__ local_t, int L)
@@ -505,9 +571,49 @@ hipError_t grawa_launch_estimate(const grawa_plan *p, double gamma, hipStream_t 
     return hipGetLastError();
 }
 
+// step: a recorded step, whose sums are to be folded in; null: only what is pending.
+hipError_t grawa_launch_fold(const grawa_plan *p, const GrawaFold *step, hipStream_t s)
+{
+    const GrawaFold f = step ? *step : grawa_fold_of(p, 0.0, 0, 0);
+    const unsigned units = (unsigned)p->K * (unsigned)p->L;
+    const dim3 grid(f.by_wave ? (units + 3) / 4 : units), block(f.by_wave ? 256 : GRAWA_FOLD_LANES);
+#define GRAWA_FOLD_GO(THREADS, MODE) k_fold<THREADS, MODE><<<grid, block, 0, s>>>(f, p->d_sums, p->n_rtiles)
+    if (f.by_wave && step) GRAWA_FOLD_GO(256, GRAWA_FOLD_SUMS);
+    else if (f.by_wave) GRAWA_FOLD_GO(256, GRAWA_FOLD_ONLY);
+    else if (step) GRAWA_FOLD_GO(GRAWA_FOLD_LANES, GRAWA_FOLD_SUMS);
+    else GRAWA_FOLD_GO(GRAWA_FOLD_LANES, GRAWA_FOLD_ONLY);
+#undef GRAWA_FOLD_GO
+    return hipGetLastError();
+}
+
+// Whether what is sent to the stream is recorded into a graph, and a number of the recording that is not 0.
+bool grawa_is_recorded(hipStream_t s, unsigned long long *id)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    const hipError_t e = hipStreamGetCaptureInfo(s, &st, id);
+    *id += 1;
+    if (e == hipSuccess) return st != hipStreamCaptureStatusNone;
+    (void)hipGetLastError(); // the launch then fails as well
+    return false;
+}
+
 hipError_t grawa_launch_local_weights(const grawa_plan *p, double gamma, int per_layer, float *beta_user,
                                       float *est_user, hipStream_t s)
 {
+    if (p->fold_later) {
+        unsigned long long id = 0;
+        const bool recorded = grawa_is_recorded(s, &id);
+        const GrawaFold f = grawa_fold_of(p, gamma, 0, 0);
+        if ((!per_layer || !f.by_wave) && !grawa_all_folded(p->steps, recorded, id)) {
+            const hipError_t e = grawa_launch_fold(p, nullptr, s);
+            if (e != hipSuccess) return e;
+        }
+        const int fold_waves = GRAWA_FOLD_LANES / GRAWA_WAVE, all = p->K < GRAWA_FIN_WAVES ? p->K : GRAWA_FIN_WAVES;
+        const int waves = !per_layer ? GRAWA_LW_BLOCK_MODEL / GRAWA_WAVE : !f.by_wave ? fold_waves : p->max_rtiles <= 16 || p->K < 4 ? 4 : all;
+        k_fold_weights<<<dim3(per_layer ? (unsigned)p->L : 1u), dim3(waves * GRAWA_WAVE), 0, s>>>(
+            f, p->d_sums, p->n_rtiles, per_layer, p->d_consumed, per_layer ? p->d_beta_layer : p->d_beta_model, beta_user, est_user);
+        return hipGetLastError();
+    }
     k_local_weights<<<dim3(per_layer ? (unsigned)p->L : 1u), dim3(per_layer ? GRAWA_LW_BLOCK_LAYER : GRAWA_LW_BLOCK_MODEL), 0, s>>>(
         p->d_mvg, gamma, p->d_local_t, p->K, p->L, per_layer, per_layer ? p->d_beta_layer : p->d_beta_model,
         beta_user, est_user, p->d_flags);
@@ -516,6 +622,10 @@ hipError_t grawa_launch_local_weights(const grawa_plan *p, double gamma, int per
 
 hipError_t grawa_launch_zero_estimate(const grawa_plan *p, hipStream_t s)
 {
+    if (p->fold_later) {
+        k_fold_reset<<<dim3((unsigned)((p->L + GRAWA_BLOCK - 1) / GRAWA_BLOCK)), dim3(GRAWA_BLOCK), 0, s>>>(p->d_est, p->L, p->d_consumed);
+        return hipGetLastError();
+    }
     const int64_t n = (int64_t)p->K * p->L;
     k_zero_estimate<<<dim3((unsigned)((n + GRAWA_BLOCK - 1) / GRAWA_BLOCK)), dim3(GRAWA_BLOCK), 0, s>>>(p->d_mvg, n,
                                                                                                     p->d_local_t, p->L);

@@ -209,6 +209,57 @@ static inline int grawa_step_by_layers(int K, int L, int64_t P, int64_t max_tile
     return max_tiles <= GRAWA_LAYER_SHORT_MAX_TILES && elems <= GRAWA_LAYER_SHORT_MAX_ELEMS && blocks <= GRAWA_LAYER_SHORT_MAX_BLOCKS ? 256 : 0;
 }
 
+// Scored step: whether its tile sums are left to the launch that needs them next (grawa_fold.h) instead of a launch of their own.
+// It saves that launch and its boundary, about 5 us on the device and 3 on the host, for every step but the last of a round, and
+// against a block per layer (k_layer_step with 1024 threads, which it replaced) the time one CU takes for the longest layer.  A round of four
+// steps with the center and the communication, fp32, us, before / now (in brackets replayed as a graph): ResNet-20, 59 layers, 4 workers 42.7 / 32.4
+// (42.7 / 31.0), 8 workers 48.0 / 37.8 (48.1 / 37.9); 16 workers, 200 k columns, 150 layers 68.7 / 49.5 (69.1 / 50.2); 4 workers, 1 M, one layer 67.3 /
+// 59.7 (67.9 / 60.6), 60 layers 71.9 / 61.0; 64 workers, 300 k, 100 layers 198 / 188; 16 workers, 3 M 510 / 493; 2 workers, 20 M, one layer 428 / 409.
+// One step and the communication, 8 workers, 8 M columns 214.7 / 216.0.
+// The step by layers stays where no layer has more than 7 tiles: with many of them it is the shorter launch (4 workers, 200 k columns, 300
+// layers, replayed 34 here, 29.4 by layers; up to 10 tiles, 16 workers, 150 layers 48.7 / 51.4).  Beyond 2^17 blocks a step lasts 300 us and more,
+// and the buffers take memory.
+#define GRAWA_FOLD_MAX_BLOCKS ((int64_t)1 << 17)
+#define GRAWA_FOLD_WAVE_TILES 512 // up to here a wave adds the tiles of a layer, beyond it a block
+static inline bool grawa_fold_later(int K, int L, int64_t P, int64_t max_tiles)
+{
+    if (max_tiles <= GRAWA_LAYER_SHORT_TILES && grawa_step_by_layers(K, L, P, max_tiles)) return false;
+    return (int64_t)K * ((P + 1023) / 1024) <= GRAWA_FOLD_MAX_BLOCKS && (int64_t)K * L <= GRAWA_FOLD_MAX_BLOCKS;
+}
+
+// Which buffer of tile sums a step takes there, so that it never finds its own pending, whatever is called or replayed after what.
+// Calls made one by one take 0 and 1 in turn.  A recorded call is replayed with the buffer that it was recorded with: the first step of a recording
+// takes 2 and is followed by a launch that folds it in (the recording may hold no other and be replayed twice), those after it take
+// 3 and 4 in turn.
+struct GrawaSteps {
+    unsigned sent;                // calls made one by one
+    unsigned recorded;            // calls recorded after the first one of a recording
+    unsigned long long recording; // the last one that a step was recorded in
+    bool folded;                  // that step has a launch of its own that folds it in
+};
+#define GRAWA_SUM_BUFFERS 5
+// at_once: the step is to be folded in by a launch of its own.
+static inline unsigned grawa_step_buffer(const GrawaSteps &s, bool recorded, unsigned long long id, bool *at_once)
+{
+    *at_once = recorded && s.recording != id;
+    return !recorded ? s.sent & 1u : *at_once ? 2u : 3u + (s.recorded & 1u);
+}
+static inline void grawa_step_sent(GrawaSteps &s, bool recorded, unsigned long long id)
+{
+    if (!recorded) {
+        s.sent += 1;
+        return;
+    }
+    s.folded = s.recording != id;
+    if (!s.folded) s.recorded += 1;
+    s.recording = id;
+}
+// Whether a communication that is being recorded finds nothing pending but what calls made before a replay left.
+static inline bool grawa_all_folded(const GrawaSteps &s, bool recorded, unsigned long long id)
+{
+    return recorded && s.recording == id && s.folded;
+}
+
 // 1 - gamma^t for 0 < gamma < 1, by squaring, since pow() is a chain of a microsecond in k_local_weights.  Every product keeps what its
 // rounding drops, so that the error stays at the last place however near to 1 gamma is (plain squaring loses t units of it, pow() one, and the
 // difference divides both by 1 - gamma^t).  Used on the device too (constexpr).
