@@ -34,6 +34,7 @@ class GrawaError(RuntimeError):
 
 
 _lib = None
+_addresses = {}             # of the functions that native code calls, once the library is loaded
 
 
 def lib():
@@ -78,6 +79,8 @@ def lib():
         fn = getattr(L, name)
         fn.restype = res
         fn.argtypes = args
+    for name in ("grawa_lgrawa_update", "grawa_local_step_scored", "grawa_local_lgrawa_update", "grawa_local_mgrawa_update"):
+        _addresses[name] = C.cast(getattr(L, name), vp).value
     _lib = L
     return L
 
@@ -112,13 +115,18 @@ def _stream_no_tensors(stream=None):
 # The checks of _params and _grads on a CUDA tensor by native code (csrc/grawa_rows.cpp): (pointer, row stride, dtype code), or
 # None for whatever is not plainly in order; the Python checks below look again then, and raise.  The module reads torch's
 # objects by the layout it was compiled for: one of another torch or Python may load all the same and is not used.
+# The same of whole calls: their status, or None for any argument that is not plainly in order; the Python call follows then.
 try:
-    from ._rows import built_for, rows as _native_rows
+    from ._rows import built_for, rows as _native_rows, scored as _native_scored, local as _native_local, lgrawa as _native_lgrawa
     if built_for != buildlib.rows_built_for():
         raise ImportError("_rows.so is for %s" % built_for)
 except Exception:                        # not built, or not for this torch: the Python checks alone
     def _native_rows(t, K, P, grads):
         return None
+
+    def _native_scored(*args):
+        return None
+    _native_local = _native_lgrawa = _native_scored
 
 
 _NULL = C.c_void_p(0)
@@ -292,6 +300,11 @@ class Plan:
                "grawa_mgrawa_update")
 
     def lgrawa_update(self, x, g, lam, center_out=None, weights_out=None, stream=None):
+        if stream is None:
+            st = _native_lgrawa(_addresses.get("grawa_lgrawa_update"), self._h.value, x, g, self.K, self.P, self.L, lam, center_out,
+                                weights_out, _stream)
+            if st is not None:
+                return _check(st, "grawa_lgrawa_update")
         xp, ldx, gp, ldg, dt = self._xg(x, g)
         _check(lib().grawa_lgrawa_update(self._h, xp, ldx, gp, ldg, dt, float(lam),
                                          _vector(center_out, self.P, "center_out"),
@@ -331,12 +344,22 @@ class Plan:
 
     # -- Local MGRAWA / LGRAWA (Appendix G) -----------------------------------------
     def local_step_scored(self, x, g, lr, gamma, center=None, mu=0.0, tau=1.0, stream=None):
+        if stream is None:
+            st = _native_scored(_addresses.get("grawa_local_step_scored"), self._h.value, x, g, self.K, self.P, lr, gamma, center, mu, tau,
+                                _stream)
+            if st is not None:
+                return _check(st, "grawa_local_step_scored")
         xp, ldx, gp, ldg, dt = self._xg(x, g)
         _check(lib().grawa_local_step_scored(self._h, xp, ldx, gp, ldg, dt, float(lr),
                                              _vector(center, self.P, "center"), float(mu), float(tau), float(gamma),
                                              _stream(stream)), "grawa_local_step_scored")
 
     def local_lgrawa_update(self, x, lam, center_out=None, weights_out=None, est_out=None, stream=None):
+        if stream is None:
+            st = _native_local(_addresses.get("grawa_local_lgrawa_update"), self._h.value, x, self.K, self.P, self.L, 1, lam, center_out,
+                               weights_out, est_out, _stream)
+            if st is not None:
+                return _check(st, "grawa_local_lgrawa_update")
         xp, ldx = _params(x, self.K, self.P)
         _check(lib().grawa_local_lgrawa_update(self._h, xp, ldx, float(lam), _vector(center_out, self.P, "center_out"),
                                                _table(weights_out, (self.K, self.L), "weights_out"),
@@ -344,6 +367,11 @@ class Plan:
                "grawa_local_lgrawa_update")
 
     def local_mgrawa_update(self, x, lam, center_out=None, weights_out=None, est_out=None, stream=None):
+        if stream is None:
+            st = _native_local(_addresses.get("grawa_local_mgrawa_update"), self._h.value, x, self.K, self.P, self.L, 0, lam, center_out,
+                               weights_out, est_out, _stream)
+            if st is not None:
+                return _check(st, "grawa_local_mgrawa_update")
         xp, ldx = _params(x, self.K, self.P)
         _check(lib().grawa_local_mgrawa_update(self._h, xp, ldx, float(lam), _vector(center_out, self.P, "center_out"),
                                                _table(weights_out, (self.K,), "weights_out"),
