@@ -4,19 +4,20 @@
 //
 // The step counts live on the device, so that replayed calls count.  What a launch folds in lies in another buffer than the sums
 // that it writes (grawa_step_buffer).
-// A communication writes nothing but d_consumed, which says that everything up to that step is used up; what is left of mvg
-// is then taken as zero.  Every sum runs in the same order wherever it is formed, so that a replay gives the bits of the calls.
+// A communication writes nothing but counts (d_consumed, d_seen), which say that everything up to that step is used up; what is left
+// of mvg is then taken as zero.  Every sum runs in the same order wherever it is formed, so that a replay gives the bits of the calls.
 #pragma once
 #include "grawa_route.h"
 #include "grawa_scores.h"
 
 struct GrawaFold {
     GrawaEstimate *est;
-    const unsigned *consumed;
+    const unsigned *consumed; // [2 L]
     const int32_t *layer_tile0; // [L+1]
     unsigned *flags;
     int64_t pitch; // sums in one of the buffers
     int K, L, by_wave;
+    int lanes;       // of a wave that add the tiles of a worker: as many as in the pull, where that folds in (wave_layer_weights)
     unsigned buffer; // that the sums of this launch go to
     unsigned blocks; // of every row of a step's grid that fold
     double gamma;    // of the step that this launch takes
@@ -84,6 +85,9 @@ __device__ __forceinline__ double block_tile_sum(const double *__restrict__ p, i
     return tot;
 }
 
+// The step that the last communication took into account: the later one of what launches of the weights and pulls noted.  n: steps so far.
+__device__ __forceinline__ unsigned last_used(unsigned n, unsigned a, unsigned b) { return n - a < n - b ? a : b; }
+
 __device__ __forceinline__ bool estimate_pending(const GrawaEstimate &e, unsigned consumed) { return e.n != consumed && e.n != e.folded; }
 
 // g_mvg up to step e.n; `sum`: the squares of that step, if they are pending.
@@ -112,13 +116,13 @@ __device__ __forceinline__ void fold_all(const GrawaFold &f, const double *__res
     for (unsigned u = f.by_wave ? first * WAVES + wave : first; u < units; u += step) {
         const unsigned k = u / (unsigned)f.L, l = u - k * (unsigned)f.L;
         GrawaEstimate e = f.est[u];
-        const unsigned consumed = f.consumed[l];
+        const unsigned consumed = last_used(e.n, f.consumed[l], f.consumed[f.L + l]);
         const int t0 = f.layer_tile0[l], t1 = f.layer_tile0[l + 1];
         const double *p = sums + (int64_t)k * n_tiles;
         if (!f.by_wave) __syncthreads(); // every wave has read what thread 0 writes below
         double next = 0.0, tot = 0.0;
         const auto sum = [&](unsigned buffer) {
-            return f.by_wave ? wave_strided_sum(p + buffer * f.pitch, t0, t1, lane, GRAWA_WAVE)
+            return f.by_wave ? wave_strided_sum(p + buffer * f.pitch, lane < f.lanes ? t0 : t1, t1, lane, f.lanes)
                              : block_tile_sum<THREADS>(p + buffer * f.pitch, t0, t1, part);
         };
         if (MODE == GRAWA_FOLD_SUMS) next = sum(f.buffer);
@@ -143,5 +147,5 @@ __device__ __forceinline__ void fold_all(const GrawaFold &f, const double *__res
 static inline GrawaFold grawa_fold_of(const grawa_plan *p, double gamma, unsigned buffer, unsigned blocks)
 {
     return GrawaFold{p->d_est, p->d_consumed, p->d_layer_rtile0, p->d_flags, (int64_t)p->K * p->n_rtiles, p->K, p->L,
-                     p->max_rtiles <= GRAWA_FOLD_WAVE_TILES, buffer, blocks, gamma};
+                     p->max_rtiles <= GRAWA_FOLD_WAVE_TILES, p->d_seen ? grawa_group_lanes(p->K) : 64, buffer, blocks, gamma};
 }

@@ -24,6 +24,13 @@ struct GrawaEstimate {
     unsigned buffer; // of d_sums that holds the sums of step n
 };
 
+// What grawa_launch_local_weights leaves to the pull that is launched next.
+struct GrawaLocalWeights {
+    bool in_pull;
+    double gamma;
+    float *weights_out, *est_out;
+};
+
 struct grawa_plan {
     int K;
     int L;
@@ -57,7 +64,9 @@ struct grawa_plan {
     double *d_sums;         // [GRAWA_SUM_BUFFERS][K][n_rtiles] tile sums of scored steps
     mutable GrawaSteps steps;
     GrawaEstimate *d_est;   // [K][L]
-    unsigned *d_consumed;   // [L], all equal: the step that the last communication took into account
+    unsigned *d_consumed;   // [2][L], each half all equal: the step that the last communication took into account, a launch of the weights and a pull
+    unsigned *d_seen;       // [n_cells] the same, for each block of such a pull; null: no pull works the weights out
+    mutable GrawaLocalWeights local;
     unsigned *d_flags;      // device: GRAWA_NONFINITE_* bits, sticky until read-and-cleared (may be null)
     int64_t local_t;        // host mirror of the counter as of the last enqueued call (argument checks only)
     double local_gamma;     // momentum of the running estimate used so far (0 = none yet)

@@ -381,7 +381,7 @@ __global__ __launch_bounds__(GRAWA_FIN_BLOCK) void k_fold_weights(const GrawaFol
     const int l0 = per_layer ? (int)blockIdx.x : 0;
     const int K = f.K, L = f.L;
     const GrawaEstimate e0 = f.est[l0]; // counts and buffer: the same for all workers and layers
-    const unsigned n = e0.n, used = consumed[l0];
+    const unsigned n = e0.n, used = last_used(n, consumed[l0], consumed[L + l0]);
     const bool pending = estimate_pending(e0, used);
     if (per_layer) {
         const int t0 = f.layer_tile0[l0], t1 = f.layer_tile0[l0 + 1], tiles = t1 - t0;
@@ -600,6 +600,11 @@ bool grawa_is_recorded(hipStream_t s, unsigned long long *id)
 hipError_t grawa_launch_local_weights(const grawa_plan *p, double gamma, int per_layer, float *beta_user,
                                       float *est_user, hipStream_t s)
 {
+    p->local = GrawaLocalWeights{};
+    if (per_layer && p->d_seen) {
+        p->local = GrawaLocalWeights{true, gamma, beta_user, est_user};
+        return hipSuccess;
+    }
     if (p->fold_later) {
         unsigned long long id = 0;
         const bool recorded = grawa_is_recorded(s, &id);

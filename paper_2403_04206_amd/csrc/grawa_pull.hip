@@ -7,9 +7,9 @@
 // 256-byte piece of every row (one 32-bit element per lane per row), blocks are small and many,
 // and accesses are non-temporal -- provided every row starts on a 128-byte boundary, so that no
 // cache line is written in two parts.  There is no dense contraction, hence no matrix-core code.
+#include "grawa_fold.h"
 #include "grawa_offsets.h"
 #include "grawa_route.h"
-#include "grawa_scores.h"
 
 // ---------------------------------------------------------------------------------
 // center + pull (+ SGD on the way in)
@@ -105,6 +105,33 @@ struct TileWeights {
     int shift;                            // without the maps: tiles of 2^shift columns, found in the offsets
 };
 
+// The same from the running estimate (the communication of a local round): what a scored step left pending is folded in on
+// the way.  Every block keeps the step that it has used everything up to (`seen`), since no block may write what another one of
+// the launch reads; the cell that a layer starts in tells the other launches.
+struct EstimateWeights : TileWeights { // partials: the buffers of sums
+    const GrawaEstimate *est;
+    const unsigned *consumed;    // [2 L]
+    unsigned *consumed_by_pulls; // [L], the second half
+    unsigned *seen;              // [cells]
+    float *est_out;              // [K][L] or null
+    int64_t buffer;              // sums in one
+    double gamma;
+};
+struct EstimateScore {
+    typedef GrawaEstimate State;
+    const EstimateWeights &w;
+    int L;
+    unsigned n, used;
+    double scale;
+    __device__ __forceinline__ State load(int k, int l) const { return w.est[(int64_t)k * L + l]; }
+    __device__ __forceinline__ double score(const State &e, double sum) const { return scale * estimate_value(e, used, sum); }
+    __device__ __forceinline__ void publish(int k, int l, double a) const
+    {
+        if (k == 0) w.consumed_by_pulls[l] = n;
+        if (w.est_out) w.est_out[(int64_t)k * L + l] = (float)a;
+    }
+};
+
 template <int K> struct CellWeights {
     float beta[GRAWA_CELL * K]; // [layer of the cell][K]
     int start[GRAWA_CELL];      // first column of the layer, relative to the cell
@@ -117,9 +144,10 @@ template <int K> struct CellWeights {
 // takes two rounds at most, for 3 layers as for 256 (a wave per layer in turn took 16 rounds, and lanes that walked
 // all tiles of their layer more: 4 workers, 600 k columns, of which the first 60 or 100 are layers of their own, update on the
 // device 24.6 and 174 us; with the weights as a launch 17.3 and 21.8; now 11.4 and 11.7).
-template <int K, bool SLOTS>
-__device__ __forceinline__ int cell_weights(const TileWeights &w, const int64_t *__restrict__ off, int L, int64_t P,
-                                            int64_t cell0, int l0, bool boundary, CellWeights<K> &sh)
+template <int K, bool SLOTS, typename Score>
+__device__ __forceinline__ int cell_weights(const TileWeights &w, const Score &scores, const double *partials,
+                                            const int64_t *__restrict__ off, int L, int64_t P, int64_t cell0, int l0, bool boundary,
+                                            CellWeights<K> &sh)
 {
     const int lane = threadIdx.x & (GRAWA_WAVE - 1);
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / GRAWA_WAVE));
@@ -139,7 +167,7 @@ __device__ __forceinline__ int cell_weights(const TileWeights &w, const int64_t 
         int t0, t1;
         if constexpr (SLOTS) layer_slots(off, l, P, w.shift, t0, t1);
         else t0 = w.tile_begin[l], t1 = w.tile_end[l];
-        wave_layer_weights(w.partials, w.pitch, t0, t1, K, w.group, sh.beta + i * K,
+        wave_layer_weights(scores, l, partials, w.pitch, t0, t1, K, w.group, sh.beta + i * K,
                            off[l] >= cell0, w.weights_out ? w.weights_out + l : nullptr, L, w.flags);
     } else if (wave >= 2) {
         for (int i = 1 + (int)threadIdx.x - 2 * GRAWA_WAVE; i < nl - 1; i += GRAWA_CELL - 2 * GRAWA_WAVE) {
@@ -147,7 +175,7 @@ __device__ __forceinline__ int cell_weights(const TileWeights &w, const int64_t 
             int t0, t1;
             if constexpr (SLOTS) layer_slots(off, l, P, w.shift, t0, t1);
             else t0 = w.tile_begin[l], t1 = w.tile_end[l];
-            lane_layer_weights<K>(w.partials, w.pitch, t0, t1, sh.beta + i * K,
+            lane_layer_weights<K>(scores, l, partials, w.pitch, t0, t1, sh.beta + i * K,
                                   w.weights_out ? w.weights_out + l : nullptr, L, w.flags);
         }
     }
@@ -178,14 +206,16 @@ template <int K> __device__ __forceinline__ int cell_layer_of(const CellWeights<
 // center used and stored is c0 + rho (c - c0).
 // WPE caps the waves per SIMD (grawa_waves_for; cached accesses: launch_plain): more only queues requests to K far-apart rows and costs DRAM
 // efficiency (measured: K = 16 at 3 waves 6.1 TB/s, at 8 waves 5.7; K = 8 at 4 waves 6.5, at 8 waves 6.2).
-// TILES: weights from the tile sums, by the maps of a plan or found in the offsets (GRAWA_TILES_SLOTS).
-enum { GRAWA_TILES_NONE = 0, GRAWA_TILES_MAPS = 1, GRAWA_TILES_SLOTS = 2 };
+// TILES: weights from the tile sums, by the maps of a plan or found in the offsets (GRAWA_TILES_SLOTS), or from the running estimate.
+enum { GRAWA_TILES_NONE = 0, GRAWA_TILES_MAPS = 1, GRAWA_TILES_SLOTS = 2, GRAWA_TILES_ESTIMATE = 3 };
+template <int TILES> struct WeightsOf { typedef TileWeights T; };
+template <> struct WeightsOf<GRAWA_TILES_ESTIMATE> { typedef EstimateWeights T; };
 template <int K, bool SGD, typename GT, bool NT, int WPE, int TILES>
 __global__ __launch_bounds__(GRAWA_CELL) __attribute__((amdgpu_waves_per_eu(1, WPE))) void k_center_pull(
     float *__restrict__ x, int64_t ldx, const GT *__restrict__ g, int64_t ldg, float lr,
     const float *__restrict__ beta, int64_t beta_stride, const int32_t *__restrict__ cell_layer,
     const int64_t *__restrict__ off, int L, int64_t P, float lambda,
-    float *__restrict__ center_out, float rho, int moving, const TileWeights tw)
+    float *__restrict__ center_out, float rho, int moving, const typename WeightsOf<TILES>::T tw)
 {
     const int64_t cell0 = (int64_t)blockIdx.x * GRAWA_CELL; // wave-uniform
     const unsigned col = threadIdx.x;
@@ -219,7 +249,18 @@ __global__ __launch_bounds__(GRAWA_CELL) __attribute__((amdgpu_waves_per_eu(1, W
     float c = 0.f;
     if constexpr (TILES) {
         __shared__ CellWeights<K> cw;
-        const int nl = cell_weights<K, TILES == GRAWA_TILES_SLOTS>(tw, off, L, P, cell0, info >= 0 ? info : ~info, info < 0, cw);
+        const int l0 = info >= 0 ? info : ~info;
+        int nl;
+        if constexpr (TILES == GRAWA_TILES_ESTIMATE) {
+            const GrawaEstimate e = tw.est[l0]; // counts and buffer: the same for all workers and layers
+            const unsigned used = last_used(e.n, tw.consumed[l0], tw.seen[blockIdx.x]);
+            const double scale = e.n != used ? tw.gamma / grawa_one_minus_power(tw.gamma, (int64_t)(e.n - used)) : 0.0;
+            nl = cell_weights<K, false>(tw, EstimateScore{tw, L, e.n, used, scale}, tw.partials + e.buffer * tw.buffer, off, L, P, cell0, l0,
+                                        info < 0, cw);
+            if (threadIdx.x == 0) tw.seen[blockIdx.x] = e.n; // after the barrier at whose end every thread has read it
+        } else {
+            nl = cell_weights<K, TILES == GRAWA_TILES_SLOTS>(tw, NormScore{}, tw.partials, off, L, P, cell0, l0, info < 0, cw);
+        }
         const float *b = cw.beta + cell_layer_of<K>(cw, nl, (int)col) * K;
 #pragma unroll
         for (int k = 0; k < K; ++k) c = fmaf(b[k], v[k], c);
@@ -543,12 +584,14 @@ constexpr int grawa_waves_for(int k, bool sgd, bool bf16)
 
 #define GRAWA_CP_ARGS                                                                                                 \
     const grawa_plan *p, float *x, int64_t ldx, const void *g, int64_t ldg, float lr, const float *beta, int per_layer, \
-        float lambda, float *center_out, float rho, int moving, [[maybe_unused]] const TileWeights &tw,                 \
+        float lambda, float *center_out, float rho, int moving, [[maybe_unused]] const EstimateWeights &tw,                 \
         [[maybe_unused]] bool capped, hipStream_t s,                                                                   \
         hipEvent_t e0, hipEvent_t e1
 #define GRAWA_CP_PASS p, x, ldx, g, ldg, lr, beta, per_layer, lambda, center_out, rho, moving, tw, capped, s, e0, e1
 #define GRAWA_CP_STRIDE per_layer ? (int64_t)p->L : (int64_t)1
 #define GRAWA_CP_CELLS per_layer ? (const int32_t *)p->d_cell_layer : (const int32_t *)nullptr
+
+template <int TILES> static const typename WeightsOf<TILES>::T &weights_arg(const EstimateWeights &w) { return w; }
 
 template <int K, bool SGD, typename GT, bool NT, int TILES> static void launch_plain(GRAWA_CP_ARGS)
 {
@@ -563,7 +606,7 @@ template <int K, bool SGD, typename GT, bool NT, int TILES> static void launch_p
     const size_t lds = WPE > CAP && capped ? ((size_t)160 << 10) / (CAP + 1) + 1024 : 0;
     hipExtLaunchKernelGGL((k_center_pull<K, SGD, GT, NT, WPE, TILES>), dim3((unsigned)p->n_cells), dim3(GRAWA_CELL), lds, s, e0,
                           e1, 0, x, ldx, (const GT *)g, ldg, lr, beta, GRAWA_CP_STRIDE, GRAWA_CP_CELLS,
-                          (const int64_t *)p->d_off, p->L, p->P, lambda, center_out, rho, moving, tw);
+                          (const int64_t *)p->d_off, p->L, p->P, lambda, center_out, rho, moving, weights_arg<TILES>(tw));
 }
 
 // The wide form's cap (best of 2, 3, 4 and 8 waves; one too many costs 3 to 5 %, and more than it gains over the plain form).
@@ -686,11 +729,16 @@ template <bool SGD, typename GT> static hipError_t dispatch_cp_tiles(GRAWA_CP_AR
 {
 #define GRAWA_CP_TILES(N)                                                                                      \
     case N:                                                                                                    \
-        if constexpr (!SGD) /* the call without maps has no fused step */                                      \
+        if constexpr (!SGD) { /* neither the call without maps nor the communication has a fused step */       \
+            if (tw.est) {                                                                                      \
+                launch_plain<N, SGD, GT, false, GRAWA_TILES_ESTIMATE>(GRAWA_CP_PASS);                          \
+                return hipGetLastError();                                                                      \
+            }                                                                                                  \
             if (p->tile_shift) {                                                                               \
                 launch_plain<N, SGD, GT, false, GRAWA_TILES_SLOTS>(GRAWA_CP_PASS);                             \
                 return hipGetLastError();                                                                      \
             }                                                                                                  \
+        }                                                                                                      \
         launch_plain<N, SGD, GT, false, GRAWA_TILES_MAPS>(GRAWA_CP_PASS);                                      \
         return hipGetLastError();
     switch (p->K) {
@@ -707,11 +755,23 @@ hipError_t grawa_launch_center_pull(const grawa_plan *p, float *x, int64_t ldx, 
                                     grawa_dtype_t dt, float lr, int fuse_sgd, float *center_out, float rho,
                                     int moving, float *weights_out, hipStream_t s, hipEvent_t e0, hipEvent_t e1)
 {
-    TileWeights tw = {};
-    if (!beta) {
-        int group = GRAWA_WAVE;
-        while (group * p->K > GRAWA_WAVE) group >>= 1;
-        tw = TileWeights{p->d_partials, p->n_tiles, p->d_layer_tile0, p->d_layer_tile1, weights_out, p->d_flags, group, p->tile_shift};
+    EstimateWeights tw = {};
+    const GrawaLocalWeights local = p->local;
+    p->local = GrawaLocalWeights{};
+    const int group = grawa_group_lanes(p->K);
+    if (local.in_pull && beta == p->d_beta_layer) {
+        beta = nullptr;
+        static_cast<TileWeights &>(tw) = TileWeights{p->d_sums, p->n_rtiles, p->d_layer_rtile0, p->d_layer_rtile0 + 1, local.weights_out,
+                                                     p->d_flags, group, 0};
+        tw.est = p->d_est;
+        tw.consumed = p->d_consumed;
+        tw.consumed_by_pulls = p->d_consumed + p->L;
+        tw.seen = p->d_seen;
+        tw.est_out = local.est_out;
+        tw.buffer = (int64_t)p->K * p->n_rtiles;
+        tw.gamma = local.gamma;
+    } else if (!beta) {
+        static_cast<TileWeights &>(tw) = TileWeights{p->d_partials, p->n_tiles, p->d_layer_tile0, p->d_layer_tile1, weights_out, p->d_flags, group, p->tile_shift};
     }
     // Streaming accesses pay off only when the arrays do not fit the last-level cache anyway: x, and g where the step is fused.
     // (By x alone, fused LGRAWA updates, three sets in turn, us, line-aligned rows / rows off the grid: 70 MB fp32 2 workers 57.3 ->

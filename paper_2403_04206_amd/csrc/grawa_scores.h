@@ -79,17 +79,28 @@ __device__ __forceinline__ void group_weights(const double *sA, int K, float *be
     }
 }
 
-// The same weights for one layer straight from its tile sums, by one full wave (K <= 64): `group` = the largest
+// The score of a worker and layer from its sum of squares: its norm.  load() comes before the sums are read, publish() where the weights
+// are written out.
+struct NormScore {
+    struct State {};
+    __device__ __forceinline__ State load(int, int) const { return State{}; }
+    __device__ __forceinline__ double score(const State &, double sum) const { return sqrt(sum); }
+    __device__ __forceinline__ void publish(int, int, double) const {}
+};
+
+// The same weights for one layer l straight from its tile sums, by one full wave (K <= 64): `group` = the largest
 // power of two not above 64 / K lanes share a worker's tiles t0 .. t1 - 1.  out[k] (LDS) receives beta_k;
 // beta_user[k * L] too if not null, and a score that is not finite is flagged then.
-__device__ __forceinline__ void wave_layer_weights(const double *__restrict__ partials, int64_t pitch, int t0, int t1,
-                                                   int K, int group, float *out, bool owner, float *beta_user, int L,
-                                                   unsigned *flags)
+template <typename Score>
+__device__ __forceinline__ void wave_layer_weights(const Score &scores, int l, const double *__restrict__ partials, int64_t pitch,
+                                                   int t0, int t1, int K, int group, float *out, bool owner,
+                                                   float *beta_user, int L, unsigned *flags)
 {
     const int lane = threadIdx.x & (GRAWA_WAVE - 1);
     const int k = lane / group, i = lane % group;
     const bool active = k < K, head = active && i == 0;
     const double *p = partials + (int64_t)(active ? k : 0) * pitch;
+    const typename Score::State state = scores.load(active ? k : 0, l);
     double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
     int t = t0 + i;
     for (; t + 3 * group < t1; t += 4 * group) {
@@ -101,7 +112,7 @@ __device__ __forceinline__ void wave_layer_weights(const double *__restrict__ pa
     for (; t < t1; t += group) s0 += p[t];
     double s = (s0 + s1) + (s2 + s3);
     for (int m = 1; m < group; m <<= 1) s += __shfl_xor(s, m, GRAWA_WAVE);
-    const double a = sqrt(s);
+    const double a = scores.score(state, s);
     const double a_min = wave_min(active ? a : (double)INFINITY);
     const double n_zero = wave_sum(head && a == 0.0 ? 1.0 : 0.0);
     const double z = wave_sum(head && n_zero == 0.0 ? a_min / a : 0.0);
@@ -110,13 +121,14 @@ __device__ __forceinline__ void wave_layer_weights(const double *__restrict__ pa
         out[k] = (float)b;
         if (owner && beta_user) beta_user[(int64_t)k * L] = (float)b;
         if (owner && flags && !isfinite(a)) atomicOr(flags, GRAWA_NONFINITE_LAYER_SCORE);
+        if (owner) scores.publish(k, l, a);
     }
 }
 
 // The same by one lane, for a layer of few tiles; the whole row of weights.
-template <int K>
-__device__ __forceinline__ void lane_layer_weights(const double *__restrict__ partials, int64_t pitch, int t0, int t1,
-                                                   float *out, float *beta_user, int L, unsigned *flags)
+template <int K, typename Score>
+__device__ __forceinline__ void lane_layer_weights(const Score &scores, int l, const double *__restrict__ partials, int64_t pitch,
+                                                   int t0, int t1, float *out, float *beta_user, int L, unsigned *flags)
 {
     double a[K];
 #pragma unroll
@@ -128,7 +140,8 @@ __device__ __forceinline__ void lane_layer_weights(const double *__restrict__ pa
     bool bad = false;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        a[k] = sqrt(a[k]);
+        a[k] = scores.score(scores.load(k, l), a[k]);
+        scores.publish(k, l, a[k]);
         a_min = fmin(a_min, a[k]);
         n_zero += a[k] == 0.0 ? 1.0 : 0.0;
         bad = bad || !isfinite(a[k]);

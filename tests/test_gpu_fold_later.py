@@ -14,14 +14,17 @@ DEV = "cuda:0"
 T = 1024
 CASES = [(4, [40000, 9000, 1, 3, 16, 16, 2304, 7, 5000]), (2, [4 * T, 4 * T + 1, 16 * T, 16 * T + 1, 63 * T + 5, 64 * T + 1]),
          (17, [300] * 40 + [8 * T + 1, 255, 256, 257, 511, 513, 1, 2, 1]), (3, [512 * T, 1]), (3, [512 * T + 1, 30000, 5]),
-         (2, [1_500_000]), (40, [30000, 17])]
+         (2, [1_500_000]), (40, [30000, 17]),
+         # the pull works the weights out: up to 512 tiles of a layer times workers; more layers in a cell than a wave has lanes
+         (15, [34 * T, 5, 100]), (15, [35 * T, 5, 100]), (4, [1] * 300 + [128 * T]), (1, [9 * T, 1, 1, 512 * T])]
 # s: a call on both; S: a call, and the replay of one recorded step; 2, 3: that many calls, and the replay of such a recording;
 # R: a round of two steps, recorded; c, C: a communication, and its replay; r: a reset
 ORDERS = ["sc", "ssc", "sSc", "sC", "SsC", "SSSC", "SSsc", "3C", "33C", "2C", "22C", "23C", "s3sc", "3S2C", "3R", "RsC", "RR", "2R2C",
-          "33sc", "s3C", "srSSsc", "srsC", "ssCSSCsSsc", "3s2s3sC"]
+          "33sc", "s3C", "srSSsc", "srsC", "ssCSSCsSsc", "3s2s3sC", "scssc",
+          "scsscSsc", "scscrsscsc"]
 
 
-@pytest.mark.parametrize("policy", ["lgrawa", "mgrawa"])
+@pytest.mark.parametrize("policy", ["lgrawa", "mgrawa", "both"])
 @pytest.mark.parametrize("case", range(len(CASES)))
 def test_calls_and_replays(case, policy):
     K, sizes = CASES[case]
@@ -30,7 +33,9 @@ def test_calls_and_replays(case, policy):
     P, L = w.P, w.L
     cen = torch.empty(W.round_up(P, 4), device=DEV).normal_(0.0, 0.05, generator=torch.Generator(device=DEV).manual_seed(case))
     est = [torch.zeros((K, L), device=DEV) for _ in range(2)]
-    wts = [torch.zeros((K, L) if policy == "lgrawa" else (K,), device=DEV) for _ in range(2)]
+    wts = [torch.zeros((K, L), device=DEV) for _ in range(2)]
+    models = [torch.zeros(K, device=DEV) for _ in range(2)]
+    rounds = [0, 0]
     xs = [x.clone(), x.clone()]
     plans = [grawa.Plan(K, P, w.offsets) for _ in range(2)]
 
@@ -38,8 +43,11 @@ def test_calls_and_replays(case, policy):
         plans[i].local_step_scored(xs[i][:, :P], g[:, :P], 0.05, 0.9, center=cen if prox else None, mu=0.05, tau=4.0)
 
     def communicate(i):
-        update = plans[i].local_lgrawa_update if policy == "lgrawa" else plans[i].local_mgrawa_update
-        update(xs[i][:, :P], 0.3, est_out=est[i], weights_out=wts[i])
+        rounds[i] += 1
+        if policy == "lgrawa" or (policy == "both" and rounds[i] % 2):
+            plans[i].local_lgrawa_update(xs[i][:, :P], 0.3, est_out=est[i], weights_out=wts[i])
+        else:
+            plans[i].local_mgrawa_update(xs[i][:, :P], 0.3, est_out=est[i], weights_out=models[i])
 
     def record(*calls):
         graph = torch.cuda.CUDAGraph()
@@ -51,10 +59,14 @@ def test_calls_and_replays(case, policy):
     stream = torch.cuda.Stream()
     with torch.cuda.stream(stream):
         step(1)
+        rounds[1] = 0
         graphs = {"C": record(communicate), "S": record(step), "R": record(step, step, communicate), "2": record(step, step),
                   "3": record(step, step, step)}
         torch.cuda.synchronize()
         for order in ORDERS:
+            if policy == "both" and set(order) & set("CR"):
+                continue                            # a replay has the policy that it was recorded with
+            rounds[:] = [0, 0]
             for i in range(2):
                 xs[i].copy_(x)
                 plans[i].local_scores_reset()
@@ -70,7 +82,7 @@ def test_calls_and_replays(case, policy):
                 else:
                     {"s": lambda: step(1), "c": lambda: communicate(1), "r": plans[1].local_scores_reset}[ch]()
             torch.cuda.synchronize()
-            assert torch.equal(xs[0], xs[1]) and torch.equal(est[0], est[1]) and torch.equal(wts[0], wts[1]), order
+            assert torch.equal(xs[0], xs[1]) and torch.equal(est[0], est[1]) and torch.equal(wts[0], wts[1]) and torch.equal(models[0], models[1]), order
         # and three steps called one by one are the oracle's
         for i in range(2):
             plans[i].local_scores_reset()
@@ -81,11 +93,12 @@ def test_calls_and_replays(case, policy):
         communicate(0)
         torch.cuda.synchronize()
         assert_table_close(est[0].cpu().numpy(), scores.g_est, TIGHT, "g_est")
-        # no step since: the plain average
+        # no step since: the plain average (the recorded communication is the first kind of "both")
         graphs["C"].replay()
         graphs["C"].replay()
         torch.cuda.synchronize()
-        assert float(est[1].abs().max()) == 0.0 and torch.all(wts[1] == np.float32(1.0 / K))
+        assert float(est[1].abs().max()) == 0.0
+        assert torch.all((models if policy == "mgrawa" else wts)[1] == np.float32(1.0 / K))
     del plans
 
 
