@@ -140,8 +140,10 @@ template <int K> struct CellWeights {
 // Fills `sh` for the cell at column cell0 whose first layer is l0; returns the number of layers.  Called by the whole
 // block (4 waves); ends with a barrier.  The first and the last layer of the cell may have tiles in other cells, any
 // number of them: a wave for each.  The layers between have all their columns in the cell, so one tile each (tiles are
-// cut at multiples of at least 4096): a lane for each, with the loads of its K workers in flight together.  So a cell
-// takes two rounds at most, for 3 layers as for 256 (a wave per layer in turn took 16 rounds, and lanes that walked
+// cut at multiples of at least 1024): a segment of lanes for each, a lane per worker, as long as that takes two rounds, else a
+// lane for each, with the loads of its K workers in flight together.  (A lane's K roots and quotients, one after the other, are the longest
+// chain of the launch.  Update, us, a lane for each / segments: ResNet-20, 59 layers, 8 workers 10.3 / 9.5, without maps and with the center
+// 11.5 / 10.7; 15 workers, 170 k columns, 60 layers 13.5 / 11.6; 4 workers, 200 k, 150 layers 8.1 / 7.9.)  So a cell takes two rounds at most, for 3 layers as for 256 (a wave per layer in turn took 16 rounds, and lanes that walked
 // all tiles of their layer more: 4 workers, 600 k columns, of which the first 60 or 100 are layers of their own, update on the
 // device 24.6 and 174 us; with the weights as a launch 17.3 and 21.8; now 11.4 and 11.7).
 template <int K, bool SLOTS, typename Score>
@@ -170,13 +172,24 @@ __device__ __forceinline__ int cell_weights(const TileWeights &w, const Score &s
         wave_layer_weights(scores, l, partials, w.pitch, t0, t1, K, w.group, sh.beta + i * K,
                            off[l] >= cell0, w.weights_out ? w.weights_out + l : nullptr, L, w.flags);
     } else if (wave >= 2) {
-        for (int i = 1 + (int)threadIdx.x - 2 * GRAWA_WAVE; i < nl - 1; i += GRAWA_CELL - 2 * GRAWA_WAVE) {
+        const auto at = [&](int i, bool segment, bool here) {
             const int l = l0 + i;
             int t0, t1;
             if constexpr (SLOTS) layer_slots(off, l, P, w.shift, t0, t1);
             else t0 = w.tile_begin[l], t1 = w.tile_end[l];
-            lane_layer_weights<K>(scores, l, partials, w.pitch, t0, t1, sh.beta + i * K,
-                                  w.weights_out ? w.weights_out + l : nullptr, L, w.flags);
+            float *out = sh.beta + i * K, *user = w.weights_out ? w.weights_out + l : nullptr;
+            if (segment) segment_layer_weights<K>(scores, l, here, partials, w.pitch, t0, t1, out, user, L, w.flags);
+            else lane_layer_weights<K>(scores, l, partials, w.pitch, t0, t1, out, user, L, w.flags);
+        };
+        constexpr int G = Segment<K>::G, ROUND = 2 * (GRAWA_WAVE / G); // layers that two waves take at a time
+        const int lane2 = (int)threadIdx.x - 2 * GRAWA_WAVE;
+        if (nl - 2 <= 2 * ROUND) {
+            for (int base = 1; base < nl - 1; base += ROUND) {
+                const int i = base + lane2 / G;
+                at(i < nl - 1 ? i : 1, true, i < nl - 1);
+            }
+        } else {
+            for (int i = 1 + lane2; i < nl - 1; i += GRAWA_CELL - 2 * GRAWA_WAVE) at(i, false, true);
         }
     }
     __syncthreads();

@@ -114,7 +114,7 @@ __device__ __forceinline__ void wave_layer_weights(const Score &scores, int l, c
     for (int m = 1; m < group; m <<= 1) s += __shfl_xor(s, m, GRAWA_WAVE);
     const double a = scores.score(state, s);
     const double a_min = wave_min(active ? a : (double)INFINITY);
-    const double n_zero = wave_sum(head && a == 0.0 ? 1.0 : 0.0);
+    const double n_zero = __popcll(__ballot(head && a == 0.0));
     const double z = wave_sum(head && n_zero == 0.0 ? a_min / a : 0.0);
     if (head) {
         const double b = n_zero > 0.0 ? (a == 0.0 ? 1.0 / n_zero : 0.0) : (a_min / a) / z;
@@ -125,7 +125,49 @@ __device__ __forceinline__ void wave_layer_weights(const Score &scores, int l, c
     }
 }
 
-// The same by one lane, for a layer of few tiles; the whole row of weights.
+// The same by a segment of G lanes, the smallest power of two not below K, one worker each; a wave takes 64 / G layers at a time, and all
+// its lanes take part (`here`: the segment has a layer).  For layers of few tiles; the whole row of weights.
+template <int K> struct Segment {
+    static constexpr int G = K <= 1 ? 1 : K <= 2 ? 2 : K <= 4 ? 4 : K <= 8 ? 8 : 16;
+};
+template <int G, typename Op> __device__ __forceinline__ double segment_reduce(double v, const Op &op)
+{
+    static_assert(G <= 16, "within a row of lanes");
+    if constexpr (G > 1) v = op(v, dpp_move_f64<0xB1>(v));  // lane ^ 1
+    if constexpr (G > 2) v = op(v, dpp_move_f64<0x4E>(v));  // lane ^ 2
+    if constexpr (G > 4) v = op(v, dpp_move_f64<0x141>(v)); // other quad of the half row
+    if constexpr (G > 8) v = op(v, dpp_move_f64<0x140>(v)); // other half of the row
+    return v;
+}
+template <int K, typename Score>
+__device__ __forceinline__ void segment_layer_weights(const Score &scores, int l, bool here, const double *__restrict__ partials,
+                                                      int64_t pitch, int t0, int t1, float *out, float *beta_user, int L,
+                                                      unsigned *flags)
+{
+    constexpr int G = Segment<K>::G;
+    const int lane = threadIdx.x & (GRAWA_WAVE - 1), k = lane % G;
+    const bool active = here && k < K;
+    double a = INFINITY;
+    if (active) {
+        const typename Score::State state = scores.load(k, l);
+        double s = 0.0;
+        for (int t = t0; t < t1; ++t) s += partials[(int64_t)k * pitch + t];
+        a = scores.score(state, s);
+    }
+    const double a_min = segment_reduce<G>(a, [](double p, double q) { return fmin(p, q); });
+    const unsigned long long zero = __ballot(active && a == 0.0) >> (lane - k) & (~0ull >> (GRAWA_WAVE - G));
+    const double n_zero = __popcll(zero);
+    const double z = segment_reduce<G>(active && n_zero == 0.0 ? a_min / a : 0.0, [](double p, double q) { return p + q; });
+    if (active) {
+        const float b = (float)(n_zero > 0.0 ? (a == 0.0 ? 1.0 / n_zero : 0.0) : (a_min / a) / z);
+        out[k] = b;
+        if (beta_user) beta_user[(int64_t)k * L] = b;
+        if (flags && !isfinite(a)) atomicOr(flags, GRAWA_NONFINITE_LAYER_SCORE);
+        scores.publish(k, l, a);
+    }
+}
+
+// The same by one lane, which walks the workers.
 template <int K, typename Score>
 __device__ __forceinline__ void lane_layer_weights(const Score &scores, int l, const double *__restrict__ partials, int64_t pitch,
                                                    int t0, int t1, float *out, float *beta_user, int L, unsigned *flags)
