@@ -42,6 +42,27 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
+// The same of N values side by side: the steps of one wait for nothing of the others.
+template <int N> __device__ __forceinline__ void wave_sums(double (&v)[N])
+{
+#pragma unroll
+    for (int j = 0; j < N; ++j) v[j] += dpp_move_f64<0xB1>(v[j]);
+#pragma unroll
+    for (int j = 0; j < N; ++j) v[j] += dpp_move_f64<0x4E>(v[j]);
+#pragma unroll
+    for (int j = 0; j < N; ++j) v[j] += dpp_move_f64<0x141>(v[j]);
+#pragma unroll
+    for (int j = 0; j < N; ++j) v[j] += dpp_move_f64<0x140>(v[j]);
+#pragma unroll
+    for (int m = 16; m < GRAWA_WAVE; m <<= 1) {
+        double w[N];
+#pragma unroll
+        for (int j = 0; j < N; ++j) w[j] = __shfl_xor(v[j], m, GRAWA_WAVE);
+#pragma unroll
+        for (int j = 0; j < N; ++j) v[j] += w[j];
+    }
+}
+
 __device__ __forceinline__ double wave_min(double v)
 {
     v = fmin(v, dpp_move_f64<0xB1>(v));

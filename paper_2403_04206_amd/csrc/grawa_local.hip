@@ -145,21 +145,37 @@ __global__ __launch_bounds__(GRAWA_CELL) __attribute__((amdgpu_waves_per_eu(1, P
                     lo = (int)(tile.start - (int64_t)m * GRAWA_ROW_BLOCK);
                     hi = lo + tile.len;
                 }
-                for (unsigned long long in = __ballot(lo < end && hi > begin); in; in &= in - 1) {
-                    const int i = __builtin_ctzll(in);
-                    const int a = __builtin_amdgcn_readlane(lo, i), b = __builtin_amdgcn_readlane(hi, i);
-                    double acc = 0.0;
+                constexpr int N = 2; // tiles whose sums go on together: a round of four steps 28.9 -> 28.0 us (ResNet-20, 4 workers); 4: 27.9, but with few layers 26.6 -> 27.4
+                for (unsigned long long in = __ballot(lo < end && hi > begin); in;) {
+                    double acc[N];
+                    int id[N], from[N], to[N];
 #pragma unroll
-                    for (int e = 0; e < V; ++e) acc = (at + e >= a && at + e < b) ? sq_add(gf[0][e], acc) : acc;
-                    const double tot = wave_sum(acc);
-                    if (a < begin) {
-                        head_at = t + i;
-                        if (lane == 0) sm[wave] = tot;
-                    } else if (b > end) {
-                        tail_at = t + i;
-                        if (lane == 0) tail[wave] = tot;
-                    } else if (lane == 0) {
-                        put(t + i, tot);
+                    for (int j = 0; j < N; ++j) {
+                        acc[j] = 0.0;
+                        id[j] = in ? __builtin_ctzll(in) : -1;
+                        in &= in - 1; // 0 stays 0
+                        from[j] = id[j] < 0 ? 0 : __builtin_amdgcn_readlane(lo, id[j]);
+                        to[j] = id[j] < 0 ? 0 : __builtin_amdgcn_readlane(hi, id[j]);
+                    }
+#pragma unroll
+                    for (int e = 0; e < V; ++e)
+#pragma unroll
+                        for (int j = 0; j < N; ++j)
+                            acc[j] = (at + e >= from[j] && at + e < to[j]) ? sq_add(gf[0][e], acc[j]) : acc[j];
+                    if (id[N - 1] < 0) acc[0] = wave_sum(acc[0]);
+                    else wave_sums<N>(acc);
+#pragma unroll
+                    for (int j = 0; j < N; ++j) {
+                        if (id[j] < 0) continue;
+                        if (from[j] < begin) {
+                            head_at = t + id[j];
+                            if (lane == 0) sm[wave] = acc[j];
+                        } else if (to[j] > end) {
+                            tail_at = t + id[j];
+                            if (lane == 0) tail[wave] = acc[j];
+                        } else if (lane == 0) {
+                            put(t + id[j], acc[j]);
+                        }
                     }
                 }
             }
@@ -168,23 +184,13 @@ __global__ __launch_bounds__(GRAWA_CELL) __attribute__((amdgpu_waves_per_eu(1, P
                 tail_tile[wave] = tail_at;
             }
             __syncthreads();
-            if (threadIdx.x == 0) {
-                int t = -1; // the tile that goes on
-                double tot = 0.0;
+            if (threadIdx.x < GRAWA_BLOCK / GRAWA_WAVE && tail_tile[threadIdx.x] >= 0) { // a tile that goes on begins in this wave
+                const int t = tail_tile[threadIdx.x];
+                double tot = tail[threadIdx.x];
 #pragma unroll
-                for (int w = 0; w < GRAWA_BLOCK / GRAWA_WAVE; ++w) {
-                    if (t >= 0 && head_tile[w] != t) {
-                        put(t, tot);
-                        t = -1;
-                    }
-                    if (head_tile[w] >= 0) tot += sm[w];
-                    if (tail_tile[w] >= 0) {
-                        if (t >= 0) put(t, tot);
-                        t = tail_tile[w];
-                        tot = tail[w];
-                    }
-                }
-                if (t >= 0) put(t, tot);
+                for (int w = 1; w < GRAWA_BLOCK / GRAWA_WAVE; ++w) // no tile begins before the block
+                    if (w > (int)threadIdx.x && head_tile[w] == t) tot += sm[w];
+                put(t, tot);
             }
         }
     }
