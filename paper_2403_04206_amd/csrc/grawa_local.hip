@@ -33,10 +33,10 @@
 // SCORE: only after its loads are issued does a block consult the 1024-column tile map (tiles
 // block_tile0[m] .. block_tile0[m+1]-1 lie in aligned block m, each inside one layer).  Nearly
 // every block holds one tile; in a block that contains layer boundaries every wave adds the tiles of its own columns (the block
-// reducing once per tile, with two barriers each: 4 workers, ResNet-20's 59 tensors 6.1 us, now 5.7).
+// reducing once per tile, with two barriers each: 4 workers, ResNet-20's 59 tensors 6.1 us, now 5.4; one tile a block would take 4.3).
 // The tile sums go to k_estimate, to k_fold or, GRAWA_SCORE_LATER, to the launch that needs them next (grawa_fold.h): a few blocks at
-// the head of the rows fold in those of the step before, 5 us of a launch that they hide (5.7 us in all on that model; a row
-// of blocks of their own, most of them empty, took large steps 3 us).  (Updating the estimate inside this launch, by the block that brings the last tile of a (worker, layer), was
+// the head of the rows fold in those of the step before, a launch of 5 us that this one hides (a row of blocks of
+// their own, most of them empty, took large steps 3 us).  (Updating the estimate inside this launch, by the block that brings the last tile of a (worker, layer), was
 // tried: its device-scope traffic costs more than the launch from about 1000 blocks or 30 tiles per layer on, 4 steps and
 // the communication on 8 workers 117 us instead of 45.)  The maps are parameters of their own, each __restrict__: as
 // members of a struct they may alias the stores, and a block with many tiles then reads them by vector loads that wait for

@@ -194,6 +194,7 @@ static constexpr int64_t grawa_row_step_merges_from(bool bf16, bool center, bool
 // without it 18 23 / 22, 27 23 / 25, 39 23 / 30 (32 / 34); 32 workers, with it, 18 29 / 28, 39 33 / 41.
 // Threads: 256 up to 7 tiles (23 / 22), beyond it 1024 as long as the blocks and elements are few enough (9 tiles 22 / 24 with 256, 23 / 20 with
 // 1024, 10 tiles 22 / 26 and 23 / 20); where they are too many, 256 up to 10 tiles (16 workers, 59 layers 47 / 39).
+// (In use up to GRAWA_LAYER_SHORT_TILES: beyond, the sums are left to the next launch, grawa_fold_later, and the figures above are what that replaced.)
 #define GRAWA_LAYER_MAX_TILES 40
 #define GRAWA_LAYER_MAX_ELEMS ((int64_t)7 << 18)
 #define GRAWA_LAYER_MAX_BLOCKS 640
@@ -212,8 +213,8 @@ static inline int grawa_step_by_layers(int K, int L, int64_t P, int64_t max_tile
 // Scored step: whether its tile sums are left to the launch that needs them next (grawa_fold.h) instead of a launch of their own.
 // It saves that launch and its boundary, about 5 us on the device and 3 on the host, for every step but the last of a round, and
 // against a block per layer (k_layer_step with 1024 threads, which it replaced) the time one CU takes for the longest layer.  A round of four
-// steps with the center and the communication, fp32, us, before / now (in brackets replayed as a graph): ResNet-20, 59 layers, 4 workers 42.7 / 32.4
-// (42.7 / 31.0), 8 workers 48.0 / 37.8 (48.1 / 37.9); 16 workers, 200 k columns, 150 layers 68.7 / 49.5 (69.1 / 50.2); 4 workers, 1 M, one layer 67.3 /
+// steps with the center and the communication, fp32, us, before / now (in brackets replayed as a graph): ResNet-20, 59 layers, 4 workers 42.7 / 28.1
+// (42.7 / 28.0), 8 workers 48.0 / 34.3 (48.1 / 34.5), both with the weights in the pull (below); 16 workers, 200 k columns, 150 layers 68.7 / 49.5 (69.1 / 50.2); 4 workers, 1 M, one layer 67.3 /
 // 59.7 (67.9 / 60.6), 60 layers 71.9 / 61.0; 64 workers, 300 k, 100 layers 198 / 188; 16 workers, 3 M 510 / 493; 2 workers, 20 M, one layer 428 / 409.
 // One step and the communication, 8 workers, 8 M columns 214.7 / 216.0.
 // The step by layers stays where no layer has more than 7 tiles: with many of them it is the shorter launch (4 workers, 200 k columns, 300
