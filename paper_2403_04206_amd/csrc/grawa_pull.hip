@@ -811,7 +811,12 @@ hipError_t grawa_launch_center_pull(const grawa_plan *p, float *x, int64_t ldx, 
      : nt   ? dispatch_cp<SGD, GT, true>(GRAWA_CP_PASS)                           \
      : off_grid ? dispatch_cp_off_grid<SGD, GT>(GRAWA_CP_PASS)                    \
             : dispatch_cp<SGD, GT, false>(GRAWA_CP_PASS))
-    if (!fuse_sgd) return GRAWA_CP_GO(false, float);
+    if (!fuse_sgd) {
+        const hipError_t e = GRAWA_CP_GO(false, float);
+        // The communication has used the estimate up, also if its pull could not be launched.
+        if (e != hipSuccess && tw.est) (void)grawa_launch_zero_estimate(p, s);
+        return e;
+    }
     return dt == GRAWA_BF16 ? GRAWA_CP_GO(true, uint16_t) : GRAWA_CP_GO(true, float);
 #undef GRAWA_CP_GO
 }
