@@ -451,10 +451,17 @@ grawa_status_t local_update(grawa_plan_t *p, float *x, int64_t ldx, int per_laye
     if (p->local_t < 1) return GRAWA_ERR_INVALID_ARG; /* no local step since the last communication */
     DeviceGuard guard(p->device);
     if (!guard.ok) return GRAWA_ERR_HIP;
-    GRAWA_TRY_HIP(grawa_launch_local_weights(p, p->local_gamma, per_layer, weights_out, est_out, s));
-    p->local_t = 0; // the weights have consumed the estimate: also if the launch below fails
     const bool prof = prof_active(p);
     hipEvent_t *ev = prof ? p->ev + 4 * (size_t)p->profile_n : nullptr;
+    if (per_layer && p->d_seen) { // one launch: if it fails, nothing has been used up
+        GRAWA_TRY_HIP(grawa_launch_local_pull(p, x, ldx, p->local_gamma, lambda, center_out, weights_out, est_out, s, prof ? ev[2] : nullptr,
+                                              prof ? ev[3] : nullptr));
+        p->local_t = 0;
+        if (prof) prof_commit(p, false);
+        return GRAWA_OK;
+    }
+    GRAWA_TRY_HIP(grawa_launch_local_weights(p, p->local_gamma, per_layer, weights_out, est_out, s));
+    p->local_t = 0; // the weights have consumed the estimate: also if the launch below fails
     GRAWA_TRY_HIP(grawa_launch_center_pull(p, x, ldx, per_layer ? p->d_beta_layer : p->d_beta_model, per_layer,
                                            lambda, nullptr, 0, GRAWA_F32, 0.f, 0, center_out, 0.f, 0, nullptr, s,
                                            prof ? ev[2] : nullptr, prof ? ev[3] : nullptr));

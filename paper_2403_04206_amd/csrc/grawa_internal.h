@@ -24,13 +24,6 @@ struct GrawaEstimate {
     unsigned buffer; // of d_sums that holds the sums of step n
 };
 
-// What grawa_launch_local_weights leaves to the pull that is launched next.
-struct GrawaLocalWeights {
-    bool in_pull;
-    double gamma;
-    float *weights_out, *est_out;
-};
-
 struct grawa_plan {
     int K;
     int L;
@@ -62,11 +55,10 @@ struct grawa_plan {
     int64_t *d_local_t;     // [L], all equal: local steps since the last communication (what the kernels use)
     int fold_later;         // the scored step leaves its sums to the next launch (grawa_fold_later); then, instead of d_mvg and d_local_t:
     double *d_sums;         // [GRAWA_SUM_BUFFERS][K][n_rtiles] tile sums of scored steps
-    mutable GrawaSteps steps;
+    GrawaSteps steps;
     GrawaEstimate *d_est;   // [K][L]
     unsigned *d_consumed;   // [2][L], each half all equal: the step that the last communication took into account, a launch of the weights and a pull
     unsigned *d_seen;       // [n_cells] the same, for each block of such a pull; null: no pull works the weights out
-    mutable GrawaLocalWeights local;
     unsigned *d_flags;      // device: GRAWA_NONFINITE_* bits, sticky until read-and-cleared (may be null)
     int64_t local_t;        // host mirror of the counter as of the last enqueued call (argument checks only)
     double local_gamma;     // momentum of the running estimate used so far (0 = none yet)
@@ -134,7 +126,7 @@ hipError_t grawa_launch_zero_estimate(const grawa_plan *p, hipStream_t s);
 hipError_t grawa_launch_clear_flags(const grawa_plan *p, hipStream_t s);
 hipError_t grawa_launch_row_step(float *x, int64_t ldx, const void *g, int64_t ldg, grawa_dtype_t dt, float lr,
                                  const float *center, float w, int K, int64_t P, hipStream_t s);
-hipError_t grawa_launch_row_step_scored(const grawa_plan *p, float *x, int64_t ldx, const void *g, int64_t ldg,
+hipError_t grawa_launch_row_step_scored(grawa_plan *p, float *x, int64_t ldx, const void *g, int64_t ldg,
                                         grawa_dtype_t dt, float lr, const float *center, float w, double gamma,
                                         hipStream_t s);
 // Whether the pull pass of a per-layer update takes its weights straight from the tile sums (grawa_pull.hip).
@@ -145,6 +137,9 @@ hipError_t grawa_launch_center_pull(const grawa_plan *p, float *x, int64_t ldx, 
                                     int64_t ldg_sgd, grawa_dtype_t dt, float lr, int fuse_sgd,
                                     float *center_out, float rho, int moving, float *weights_out, hipStream_t s,
                                     hipEvent_t e0, hipEvent_t e1);
+// The communication of a plan with d_seen, per-layer weights: one launch that forms them from the running estimate and pulls.
+hipError_t grawa_launch_local_pull(const grawa_plan *p, float *x, int64_t ldx, double gamma, float lambda, float *center_out,
+                                   float *weights_out, float *est_out, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
 hipError_t grawa_launch_nesterov(float *x, int64_t ldx, const void *g, int64_t ldg, grawa_dtype_t dt,
                                  float *buf, int64_t ldb, int K, int64_t P, float lr, float momentum,
                                  float wd, hipStream_t s);

@@ -385,7 +385,7 @@ __global__ __launch_bounds__(GRAWA_COPY_BLOCK) void k_stream_copy(v4u *__restric
 // The plain step only from 512 MB on: below, the pull that follows would lose the part of x a cached step leaves in the
 // cache (step and LSGD phase, bf16, 3 and 16 workers: 300 MB 210 / 222 and 216 / 229, 520 MB 364 / 376 and 388 / 402, 800 MB
 // 609 / 596 and 638 / 626).
-static hipError_t launch_row_step(const grawa_plan *p, float *x, int64_t ldx, const void *g, int64_t ldg,
+static hipError_t launch_row_step(grawa_plan *p, float *x, int64_t ldx, const void *g, int64_t ldg,
                                   grawa_dtype_t dt, float lr, const float *center, float w, int K, int64_t P,
                                   double gamma, hipStream_t s)
 {
@@ -479,7 +479,7 @@ hipError_t grawa_launch_row_step(float *x, int64_t ldx, const void *g, int64_t l
     return launch_row_step(nullptr, x, ldx, g, ldg, dt, lr, center, w, K, P, 0.0, s);
 }
 
-hipError_t grawa_launch_row_step_scored(const grawa_plan *p, float *x, int64_t ldx, const void *g, int64_t ldg,
+hipError_t grawa_launch_row_step_scored(grawa_plan *p, float *x, int64_t ldx, const void *g, int64_t ldg,
                                         grawa_dtype_t dt, float lr, const float *center, float w, double gamma,
                                         hipStream_t s)
 {

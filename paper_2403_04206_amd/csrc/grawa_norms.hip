@@ -600,11 +600,6 @@ bool grawa_is_recorded(hipStream_t s, unsigned long long *id)
 hipError_t grawa_launch_local_weights(const grawa_plan *p, double gamma, int per_layer, float *beta_user,
                                       float *est_user, hipStream_t s)
 {
-    p->local = GrawaLocalWeights{};
-    if (per_layer && p->d_seen) {
-        p->local = GrawaLocalWeights{true, gamma, beta_user, est_user};
-        return hipSuccess;
-    }
     if (p->fold_later) {
         unsigned long long id = 0;
         const bool recorded = grawa_is_recorded(s, &id);

@@ -597,14 +597,12 @@ constexpr int grawa_waves_for(int k, bool sgd, bool bf16)
 
 #define GRAWA_CP_ARGS                                                                                                 \
     const grawa_plan *p, float *x, int64_t ldx, const void *g, int64_t ldg, float lr, const float *beta, int per_layer, \
-        float lambda, float *center_out, float rho, int moving, [[maybe_unused]] const EstimateWeights &tw,                 \
+        float lambda, float *center_out, float rho, int moving, [[maybe_unused]] const TileWeights &tw,                     \
         [[maybe_unused]] bool capped, hipStream_t s,                                                                   \
         hipEvent_t e0, hipEvent_t e1
 #define GRAWA_CP_PASS p, x, ldx, g, ldg, lr, beta, per_layer, lambda, center_out, rho, moving, tw, capped, s, e0, e1
 #define GRAWA_CP_STRIDE per_layer ? (int64_t)p->L : (int64_t)1
 #define GRAWA_CP_CELLS per_layer ? (const int32_t *)p->d_cell_layer : (const int32_t *)nullptr
-
-template <int TILES> static const typename WeightsOf<TILES>::T &weights_arg(const EstimateWeights &w) { return w; }
 
 template <int K, bool SGD, typename GT, bool NT, int TILES> static void launch_plain(GRAWA_CP_ARGS)
 {
@@ -619,7 +617,7 @@ template <int K, bool SGD, typename GT, bool NT, int TILES> static void launch_p
     const size_t lds = WPE > CAP && capped ? ((size_t)160 << 10) / (CAP + 1) + 1024 : 0;
     hipExtLaunchKernelGGL((k_center_pull<K, SGD, GT, NT, WPE, TILES>), dim3((unsigned)p->n_cells), dim3(GRAWA_CELL), lds, s, e0,
                           e1, 0, x, ldx, (const GT *)g, ldg, lr, beta, GRAWA_CP_STRIDE, GRAWA_CP_CELLS,
-                          (const int64_t *)p->d_off, p->L, p->P, lambda, center_out, rho, moving, weights_arg<TILES>(tw));
+                          (const int64_t *)p->d_off, p->L, p->P, lambda, center_out, rho, moving, tw);
 }
 
 // The wide form's cap (best of 2, 3, 4 and 8 waves; one too many costs 3 to 5 %, and more than it gains over the plain form).
@@ -742,16 +740,11 @@ template <bool SGD, typename GT> static hipError_t dispatch_cp_tiles(GRAWA_CP_AR
 {
 #define GRAWA_CP_TILES(N)                                                                                      \
     case N:                                                                                                    \
-        if constexpr (!SGD) { /* neither the call without maps nor the communication has a fused step */       \
-            if (tw.est) {                                                                                      \
-                launch_plain<N, SGD, GT, false, GRAWA_TILES_ESTIMATE>(GRAWA_CP_PASS);                          \
-                return hipGetLastError();                                                                      \
-            }                                                                                                  \
+        if constexpr (!SGD) /* the call without maps has no fused step */                                      \
             if (p->tile_shift) {                                                                               \
                 launch_plain<N, SGD, GT, false, GRAWA_TILES_SLOTS>(GRAWA_CP_PASS);                             \
                 return hipGetLastError();                                                                      \
             }                                                                                                  \
-        }                                                                                                      \
         launch_plain<N, SGD, GT, false, GRAWA_TILES_MAPS>(GRAWA_CP_PASS);                                      \
         return hipGetLastError();
     switch (p->K) {
@@ -761,6 +754,34 @@ template <bool SGD, typename GT> static hipError_t dispatch_cp_tiles(GRAWA_CP_AR
 #undef GRAWA_CP_TILES
 }
 
+// Weights from the running estimate (EstimateWeights): arrays of at most 10 MB, so cached accesses without a cap.
+hipError_t grawa_launch_local_pull(const grawa_plan *p, float *x, int64_t ldx, double gamma, float lambda, float *center_out,
+                                   float *weights_out, float *est_out, hipStream_t s, hipEvent_t e0, hipEvent_t e1)
+{
+    EstimateWeights w = {};
+    static_cast<TileWeights &>(w) = TileWeights{p->d_sums, p->n_rtiles, p->d_layer_rtile0, p->d_layer_rtile0 + 1, weights_out, p->d_flags,
+                                                grawa_group_lanes(p->K), 0};
+    w.est = p->d_est;
+    w.consumed = p->d_consumed;
+    w.consumed_by_pulls = p->d_consumed + p->L;
+    w.seen = p->d_seen;
+    w.est_out = est_out;
+    w.buffer = (int64_t)p->K * p->n_rtiles;
+    w.gamma = gamma;
+#define GRAWA_LOCAL_PULL(N)                                                                                                  \
+    case N:                                                                                                                  \
+        hipExtLaunchKernelGGL((k_center_pull<N, false, float, false, 8, GRAWA_TILES_ESTIMATE>), dim3((unsigned)p->n_cells),  \
+                              dim3(GRAWA_CELL), 0, s, e0, e1, 0, x, ldx, (const float *)nullptr, (int64_t)0, 0.f,            \
+                              (const float *)nullptr, (int64_t)p->L, (const int32_t *)p->d_cell_layer,                       \
+                              (const int64_t *)p->d_off, p->L, p->P, lambda, center_out, 0.f, 0, w);                         \
+        return hipGetLastError();
+    switch (p->K) {
+        GRAWA_TILES_COUNTS(GRAWA_LOCAL_PULL)
+    }
+    return hipErrorInvalidValue;
+#undef GRAWA_LOCAL_PULL
+}
+
 bool grawa_pull_from_tiles(const grawa_plan *p) { return grawa_weights_in_pull(p->K, p->n_cells); }
 
 hipError_t grawa_launch_center_pull(const grawa_plan *p, float *x, int64_t ldx, const float *beta,
@@ -768,24 +789,9 @@ hipError_t grawa_launch_center_pull(const grawa_plan *p, float *x, int64_t ldx, 
                                     grawa_dtype_t dt, float lr, int fuse_sgd, float *center_out, float rho,
                                     int moving, float *weights_out, hipStream_t s, hipEvent_t e0, hipEvent_t e1)
 {
-    EstimateWeights tw = {};
-    const GrawaLocalWeights local = p->local;
-    p->local = GrawaLocalWeights{};
-    const int group = grawa_group_lanes(p->K);
-    if (local.in_pull && beta == p->d_beta_layer) {
-        beta = nullptr;
-        static_cast<TileWeights &>(tw) = TileWeights{p->d_sums, p->n_rtiles, p->d_layer_rtile0, p->d_layer_rtile0 + 1, local.weights_out,
-                                                     p->d_flags, group, 0};
-        tw.est = p->d_est;
-        tw.consumed = p->d_consumed;
-        tw.consumed_by_pulls = p->d_consumed + p->L;
-        tw.seen = p->d_seen;
-        tw.est_out = local.est_out;
-        tw.buffer = (int64_t)p->K * p->n_rtiles;
-        tw.gamma = local.gamma;
-    } else if (!beta) {
-        static_cast<TileWeights &>(tw) = TileWeights{p->d_partials, p->n_tiles, p->d_layer_tile0, p->d_layer_tile1, weights_out, p->d_flags, group, p->tile_shift};
-    }
+    TileWeights tw = {};
+    if (!beta)
+        tw = TileWeights{p->d_partials, p->n_tiles, p->d_layer_tile0, p->d_layer_tile1, weights_out, p->d_flags, grawa_group_lanes(p->K), p->tile_shift};
     // Streaming accesses pay off only when the arrays do not fit the last-level cache anyway: x, and g where the step is fused.
     // (By x alone, fused LGRAWA updates, three sets in turn, us, line-aligned rows / rows off the grid: 70 MB fp32 2 workers 57.3 ->
     // 53.8 / 58.4 -> 52.4, 6 55.2 -> 51.8 / 57.3 -> 56.7, 48 64.4 -> 60.9 / 67.1 -> 60.8; 95 MB bf16 2 68.4 -> 56.6 / 70.2 -> 57.4, 12
@@ -811,12 +817,7 @@ hipError_t grawa_launch_center_pull(const grawa_plan *p, float *x, int64_t ldx, 
      : nt   ? dispatch_cp<SGD, GT, true>(GRAWA_CP_PASS)                           \
      : off_grid ? dispatch_cp_off_grid<SGD, GT>(GRAWA_CP_PASS)                    \
             : dispatch_cp<SGD, GT, false>(GRAWA_CP_PASS))
-    if (!fuse_sgd) {
-        const hipError_t e = GRAWA_CP_GO(false, float);
-        // The communication has used the estimate up, also if its pull could not be launched.
-        if (e != hipSuccess && tw.est) (void)grawa_launch_zero_estimate(p, s);
-        return e;
-    }
+    if (!fuse_sgd) return GRAWA_CP_GO(false, float);
     return dt == GRAWA_BF16 ? GRAWA_CP_GO(true, uint16_t) : GRAWA_CP_GO(true, float);
 #undef GRAWA_CP_GO
 }

@@ -6,7 +6,7 @@
 
 #include "grawa_internal.h"
 
-static int fail_weights, fail_pull, n_pulls;
+static int fail_weights, fail_pull, n_pulls, n_one_launch, n_resets;
 
 extern "C" {
 hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
@@ -29,10 +29,20 @@ hipError_t grawa_launch_local_weights(const grawa_plan *, double, int, float *, 
 {
     return fail_weights ? hipErrorLaunchFailure : hipSuccess;
 }
-hipError_t grawa_launch_zero_estimate(const grawa_plan *, hipStream_t) { return hipSuccess; }
+hipError_t grawa_launch_local_pull(const grawa_plan *, float *, int64_t, double, float, float *, float *, float *, hipStream_t, hipEvent_t, hipEvent_t)
+{
+    if (fail_pull) return hipErrorInvalidConfiguration;
+    ++n_one_launch;
+    return hipSuccess;
+}
+hipError_t grawa_launch_zero_estimate(const grawa_plan *, hipStream_t)
+{
+    ++n_resets;
+    return hipSuccess;
+}
 hipError_t grawa_launch_clear_flags(const grawa_plan *, hipStream_t) { return hipSuccess; }
 hipError_t grawa_launch_row_step(float *, int64_t, const void *, int64_t, grawa_dtype_t, float, const float *, float, int, int64_t, hipStream_t) { return hipSuccess; }
-hipError_t grawa_launch_row_step_scored(const grawa_plan *, float *, int64_t, const void *, int64_t, grawa_dtype_t, float, const float *, float, double, hipStream_t) { return hipSuccess; }
+hipError_t grawa_launch_row_step_scored(grawa_plan *, float *, int64_t, const void *, int64_t, grawa_dtype_t, float, const float *, float, double, hipStream_t) { return hipSuccess; }
 hipError_t grawa_launch_center_pull(const grawa_plan *, float *, int64_t, const float *, int, float, const void *, int64_t, grawa_dtype_t, float, int, float *, float, int, float *, hipStream_t, hipEvent_t, hipEvent_t)
 {
     if (fail_pull) return hipErrorInvalidConfiguration;
@@ -82,6 +92,21 @@ int main()
         EXPECT(update() == GRAWA_ERR_INVALID_ARG && n_pulls == 0);
         EXPECT(step() == GRAWA_OK && update() == GRAWA_OK && n_pulls == 1);
     }
+    EXPECT(grawa_plan_destroy(p) == GRAWA_OK);
+
+    // Weights and pull in one launch (a small model with a layer of more than 7 tiles): where it fails nothing is used up, so the
+    // call may be repeated, and nothing else is launched.
+    alignas(16) static float y[3 * 9000];
+    const int64_t long_off[3] = {0, 8900, 9000};
+    EXPECT(grawa_plan_create(&p, 3, 9000, 2, long_off) == GRAWA_OK && p);
+    const auto update = [&] { return grawa_local_lgrawa_update(p, y, 9000, 0.5f, nullptr, nullptr, nullptr, nullptr); };
+    EXPECT(update() == GRAWA_ERR_INVALID_ARG);
+    EXPECT(grawa_local_step_scored(p, y, 9000, y, 9000, GRAWA_F32, 0.1f, nullptr, 0.f, 1.f, 0.9f, nullptr) == GRAWA_OK);
+    n_pulls = n_one_launch = n_resets = 0;
+    for (fail_pull = 2; fail_pull > 0; --fail_pull) EXPECT(update() == GRAWA_ERR_HIP);
+    EXPECT(n_one_launch == 0 && n_resets == 0);
+    EXPECT(update() == GRAWA_OK && n_one_launch == 1 && n_pulls == 0);
+    EXPECT(update() == GRAWA_ERR_INVALID_ARG);
     EXPECT(grawa_plan_destroy(p) == GRAWA_OK);
     std::puts("ok");
     return 0;
