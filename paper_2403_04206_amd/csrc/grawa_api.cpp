@@ -168,8 +168,8 @@ static grawa_status_t plan_create_impl(grawa_plan_t **out, int K, int64_t P, int
     const bool later = grawa_fold_later(K, L, P, max_rtiles);
     const size_t b_sums = later ? round256(sizeof(double) * GRAWA_SUM_BUFFERS * (size_t)K * (size_t)nrt) : 0;
     const size_t b_est = later ? round256(sizeof(GrawaEstimate) * (size_t)K * (size_t)L) : 0;
-    const size_t b_used = later ? round256(sizeof(unsigned) * 2 * (size_t)L) : 0;
-    const size_t b_seen = later && grawa_estimate_in_pull(K, nc, max_rtiles) ? round256(sizeof(unsigned) * (size_t)nc) : 0;
+    const size_t b_used = later ? round256(sizeof(uint64_t) * 2 * (size_t)L) : 0;
+    const size_t b_seen = later && grawa_estimate_in_pull(K, nc, max_rtiles) ? round256(sizeof(uint64_t) * (size_t)nc) : 0;
     const size_t b_words = 256; // flag word, arrival counter
     const size_t b_zeroed = b_part + b_S + b_bl + b_bm + b_mvg + b_t + b_sums + b_est + b_used + b_seen + b_words;
     const size_t b_host = b_off + b_cells + b_tiles + b_lt0 + b_rtiles + b_lt0 + b_brt0 + b_bm;
@@ -217,8 +217,8 @@ static grawa_status_t plan_create_impl(grawa_plan_t **out, int K, int64_t P, int
     p->d_local_t = reinterpret_cast<int64_t *>(w); w += b_t;
     p->d_sums = reinterpret_cast<double *>(w); w += b_sums;
     p->d_est = reinterpret_cast<GrawaEstimate *>(w); w += b_est;
-    p->d_consumed = reinterpret_cast<unsigned *>(w); w += b_used;
-    p->d_seen = b_seen ? reinterpret_cast<unsigned *>(w) : nullptr; w += b_seen;
+    p->d_consumed = reinterpret_cast<uint64_t *>(w); w += b_used;
+    p->d_seen = b_seen ? reinterpret_cast<uint64_t *>(w) : nullptr; w += b_seen;
     p->d_flags = reinterpret_cast<unsigned *>(w);
     p->d_cnt_all = reinterpret_cast<unsigned *>(w + 128);
 

@@ -12,7 +12,7 @@
 
 struct GrawaFold {
     GrawaEstimate *est;
-    const unsigned *consumed; // [2 L]
+    const uint64_t *consumed; // [2 L]
     const int32_t *layer_tile0; // [L+1]
     unsigned *flags;
     int64_t pitch; // sums in one of the buffers
@@ -85,19 +85,6 @@ __device__ __forceinline__ double block_tile_sum(const double *__restrict__ p, i
     return tot;
 }
 
-// The step that the last communication took into account: the later one of what launches of the weights and pulls noted.  n: steps so far.
-__device__ __forceinline__ unsigned last_used(unsigned n, unsigned a, unsigned b) { return n - a < n - b ? a : b; }
-
-__device__ __forceinline__ bool estimate_pending(const GrawaEstimate &e, unsigned consumed) { return e.n != consumed && e.n != e.folded; }
-
-// g_mvg up to step e.n; `sum`: the squares of that step, if they are pending.
-__device__ __forceinline__ double estimate_value(const GrawaEstimate &e, unsigned consumed, double sum)
-{
-    if (e.n == consumed) return 0.0;
-    const double before = e.folded == consumed ? 0.0 : e.mvg;
-    return estimate_pending(e, consumed) ? e.gamma * before + (1.0 - e.gamma) * sqrt(sum) : e.mvg;
-}
-
 // Brings the estimates of all workers and layers up to the last step: block `first` of `blocks`, of THREADS threads; a wave takes
 // a worker and layer, or, where layers are long, the block.
 //   FOLD_STEP   and this launch takes the next step, whose sums stay pending
@@ -116,7 +103,7 @@ __device__ __forceinline__ void fold_all(const GrawaFold &f, const double *__res
     for (unsigned u = f.by_wave ? first * WAVES + wave : first; u < units; u += step) {
         const unsigned k = u / (unsigned)f.L, l = u - k * (unsigned)f.L;
         GrawaEstimate e = f.est[u];
-        const unsigned consumed = last_used(e.n, f.consumed[l], f.consumed[f.L + l]);
+        const uint64_t used = grawa_last_used(f.consumed[l], f.consumed[f.L + l]);
         const int t0 = f.layer_tile0[l], t1 = f.layer_tile0[l + 1];
         const double *p = sums + (int64_t)k * n_tiles;
         if (!f.by_wave) __syncthreads(); // every wave has read what thread 0 writes below
@@ -126,18 +113,19 @@ __device__ __forceinline__ void fold_all(const GrawaFold &f, const double *__res
                              : block_tile_sum<THREADS>(p + buffer * f.pitch, t0, t1, part);
         };
         if (MODE == GRAWA_FOLD_SUMS) next = sum(f.buffer);
-        if (estimate_pending(e, consumed)) tot = sum(e.buffer); // the same for all units
+        if (grawa_estimate_pending(e, used)) tot = sum(e.buffer); // the same for all units
         if (f.by_wave ? lane == 0 : threadIdx.x == 0) {
-            e.mvg = estimate_value(e, consumed, tot);
-            e.folded = e.n;
+            e.mvg = grawa_estimate_value(e, used, sqrt(tot));
+            e.left = 0;
             if (MODE != GRAWA_FOLD_ONLY) {
                 e.gamma = f.gamma;
                 e.buffer = f.buffer;
                 e.n += 1;
+                e.left = 1;
             }
             if (MODE == GRAWA_FOLD_SUMS) {
-                e.mvg = estimate_value(e, consumed, next);
-                e.folded = e.n;
+                e.mvg = grawa_estimate_value(e, used, sqrt(next));
+                e.left = 0;
             }
             f.est[u] = e;
         }

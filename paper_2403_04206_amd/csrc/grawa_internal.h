@@ -14,16 +14,6 @@
 
 #define GRAWA_PROFILE_SLOTS 4096
 
-// Running estimate of one worker and layer where the sums of a scored step are folded in by the launch that needs them next
-// (grawa_fold.h).  Counts of steps; they wrap.
-struct GrawaEstimate {
-    double mvg;      // moving average up to step `folded`
-    double gamma;    // of step n
-    unsigned n;      // scored steps so far
-    unsigned folded; // n or n - 1
-    unsigned buffer; // of d_sums that holds the sums of step n
-};
-
 struct grawa_plan {
     int K;
     int L;
@@ -57,8 +47,8 @@ struct grawa_plan {
     double *d_sums;         // [GRAWA_SUM_BUFFERS][K][n_rtiles] tile sums of scored steps
     GrawaSteps steps;
     GrawaEstimate *d_est;   // [K][L]
-    unsigned *d_consumed;   // [2][L], each half all equal: the step that the last communication took into account, a launch of the weights and a pull
-    unsigned *d_seen;       // [n_cells] the same, for each block of such a pull; null: no pull works the weights out
+    uint64_t *d_consumed;   // [2][L], each half all equal: the step that the last communication took into account, a launch of the weights and a pull
+    uint64_t *d_seen;       // [n_cells] the same, for each block of such a pull; null: no pull works the weights out
     unsigned *d_flags;      // device: GRAWA_NONFINITE_* bits, sticky until read-and-cleared (may be null)
     int64_t local_t;        // host mirror of the counter as of the last enqueued call (argument checks only)
     double local_gamma;     // momentum of the running estimate used so far (0 = none yet)

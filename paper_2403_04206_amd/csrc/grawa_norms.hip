@@ -370,7 +370,7 @@ __global__ __launch_bounds__(GRAWA_LW_BLOCK_MODEL) void k_local_weights(double *
 // by a thread per worker, a wave per worker in turn, or the block for one worker after the other, as the layers are longer.  Model level:
 // grid 1.  Where layers are long, and for the model level, k_fold goes before; what is still pending then was replayed after calls made one by one.
 __global__ __launch_bounds__(GRAWA_FIN_BLOCK) void k_fold_weights(const GrawaFold f, const double *__restrict__ sums, int64_t n_tiles,
-                                                                   int per_layer, unsigned *__restrict__ consumed,
+                                                                   int per_layer, uint64_t *__restrict__ consumed,
                                                                    float *__restrict__ beta, float *__restrict__ beta_user,
                                                                    float *__restrict__ est_user)
 {
@@ -381,8 +381,8 @@ __global__ __launch_bounds__(GRAWA_FIN_BLOCK) void k_fold_weights(const GrawaFol
     const int l0 = per_layer ? (int)blockIdx.x : 0;
     const int K = f.K, L = f.L;
     const GrawaEstimate e0 = f.est[l0]; // counts and buffer: the same for all workers and layers
-    const unsigned n = e0.n, used = last_used(n, consumed[l0], consumed[L + l0]);
-    const bool pending = estimate_pending(e0, used);
+    const uint64_t n = e0.n, used = grawa_last_used(consumed[l0], consumed[L + l0]);
+    const bool pending = grawa_estimate_pending(e0, used);
     if (per_layer) {
         const int t0 = f.layer_tile0[l0], t1 = f.layer_tile0[l0 + 1], tiles = t1 - t0;
         const double *p = sums + e0.buffer * f.pitch;
@@ -405,7 +405,7 @@ __global__ __launch_bounds__(GRAWA_FIN_BLOCK) void k_fold_weights(const GrawaFol
             if (pending) s = tiles <= 4    ? few_tiles_sum<4>(p + (int64_t)k * n_tiles, t0, t1)
                              : tiles <= 16 ? few_tiles_sum<16>(p + (int64_t)k * n_tiles, t0, t1)
                                            : sA[k];
-            const double v = scale * estimate_value(f.est[(int64_t)k * L + l0], used, s);
+            const double v = scale * grawa_estimate_value(f.est[(int64_t)k * L + l0], used, sqrt(s));
             sA[k] = v;
             if (est_user) est_user[(int64_t)k * L + l0] = (float)v;
         }
@@ -422,7 +422,7 @@ __global__ __launch_bounds__(GRAWA_FIN_BLOCK) void k_fold_weights(const GrawaFol
         for (int k = wave; k < K; k += waves) {
             double s = 0.0;
             for (int l = lane; l < L; l += GRAWA_WAVE) {
-                const double v = scale * estimate_value(f.est[(int64_t)k * L + l], used, 0.0);
+                const double v = scale * grawa_estimate_value(f.est[(int64_t)k * L + l], used, 0.0);
                 s += v;
                 if (est_user) est_user[(int64_t)k * L + l] = (float)v;
             }
@@ -443,7 +443,7 @@ __global__ __launch_bounds__(THREADS) void k_fold(const GrawaFold f, const doubl
 }
 
 // An explicit reset: everything so far is used up.
-__global__ __launch_bounds__(GRAWA_BLOCK) void k_fold_reset(const GrawaEstimate *__restrict__ est, int L, unsigned *__restrict__ consumed)
+__global__ __launch_bounds__(GRAWA_BLOCK) void k_fold_reset(const GrawaEstimate *__restrict__ est, int L, uint64_t *__restrict__ consumed)
 {
     const int l = blockIdx.x * GRAWA_BLOCK + threadIdx.x;
     if (l < L) consumed[l] = est[l].n;

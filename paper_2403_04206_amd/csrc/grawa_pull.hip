@@ -110,9 +110,9 @@ struct TileWeights {
 // the launch reads; the cell that a layer starts in tells the other launches.
 struct EstimateWeights : TileWeights { // partials: the buffers of sums
     const GrawaEstimate *est;
-    const unsigned *consumed;    // [2 L]
-    unsigned *consumed_by_pulls; // [L], the second half
-    unsigned *seen;              // [cells]
+    const uint64_t *consumed;    // [2 L]
+    uint64_t *consumed_by_pulls; // [L], the second half
+    uint64_t *seen;              // [cells]
     float *est_out;              // [K][L] or null
     int64_t buffer;              // sums in one
     double gamma;
@@ -121,10 +121,10 @@ struct EstimateScore {
     typedef GrawaEstimate State;
     const EstimateWeights &w;
     int L;
-    unsigned n, used;
+    uint64_t n, used;
     double scale;
     __device__ __forceinline__ State load(int k, int l) const { return w.est[(int64_t)k * L + l]; }
-    __device__ __forceinline__ double score(const State &e, double sum) const { return scale * estimate_value(e, used, sum); }
+    __device__ __forceinline__ double score(const State &e, double sum) const { return scale * grawa_estimate_value(e, used, sqrt(sum)); }
     __device__ __forceinline__ void publish(int k, int l, double a) const
     {
         if (k == 0) w.consumed_by_pulls[l] = n;
@@ -266,7 +266,7 @@ __global__ __launch_bounds__(GRAWA_CELL) __attribute__((amdgpu_waves_per_eu(1, W
         int nl;
         if constexpr (TILES == GRAWA_TILES_ESTIMATE) {
             const GrawaEstimate e = tw.est[l0]; // counts and buffer: the same for all workers and layers
-            const unsigned used = last_used(e.n, tw.consumed[l0], tw.seen[blockIdx.x]);
+            const uint64_t used = grawa_last_used(tw.consumed[l0], tw.seen[blockIdx.x]);
             const double scale = e.n != used ? tw.gamma / grawa_one_minus_power(tw.gamma, (int64_t)(e.n - used)) : 0.0;
             nl = cell_weights<K, false>(tw, EstimateScore{tw, L, e.n, used, scale}, tw.partials + e.buffer * tw.buffer, off, L, P, cell0, l0,
                                         info < 0, cw);

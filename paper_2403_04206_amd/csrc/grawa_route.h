@@ -278,6 +278,25 @@ static inline bool grawa_all_folded(const GrawaSteps &s, bool recorded, unsigned
     return recorded && s.recording == id && s.folded;
 }
 
+// Running estimate of one worker and layer there.
+struct GrawaEstimate {
+    double mvg;      // moving average up to step n, with `left` up to the step before
+    double gamma;    // of step n
+    uint64_t n;      // scored steps since the plan was made: 64 bits, since the counts of communications below stay behind for good where a program uses only one kind
+    uint32_t buffer; // of d_sums that holds the sums of step n
+    uint32_t left;   // 1: they are not folded in yet
+};
+// The step that the last communication took into account: the later one of what launches of the weights and what pulls noted.
+static constexpr uint64_t grawa_last_used(uint64_t by_weights, uint64_t by_pull) { return by_weights > by_pull ? by_weights : by_pull; }
+static constexpr bool grawa_estimate_pending(const GrawaEstimate &e, uint64_t used) { return e.left && e.n != used; }
+// Moving average up to step e.n, which is 0 after a communication; `norm`: of that step, if it is pending.
+static constexpr double grawa_estimate_value(const GrawaEstimate &e, uint64_t used, double norm)
+{
+    if (e.n == used) return 0.0;
+    if (!grawa_estimate_pending(e, used)) return e.mvg;
+    return e.gamma * (e.n - 1 == used ? 0.0 : e.mvg) + (1.0 - e.gamma) * norm;
+}
+
 // 1 - gamma^t for 0 < gamma < 1, by squaring, since pow() is a chain of a microsecond in k_local_weights.  Every product keeps what its
 // rounding drops, so that the error stays at the last place however near to 1 gamma is (plain squaring loses t units of it, pow() one, and the
 // difference divides both by 1 - gamma^t).  Used on the device too (constexpr).

@@ -1,5 +1,6 @@
 """Which buffer of tile sums a scored step takes (paper_2403_04206_amd/csrc/grawa_route.h): never the one that holds sums which
-are not folded in yet, whatever is called, recorded and replayed after what.  A small program plays random sequences."""
+are not folded in yet, whatever is called, recorded and replayed after what (a small program plays random sequences); and the estimate where
+the counts of steps pass 32 bits."""
 import os
 import shutil
 import subprocess
@@ -66,6 +67,51 @@ def test_a_step_never_finds_its_own_buffer_pending(tmp_path):
     src, out = str(tmp_path / "steps.cpp"), str(tmp_path / "steps")
     with open(src, "w") as f:
         f.write(PROGRAM)
+    res = subprocess.run(["g++", "-std=c++17", "-Wall", "-Wextra", "-Werror", "-I", os.path.join(ROOT, "paper_2403_04206_amd", "csrc"),
+                          src, "-o", out], capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr
+    res = subprocess.run([out], capture_output=True, text=True)
+    assert res.returncode == 0 and res.stdout.strip() == "1", res.stdout
+
+
+COUNTS = r"""
+#include <cmath>
+#include <cstdio>
+#include "grawa_route.h"
+// A round of two steps before and after each of the four communications around step 2^32, noted by launches of the weights alone (what pulls
+// noted stays 0) or by pulls alone: the estimate is that of the steps since the last communication.
+int main()
+{
+    for (int by_pull = 0; by_pull < 2; ++by_pull)
+        for (uint64_t first = 4294967288ull; first < 4294967298ull; ++first) {
+            uint64_t noted = first;
+            GrawaEstimate e = {7.0, 0.5, first, 0, 0}; // 7: left from the round before, which is used up
+            for (int round = 0; round < 6; ++round) {
+                for (int step = 1; step <= 2; ++step) {
+                    const uint64_t used = by_pull ? grawa_last_used(0, noted) : grawa_last_used(noted, 0);
+                    e.mvg = grawa_estimate_value(e, used, 1.0); // folded in by the next step: norm 1
+                    e.n += 1;
+                    e.left = 1;
+                }
+                const uint64_t used = by_pull ? grawa_last_used(0, noted) : grawa_last_used(noted, 0);
+                const double v = grawa_estimate_value(e, used, 1.0);
+                if (e.n - used != 2 || std::fabs(v - 0.75) > 1e-15) {
+                    std::printf("step %llu, used %llu: %g\n", (unsigned long long)e.n, (unsigned long long)used, v);
+                    return 1;
+                }
+                noted = e.n;
+            }
+        }
+    std::puts("1");
+    return 0;
+}
+"""
+
+
+def test_estimate_where_the_counts_pass_32_bits(tmp_path):
+    src, out = str(tmp_path / "counts.cpp"), str(tmp_path / "counts")
+    with open(src, "w") as f:
+        f.write(COUNTS)
     res = subprocess.run(["g++", "-std=c++17", "-Wall", "-Wextra", "-Werror", "-I", os.path.join(ROOT, "paper_2403_04206_amd", "csrc"),
                           src, "-o", out], capture_output=True, text=True)
     assert res.returncode == 0, res.stderr
