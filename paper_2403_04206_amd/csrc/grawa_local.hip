@@ -417,13 +417,14 @@ static hipError_t launch_row_step(grawa_plan *p, float *x, int64_t ldx, const vo
     bool at_once = false;
     const unsigned buffer = later ? grawa_step_buffer(p->steps, recorded, id, &at_once) : 0;
     unsigned fold_blocks = 0;
+    const bool single = later && grawa_fold_single(K, p->L, p->max_rtiles, GRAWA_FOLD_SINGLE_STEP);
     if (later && !at_once) {
-        const int64_t units = (int64_t)K * p->L, blocks = p->max_rtiles <= GRAWA_FOLD_WAVE_TILES ? (units + 3) / 4 : units;
+        const int64_t units = (int64_t)K * p->L, per = single ? 1 : GRAWA_CELL / GRAWA_WAVE, blocks = (units + per - 1) / per;
         fold_blocks = (unsigned)((blocks + K * n_groups - 1) / (K * n_groups));
         if (group >= 256) fold_blocks = (fold_blocks + 7) / 8 * 8;
     }
     GrawaFold fold = {}; // no flags either: k_estimate looks at the norms
-    if (later) fold = grawa_fold_of(p, gamma, buffer, fold_blocks);
+    if (later) fold = grawa_fold_of(p, gamma, buffer, fold_blocks, single);
     const dim3 grid((unsigned)group + fold_blocks, (unsigned)K, (unsigned)n_groups), block(GRAWA_CELL);
     const bool aligned = rows_line_aligned(x, ldx, 4) && rows_line_aligned(g, ldg, dt == GRAWA_BF16 ? 2 : 4);
     const int64_t bytes = (int64_t)K * P * 4;

@@ -366,35 +366,63 @@ __global__ __launch_bounds__(GRAWA_LW_BLOCK_MODEL) void k_local_weights(double *
     }
 }
 
-// The same where the last step's sums may not be folded in yet (grawa_fold.h).  per_layer: grid L, and what is pending is folded in on the way:
-// by a thread per worker, a wave per worker in turn, or the block for one worker after the other, as the layers are longer.  Model level:
-// grid 1.  Where layers are long, and for the model level, k_fold goes before; what is still pending then was replayed after calls made one by one.
+// The same where the last step's sums may not be folded in yet (grawa_fold.h).  per_layer: grid L, and what is pending is folded in on the way: by a
+// thread per worker, a wave per worker in turn, or, for a layer of more than GRAWA_FOLD_WAVE_TILES tiles, all waves for the workers' parts, N
+// parts of a worker side by side (each what a wave of block_tile_sum adds, so that the sum is the same; two side by side take 5.9 us for 8
+// workers and 586 tiles, four 5.0), as long as grawa_fold_long_in_weights; beyond, and at the model level (grid 1), k_fold goes before.
 __global__ __launch_bounds__(GRAWA_FIN_BLOCK) void k_fold_weights(const GrawaFold f, const double *__restrict__ sums, int64_t n_tiles,
                                                                    int per_layer, uint64_t *__restrict__ consumed,
                                                                    float *__restrict__ beta, float *__restrict__ beta_user,
                                                                    float *__restrict__ est_user)
 {
+    constexpr int PARTS = GRAWA_FOLD_LANES / GRAWA_WAVE, N = 4;
     __shared__ double sA[GRAWA_MAX_WORKERS];
-    __shared__ double part[GRAWA_FOLD_LANES / GRAWA_WAVE];
+    __shared__ double part[GRAWA_FOLD_LONG_WORKERS * PARTS];
     const int lane = threadIdx.x & (GRAWA_WAVE - 1);
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / GRAWA_WAVE)), waves = (int)blockDim.x / GRAWA_WAVE;
     const int l0 = per_layer ? (int)blockIdx.x : 0;
     const int K = f.K, L = f.L;
     const GrawaEstimate e0 = f.est[l0]; // counts and buffer: the same for all workers and layers
     const uint64_t n = e0.n, used = grawa_last_used(consumed[l0], consumed[L + l0]);
-    const bool pending = grawa_estimate_pending(e0, used);
     if (per_layer) {
+        const bool pending = grawa_estimate_pending(e0, used);
         const int t0 = f.layer_tile0[l0], t1 = f.layer_tile0[l0 + 1], tiles = t1 - t0;
         const double *p = sums + e0.buffer * f.pitch;
-        if (pending && tiles > 16 && f.by_wave) {
+        if (pending && tiles > GRAWA_FOLD_WAVE_TILES) { // grawa_fold_long_in_weights
+            for (int j = N * wave; j < K * PARTS; j += N * waves) {
+                const double *row = p + (int64_t)(j / PARTS) * n_tiles;
+                const int first = t0 + (j % PARTS) * GRAWA_WAVE + lane;
+                double w[N], half[2][N];
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    double s[N][4];
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+#pragma unroll
+                        for (int h = 0; h < N; ++h) {
+                            const int at = first + h * GRAWA_WAVE + (4 * u + v) * GRAWA_FOLD_LANES;
+                            s[h][v] = at < t1 ? row[at] : 0.0;
+                        }
+#pragma unroll
+                    for (int h = 0; h < N; ++h) half[u][h] = (s[h][0] + s[h][1]) + (s[h][2] + s[h][3]);
+                }
+#pragma unroll
+                for (int h = 0; h < N; ++h) w[h] = half[0][h] + half[1][h];
+                wave_sums<N>(w);
+#pragma unroll
+                for (int h = 0; h < N; ++h)
+                    if (lane == 0) part[j + h] = w[h];
+            }
+            __syncthreads();
+            if ((int)threadIdx.x < K) { // in the order of block_tile_sum
+                double tot = 0.0;
+                for (int w = 0; w < PARTS; ++w) tot += part[threadIdx.x * PARTS + w];
+                sA[threadIdx.x] = tot;
+            }
+        } else if (pending && tiles > 16) {
             for (int k = wave; k < K; k += waves) {
                 const double s = wave_strided_sum(p + (int64_t)k * n_tiles, t0, t1, lane, GRAWA_WAVE);
                 if (lane == 0) sA[k] = s;
-            }
-        } else if (pending && tiles > 16) {
-            for (int k = 0; k < K; ++k) { // GRAWA_FOLD_LANES threads
-                const double s = block_tile_sum<GRAWA_FOLD_LANES>(p + (int64_t)k * n_tiles, t0, t1, part);
-                if (threadIdx.x == 0) sA[k] = s;
             }
         }
         const double scale = n != used ? f.gamma / grawa_one_minus_power(f.gamma, (int64_t)(n - used)) : 0.0;
@@ -414,11 +442,6 @@ __global__ __launch_bounds__(GRAWA_FIN_BLOCK) void k_fold_weights(const GrawaFol
             group_weights(sA, K, beta + l0, L, beta_user ? beta_user + l0 : nullptr, f.flags, GRAWA_NONFINITE_LAYER_SCORE);
     } else {
         const double scale = n != used ? f.gamma / grawa_one_minus_power(f.gamma, (int64_t)(n - used)) : 0.0;
-        if (pending) {
-            __syncthreads(); // every thread has read e0
-            fold_all<GRAWA_LW_BLOCK_MODEL, GRAWA_FOLD_ONLY>(f, sums, n_tiles, 0, 1);
-            __syncthreads();
-        }
         for (int k = wave; k < K; k += waves) {
             double s = 0.0;
             for (int l = lane; l < L; l += GRAWA_WAVE) {
@@ -574,12 +597,13 @@ hipError_t grawa_launch_estimate(const grawa_plan *p, double gamma, hipStream_t 
 // step: a recorded step, whose sums are to be folded in; null: only what is pending.
 hipError_t grawa_launch_fold(const grawa_plan *p, const GrawaFold *step, hipStream_t s)
 {
-    const GrawaFold f = step ? *step : grawa_fold_of(p, 0.0, 0, 0);
-    const unsigned units = (unsigned)p->K * (unsigned)p->L;
-    const dim3 grid(f.by_wave ? (units + 3) / 4 : units), block(f.by_wave ? 256 : GRAWA_FOLD_LANES);
+    const bool single = grawa_fold_single(p->K, p->L, p->max_rtiles, GRAWA_FOLD_SINGLE);
+    const GrawaFold f = grawa_fold_of(p, step ? step->gamma : 0.0, step ? step->buffer : 0, 0, single);
+    const unsigned units = (unsigned)p->K * (unsigned)p->L, threads = f.has_long ? GRAWA_FOLD_LANES : 256, per = single ? 1 : threads / GRAWA_WAVE;
+    const dim3 grid((units + per - 1) / per), block(threads);
 #define GRAWA_FOLD_GO(THREADS, MODE) k_fold<THREADS, MODE><<<grid, block, 0, s>>>(f, p->d_sums, p->n_rtiles)
-    if (f.by_wave && step) GRAWA_FOLD_GO(256, GRAWA_FOLD_SUMS);
-    else if (f.by_wave) GRAWA_FOLD_GO(256, GRAWA_FOLD_ONLY);
+    if (!f.has_long && step) GRAWA_FOLD_GO(256, GRAWA_FOLD_SUMS);
+    else if (!f.has_long) GRAWA_FOLD_GO(256, GRAWA_FOLD_ONLY);
     else if (step) GRAWA_FOLD_GO(GRAWA_FOLD_LANES, GRAWA_FOLD_SUMS);
     else GRAWA_FOLD_GO(GRAWA_FOLD_LANES, GRAWA_FOLD_ONLY);
 #undef GRAWA_FOLD_GO
@@ -603,13 +627,14 @@ hipError_t grawa_launch_local_weights(const grawa_plan *p, double gamma, int per
     if (p->fold_later) {
         unsigned long long id = 0;
         const bool recorded = grawa_is_recorded(s, &id);
-        const GrawaFold f = grawa_fold_of(p, gamma, 0, 0);
-        if ((!per_layer || !f.by_wave) && !grawa_all_folded(p->steps, recorded, id)) {
+        const GrawaFold f = grawa_fold_of(p, gamma, 0, 0, false);
+        const bool before = !per_layer || (f.has_long && !grawa_fold_long_in_weights(p->K, p->max_rtiles));
+        if (before && !grawa_all_folded(p->steps, recorded, id)) {
             const hipError_t e = grawa_launch_fold(p, nullptr, s);
             if (e != hipSuccess) return e;
         }
-        const int fold_waves = GRAWA_FOLD_LANES / GRAWA_WAVE, all = p->K < GRAWA_FIN_WAVES ? p->K : GRAWA_FIN_WAVES;
-        const int waves = !per_layer ? GRAWA_LW_BLOCK_MODEL / GRAWA_WAVE : !f.by_wave ? fold_waves : p->max_rtiles <= 16 || p->K < 4 ? 4 : all;
+        const int want = !per_layer ? GRAWA_FIN_WAVES : p->max_rtiles <= 16 || before ? 4 : f.has_long ? 4 * p->K : p->K;
+        const int waves = want < 4 ? 4 : want < GRAWA_FIN_WAVES ? want : GRAWA_FIN_WAVES;
         k_fold_weights<<<dim3(per_layer ? (unsigned)p->L : 1u), dim3(waves * GRAWA_WAVE), 0, s>>>(
             f, p->d_sums, p->n_rtiles, per_layer, p->d_consumed, per_layer ? p->d_beta_layer : p->d_beta_model, beta_user, est_user);
         return hipGetLastError();

@@ -228,6 +228,26 @@ static inline bool grawa_fold_later(int K, int L, int64_t P, int64_t max_tiles)
     return (int64_t)K * ((P + 1023) / 1024) <= GRAWA_FOLD_MAX_BLOCKS && (int64_t)K * L <= GRAWA_FOLD_MAX_BLOCKS;
 }
 
+// Folding the sums in (fold_all) where some layer is longer than a wave adds: a block for each worker and layer while they are few, so that all long ones
+// go on at once, else a wave for each of the others and the block for the long ones among those of its waves.  A block for each whatever their number
+// made rounds of one step and the communication, us, without sums left to the next launch / a block for each / this: 8 workers, one layer of 600 k
+// columns and 300 of 700 31.7 / 36.6 / 32.2, 1000 of 1050 50.4 / 77.5 / 56.5, ResNet-18 296 / 298 / 294, of four steps 86.6 / 82.9 / 78.7,
+// 139 / 172 / 141, 833 / 824 / 815; ResNet-50 on 2 177.0 / 178.5 / 174.2 and 503 / 497 / 485.
+#define GRAWA_FOLD_SINGLE 2048     // in a launch of its own
+#define GRAWA_FOLD_SINGLE_STEP 256 // in a scored step, which takes longer than a few of them one after the other
+static inline bool grawa_fold_single(int K, int L, int64_t max_tiles, int64_t most)
+{
+    return max_tiles > GRAWA_FOLD_WAVE_TILES && (int64_t)K * L <= most;
+}
+
+// Whether the launch of the weights adds the tiles of long layers itself: up to 8 workers, whose parts its 16 waves take at once, and 4096 tiles, 8 of
+// them to a lane.  Else k_fold goes before, a launch of 5 us.  One step and the communication, us, k_fold / this: 2 workers, one layer of 600 k
+// columns and 250 of 3 k 24.4 / 21.5, of 1.5 M alone 23.6 / 21.4; 8 workers, 600 k alone 26.1 / 24.7, ResNet-18 295.4 / 293.9; beyond, 16 workers
+// (twice as many parts): 600 k alone 39.0 / 38.9, three of 2 M 310 / 314.
+#define GRAWA_FOLD_LONG_WORKERS 8
+#define GRAWA_FOLD_LONG_TILES 4096
+static inline bool grawa_fold_long_in_weights(int K, int64_t max_tiles) { return K <= GRAWA_FOLD_LONG_WORKERS && max_tiles <= GRAWA_FOLD_LONG_TILES; }
+
 // Lanes of a wave that share a worker's tiles where the wave takes all K workers of a layer: the largest power of two not above 64 / K.
 static inline int grawa_group_lanes(int K)
 {

@@ -64,6 +64,16 @@ int main(int argc, char **argv)
                         grawa_step_by_layers(std::atoi(argv[i]), std::atoi(argv[i + 1]), std::atoll(argv[i + 2]), std::atoll(argv[i + 3])));
         return 0;
     }
+    if (!std::strcmp(argv[1], "fold")) {
+        for (int i = 2; i + 3 < argc; i += 4) {
+            const int K = std::atoi(argv[i]), L = std::atoi(argv[i + 1]);
+            const int64_t P = std::atoll(argv[i + 2]), tiles = std::atoll(argv[i + 3]);
+            std::printf("%d %d %d %d %d\n", grawa_fold_later(K, L, P, tiles), grawa_estimate_in_pull(K, (P + 255) / 256, tiles),
+                        grawa_fold_single(K, L, tiles, GRAWA_FOLD_SINGLE_STEP), grawa_fold_single(K, L, tiles, GRAWA_FOLD_SINGLE),
+                        grawa_fold_long_in_weights(K, tiles));
+        }
+        return 0;
+    }
     if (!std::strcmp(argv[1], "cachedg")) {
         for (int i = 2; i + 2 < argc; i += 3)
             std::printf("%s %s %s %lld\n", argv[i], argv[i + 1], argv[i + 2],

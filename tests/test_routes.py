@@ -107,6 +107,17 @@ def test_scored_step_by_layers(driver):
     assert ask(1024, 1 << 30, 1 << 31, 1) == 0 and ask(1024, 1, 1 << 31, 1 << 21) == 0
 
 
+def test_folding_of_long_layers(driver):
+    ask = lambda *case: driver("fold", *case)[0]
+    # (workers, layers, columns, tiles of the longest): a block for each worker and layer in the step, in a launch of its own
+    for case, single in (((4, 64, 1 << 20, 513), [1, 1]), ((4, 65, 1 << 20, 513), [0, 1]), ((8, 256, 1 << 20, 513), [0, 1]),
+                         ((8, 257, 1 << 20, 513), [0, 0]), ((8, 1001, 1650000, 586), [0, 0]), ((1, 1, 1 << 20, 512), [0, 0])):
+        assert ask(*case)[2:4] == single, case
+    # the launch of the weights adds them itself
+    for case, yes in (((8, 1, 1 << 22, 4096), 1), ((9, 1, 1 << 20, 1024), 0), ((8, 2, 1 << 23, 4097), 0), ((1, 1, 1 << 20, 1024), 1)):
+        assert ask(*case)[4] == yes, case
+
+
 def test_columns_of_g_read_through_the_caches(driver):
     cases = [(k, p, e) for k in (1, 2, 3, 7, 64, 1000, 1024) for p in (1, 255, 60000, 1 << 20, (1 << 32) - 1) for e in (2, 4)]
     for k, p, e, cols in driver("cachedg", *[v for c in cases for v in c]):
