@@ -17,8 +17,7 @@ struct GrawaFold {
     unsigned *flags;
     int64_t pitch; // sums in one of the buffers
     int K, L;
-    int has_long; // some layer has more than GRAWA_FOLD_WAVE_TILES tiles
-    int single;   // a block of fold_all takes one worker and layer at a time
+    int by_wave;     // no layer has more than GRAWA_FOLD_WAVE_TILES tiles
     int lanes;       // of a wave that add the tiles of a worker: as many as in the pull, where that folds in (wave_layer_weights)
     unsigned buffer; // that the sums of this launch go to
     unsigned blocks; // of every row of a step's grid that fold
@@ -88,85 +87,54 @@ __device__ __forceinline__ double block_tile_sum(const double *__restrict__ p, i
 }
 
 // Brings the estimates of all workers and layers up to the last step: block `first` of `blocks`, of THREADS threads.  A wave takes a worker
-// and layer of up to GRAWA_FOLD_WAVE_TILES tiles; a longer layer the block, one worker after the other.  A block takes as many of them at
-// a time as it has waves, or (f.single) one.
+// and layer, or, where some layer is longer than a wave adds, the block.
 //   FOLD_STEP   and this launch takes the next step, whose sums stay pending
 //   FOLD_ONLY   nothing more
 //   FOLD_SUMS   and the sums of the next step, in f.buffer, are folded in as well
 enum { GRAWA_FOLD_STEP, GRAWA_FOLD_ONLY, GRAWA_FOLD_SUMS };
-// What is pending of worker and layer u (and, FOLD_SUMS, what comes after it); `sum`: of a buffer's tiles.
-template <int MODE, typename Sum>
-__device__ __forceinline__ void fold_unit(const GrawaFold &f, unsigned u, GrawaEstimate e, uint64_t used, bool writes, const Sum &sum)
-{
-    double next = 0.0, tot = 0.0;
-    if (MODE == GRAWA_FOLD_SUMS) next = sum(f.buffer);
-    if (grawa_estimate_pending(e, used)) tot = sum(e.buffer); // the same for all units
-    if (writes) {
-        e.mvg = grawa_estimate_value(e, used, sqrt(tot));
-        e.left = 0;
-        if (MODE != GRAWA_FOLD_ONLY) {
-            e.gamma = f.gamma;
-            e.buffer = f.buffer;
-            e.n += 1;
-            e.left = 1;
-        }
-        if (MODE == GRAWA_FOLD_SUMS) {
-            e.mvg = grawa_estimate_value(e, used, sqrt(next));
-            e.left = 0;
-        }
-        f.est[u] = e;
-    }
-}
-
 template <int THREADS, int MODE>
 __device__ __forceinline__ void fold_all(const GrawaFold &f, const double *__restrict__ sums, int64_t n_tiles, unsigned first, unsigned blocks)
 {
+    __shared__ double part[GRAWA_FOLD_LANES / GRAWA_WAVE];
     constexpr unsigned WAVES = THREADS / GRAWA_WAVE;
     const int lane = threadIdx.x & (GRAWA_WAVE - 1);
     const unsigned wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / GRAWA_WAVE));
-    const unsigned units = (unsigned)f.K * (unsigned)f.L; // at most GRAWA_FOLD_MAX_BLOCKS
-    if (!f.has_long) {
-        for (unsigned u = first * WAVES + wave; u < units; u += blocks * WAVES) {
-            const unsigned k = u / (unsigned)f.L, l = u - k * (unsigned)f.L;
-            const GrawaEstimate e = f.est[u];
-            const uint64_t used = grawa_last_used(f.consumed[l], f.consumed[f.L + l]);
-            const int t0 = f.layer_tile0[l], t1 = f.layer_tile0[l + 1];
-            const double *p = sums + (int64_t)k * n_tiles;
-            fold_unit<MODE>(f, u, e, used, lane == 0, [&](unsigned buffer) {
-                return wave_strided_sum(p + buffer * f.pitch, lane < f.lanes ? t0 : t1, t1, lane, f.lanes);
-            });
-        }
-        return;
-    }
-    __shared__ double part[GRAWA_FOLD_LANES / GRAWA_WAVE];
-    const unsigned per = f.single ? 1u : WAVES;
-    for (unsigned base = first * per; base < units; base += blocks * per) {
-        if (wave < per && base + wave < units) {
-            const unsigned u = base + wave, k = u / (unsigned)f.L, l = u - k * (unsigned)f.L;
-            const GrawaEstimate e = f.est[u];
-            const uint64_t used = grawa_last_used(f.consumed[l], f.consumed[f.L + l]);
-            const int t0 = f.layer_tile0[l], t1 = f.layer_tile0[l + 1];
-            const double *p = sums + (int64_t)k * n_tiles;
-            if (t1 - t0 <= GRAWA_FOLD_WAVE_TILES)
-                fold_unit<MODE>(f, u, e, used, lane == 0, [&](unsigned buffer) { return wave_strided_sum(p + buffer * f.pitch, t0, t1, lane, GRAWA_WAVE); });
-        }
-        const unsigned mine = (base + lane) % (unsigned)f.L; // the long ones among these: the same in every wave
-        for (unsigned long long todo = __ballot((unsigned)lane < per && base + lane < units &&
-                                                f.layer_tile0[mine + 1] - f.layer_tile0[mine] > GRAWA_FOLD_WAVE_TILES);
-             todo; todo &= todo - 1) {
-            const unsigned u = base + (unsigned)__builtin_ctzll(todo), k = u / (unsigned)f.L, l = u - k * (unsigned)f.L;
-            const int t0 = f.layer_tile0[l], t1 = f.layer_tile0[l + 1];
-            const double *p = sums + (int64_t)k * n_tiles;
-            const GrawaEstimate e = f.est[u];
-            const uint64_t used = grawa_last_used(f.consumed[l], f.consumed[f.L + l]);
-            __syncthreads(); // every wave has read what thread 0 writes
-            fold_unit<MODE>(f, u, e, used, threadIdx.x == 0, [&](unsigned buffer) { return block_tile_sum<THREADS>(p + buffer * f.pitch, t0, t1, part); });
+    const unsigned units = (unsigned)f.K * (unsigned)f.L; // at most GRAWA_FOLD_MAX_UNITS
+    const unsigned step = f.by_wave ? blocks * WAVES : blocks;
+    for (unsigned u = f.by_wave ? first * WAVES + wave : first; u < units; u += step) {
+        const unsigned k = u / (unsigned)f.L, l = u - k * (unsigned)f.L;
+        GrawaEstimate e = f.est[u];
+        const uint64_t used = grawa_last_used(f.consumed[l], f.consumed[f.L + l]);
+        const int t0 = f.layer_tile0[l], t1 = f.layer_tile0[l + 1];
+        const double *p = sums + (int64_t)k * n_tiles;
+        if (!f.by_wave) __syncthreads(); // every wave has read what thread 0 writes below
+        double next = 0.0, tot = 0.0;
+        const auto sum = [&](unsigned buffer) {
+            return t1 - t0 > GRAWA_FOLD_WAVE_TILES ? block_tile_sum<THREADS>(p + buffer * f.pitch, t0, t1, part)
+                                                   : wave_strided_sum(p + buffer * f.pitch, lane < f.lanes ? t0 : t1, t1, lane, f.lanes);
+        };
+        if (MODE == GRAWA_FOLD_SUMS) next = sum(f.buffer);
+        if (grawa_estimate_pending(e, used)) tot = sum(e.buffer); // the same for all units
+        if (f.by_wave ? lane == 0 : threadIdx.x == 0) {
+            e.mvg = grawa_estimate_value(e, used, sqrt(tot));
+            e.left = 0;
+            if (MODE != GRAWA_FOLD_ONLY) {
+                e.gamma = f.gamma;
+                e.buffer = f.buffer;
+                e.n += 1;
+                e.left = 1;
+            }
+            if (MODE == GRAWA_FOLD_SUMS) {
+                e.mvg = grawa_estimate_value(e, used, sqrt(next));
+                e.left = 0;
+            }
+            f.est[u] = e;
         }
     }
 }
 
-static inline GrawaFold grawa_fold_of(const grawa_plan *p, double gamma, unsigned buffer, unsigned blocks, bool single)
+static inline GrawaFold grawa_fold_of(const grawa_plan *p, double gamma, unsigned buffer, unsigned blocks)
 {
     return GrawaFold{p->d_est, p->d_consumed, p->d_layer_rtile0, p->d_flags, (int64_t)p->K * p->n_rtiles, p->K, p->L,
-                     p->max_rtiles > GRAWA_FOLD_WAVE_TILES, single, p->d_seen ? grawa_group_lanes(p->K) : 64, buffer, blocks, gamma};
+                     p->max_rtiles <= GRAWA_FOLD_WAVE_TILES, p->d_seen ? grawa_group_lanes(p->K) : 64, buffer, blocks, gamma};
 }

@@ -392,7 +392,7 @@ static hipError_t launch_row_step(grawa_plan *p, float *x, int64_t ldx, const vo
     const int64_t nb = (P + GRAWA_ROW_BLOCK - 1) / GRAWA_ROW_BLOCK;
     const bool prox = center != nullptr;
     const bool later = p && p->fold_later;
-    if (p && !later && grawa_step_by_layers(K, p->L, P, p->max_rtiles) == GRAWA_LAYER_THREADS) {
+    if (p && !later && grawa_step_by_layers(K, p->L, P, p->max_rtiles)) {
 #define GRAWA_LS_GO(GT, PROX)                                                                                              \
     k_layer_step<GT, PROX><<<dim3((unsigned)p->L, (unsigned)K), dim3(GRAWA_LAYER_THREADS), 0, s>>>(                        \
         x, ldx, (const GT *)g, ldg, lr, center, w, p->d_off, p->L, p->d_mvg, gamma, p->d_local_t, p->d_flags)
@@ -417,14 +417,13 @@ static hipError_t launch_row_step(grawa_plan *p, float *x, int64_t ldx, const vo
     bool at_once = false;
     const unsigned buffer = later ? grawa_step_buffer(p->steps, recorded, id, &at_once) : 0;
     unsigned fold_blocks = 0;
-    const bool single = later && grawa_fold_single(K, p->L, p->max_rtiles, GRAWA_FOLD_SINGLE_STEP);
     if (later && !at_once) {
-        const int64_t units = (int64_t)K * p->L, per = single ? 1 : GRAWA_CELL / GRAWA_WAVE, blocks = (units + per - 1) / per;
+        const int64_t units = (int64_t)K * p->L, blocks = p->max_rtiles <= GRAWA_FOLD_WAVE_TILES ? (units + 3) / 4 : units;
         fold_blocks = (unsigned)((blocks + K * n_groups - 1) / (K * n_groups));
         if (group >= 256) fold_blocks = (fold_blocks + 7) / 8 * 8;
     }
     GrawaFold fold = {}; // no flags either: k_estimate looks at the norms
-    if (later) fold = grawa_fold_of(p, gamma, buffer, fold_blocks, single);
+    if (later) fold = grawa_fold_of(p, gamma, buffer, fold_blocks);
     const dim3 grid((unsigned)group + fold_blocks, (unsigned)K, (unsigned)n_groups), block(GRAWA_CELL);
     const bool aligned = rows_line_aligned(x, ldx, 4) && rows_line_aligned(g, ldg, dt == GRAWA_BF16 ? 2 : 4);
     const int64_t bytes = (int64_t)K * P * 4;

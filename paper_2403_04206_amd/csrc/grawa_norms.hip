@@ -597,13 +597,12 @@ hipError_t grawa_launch_estimate(const grawa_plan *p, double gamma, hipStream_t 
 // step: a recorded step, whose sums are to be folded in; null: only what is pending.
 hipError_t grawa_launch_fold(const grawa_plan *p, const GrawaFold *step, hipStream_t s)
 {
-    const bool single = grawa_fold_single(p->K, p->L, p->max_rtiles, GRAWA_FOLD_SINGLE);
-    const GrawaFold f = grawa_fold_of(p, step ? step->gamma : 0.0, step ? step->buffer : 0, 0, single);
-    const unsigned units = (unsigned)p->K * (unsigned)p->L, threads = f.has_long ? GRAWA_FOLD_LANES : 256, per = single ? 1 : threads / GRAWA_WAVE;
-    const dim3 grid((units + per - 1) / per), block(threads);
+    const GrawaFold f = step ? *step : grawa_fold_of(p, 0.0, 0, 0);
+    const unsigned units = (unsigned)p->K * (unsigned)p->L;
+    const dim3 grid(f.by_wave ? (units + 3) / 4 : units), block(f.by_wave ? 256 : GRAWA_FOLD_LANES);
 #define GRAWA_FOLD_GO(THREADS, MODE) k_fold<THREADS, MODE><<<grid, block, 0, s>>>(f, p->d_sums, p->n_rtiles)
-    if (!f.has_long && step) GRAWA_FOLD_GO(256, GRAWA_FOLD_SUMS);
-    else if (!f.has_long) GRAWA_FOLD_GO(256, GRAWA_FOLD_ONLY);
+    if (f.by_wave && step) GRAWA_FOLD_GO(256, GRAWA_FOLD_SUMS);
+    else if (f.by_wave) GRAWA_FOLD_GO(256, GRAWA_FOLD_ONLY);
     else if (step) GRAWA_FOLD_GO(GRAWA_FOLD_LANES, GRAWA_FOLD_SUMS);
     else GRAWA_FOLD_GO(GRAWA_FOLD_LANES, GRAWA_FOLD_ONLY);
 #undef GRAWA_FOLD_GO
@@ -627,13 +626,13 @@ hipError_t grawa_launch_local_weights(const grawa_plan *p, double gamma, int per
     if (p->fold_later) {
         unsigned long long id = 0;
         const bool recorded = grawa_is_recorded(s, &id);
-        const GrawaFold f = grawa_fold_of(p, gamma, 0, 0, false);
-        const bool before = !per_layer || (f.has_long && !grawa_fold_long_in_weights(p->K, p->max_rtiles));
+        const GrawaFold f = grawa_fold_of(p, gamma, 0, 0);
+        const bool before = !per_layer || (!f.by_wave && !grawa_fold_long_in_weights(p->K, p->max_rtiles));
         if (before && !grawa_all_folded(p->steps, recorded, id)) {
             const hipError_t e = grawa_launch_fold(p, nullptr, s);
             if (e != hipSuccess) return e;
         }
-        const int want = !per_layer ? GRAWA_FIN_WAVES : p->max_rtiles <= 16 || before ? 4 : f.has_long ? 4 * p->K : p->K;
+        const int want = !per_layer ? GRAWA_FIN_WAVES : p->max_rtiles <= 16 || before ? 4 : f.by_wave ? p->K : 4 * p->K;
         const int waves = want < 4 ? 4 : want < GRAWA_FIN_WAVES ? want : GRAWA_FIN_WAVES;
         k_fold_weights<<<dim3(per_layer ? (unsigned)p->L : 1u), dim3(waves * GRAWA_WAVE), 0, s>>>(
             f, p->d_sums, p->n_rtiles, per_layer, p->d_consumed, per_layer ? p->d_beta_layer : p->d_beta_model, beta_user, est_user);

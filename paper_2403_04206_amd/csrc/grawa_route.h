@@ -1,5 +1,5 @@
-// Launch shapes of the center+pull pass (host side).  Plain C++ with no GPU dependency, so that the rules can be
-// checked on the CPU for sizes that no test allocates.
+// The rules that choose between kernels and launch shapes, and what host and device share of the running estimate.  Plain C++ with no GPU
+// dependency, so that they can be checked on the CPU for sizes that no test allocates.
 #ifndef GRAWA_ROUTE_H
 #define GRAWA_ROUTE_H
 
@@ -179,35 +179,26 @@ static constexpr int64_t grawa_row_step_merges_from(bool bf16, bool center, bool
     return bf16 && center && !scored ? (int64_t)128 << 20 : 0;
 }
 
-// Scored step: threads of a block that owns a layer of one worker, or 0: blocks of 1024 columns, the estimate as a launch of its
-// own.  One launch saves the other and its boundary; what it costs is that the longest layer takes one block, at the rate of one
-// CU.  max_tiles: the most 1024-column tiles of a layer.  (Of the most blocks that are accepted, 2560 of 256 threads or 640 of 1024,
-// a fifth starts in a second round.)
-// The lines lie where calls made one by one gain; there the host's launches bound a round of four steps and the communication.  fp32, us, two
-// launches a step / one: 2 workers, 200 k columns, 300 layers 47.3 / 39.0; 4 workers, 270 k, 59 layers (37 k the longest) 48.5 / 43.5, 420 k,
-// 60 layers 52.0 / 43.1; 8 workers, 200 k, 20 layers 52.5 / 43.8, 300 layers 55.2 / 40.4; 16 workers, 200 k, 150 layers 61.5 / 53.0; 20 workers,
-// 200 k, 120 layers 69.7 / 63.6.  Beyond the lines: longest layer 48 k 52.2 / 54.2, 116 k 47.0 / 54.3; 2 workers, 1 M, 150 layers 49.1 / 50.7;
-// 16 workers, 200 k, 60 layers of up to 17 k 57.9 / 67.6.
-// What they cost: in a captured graph, or behind work that keeps the device busy, the device's time counts, and a long layer among
-// few loses.  The same round replayed as a graph, with the center, 4 workers, one layer of so many thousand columns (in brackets: and 58 more of
-// 2000): 5 23 / 20 (32 / 23), 11 23 / 20 (32 / 23), 14 23 / 22 (32 / 25), 18 23 / 24 (32 / 27), 27 23 / 28 (33 / 32), 39 23 / 35 (33 / 38);
-// without it 18 23 / 22, 27 23 / 25, 39 23 / 30 (32 / 34); 32 workers, with it, 18 29 / 28, 39 33 / 41.
-// Threads: 256 up to 7 tiles (23 / 22), beyond it 1024 as long as the blocks and elements are few enough (9 tiles 22 / 24 with 256, 23 / 20 with
-// 1024, 10 tiles 22 / 26 and 23 / 20); where they are too many, 256 up to 10 tiles (16 workers, 59 layers 47 / 39).
-// (In use up to GRAWA_LAYER_SHORT_TILES: beyond, the sums are left to the next launch, grawa_fold_later, and the figures above are what that replaced.)
-#define GRAWA_LAYER_MAX_TILES 40
-#define GRAWA_LAYER_MAX_ELEMS ((int64_t)7 << 18)
-#define GRAWA_LAYER_MAX_BLOCKS 640
-#define GRAWA_LAYER_SHORT_TILES 7
-#define GRAWA_LAYER_SHORT_MAX_TILES 10
-#define GRAWA_LAYER_SHORT_MAX_ELEMS ((int64_t)1 << 22)
-#define GRAWA_LAYER_SHORT_MAX_BLOCKS 2560
-static inline int grawa_step_by_layers(int K, int L, int64_t P, int64_t max_tiles)
+// Scored step: whether a block of 256 threads owns a layer of one worker and updates the estimate itself.  One launch saves the other and its
+// boundary; what it costs is that the longest layer takes one block, at the rate of one CU.  max_tiles: the most 1024-column tiles of a
+// layer.  (Of the most blocks that are accepted a fifth starts in a second round.)  A round of four steps and the communication, fp32, us:
+//   up to 7 tiles, against the estimate as a launch of its own: 2 workers, 200 k columns, 300 layers 47.3 / 39.0; 8 workers, 200 k, 20 layers
+//   52.5 / 43.8, 300 layers 55.2 / 40.4; against sums left to the next launch (below), replayed: 4 workers, 200 k, 300 layers 34 / 29.4
+//   8 to 10 tiles, sums left to the next launch / by layers, without and with the center: with many columns 4 workers, 100 layers of 9 k 43.5 /
+//   41.6 and 55.4 / 47.0, 2 workers, 220 of them 46.1 / 43.9 and 59.4 / 57.0; with fewer 8 workers, 30 of them 32.8 / 34.6 and 33.3 / 37.0, 16
+//   workers, 14 of them 35.1 / 34.0 and 35.6 / 36.7; with many blocks 16 workers, 4 of them and 60 of 2 k 39.5 / 43.5 and 39.9 / 47.8
+#define GRAWA_LAYER_TILES 7
+#define GRAWA_LAYER_MAX_ELEMS ((int64_t)1 << 22)
+#define GRAWA_LAYER_MAX_BLOCKS 2560
+#define GRAWA_LAYER_MANY_TILES 10
+#define GRAWA_LAYER_MANY_ELEMS ((int64_t)3 << 20)
+#define GRAWA_LAYER_MANY_MAX_BLOCKS 640
+static inline bool grawa_step_by_layers(int K, int L, int64_t P, int64_t max_tiles)
 {
     const int64_t blocks = (int64_t)K * L, elems = (int64_t)K * P;
-    if (max_tiles > GRAWA_LAYER_SHORT_TILES && elems <= GRAWA_LAYER_MAX_ELEMS && blocks <= GRAWA_LAYER_MAX_BLOCKS)
-        return max_tiles <= GRAWA_LAYER_MAX_TILES ? 1024 : 0;
-    return max_tiles <= GRAWA_LAYER_SHORT_MAX_TILES && elems <= GRAWA_LAYER_SHORT_MAX_ELEMS && blocks <= GRAWA_LAYER_SHORT_MAX_BLOCKS ? 256 : 0;
+    if (elems > GRAWA_LAYER_MAX_ELEMS) return false;
+    if (elems > GRAWA_LAYER_MANY_ELEMS && blocks <= GRAWA_LAYER_MANY_MAX_BLOCKS) return max_tiles <= GRAWA_LAYER_MANY_TILES;
+    return max_tiles <= GRAWA_LAYER_TILES && blocks <= GRAWA_LAYER_MAX_BLOCKS;
 }
 
 // Scored step: whether its tile sums are left to the launch that needs them next (grawa_fold.h) instead of a launch of their own.
@@ -216,28 +207,27 @@ static inline int grawa_step_by_layers(int K, int L, int64_t P, int64_t max_tile
 // steps with the center and the communication, fp32, us, before / now (in brackets replayed as a graph): ResNet-20, 59 layers, 4 workers 42.7 / 28.1
 // (42.7 / 28.0), 8 workers 48.0 / 34.3 (48.1 / 34.5), both with the weights in the pull (below); 16 workers, 200 k columns, 150 layers 68.7 / 49.5 (69.1 / 50.2); 4 workers, 1 M, one layer 67.3 /
 // 59.7 (67.9 / 60.6), 60 layers 71.9 / 61.0; 64 workers, 300 k, 100 layers 198 / 188; 16 workers, 3 M 510 / 493; 2 workers, 20 M, one layer 428 / 409.
-// One step and the communication, 8 workers, 8 M columns 214.7 / 216.0.
-// The step by layers stays where no layer has more than 7 tiles: with many of them it is the shorter launch (4 workers, 200 k columns, 300
-// layers, replayed 34 here, 29.4 by layers; up to 10 tiles, 16 workers, 150 layers 48.7 / 51.4).  Beyond 2^17 blocks a step lasts 300 us and more,
-// and the buffers take memory.
+// What it costs: a recording's first step has a launch of its own as well (grawa_step_buffer), and the kernels that fold in read more than
+// those that they replace.  Rounds of one step, us, before / now (in brackets captured, a graph's launch included): 8 workers, one layer of 8 M
+// 204.6 / 205.5 (209.3 / 210.0), 4 steps 573 / 557; 2 workers, 30 M 195.6 / 196.3 (200.4 / 201.7), 549 / 531; 64 workers, 1 M 214.2 / 214.9 (218.6 / 220.1),
+// 572 / 563; behind another kernel of 28 us ResNet-20 on 4 workers (40.1 / 39.5), and, where a block of 1024 threads took the layers before, 8 workers,
+// 12 layers of 12 k (37.0 / 38.6), 32 workers, one layer of 18 k (36.1 / 37.7), 4 workers, 9 k and 58 of 2 k (34.9 / 35.8).  A step and the
+// communication captured apart, 8 workers, 8 M 215.8 / 219.9: the communication cannot know that nothing is left to fold in.
+// The lines.  Beyond 2^17 blocks a step lasts 200 us and more, and the buffers take memory.  Layers: every one is a wave's work for each worker in the step
+// and a block in the launch of the weights: 4 workers, 2000 layers of 400 columns, four steps and one 66.5 / 54.5 and 29.1 / 25.7, 4000 layers
+// 106 / 97.5 and 38.5 / 39.4, 2 workers, 8000 116 / 104 and 44.6 / 48.3.  Sums: 64 workers, 300 layers 110 / 91 and 39 / 33, 8 workers, 5000
+// 177 / 171 and 61.8 / 63.7, 100 workers, 1000 465 / 501 and 190 / 192.  Where some layer is longer than a wave adds, a block for every sum: 8 workers, 600 k columns and
+// 127 layers of 700 78.8 / 65.5 and 28.9 / 27.5, 255 84.8 / 79.1 and 30.9 / 34.6, 400 92.2 / 91.6 and 33.9 / 40.8.
 #define GRAWA_FOLD_MAX_BLOCKS ((int64_t)1 << 17)
-#define GRAWA_FOLD_WAVE_TILES 512 // up to here a wave adds the tiles of a layer, beyond it a block
+#define GRAWA_FOLD_MAX_LAYERS 2048
+#define GRAWA_FOLD_MAX_UNITS 20480     // workers times layers
+#define GRAWA_FOLD_MAX_UNITS_LONG 1024 // where some layer is longer than a wave adds
+#define GRAWA_FOLD_WAVE_TILES 512      // up to here a wave adds the tiles of a layer, beyond it a block
 static inline bool grawa_fold_later(int K, int L, int64_t P, int64_t max_tiles)
 {
-    if (max_tiles <= GRAWA_LAYER_SHORT_TILES && grawa_step_by_layers(K, L, P, max_tiles)) return false;
-    return (int64_t)K * ((P + 1023) / 1024) <= GRAWA_FOLD_MAX_BLOCKS && (int64_t)K * L <= GRAWA_FOLD_MAX_BLOCKS;
-}
-
-// Folding the sums in (fold_all) where some layer is longer than a wave adds: a block for each worker and layer while they are few, so that all long ones
-// go on at once, else a wave for each of the others and the block for the long ones among those of its waves.  A block for each whatever their number
-// made rounds of one step and the communication, us, without sums left to the next launch / a block for each / this: 8 workers, one layer of 600 k
-// columns and 300 of 700 31.7 / 36.6 / 32.2, 1000 of 1050 50.4 / 77.5 / 56.5, ResNet-18 296 / 298 / 294, of four steps 86.6 / 82.9 / 78.7,
-// 139 / 172 / 141, 833 / 824 / 815; ResNet-50 on 2 177.0 / 178.5 / 174.2 and 503 / 497 / 485.
-#define GRAWA_FOLD_SINGLE 2048     // in a launch of its own
-#define GRAWA_FOLD_SINGLE_STEP 256 // in a scored step, which takes longer than a few of them one after the other
-static inline bool grawa_fold_single(int K, int L, int64_t max_tiles, int64_t most)
-{
-    return max_tiles > GRAWA_FOLD_WAVE_TILES && (int64_t)K * L <= most;
+    if (grawa_step_by_layers(K, L, P, max_tiles) || L > GRAWA_FOLD_MAX_LAYERS) return false;
+    const int64_t units = max_tiles > GRAWA_FOLD_WAVE_TILES ? GRAWA_FOLD_MAX_UNITS_LONG : GRAWA_FOLD_MAX_UNITS;
+    return (int64_t)K * ((P + 1023) / 1024) <= GRAWA_FOLD_MAX_BLOCKS && (int64_t)K * L <= units;
 }
 
 // Whether the launch of the weights adds the tiles of long layers itself: up to 8 workers, whose parts its 16 waves take at once, and 4096 tiles, 8 of
@@ -292,7 +282,8 @@ static inline void grawa_step_sent(GrawaSteps &s, bool recorded, unsigned long l
     if (!s.folded) s.recorded += 1;
     s.recording = id;
 }
-// Whether a communication that is being recorded finds nothing pending but what calls made before a replay left.
+// Whether a communication that is being recorded finds nothing pending: it follows a step that is folded in at once, and before that one nothing is
+// pending either, since its launch folds in what calls before the replay left.
 static inline bool grawa_all_folded(const GrawaSteps &s, bool recorded, unsigned long long id)
 {
     return recorded && s.recording == id && s.folded;

@@ -5,7 +5,9 @@
 //   offgrid <K>...       -> per line, without and with the fp32 SGD step: K, 0 or 1, form, groups, merge, 1 if that has a kernel
 //   offgrid_large <K> <sgd> <MB>... -> per triple: the triple, 1 if a pull of so many bytes takes that form (others from 128 MB on)
 //   rowstep              -> bf16, center, scored, MB beyond which loads stream and the L2 merges (-1: at no size)
-//   layers <K> <L> <P> <max_tiles>... -> per case: the case, threads of a block that owns a layer in the scored step, or 0
+//   layers <K> <L> <P> <max_tiles>... -> per case: the case, 1 if a block owns a layer in the scored step
+//   fold <K> <L> <P> <max_tiles>... -> per case: 1 if a scored step's sums are left to the next launch; there, 1 if the pull forms the weights from
+//                           the estimates, 1 if the launch of the per-layer weights adds long layers itself
 //   cachedg <K> <P> <elem_bytes>... -> per triple: the triple, columns of g that the norm pass of a fused update reads through the caches
 //   power <gamma> <t>... -> per pair, exactly (%a): gamma, 1 - gamma^t
 //   plain <K> <n_cells>... -> per pair: the pair, 1 if the one-column-per-lane form serves it
@@ -68,8 +70,7 @@ int main(int argc, char **argv)
         for (int i = 2; i + 3 < argc; i += 4) {
             const int K = std::atoi(argv[i]), L = std::atoi(argv[i + 1]);
             const int64_t P = std::atoll(argv[i + 2]), tiles = std::atoll(argv[i + 3]);
-            std::printf("%d %d %d %d %d\n", grawa_fold_later(K, L, P, tiles), grawa_estimate_in_pull(K, (P + 255) / 256, tiles),
-                        grawa_fold_single(K, L, tiles, GRAWA_FOLD_SINGLE_STEP), grawa_fold_single(K, L, tiles, GRAWA_FOLD_SINGLE),
+            std::printf("%d %d %d\n", grawa_fold_later(K, L, P, tiles), grawa_estimate_in_pull(K, (P + 255) / 256, tiles),
                         grawa_fold_long_in_weights(K, tiles));
         }
         return 0;

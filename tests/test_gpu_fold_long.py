@@ -1,6 +1,5 @@
-"""Scored steps whose tile sums the next launch folds in, where some layers are longer than a wave adds (512 tiles of 1024 columns): a block
-for each worker and layer or only for the long ones, in the step, in a launch of its own and in the launch of the weights, at either side
-of what each takes; and rows of more than one group of column blocks (with a center from 4096 blocks on), the last one short.  Calls
+"""Scored steps whose tile sums the next launch folds in, where some layers are longer than a wave adds (512 tiles of 1024 columns): in the
+step, in a launch of its own and in the launch of the weights, at either side of what each takes; and rows of more than one group of column blocks (with a center from 4096 blocks on), the last one short.  Calls
 and replays give the same bits; the estimates and every element of x against float64."""
 import numpy as np
 import pytest
@@ -14,13 +13,15 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 T = 1024
 CASES = {
-    "one block each in the step": (5, [600 * T] + [700] * 50, False),          # 255 workers and layers
-    "a wave each in the step": (5, [700] * 30 + [600 * T + 3] + [700] * 31, False),    # 310
+    "the first is long": (5, [600 * T] + [700] * 50, False),
+    "one between is long": (5, [700] * 30 + [600 * T + 3] + [700] * 31, False),
+    "1024 sums": (8, [600 * T] + [700] * 127, False),
+    "1032 sums": (8, [600 * T] + [700] * 128, False),                          # the estimate in a launch of its own
     "eight workers in the weights": (8, [513 * T + 5, 512 * T, 30, 5 * T, 17 * T], True),
     "nine workers": (9, [513 * T, 40, 17 * T], False),
     "4096 tiles": (2, [5, 4096 * T - 5, 7], False),
     "4097 tiles": (2, [5, 4096 * T + 5, 7], False),
-    "a wave each in the fold": (40, [300] * 30 + [513 * T, 600 * T] + [300] * 28, False),  # 2400
+    "two are long": (17, [300] * 30 + [513 * T, 600 * T] + [300] * 28, False),
     "three groups": (2, [500 * T] * 16 + [399 * T + 77, 5, 3000], True),
     "three groups, long layers": (3, [5000 * T, 3000 * T - 1, 400 * T + 77, 5], True),
 }

@@ -134,6 +134,10 @@ def test_step_count_of_every_layer(K, L):
     (66, [1 << 20, 9]), (66, [3, (1 << 20) + 3000]),     # more workers than waves: further trips over the workers
     (70, [11] * 700), (33, [2] * 600 + [40000]), (2, [3] * 5000),
     (5, [2] * 4100 + [(1 << 20) + 1100]),                # many layers beside a long one
+    # (up to 20480 sums, 1024 with a layer of more than 512 tiles, and 2048 layers there is no such launch: those cases pass without it)
+    (100, [7] * 250),                                    # two rows of blocks
+    (35, [5] * 30 + [600 * 1024]), (40, [3] * 30 + [(1 << 20) + 2000]),  # a wave for each worker; a block, 40 rows of them
+    (3, [1] * 2100 + [(1 << 20) + 1025]),                # a block for one worker after the other
 ])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_estimate_shapes(K, sizes, dtype):

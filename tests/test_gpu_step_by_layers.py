@@ -12,12 +12,13 @@ from parity_util import TIGHT, assert_table_close
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 RAGGED = [1, 1, 2, 1, 3, 4, 5, 6, 7, 9, 2, 1, 63, 1021, 4, 5119, 5122, 33]
-CASES = [(2, RAGGED), (5, RAGGED + [7000]),                              # 256 threads: up to 7 tiles of 1024 columns,
-         (16, [10 * 1024] + [300] * 40), (3, [1] * 640 + [10 * 1024]),       # 10 where there are too many blocks for 1024
-         (3, RAGGED + [8100, 2]),                                        # 1024 threads
+CASES = [(2, RAGGED), (5, RAGGED + [7000]),                              # up to 7 tiles of 1024 columns,
+         (16, [10 * 1024] + [300] * 40), (3, [1] * 640 + [10 * 1024]),
+         (3, RAGGED + [8100, 2]),
          (3, RAGGED + [10239, 2]), (3, RAGGED + [12001, 2]), (2, RAGGED + [20481, 40963]),
-         (4, [40000, 9000, 1]), (1, [40 * 1024, 5]), (1, [40 * 1024 + 1, 5]),                        # 40 tiles and more
-         (16, [700] * 160), (16, [700] * 161), (10, [11 * 1024] + [300] * 63), (10, [11 * 1024] + [300] * 64)]
+         (4, [40000, 9000, 1]), (1, [40 * 1024, 5]), (1, [40 * 1024 + 1, 5]),
+         (16, [700] * 160), (16, [700] * 161), (10, [11 * 1024] + [300] * 63), (10, [11 * 1024] + [300] * 64),
+         (4, [8000] * 99 + [9 * 1024 + 2]), (4, [8000] * 99 + [10 * 1024 + 2])]  # 10 where there are many columns; beyond, blocks of 1024 columns
 
 
 @pytest.mark.parametrize("case", range(len(CASES)))

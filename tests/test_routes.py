@@ -97,25 +97,44 @@ def test_local_steps_off_the_grid(driver):
 def test_scored_step_by_layers(driver):
     M = 1 << 20
     ask = lambda *case: driver("layers", *case)[0][4]
-    for tiles, threads in ((1, 256), (7, 256), (8, 1024), (40, 1024), (41, 0)):      # longest layer
-        assert ask(1, 1, 1024 * tiles, tiles) == threads
-    assert [ask(1, 100, p, 9) for p in (7 * M // 4, 7 * M // 4 + 1, 4 * M, 4 * M + 1)] == [1024, 256, 256, 0]        # elements
-    assert [ask(1, 100, p, 11) for p in (7 * M // 4, 7 * M // 4 + 1)] == [1024, 0]
-    assert [ask(k, L, 1000, 9) for k, L in ((1, 640), (64, 10), (1, 641), (1, 2560), (1024, 2), (1, 2561))] == [1024, 1024, 256, 256, 256, 0]
-    assert [ask(k, L, 1000, 11) for k, L in ((1, 640), (1, 641))] == [1024, 0]                                         # blocks
+    assert [ask(1, 1, 1024 * tiles, tiles) for tiles in (1, 7, 8, 10, 40)] == [1, 1, 0, 0, 0]             # longest layer
+    assert [ask(1, 600, p, 7) for p in (3 * M, 3 * M + 1, 4 * M, 4 * M + 1)] == [1, 1, 1, 0]               # elements
+    assert [ask(1, 600, p, 8) for p in (3 * M, 3 * M + 1, 4 * M, 4 * M + 1)] == [0, 1, 1, 0]
+    assert [ask(1, 600, p, t) for p, t in ((4 * M, 10), (4 * M, 11))] == [1, 0]
+    assert [ask(k, L, 1000, 7) for k, L in ((1, 2560), (64, 40), (1, 2561))] == [1, 1, 0]                  # blocks
+    assert [ask(1, L, 4 * M, 10) for L in (640, 641)] == [1, 0]
     # products beyond 32 bits
     assert ask(1024, 1 << 30, 1 << 31, 1) == 0 and ask(1024, 1, 1 << 31, 1 << 21) == 0
 
 
+def test_sums_left_to_the_next_launch(driver):
+    later = lambda *case: driver("fold", *case)[0][0]
+    # never what a block takes by layers
+    assert [later(4, 59, 270000, t) for t in (7, 8)] == [0, 1]
+    assert [later(4, 400, 1 << 20, t) for t in (7, 8)] == [0, 1] and [later(4, 100, 1 << 20, t) for t in (10, 11)] == [0, 1]
+    M = 1 << 17                                                                                            # blocks of 1024 columns
+    assert [later(1, 1, 1024 * n, n) for n in (M, M + 1)] == [1, 0] and [later(8, 1, 1024 * n, n) for n in (M // 8, M // 8 + 1)] == [1, 0]
+    assert later(1024, 1, (1 << 32) - 512, 1 << 22) == 0
+    assert [later(4, L, 1 << 23, 40) for L in (2048, 2049)] == [1, 0]                                     # layers
+    assert [later(64, L, 1 << 20, 40) for L in (320, 321)] == [1, 0] and later(1024, 21, 100000, 40) == 0      # sums
+    # one longer than a wave adds
+    assert [later(8, L, 1 << 21, t) for L, t in ((128, 512), (129, 512), (128, 513), (129, 513))] == [1, 1, 1, 0]
+    for tiny in ((70, 700, 7700, 1), (2, 5000, 15000, 2), (100, 250, 250 * 7, 1), (35, 31, 614550, 601), (40, 31, 1050666, 1027),
+                 (3, 2101, 1051701, 1026), (5, 4101, 1057876, 1027)):
+        assert later(*tiny) == 0, tiny               # what the GPU tests of the estimate's own launch take
+
+
+def test_weights_from_estimates_in_the_pull(driver):
+    yes = lambda *case: driver("fold", *case)[0][1]
+    assert [yes(4, 9, 270000, t) for t in (128, 129)] == [1, 0] and [yes(15, 3, 40000, t) for t in (34, 35)] == [1, 0]
+    assert yes(1, 1, 512 * 1024, 512) == 1 and yes(1, 1, 513 * 1024, 513) == 0
+    assert yes(16, 1, 20000, 20) == 0 and [yes(8, 10, 256 * n, 60) for n in (1280, 1281)] == [1, 0]
+
+
 def test_folding_of_long_layers(driver):
-    ask = lambda *case: driver("fold", *case)[0]
-    # (workers, layers, columns, tiles of the longest): a block for each worker and layer in the step, in a launch of its own
-    for case, single in (((4, 64, 1 << 20, 513), [1, 1]), ((4, 65, 1 << 20, 513), [0, 1]), ((8, 256, 1 << 20, 513), [0, 1]),
-                         ((8, 257, 1 << 20, 513), [0, 0]), ((8, 1001, 1650000, 586), [0, 0]), ((1, 1, 1 << 20, 512), [0, 0])):
-        assert ask(*case)[2:4] == single, case
     # the launch of the weights adds them itself
     for case, yes in (((8, 1, 1 << 22, 4096), 1), ((9, 1, 1 << 20, 1024), 0), ((8, 2, 1 << 23, 4097), 0), ((1, 1, 1 << 20, 1024), 1)):
-        assert ask(*case)[4] == yes, case
+        assert driver("fold", *case)[0][2] == yes, case
 
 
 def test_columns_of_g_read_through_the_caches(driver):
