@@ -159,17 +159,21 @@ static grawa_status_t plan_create_impl(grawa_plan_t **out, int K, int64_t P, int
     const size_t b_bl = round256(sizeof(float) * (size_t)K * (size_t)L);
     const size_t b_bm = round256(sizeof(float) * (size_t)K);
     const size_t b_mvg = b_S;
-    const size_t b_t = round256(sizeof(int64_t) * (size_t)L);
     int64_t max_rtiles = 0;
     for (int l = 0; l < L; ++l) {
         const int64_t n = m.layer_rtile0[(size_t)l + 1] - m.layer_rtile0[(size_t)l];
         if (n > max_rtiles) max_rtiles = n;
     }
     const bool later = grawa_fold_later(K, L, P, max_rtiles);
+    const bool in_pull = later && grawa_estimate_in_pull(K, nc, max_rtiles);
+    int64_t n_longer = 0;
+    for (int l = 0; l < L; ++l)
+        n_longer += m.layer_rtile0[(size_t)l + 1] - m.layer_rtile0[(size_t)l] > grawa_thread_tiles(in_pull ? grawa_group_lanes(K) : 64);
+    const size_t b_t = later ? 0 : round256(sizeof(int64_t) * (size_t)L);
     const size_t b_sums = later ? round256(sizeof(double) * GRAWA_SUM_BUFFERS * (size_t)K * (size_t)nrt) : 0;
     const size_t b_est = later ? round256(sizeof(GrawaEstimate) * (size_t)K * (size_t)L) : 0;
     const size_t b_used = later ? round256(sizeof(uint64_t) * 2 * (size_t)L) : 0;
-    const size_t b_seen = later && grawa_estimate_in_pull(K, nc, max_rtiles) ? round256(sizeof(uint64_t) * (size_t)nc) : 0;
+    const size_t b_seen = in_pull ? round256(sizeof(uint64_t) * (size_t)nc) : 0;
     const size_t b_words = 256; // flag word, arrival counter
     const size_t b_zeroed = b_part + b_S + b_bl + b_bm + b_mvg + b_t + b_sums + b_est + b_used + b_seen + b_words;
     const size_t b_host = b_off + b_cells + b_tiles + b_lt0 + b_rtiles + b_lt0 + b_brt0 + b_bm;
@@ -189,6 +193,7 @@ static grawa_status_t plan_create_impl(grawa_plan_t **out, int K, int64_t P, int
     p->n_cells = nc;
     p->max_rtiles = max_rtiles;
     p->fold_later = later ? 1 : 0;
+    p->n_longer = n_longer;
     if (hipGetDevice(&p->device) != hipSuccess) {
         delete p;
         return GRAWA_ERR_HIP;

@@ -12,6 +12,7 @@
 
 struct GrawaFold {
     GrawaEstimate *est;
+    double *value; // [K][L] the estimates once more, packed: written by k_fold, for the model level
     const uint64_t *consumed; // [2 L]
     const int32_t *layer_tile0; // [L+1]
     unsigned *flags;
@@ -129,12 +130,13 @@ __device__ __forceinline__ void fold_all(const GrawaFold &f, const double *__res
                 e.left = 0;
             }
             f.est[u] = e;
+            if (MODE != GRAWA_FOLD_STEP) f.value[u] = e.mvg;
         }
     }
 }
 
 static inline GrawaFold grawa_fold_of(const grawa_plan *p, double gamma, unsigned buffer, unsigned blocks)
 {
-    return GrawaFold{p->d_est, p->d_consumed, p->d_layer_rtile0, p->d_flags, (int64_t)p->K * p->n_rtiles, p->K, p->L,
+    return GrawaFold{p->d_est, p->d_mvg, p->d_consumed, p->d_layer_rtile0, p->d_flags, (int64_t)p->K * p->n_rtiles, p->K, p->L,
                      p->max_rtiles <= GRAWA_FOLD_WAVE_TILES, p->d_seen ? grawa_group_lanes(p->K) : 64, buffer, blocks, gamma};
 }

@@ -34,6 +34,7 @@ struct grawa_plan {
     int32_t *d_block_rtile0; // [ceil(P/1024)+1] first short tile of every aligned block of 1024 columns
     int64_t n_rtiles;
     int64_t max_rtiles;     // most short tiles of a layer
+    int64_t n_longer;       // layers with more of them than a thread adds (grawa_thread_tiles)
     int32_t *d_cell_layer;  // [n_cells] layer of a 256-column cell, or ~(first layer) if it holds a boundary
     double *d_partials;     // [K][n_tiles] per-tile sums of squares
     double *d_S;            // [K][L] squared Frobenius norms
@@ -41,9 +42,9 @@ struct grawa_plan {
     float *d_beta_model;    // [K] model-level weights
     float *d_beta_uniform;  // [K] 1/K each (EASGD), written once
     unsigned *d_cnt_all;    // [1] arrivals of the layers, cleared by the norm pass of the call
-    double *d_mvg;          // [K][L] moving average of the layer norms (running estimate, Appendix G)
+    double *d_mvg;          // [K][L] moving average of the layer norms (running estimate, Appendix G); with fold_later what k_fold found, for the model level
     int64_t *d_local_t;     // [L], all equal: local steps since the last communication (what the kernels use)
-    int fold_later;         // the scored step leaves its sums to the next launch (grawa_fold_later); then, instead of d_mvg and d_local_t:
+    int fold_later;         // the scored step leaves its sums to the next launch (grawa_fold_later); then, instead of d_local_t:
     double *d_sums;         // [GRAWA_SUM_BUFFERS][K][n_rtiles] tile sums of scored steps
     GrawaSteps steps;
     GrawaEstimate *d_est;   // [K][L]

@@ -369,9 +369,11 @@ __global__ __launch_bounds__(GRAWA_LW_BLOCK_MODEL) void k_local_weights(double *
 // The same where the last step's sums may not be folded in yet (grawa_fold.h).  per_layer: grid L, and what is pending is folded in on the way: by a
 // thread per worker, a wave per worker in turn, or, for a layer of more than GRAWA_FOLD_WAVE_TILES tiles, all waves for the workers' parts, N
 // parts of a worker side by side (each what a wave of block_tile_sum adds, so that the sum is the same; two side by side take 5.9 us for 8
-// workers and 586 tiles, four 5.0), as long as grawa_fold_long_in_weights; beyond, and at the model level (grid 1), k_fold goes before.
+// workers and 586 tiles, four 5.0), as long as grawa_fold_long_in_weights; beyond, k_fold goes before.  Model level: grid 1, from the packed table that
+// k_fold, or here (fold_here) the block itself, writes: 32 bytes an estimate, read by one block one after the other, made a round of one step of
+// 8 workers and 2000 layers 54 us, now 39.
 __global__ __launch_bounds__(GRAWA_FIN_BLOCK) void k_fold_weights(const GrawaFold f, const double *__restrict__ sums, int64_t n_tiles,
-                                                                   int per_layer, uint64_t *__restrict__ consumed,
+                                                                   int per_layer, int fold_here, uint64_t *__restrict__ consumed,
                                                                    float *__restrict__ beta, float *__restrict__ beta_user,
                                                                    float *__restrict__ est_user)
 {
@@ -441,14 +443,50 @@ __global__ __launch_bounds__(GRAWA_FIN_BLOCK) void k_fold_weights(const GrawaFol
         if (wave == 0)
             group_weights(sA, K, beta + l0, L, beta_user ? beta_user + l0 : nullptr, f.flags, GRAWA_NONFINITE_LAYER_SCORE);
     } else {
+        if (fold_here) { // a thread for each worker and layer; the longer ones of a wave by all of it, one after the other
+            const unsigned units = (unsigned)K * (unsigned)L;
+            const int few = (int)grawa_thread_tiles(f.lanes);
+            for (unsigned base = 0; base < units; base += blockDim.x) {
+                const unsigned u = base + lane * waves + wave, k = u / (unsigned)L, l = u - k * (unsigned)L;
+                GrawaEstimate e = {};
+                int t0 = 0, t1 = 0;
+                if (u < units) {
+                    e = f.est[u];
+                    t0 = f.layer_tile0[l];
+                    t1 = f.layer_tile0[l + 1];
+                }
+                const double *p = sums + e0.buffer * f.pitch;
+                const bool pending = u < units && grawa_estimate_pending(e, used);
+                double s = 0.0;
+                if (pending && t1 - t0 <= few) s = few_tiles_sum<16>(p + (int64_t)k * n_tiles, t0, t1);
+                for (unsigned long long todo = __ballot(pending && t1 - t0 > few); todo; todo &= todo - 1) {
+                    const int j = __builtin_ctzll(todo), a = __builtin_amdgcn_readlane(t0, j), b = __builtin_amdgcn_readlane(t1, j);
+                    const double tot = wave_strided_sum(p + (int64_t)__builtin_amdgcn_readlane((int)k, j) * n_tiles, lane < f.lanes ? a : b, b, lane, f.lanes);
+                    if (lane == j) s = tot;
+                }
+                if (u < units) f.value[u] = grawa_estimate_value(e, used, sqrt(s));
+            }
+            __syncthreads();
+        }
         const double scale = n != used ? f.gamma / grawa_one_minus_power(f.gamma, (int64_t)(n - used)) : 0.0;
         for (int k = wave; k < K; k += waves) {
+            const double *row = f.value + (int64_t)k * L;
+            float *est = est_user ? est_user + (int64_t)k * L : nullptr;
             double s = 0.0;
-            for (int l = lane; l < L; l += GRAWA_WAVE) {
-                const double v = scale * grawa_estimate_value(f.est[(int64_t)k * L + l], used, 0.0);
+            const auto take = [&](int l, double value) {
+                const double v = scale * value;
                 s += v;
-                if (est_user) est_user[(int64_t)k * L + l] = (float)v;
+                if (est) est[l] = (float)v;
+            };
+            int l = lane;
+            for (; l + 3 * GRAWA_WAVE < L; l += 4 * GRAWA_WAVE) { // four loads in flight: none may pass the stores
+                const double v0 = row[l], v1 = row[l + GRAWA_WAVE], v2 = row[l + 2 * GRAWA_WAVE], v3 = row[l + 3 * GRAWA_WAVE];
+                take(l, v0);
+                take(l + GRAWA_WAVE, v1);
+                take(l + 2 * GRAWA_WAVE, v2);
+                take(l + 3 * GRAWA_WAVE, v3);
             }
+            for (; l < L; l += GRAWA_WAVE) take(l, row[l]);
             s = wave_sum(s);
             if (lane == 0) sA[k] = s;
         }
@@ -627,15 +665,17 @@ hipError_t grawa_launch_local_weights(const grawa_plan *p, double gamma, int per
         unsigned long long id = 0;
         const bool recorded = grawa_is_recorded(s, &id);
         const GrawaFold f = grawa_fold_of(p, gamma, 0, 0);
-        const bool before = !per_layer || (!f.by_wave && !grawa_fold_long_in_weights(p->K, p->max_rtiles));
-        if (before && !grawa_all_folded(p->steps, recorded, id)) {
+        const bool folded = grawa_all_folded(p->steps, recorded, id);
+        const bool here = !per_layer && !folded && grawa_fold_in_model_weights(p->K, p->L, p->max_rtiles, p->n_longer);
+        const bool before = per_layer ? !f.by_wave && !grawa_fold_long_in_weights(p->K, p->max_rtiles) : !here;
+        if (before && !folded) {
             const hipError_t e = grawa_launch_fold(p, nullptr, s);
             if (e != hipSuccess) return e;
         }
         const int want = !per_layer ? GRAWA_FIN_WAVES : p->max_rtiles <= 16 || before ? 4 : f.by_wave ? p->K : 4 * p->K;
         const int waves = want < 4 ? 4 : want < GRAWA_FIN_WAVES ? want : GRAWA_FIN_WAVES;
         k_fold_weights<<<dim3(per_layer ? (unsigned)p->L : 1u), dim3(waves * GRAWA_WAVE), 0, s>>>(
-            f, p->d_sums, p->n_rtiles, per_layer, p->d_consumed, per_layer ? p->d_beta_layer : p->d_beta_model, beta_user, est_user);
+            f, p->d_sums, p->n_rtiles, per_layer, here, p->d_consumed, per_layer ? p->d_beta_layer : p->d_beta_model, beta_user, est_user);
         return hipGetLastError();
     }
     k_local_weights<<<dim3(per_layer ? (unsigned)p->L : 1u), dim3(per_layer ? GRAWA_LW_BLOCK_LAYER : GRAWA_LW_BLOCK_MODEL), 0, s>>>(

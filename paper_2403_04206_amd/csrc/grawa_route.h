@@ -238,6 +238,17 @@ static inline bool grawa_fold_later(int K, int L, int64_t P, int64_t max_tiles)
 #define GRAWA_FOLD_LONG_TILES 4096
 static inline bool grawa_fold_long_in_weights(int K, int64_t max_tiles) { return K <= GRAWA_FOLD_LONG_WORKERS && max_tiles <= GRAWA_FOLD_LONG_TILES; }
 
+// Whether the one block of the model-level weights adds what is pending itself: as long as a thread has one worker and layer, and its 16 waves a
+// longer one each.  Else k_fold goes before.  One step and the communication, us, k_fold / this: 4 workers, one layer of 9 k 11.6 / 9.1, and 58 of 2 k
+// 13.4 / 12.2; beyond, 8 workers, 12 layers of 12 k (96 longer ones) 16.4 / 17.9, ResNet-20 on 8 (40) 21.2 / 25.1.
+#define GRAWA_FOLD_MODEL_UNITS 1024
+#define GRAWA_FOLD_MODEL_WAVES 16
+static constexpr int64_t grawa_thread_tiles(int lanes) { return lanes < 16 ? lanes : 16; } // whose sum a thread adds in the order of `lanes` lanes
+static inline bool grawa_fold_in_model_weights(int K, int L, int64_t max_tiles, int64_t longer)
+{
+    return (int64_t)K * L <= GRAWA_FOLD_MODEL_UNITS && (int64_t)K * longer <= GRAWA_FOLD_MODEL_WAVES && max_tiles <= GRAWA_FOLD_WAVE_TILES;
+}
+
 // Lanes of a wave that share a worker's tiles where the wave takes all K workers of a layer: the largest power of two not above 64 / K.
 static inline int grawa_group_lanes(int K)
 {

@@ -137,6 +137,11 @@ def test_folding_of_long_layers(driver):
         assert driver("fold", *case)[0][2] == yes, case
 
 
+def test_folding_for_the_model_level(driver):
+    cases = [(4, 256, 17, 4), (4, 256, 17, 5), (4, 257, 17, 4), (16, 64, 512, 1), (16, 64, 513, 1), (17, 2, 30, 1), (1024, 1, 10, 0), (1025, 1, 10, 0)]
+    assert [r[0] for r in driver("fold_model", *[v for c in cases for v in c])] == [1, 0, 0, 1, 0, 0, 1, 0]
+
+
 def test_columns_of_g_read_through_the_caches(driver):
     cases = [(k, p, e) for k in (1, 2, 3, 7, 64, 1000, 1024) for p in (1, 255, 60000, 1 << 20, (1 << 32) - 1) for e in (2, 4)]
     for k, p, e, cols in driver("cachedg", *[v for c in cases for v in c]):
