@@ -371,7 +371,8 @@ __global__ __launch_bounds__(GRAWA_LW_BLOCK_MODEL) void k_local_weights(double *
 // parts of a worker side by side (each what a wave of block_tile_sum adds, so that the sum is the same; two side by side take 5.9 us for 8
 // workers and 586 tiles, four 5.0), as long as grawa_fold_long_in_weights; beyond, k_fold goes before.  Model level: grid 1, from the packed table that
 // k_fold, or here (fold_here) the block itself, writes: 32 bytes an estimate, read by one block one after the other, made a round of one step of
-// 8 workers and 2000 layers 54 us, now 39.
+// 8 workers and 2000 layers 54 us, now 39.  A thread's first estimate brings the counts too, instead of a load before it (4 workers, 2000 layers 26.6 ->
+// 25.7, 16 workers, 1000 32.0 -> 31.7).
 __global__ __launch_bounds__(GRAWA_FIN_BLOCK) void k_fold_weights(const GrawaFold f, const double *__restrict__ sums, int64_t n_tiles,
                                                                    int per_layer, int fold_here, uint64_t *__restrict__ consumed,
                                                                    float *__restrict__ beta, float *__restrict__ beta_user,
@@ -384,7 +385,12 @@ __global__ __launch_bounds__(GRAWA_FIN_BLOCK) void k_fold_weights(const GrawaFol
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / GRAWA_WAVE)), waves = (int)blockDim.x / GRAWA_WAVE;
     const int l0 = per_layer ? (int)blockIdx.x : 0;
     const int K = f.K, L = f.L;
-    const GrawaEstimate e0 = f.est[l0]; // counts and buffer: the same for all workers and layers
+    const GrawaEstimate mine = f.est[(int64_t)((int)threadIdx.x < K ? threadIdx.x : 0) * L + l0];
+    const auto uniform = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); };
+    GrawaEstimate e0 = {}; // counts and buffer: the same for all workers and layers
+    e0.n = (uint64_t)uniform((uint32_t)(mine.n >> 32)) << 32 | uniform((uint32_t)mine.n);
+    e0.buffer = uniform(mine.buffer);
+    e0.left = uniform(mine.left);
     const uint64_t n = e0.n, used = grawa_last_used(consumed[l0], consumed[L + l0]);
     if (per_layer) {
         const bool pending = grawa_estimate_pending(e0, used);
@@ -435,7 +441,9 @@ __global__ __launch_bounds__(GRAWA_FIN_BLOCK) void k_fold_weights(const GrawaFol
             if (pending) s = tiles <= 4    ? few_tiles_sum<4>(p + (int64_t)k * n_tiles, t0, t1)
                              : tiles <= 16 ? few_tiles_sum<16>(p + (int64_t)k * n_tiles, t0, t1)
                                            : sA[k];
-            const double v = scale * grawa_estimate_value(f.est[(int64_t)k * L + l0], used, sqrt(s));
+            e0.mvg = k == (int)threadIdx.x ? mine.mvg : f.est[(int64_t)k * L + l0].mvg;
+            e0.gamma = mine.gamma;
+            const double v = scale * grawa_estimate_value(e0, used, sqrt(s));
             sA[k] = v;
             if (est_user) est_user[(int64_t)k * L + l0] = (float)v;
         }
@@ -672,7 +680,7 @@ hipError_t grawa_launch_local_weights(const grawa_plan *p, double gamma, int per
             const hipError_t e = grawa_launch_fold(p, nullptr, s);
             if (e != hipSuccess) return e;
         }
-        const int want = !per_layer ? GRAWA_FIN_WAVES : p->max_rtiles <= 16 || before ? 4 : f.by_wave ? p->K : 4 * p->K;
+        const int want = !per_layer ? GRAWA_FIN_WAVES : p->max_rtiles <= 16 || before || folded ? 4 : f.by_wave ? p->K : 4 * p->K;
         const int waves = want < 4 ? 4 : want < GRAWA_FIN_WAVES ? want : GRAWA_FIN_WAVES;
         k_fold_weights<<<dim3(per_layer ? (unsigned)p->L : 1u), dim3(waves * GRAWA_WAVE), 0, s>>>(
             f, p->d_sums, p->n_rtiles, per_layer, here, p->d_consumed, per_layer ? p->d_beta_layer : p->d_beta_model, beta_user, est_user);
