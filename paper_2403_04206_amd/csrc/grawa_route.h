@@ -113,7 +113,8 @@ static inline bool grawa_plain_form(int K, int64_t n_cells)
 #define GRAWA_LAST_BLOCK_MAX_LAYERS 100
 static inline bool grawa_model_weights_by_last_block(int L) { return L <= GRAWA_LAST_BLOCK_MAX_LAYERS; }
 
-// Launch of the running estimate: y rows of blocks per layer and threads of a block.  max_tiles: the most 1024-column
+// Launch of the running estimate (of plans that neither leave their sums to the next launch nor go by layers, below; of the sizes quoted here those
+// with few layers do now): y rows of blocks per layer and threads of a block.  max_tiles: the most 1024-column
 // tiles that a layer has.  Layers of up to GRAWA_EST_WAVE_TILES tiles take a wave per worker, or, where there are many
 // layers (GRAWA_EST_BLOCKS blocks fill the chip), a wave per few workers: starting a wave costs more than such a sum.
 // A longer layer takes a block of 512 threads per worker, as long as that keeps the launch within
@@ -211,8 +212,9 @@ static inline bool grawa_step_by_layers(int K, int L, int64_t P, int64_t max_til
 // those that they replace.  Rounds of one step, us, before / now (in brackets captured, a graph's launch included): 8 workers, one layer of 8 M
 // 204.6 / 205.5 (209.3 / 210.0), 4 steps 573 / 557; 2 workers, 30 M 195.6 / 196.3 (200.4 / 201.7), 549 / 531; 64 workers, 1 M 214.2 / 214.9 (218.6 / 220.1),
 // 572 / 563; behind another kernel of 28 us ResNet-20 on 4 workers (40.1 / 39.5), and, where a block of 1024 threads took the layers before, 8 workers,
-// 12 layers of 12 k (37.0 / 38.6), 32 workers, one layer of 18 k (36.1 / 37.7), 4 workers, 9 k and 58 of 2 k (34.9 / 35.8).  A step and the
-// communication captured apart, 8 workers, 8 M 215.8 / 219.9: the communication cannot know that nothing is left to fold in.
+// 12 layers of 12 k (37.0 / 38.6), 32 workers, one layer of 18 k (36.1 / 37.7), 4 workers, 9 k and 58 of 2 k (34.9 / 35.8), 2
+// workers, 60 layers of 8.7 k (37.2 / 39.9, four steps 50.9 / 52.2).  A step and the communication captured apart, 8 workers, 8 M 215.8 / 219.9: the
+// communication cannot know that nothing is left to fold in.
 // The lines.  Beyond 2^17 blocks a step lasts 200 us and more, and the buffers take memory.  Layers: every one is a wave's work for each worker in the step
 // and a block in the launch of the weights: 4 workers, 2000 layers of 400 columns, four steps and one 66.5 / 54.5 and 29.1 / 25.7, 4000 layers
 // 106 / 97.5 and 38.5 / 39.4, 2 workers, 8000 116 / 104 and 44.6 / 48.3.  Sums: 64 workers, 300 layers 110 / 91 and 39 / 33, 8 workers, 5000
