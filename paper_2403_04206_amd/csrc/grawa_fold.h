@@ -21,7 +21,7 @@ struct GrawaFold {
     int by_wave;     // no layer has more than GRAWA_FOLD_WAVE_TILES tiles
     int lanes;       // of a wave that add the tiles of a worker: as many as in the pull, where that folds in (wave_layer_weights)
     unsigned buffer; // that the sums of this launch go to
-    unsigned blocks; // of every row of a step's grid that fold
+    unsigned blocks, rows; // of a step's grid that fold (grawa_fold_blocks)
     double gamma;    // of the step that this launch takes
 };
 
@@ -135,8 +135,8 @@ __device__ __forceinline__ void fold_all(const GrawaFold &f, const double *__res
     }
 }
 
-static inline GrawaFold grawa_fold_of(const grawa_plan *p, double gamma, unsigned buffer, unsigned blocks)
+static inline GrawaFold grawa_fold_of(const grawa_plan *p, double gamma, unsigned buffer, unsigned blocks, unsigned rows)
 {
     return GrawaFold{p->d_est, p->d_mvg, p->d_consumed, p->d_layer_rtile0, p->d_flags, (int64_t)p->K * p->n_rtiles, p->K, p->L,
-                     p->max_rtiles <= GRAWA_FOLD_WAVE_TILES, p->d_seen ? grawa_group_lanes(p->K) : 64, buffer, blocks, gamma};
+                     p->max_rtiles <= GRAWA_FOLD_WAVE_TILES, p->d_seen ? grawa_group_lanes(p->K) : 64, buffer, blocks, rows, gamma};
 }

@@ -34,9 +34,8 @@
 // block_tile0[m] .. block_tile0[m+1]-1 lie in aligned block m, each inside one layer).  Nearly
 // every block holds one tile; in a block that contains layer boundaries every wave adds the tiles of its own columns (the block
 // reducing once per tile, with two barriers each: 4 workers, ResNet-20's 59 tensors 6.1 us, now 5.4; one tile a block would take 4.3).
-// The tile sums go to k_estimate, to k_fold or, GRAWA_SCORE_LATER, to the launch that needs them next (grawa_fold.h): a few blocks at
-// the head of the rows fold in those of the step before, a launch of 5 us that this one hides (a row of blocks of
-// their own, most of them empty, took large steps 3 us).  (Updating the estimate inside this launch, by the block that brings the last tile of a (worker, layer), was
+// The tile sums go to k_estimate, to k_fold or, GRAWA_SCORE_LATER, to the launch that needs them next (grawa_fold.h): a few blocks ahead of
+// the others (grawa_fold_blocks) fold in those of the step before, a launch of 5 us that this one hides.  (Updating the estimate inside this launch, by the block that brings the last tile of a (worker, layer), was
 // tried: its device-scope traffic costs more than the launch from about 1000 blocks or 30 tiles per layer on, 4 steps and
 // the communication on 8 workers 117 us instead of 45.)  The maps are parameters of their own, each __restrict__: as
 // members of a struct they may alias the stores, and a block with many tiles then reads them by vector loads that wait for
@@ -53,15 +52,17 @@ __global__ __launch_bounds__(GRAWA_CELL) __attribute__((amdgpu_waves_per_eu(1, P
 {
     static_assert(V * U * GRAWA_CELL == GRAWA_ROW_BLOCK, "one trip covers one aligned block of columns");
     typedef typename FloatVec<V>::T XV;
-    const unsigned k = blockIdx.y;
+    unsigned k = blockIdx.y;
     unsigned m = blockIdx.z * gridDim.x + blockIdx.x;
     if constexpr (SCORE == GRAWA_SCORE_LATER) {
-        if (blockIdx.x < fold.blocks) { // the first blocks of a row fold in the sums of the step before
-            fold_all<GRAWA_CELL, GRAWA_FOLD_STEP>(fold, partials, n_tiles, (blockIdx.z * gridDim.y + k) * fold.blocks + blockIdx.x,
-                                                  gridDim.z * gridDim.y * fold.blocks);
+        if (blockIdx.x < fold.blocks || k < fold.rows) { // these fold in the sums of the step before
+            const unsigned width = fold.rows ? gridDim.x : fold.blocks, height = fold.rows ? fold.rows : gridDim.y;
+            fold_all<GRAWA_CELL, GRAWA_FOLD_STEP>(fold, partials, n_tiles, (blockIdx.z * height + k) * width + blockIdx.x,
+                                                  gridDim.z * height * width);
             return;
         }
         m = blockIdx.z * (gridDim.x - fold.blocks) + blockIdx.x - fold.blocks;
+        k -= fold.rows;
     }
     if (m >= n_blocks) return; // the last group may be short (whole block leaves, before any barrier)
     const int64_t c0 = (int64_t)m * GRAWA_ROW_BLOCK + (int64_t)threadIdx.x * V;
@@ -410,21 +411,15 @@ static hipError_t launch_row_step(grawa_plan *p, float *x, int64_t ldx, const vo
     const int64_t group = (prox && nb > GRAWA_ROW_GROUP) ? GRAWA_ROW_GROUP : nb;
     const int64_t n_groups = (nb + group - 1) / group;
     if (K > 65535 || n_groups > 65535 || group >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
-    // The blocks that fold in the step before stand at the head of the rows.  Eight in a row keep the columns of the center on
-    // the XCD that the other rows read them from.
     unsigned long long id = 0;
     const bool recorded = later && grawa_is_recorded(s, &id);
     bool at_once = false;
     const unsigned buffer = later ? grawa_step_buffer(p->steps, recorded, id, &at_once) : 0;
-    unsigned fold_blocks = 0;
-    if (later && !at_once) {
-        const int64_t units = (int64_t)K * p->L, blocks = p->max_rtiles <= GRAWA_FOLD_WAVE_TILES ? (units + 3) / 4 : units;
-        fold_blocks = (unsigned)((blocks + K * n_groups - 1) / (K * n_groups));
-        if (group >= 256) fold_blocks = (fold_blocks + 7) / 8 * 8;
-    }
+    unsigned fold_blocks = 0, fold_rows = 0;
+    if (later && !at_once) grawa_fold_blocks(K, p->L, p->max_rtiles, group, n_groups, &fold_blocks, &fold_rows);
     GrawaFold fold = {}; // no flags either: k_estimate looks at the norms
-    if (later) fold = grawa_fold_of(p, gamma, buffer, fold_blocks);
-    const dim3 grid((unsigned)group + fold_blocks, (unsigned)K, (unsigned)n_groups), block(GRAWA_CELL);
+    if (later) fold = grawa_fold_of(p, gamma, buffer, fold_blocks, fold_rows);
+    const dim3 grid((unsigned)group + fold_blocks, (unsigned)K + fold_rows, (unsigned)n_groups), block(GRAWA_CELL);
     const bool aligned = rows_line_aligned(x, ldx, 4) && rows_line_aligned(g, ldg, dt == GRAWA_BF16 ? 2 : 4);
     const int64_t bytes = (int64_t)K * P * 4;
     const bool plain = !prox && !p;

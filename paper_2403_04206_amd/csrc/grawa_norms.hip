@@ -643,7 +643,7 @@ hipError_t grawa_launch_estimate(const grawa_plan *p, double gamma, hipStream_t 
 // step: a recorded step, whose sums are to be folded in; null: only what is pending.
 hipError_t grawa_launch_fold(const grawa_plan *p, const GrawaFold *step, hipStream_t s)
 {
-    const GrawaFold f = step ? *step : grawa_fold_of(p, 0.0, 0, 0);
+    const GrawaFold f = step ? *step : grawa_fold_of(p, 0.0, 0, 0, 0);
     const unsigned units = (unsigned)p->K * (unsigned)p->L;
     const dim3 grid(f.by_wave ? (units + 3) / 4 : units), block(f.by_wave ? 256 : GRAWA_FOLD_LANES);
 #define GRAWA_FOLD_GO(THREADS, MODE) k_fold<THREADS, MODE><<<grid, block, 0, s>>>(f, p->d_sums, p->n_rtiles)
@@ -672,7 +672,7 @@ hipError_t grawa_launch_local_weights(const grawa_plan *p, double gamma, int per
     if (p->fold_later) {
         unsigned long long id = 0;
         const bool recorded = grawa_is_recorded(s, &id);
-        const GrawaFold f = grawa_fold_of(p, gamma, 0, 0);
+        const GrawaFold f = grawa_fold_of(p, gamma, 0, 0, 0);
         const bool folded = grawa_all_folded(p->steps, recorded, id);
         const bool here = !per_layer && !folded && grawa_fold_in_model_weights(p->K, p->L, p->max_rtiles, p->n_longer);
         const bool before = per_layer ? !f.by_wave && !grawa_fold_long_in_weights(p->K, p->max_rtiles) : !here;

@@ -232,6 +232,20 @@ static inline bool grawa_fold_later(int K, int L, int64_t P, int64_t max_tiles)
     return (int64_t)K * ((P + 1023) / 1024) <= GRAWA_FOLD_MAX_BLOCKS && (int64_t)K * L <= units;
 }
 
+// Where the blocks of a scored step that fold in the sums before stand in its grid (group, K, n_groups).  The length of a row decides which XCD a column goes to from
+// row to row, and with it what the launches before left in its L2, so it stays as it is, modulo 8.  Short rows: rows of their own ahead of the workers' (64
+// workers, 256 k columns, a step 28.5 us without such blocks, 33.0 with one at the head of each row, 28.9 so; with the center 28.8, 35.3, 28.7; 16 workers, four
+// layers of 64 k, a round of four steps 49.5 -> 41.8).  Long rows: eight blocks, or a multiple, at the head of each, since most of a row of their own would be
+// empty (3 us on large steps); or rows ahead, where that takes no more blocks.
+static inline void grawa_fold_blocks(int K, int L, int64_t max_tiles, int64_t group, int64_t n_groups, unsigned *blocks, unsigned *rows)
+{
+    const int64_t units = (int64_t)K * L, all = max_tiles <= GRAWA_FOLD_WAVE_TILES ? (units + 3) / 4 : units;
+    const int64_t head = ((all + K * n_groups - 1) / (K * n_groups) + 7) / 8 * 8, ahead = (all + group - 1) / group;
+    const bool apart = n_groups == 1 && (group < 256 || ahead * group <= head * K);
+    *blocks = apart ? 0 : (unsigned)head;
+    *rows = apart ? (unsigned)ahead : 0;
+}
+
 // Whether the launch of the weights adds the tiles of long layers itself: up to 8 workers, whose parts its 16 waves take at once, and 4096 tiles, 8 of
 // them to a lane.  Else k_fold goes before, a launch of 5 us.  One step and the communication, us, k_fold / this: 2 workers, one layer of 600 k
 // columns and 250 of 3 k 24.4 / 21.5, of 1.5 M alone 23.6 / 21.4; 8 workers, 600 k alone 26.1 / 24.7, ResNet-18 295.4 / 293.9; beyond, 16 workers
