@@ -369,7 +369,7 @@ __global__ __launch_bounds__(GRAWA_LW_BLOCK_MODEL) void k_local_weights(double *
 // The same where the last step's sums may not be folded in yet (grawa_fold.h).  per_layer: grid L, and what is pending is folded in on the way: by a
 // thread per worker, a wave per worker in turn, or, for a layer of more than GRAWA_FOLD_WAVE_TILES tiles, all waves for the workers' parts, N
 // parts of a worker side by side (each what a wave of block_tile_sum adds, so that the sum is the same; two side by side take 5.9 us for 8
-// workers and 586 tiles, four 5.0), as long as grawa_fold_long_in_weights; beyond, k_fold goes before.  Model level: grid 1, from the packed table that
+// workers and 586 tiles, four 5.0), as long as grawa_fold_in_weights; beyond, k_fold goes before.  Model level: grid 1, from the packed table that
 // k_fold, or here (fold_here) the block itself, writes: 32 bytes an estimate, read by one block one after the other, made a round of one step of
 // 8 workers and 2000 layers 54 us, now 39.  A thread's first estimate brings the counts too, instead of a load before it (4 workers, 2000 layers 26.6 ->
 // 25.7, 16 workers, 1000 32.0 -> 31.7).
@@ -396,7 +396,7 @@ __global__ __launch_bounds__(GRAWA_FIN_BLOCK) void k_fold_weights(const GrawaFol
         const bool pending = grawa_estimate_pending(e0, used);
         const int t0 = f.layer_tile0[l0], t1 = f.layer_tile0[l0 + 1], tiles = t1 - t0;
         const double *p = sums + e0.buffer * f.pitch;
-        if (pending && tiles > GRAWA_FOLD_WAVE_TILES) { // grawa_fold_long_in_weights
+        if (pending && tiles > GRAWA_FOLD_WAVE_TILES) { // grawa_fold_in_weights
             for (int j = N * wave; j < K * PARTS; j += N * waves) {
                 const double *row = p + (int64_t)(j / PARTS) * n_tiles;
                 const int first = t0 + (j % PARTS) * GRAWA_WAVE + lane;
@@ -675,7 +675,7 @@ hipError_t grawa_launch_local_weights(const grawa_plan *p, double gamma, int per
         const GrawaFold f = grawa_fold_of(p, gamma, 0, 0, 0);
         const bool folded = grawa_all_folded(p->steps, recorded, id);
         const bool here = !per_layer && !folded && grawa_fold_in_model_weights(p->K, p->L, p->max_rtiles, p->n_longer);
-        const bool before = per_layer ? !f.by_wave && !grawa_fold_long_in_weights(p->K, p->max_rtiles) : !here;
+        const bool before = per_layer ? !grawa_fold_in_weights(p->K, p->max_rtiles) : !here;
         if (before && !folded) {
             const hipError_t e = grawa_launch_fold(p, nullptr, s);
             if (e != hipSuccess) return e;

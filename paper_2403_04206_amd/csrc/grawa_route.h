@@ -246,13 +246,21 @@ static inline void grawa_fold_blocks(int K, int L, int64_t max_tiles, int64_t gr
     *rows = apart ? (unsigned)ahead : 0;
 }
 
-// Whether the launch of the weights adds the tiles of long layers itself: up to 8 workers, whose parts its 16 waves take at once, and 4096 tiles, 8 of
+// Whether the launch of the per-layer weights adds what is pending itself.  Layers that a wave adds: as long as its 16 waves do not walk many workers with many
+// tiles.  One step and the communication, one layer, us, k_fold before / this: 64 workers, 125 tiles 33.8 / 34.5, 250 61.1 / 63.2, 500 110.9 / 114.4; 48, 125 28.7 /
+// 28.6, 250 48.3 / 49.2; 38, 250 40.3 / 40.7; 32, 250 36.2 / 35.9, 500 59.0 / 59.2; 16, 60 14.5 / 12.7.  Longer layers: up to 8 workers, whose parts its 16 waves take at once, and 4096 tiles, 8 of
 // them to a lane.  Else k_fold goes before, a launch of 5 us.  One step and the communication, us, k_fold / this: 2 workers, one layer of 600 k
 // columns and 250 of 3 k 24.4 / 21.5, of 1.5 M alone 23.6 / 21.4; 8 workers, 600 k alone 26.1 / 24.7, ResNet-18 295.4 / 293.9; beyond, 16 workers
 // (twice as many parts): 600 k alone 39.0 / 38.9, three of 2 M 310 / 314.
 #define GRAWA_FOLD_LONG_WORKERS 8
 #define GRAWA_FOLD_LONG_TILES 4096
-static inline bool grawa_fold_long_in_weights(int K, int64_t max_tiles) { return K <= GRAWA_FOLD_LONG_WORKERS && max_tiles <= GRAWA_FOLD_LONG_TILES; }
+#define GRAWA_FOLD_WORKERS 32
+#define GRAWA_FOLD_TILES 8000 // of a layer, times workers
+static inline bool grawa_fold_in_weights(int K, int64_t max_tiles)
+{
+    if (max_tiles > GRAWA_FOLD_WAVE_TILES) return K <= GRAWA_FOLD_LONG_WORKERS && max_tiles <= GRAWA_FOLD_LONG_TILES;
+    return K <= GRAWA_FOLD_WORKERS || max_tiles * K < GRAWA_FOLD_TILES;
+}
 
 // Whether the one block of the model-level weights adds what is pending itself: as long as a thread has one worker and layer, and its 16 waves a
 // longer one each.  Else k_fold goes before.  One step and the communication, us, k_fold / this: 4 workers, one layer of 9 k 11.6 / 9.1, and 58 of 2 k

@@ -7,7 +7,7 @@
 //   rowstep              -> bf16, center, scored, MB beyond which loads stream and the L2 merges (-1: at no size)
 //   layers <K> <L> <P> <max_tiles>... -> per case: the case, 1 if a block owns a layer in the scored step
 //   fold <K> <L> <P> <max_tiles>... -> per case: 1 if a scored step's sums are left to the next launch; there, 1 if the pull forms the weights from
-//                           the estimates, 1 if the launch of the per-layer weights adds long layers itself
+//                           the estimates, 1 if the launch of the per-layer weights adds what is pending itself
 //   fold_blocks <K> <L> <max_tiles> <group> <n_groups>... -> per case: the case, blocks at the head of a row, rows ahead
 //   fold_model <K> <L> <max_tiles> <longer>... -> per case: 1 if the launch of the model-level weights folds in itself
 //   cachedg <K> <P> <elem_bytes>... -> per triple: the triple, columns of g that the norm pass of a fused update reads through the caches
@@ -73,7 +73,7 @@ int main(int argc, char **argv)
             const int K = std::atoi(argv[i]), L = std::atoi(argv[i + 1]);
             const int64_t P = std::atoll(argv[i + 2]), tiles = std::atoll(argv[i + 3]);
             std::printf("%d %d %d\n", grawa_fold_later(K, L, P, tiles), grawa_estimate_in_pull(K, (P + 255) / 256, tiles),
-                        grawa_fold_long_in_weights(K, tiles));
+                        grawa_fold_in_weights(K, tiles));
         }
         return 0;
     }

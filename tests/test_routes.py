@@ -132,8 +132,9 @@ def test_weights_from_estimates_in_the_pull(driver):
 
 
 def test_folding_of_long_layers(driver):
-    # the launch of the weights adds them itself
-    for case, yes in (((8, 1, 1 << 22, 4096), 1), ((9, 1, 1 << 20, 1024), 0), ((8, 2, 1 << 23, 4097), 0), ((1, 1, 1 << 20, 1024), 1)):
+    # the launch of the weights adds them itself; and what many workers have beyond 8000 tiles, a launch before it
+    for case, yes in (((64, 1, 126000, 124), 1), ((64, 1, 128000, 125), 0), ((33, 1, 250000, 243), 0), ((33, 1, 250000, 242), 1), ((32, 1, 1 << 19, 512), 1),
+                      ((8, 1, 1 << 22, 4096), 1), ((9, 1, 1 << 20, 1024), 0), ((8, 2, 1 << 23, 4097), 0), ((1, 1, 1 << 20, 1024), 1)):
         assert driver("fold", *case)[0][2] == yes, case
 
 
