@@ -416,7 +416,7 @@ static hipError_t launch_row_step(grawa_plan *p, float *x, int64_t ldx, const vo
     bool at_once = false;
     const unsigned buffer = later ? grawa_step_buffer(p->steps, recorded, id, &at_once) : 0;
     unsigned fold_blocks = 0, fold_rows = 0;
-    if (later && !at_once) grawa_fold_blocks(K, p->L, p->max_rtiles, group, n_groups, &fold_blocks, &fold_rows);
+    if (later && !at_once) grawa_fold_blocks(K, p->L, p->max_rtiles, prox, group, n_groups, &fold_blocks, &fold_rows);
     GrawaFold fold = {}; // no flags either: k_estimate looks at the norms
     if (later) fold = grawa_fold_of(p, gamma, buffer, fold_blocks, fold_rows);
     const dim3 grid((unsigned)group + fold_blocks, (unsigned)K + fold_rows, (unsigned)n_groups), block(GRAWA_CELL);

@@ -232,16 +232,22 @@ static inline bool grawa_fold_later(int K, int L, int64_t P, int64_t max_tiles)
     return (int64_t)K * ((P + 1023) / 1024) <= GRAWA_FOLD_MAX_BLOCKS && (int64_t)K * L <= units;
 }
 
-// Where the blocks of a scored step that fold in the sums before stand in its grid (group, K, n_groups).  The length of a row decides which XCD a column goes to from
-// row to row, and with it what the launches before left in its L2, so it stays as it is, modulo 8.  Short rows: rows of their own ahead of the workers' (64
-// workers, 256 k columns, a step 28.5 us without such blocks, 33.0 with one at the head of each row, 28.9 so; with the center 28.8, 35.3, 28.7; 16 workers, four
-// layers of 64 k, a round of four steps 49.5 -> 41.8).  Long rows: eight blocks, or a multiple, at the head of each, since most of a row of their own would be
-// empty (3 us on large steps); or rows ahead, where that takes no more blocks.
-static inline void grawa_fold_blocks(int K, int L, int64_t max_tiles, int64_t group, int64_t n_groups, unsigned *blocks, unsigned *rows)
+// Where the blocks of a scored step that fold in the sums before stand in its grid (group, K, n_groups): at the head of each row, or as rows ahead of the
+// workers', whatever takes fewer blocks.  The length of a row, modulo 8, decides which XCD a column goes to from row to row, and with it what lies in its
+// L2, so it stays as it is (64 workers, 256 k columns, a step 28.5 us without such blocks, 33.0 with one at the head of each row, 28.9 so; with the center 28.8,
+// 35.3, 28.7; 16 workers, four layers of 64 k, a round of four steps 49.5 -> 41.7).  With the center it becomes a multiple of 8, so that all rows read a
+// column of it from one XCD: rounds of four steps, us, as it is / so: 8 workers, 1 M columns 94.3 / 80.1, 3 M 257 / 223, 16 workers, 1 M 171 / 145, 3 M
+// 500 / 429, 32 workers, 250 k 83.2 / 79.5, 3 M 967 / 824.  Not for short rows and many workers: 64 workers, 60 k 43.5 / 45.9, 500 k 289 / 298, 24 workers,
+// 128 k 37.8 / 39.4.
+#define GRAWA_FOLD_ALIGN_GROUP 200
+#define GRAWA_FOLD_ALIGN_WORKERS 40
+static inline void grawa_fold_blocks(int K, int L, int64_t max_tiles, bool center, int64_t group, int64_t n_groups, unsigned *blocks, unsigned *rows)
 {
     const int64_t units = (int64_t)K * L, all = max_tiles <= GRAWA_FOLD_WAVE_TILES ? (units + 3) / 4 : units;
-    const int64_t head = ((all + K * n_groups - 1) / (K * n_groups) + 7) / 8 * 8, ahead = (all + group - 1) / group;
-    const bool apart = n_groups == 1 && (group < 256 || ahead * group <= head * K);
+    const bool align = center && group >= GRAWA_FOLD_ALIGN_GROUP && K <= GRAWA_FOLD_ALIGN_WORKERS;
+    const int64_t least = (all + K * n_groups - 1) / (K * n_groups), from = align ? group : 0;
+    const int64_t head = (from + least + 7) / 8 * 8 - from, ahead = (all + group - 1) / group;
+    const bool apart = n_groups == 1 && ahead * group < head * K && !(align && group % 8);
     *blocks = apart ? 0 : (unsigned)head;
     *rows = apart ? (unsigned)ahead : 0;
 }

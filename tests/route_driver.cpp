@@ -8,7 +8,7 @@
 //   layers <K> <L> <P> <max_tiles>... -> per case: the case, 1 if a block owns a layer in the scored step
 //   fold <K> <L> <P> <max_tiles>... -> per case: 1 if a scored step's sums are left to the next launch; there, 1 if the pull forms the weights from
 //                           the estimates, 1 if the launch of the per-layer weights adds what is pending itself
-//   fold_blocks <K> <L> <max_tiles> <group> <n_groups>... -> per case: the case, blocks at the head of a row, rows ahead
+//   fold_blocks <K> <L> <max_tiles> <center> <group> <n_groups>... -> per case: the case, blocks at the head of a row, rows ahead
 //   fold_model <K> <L> <max_tiles> <longer>... -> per case: 1 if the launch of the model-level weights folds in itself
 //   cachedg <K> <P> <elem_bytes>... -> per triple: the triple, columns of g that the norm pass of a fused update reads through the caches
 //   power <gamma> <t>... -> per pair, exactly (%a): gamma, 1 - gamma^t
@@ -78,10 +78,11 @@ int main(int argc, char **argv)
         return 0;
     }
     if (!std::strcmp(argv[1], "fold_blocks")) {
-        for (int i = 2; i + 4 < argc; i += 5) {
+        for (int i = 2; i + 5 < argc; i += 6) {
             unsigned blocks = 0, rows = 0;
-            grawa_fold_blocks(std::atoi(argv[i]), std::atoi(argv[i + 1]), std::atoll(argv[i + 2]), std::atoll(argv[i + 3]), std::atoll(argv[i + 4]), &blocks, &rows);
-            std::printf("%s %s %s %s %s %u %u\n", argv[i], argv[i + 1], argv[i + 2], argv[i + 3], argv[i + 4], blocks, rows);
+            grawa_fold_blocks(std::atoi(argv[i]), std::atoi(argv[i + 1]), std::atoll(argv[i + 2]), std::atoi(argv[i + 3]), std::atoll(argv[i + 4]),
+                              std::atoll(argv[i + 5]), &blocks, &rows);
+            std::printf("%s %s %s %s %s %s %u %u\n", argv[i], argv[i + 1], argv[i + 2], argv[i + 3], argv[i + 4], argv[i + 5], blocks, rows);
         }
         return 0;
     }

@@ -20,7 +20,7 @@ CASES = [(4, [40000, 9000, 1, 3, 16, 16, 2304, 7, 5000]), (2, [4 * T, 4 * T + 1,
          # model level: the one block adds up to 16 longer sums itself; a thread has one sum or more; loads of four layers side by side
          (4, [17 * T] * 4 + [9] * 252), (4, [17 * T] * 5 + [9] * 20), (5, [50] * 204 + [9 * T]), (16, [65 * T] + [30] * 63),
          (6, [8 * T] * 2 + [9 * T] * 2 + [5] * 9), (2, [8 * T + 1] + [3] * 2047), (9, [300] * 257 + [18 * T]),
-         (40, [300 * T])]  # a row ahead of longer ones; many workers' tiles by a launch before the weights
+         (40, [300 * T]), (5, [200 * T] * 2 + [5 * T] * 30)]  # a row ahead of longer ones; many workers' tiles by a launch before the weights
 # s: a call on both; S: a call, and the replay of one recorded step; 2, 3: that many calls, and the replay of such a recording;
 # R: a round of two steps, recorded; c, C: a communication, and its replay; r: a reset
 ORDERS = ["sc", "ssc", "sSc", "sC", "SsC", "SSSC", "SSsc", "3C", "33C", "2C", "22C", "23C", "s3sc", "3S2C", "3R", "RsC", "RR", "2R2C",

@@ -139,15 +139,16 @@ def test_folding_of_long_layers(driver):
 
 
 def test_blocks_that_fold_in_the_step(driver):
-    # all sums have a wave or block, and the columns of every row stay on the XCDs (8 blocks apart) that they have without them
-    cases = [(K, L, t, group, z) for K in (1, 2, 7, 64, 1024) for L in (1, 20, 1024) for t in (1, 512, 513) for group in (1, 9, 255, 256, 300, 4096, 50000)
-             for z in (1, 3) if z == 1 or group == 4096]
-    for K, L, t, group, z, blocks, rows in driver("fold_blocks", *[v for c in cases for v in c]):
+    # all sums have a wave or block; the columns of every row stay on the XCDs (8 blocks apart) that they have without them, or, with the center, on one
+    cases = [(K, L, t, c, group, z) for K in (1, 2, 7, 40, 41, 64, 1024) for L in (1, 20, 1024) for t in (1, 512, 513) for c in (0, 1)
+             for group in (1, 9, 199, 200, 201, 255, 300, 4096, 50000) for z in (1, 3) if z == 1 or group == 4096]
+    for K, L, t, c, group, z, blocks, rows in driver("fold_blocks", *[v for case in cases for v in case]):
         want = K * L if t > 512 else -(-K * L // 4)
-        assert (blocks > 0) != (rows > 0) and blocks % 8 == 0 and (rows == 0 or z == 1)
+        assert (blocks > 0) != (rows > 0) and (rows == 0 or z == 1) and rows + K <= 65535
         assert blocks * K * z >= want or rows * group >= want
-        assert group >= 256 or rows > 0
-    assert [r[5:] for r in driver("fold_blocks", 64, 1, 300, 300, 1, 4, 60, 40, 300, 1)] == [[0, 1], [16, 0]]
+        assert (group + blocks) % 8 == 0 if c and K <= 40 and group >= 200 else blocks % 8 == 0
+    assert [r[6:] for r in driver("fold_blocks", 64, 1, 300, 0, 300, 1, 4, 60, 40, 0, 300, 1, 4, 60, 40, 1, 300, 1, 40, 1, 300, 1, 304, 1)] == \
+        [[0, 1], [16, 0], [20, 0], [0, 1]]
 
 
 def test_folding_for_the_model_level(driver):
